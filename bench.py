@@ -116,7 +116,7 @@ def pmc_traffic(workload: str):
 COPY_BYTES = 1 << 30   # calibration copy: 1 GiB read + 1 GiB written
 # the timed family: level-0 smoother steps of AMG(A) with a matrix product (the first, middle and
 # last Chebyshev steps; the zero-initial-guess step has no product and is not timed)
-SMOOTH_RE = r"smooth_rl3_k<double, (true|false), (true|false), false>"
+SMOOTH_RE = r"smooth_rl3_k<double, (true|false), (true|false), false, [0-9]+>"
 
 
 def _pmc_rows(d, counter):
@@ -211,9 +211,9 @@ def _kt_bytes(levels):
                         byts = mat + nr * (4.0 + vec * (3 + rd + wd))
                         zero = nr * (4.0 + vec * (2 + wd))
                         if b == 3 and l == 0:
-                            g = ceil(ceil(nr / 64) / 4) * 256
-                            add(f"smooth_rl3_k<{tn},{rd},{wd},0>", g, byts, f"{name}{l}")
-                            add(f"smooth_rl3_k<{tn},0,{wd},1>", g, zero, f"{name}{l}")
+                            for w in (1, 2, 4, 8):
+                                add(f"smooth_rl3_k<{tn},{rd},{wd},0,{w}>", slice_grid(nr, 1, w), byts, f"{name}{l}")
+                            add(f"smooth_rl3_k<{tn},0,{wd},1,1>", slice_grid(nr, 1, 1), zero, f"{name}{l}")
                         for w in (1, 2, 4, 8, 16):
                             add(f"smooth_k<{tn},{b},{rd},{wd},0,{w}>", slice_grid(nr, b, w), byts, f"{name}{l}")
                             add(f"smooth_k<{tn},{b},0,{wd},1,{w}>", slice_grid(nr, b, w), zero, f"{name}{l}")
@@ -227,7 +227,8 @@ def _kt_bytes(levels):
                     nv = 2 if mode == 0 else 3
                     byts = mat + nr * (4.0 + vec * nv)
                     if b == 3 and l == 0:
-                        add(f"sell_mv_rl3_k<{tn},3,{mode}>", ceil(ceil(nr / 64) / 4) * 256, byts, f"{name}{l} A")
+                        for w in (1, 2, 4, 8):
+                            add(f"sell_mv_rl3_k<{tn},3,{mode},{w}>", slice_grid(nr, 1, w), byts, f"{name}{l} A")
                     for w in (1, 2, 4, 8, 16):
                         add(f"sell_mv_k<{tn},{b},{b},{mode},{w}>", slice_grid(nr, b, w), byts, f"{name}{l} A")
                         if b == 1:
@@ -237,7 +238,8 @@ def _kt_bytes(levels):
                 nc, nnzp = L["nagg"], L["nnzP"]
                 pbytes = nnzp * (b * k * tb + 4.0) + nc * k * tb + nr * (4.0 + 2 * b * tb)
                 if b == 3 and l == 0:
-                    add(f"sell_mv_rl3_k<{tn},{k},2>", ceil(ceil(nr / 64) / 4) * 256, pbytes, f"{name}{l} P")
+                    for w in (1, 2, 4, 8):
+                        add(f"sell_mv_rl3_k<{tn},{k},2,{w}>", slice_grid(nr, 1, w), pbytes, f"{name}{l} P")
                 for w in (1, 2, 4, 8, 16):
                     add(f"sell_mv_k<{tn},{b},{k},2,{w}>", slice_grid(nr, b, w), pbytes, f"{name}{l} P")
                     if b == 1:

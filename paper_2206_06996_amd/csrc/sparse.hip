@@ -394,6 +394,7 @@ __device__ __forceinline__ T ld_stream(const T* p) {
     if (BC >= 3 && sizeof(T) == 8) return __builtin_nontemporal_load(p);
     return *p;
 }
+// (6-wide rows: four slots per step measured 5 % slower per FP64 V-cycle at 300k nodes, 1-2 % in FP32)
 template <int BC> struct Unroll { static constexpr int U = BC == 1 ? 8 : (BC <= 4 ? 4 : 2); };
 
 // the BC values of slot t of a lane (layout of sell_vidx)
@@ -492,15 +493,14 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
     if constexpr (BC == 1 && RPS == WAVE) return sell_row_dot_g<T>(o0, o1, lane, ci, v, xat);
     constexpr int U = Unroll<BC>::U;
     T acc = 0;
-    int64_t t = o0;
+    if (o0 >= o1) return acc;
     // software-pipelined as the block-row-lane loop: column indices one step ahead, x gathers and
-    // the next indices issued before the values, one memory round trip per step
+    // the next indices issued before the values, one memory round trip per step; a last step that is
+    // not full repeats the last slot with zero values
     int32_t c[U];     // int32 until used, so that no sign extension waits for the load
-    if (t + U <= o1) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = ci[(t + u) * RPS + cl];
-    }
-    for (; t + U <= o1; t += U) {
+    for (int u = 0; u < U; ++u) c[u] = ci[(o0 + u < o1 ? o0 + u : o1 - 1) * RPS + cl];
+    for (int64_t t = o0; t < o1; t += U) {
         T xx[U][BC], vv[U][BC];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -508,26 +508,23 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
             for (int k = 0; k < BC; ++k) xx[u][k] = xat((int64_t)c[u], k);
         int32_t cn[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            int64_t q = t + U + u < o1 ? t + U + u : o1 - 1;     // stays inside the slice
-            cn[u] = ci[q * RPS + cl];
-        }
+        for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * RPS + cl];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) sell_vals<T, BC>(v, t + u, lane, vv[u]);
+        for (int u = 0; u < U; ++u) {
+            const bool in = t + u < o1;
+            sell_vals<T, BC>(v, in ? t + u : o1 - 1, lane, vv[u]);
+            if (u > 0 && !in) {
+#pragma unroll
+                for (int k = 0; k < BC; ++k) vv[u][k] = 0;
+            }
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < BC; ++k) acc += vv[u][k] * xx[u][k];
 #pragma unroll
         for (int u = 0; u < U; ++u) c[u] = cn[u];
-    }
-    for (; t < o1; ++t) {
-        int64_t c = ci[t * RPS + cl];
-        T vv[BC];
-        sell_vals<T, BC>(v, t, lane, vv);
-#pragma unroll
-        for (int k = 0; k < BC; ++k) acc += vv[k] * xat(c, k);
     }
     return acc;
 }
@@ -554,14 +551,20 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
                                                  const T* __restrict__ v, const T* __restrict__ x,
                                                  const T* __restrict__ b, T* __restrict__ y) {
     constexpr int RPS = WAVE / BR;
-    int wv = threadIdx.x / WAVE;
-    int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
-    int lane = threadIdx.x & (WAVE - 1);
-    bool live = sl < nslices;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const bool live = sl < nslices;
     auto xat = [&](int64_t c, int k) { return x[c * BC + k]; };
-    int cl = lane / BR < RPS ? lane / BR : RPS - 1;
-    T acc = 0;
+    const int cl = lane / BR < RPS ? lane / BR : RPS - 1;
+    T acc = 0, old = 0;
+    int64_t i = -1;
     if (live) {
+        // the finishing wavefront's row data are on their way while the slots stream
+        if (wv % WPS == 0 && lane < RPS * BR) {
+            i = rowid[sl * RPS + cl];
+            if (MODE != 0 && i >= 0) old = MODE == 1 ? b[i * BR + lane % BR] : y[i * BR + lane % BR];
+        }
         int64_t a, e;
         slice_part<WPS, (BR == 1 && BC == 1) ? SELL_G : 1>(off[sl], off[sl + 1], wv % WPS, a, e);
         acc = sell_row_dot<T, BC, RPS>(a, e, lane, cl, ci, v, xat);
@@ -571,16 +574,14 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
         red[wv][lane] = acc;
         __syncthreads();
         if (wv % WPS != 0) return;
+#pragma unroll
         for (int w = 1; w < WPS; ++w) acc += red[wv + w][lane];
     }
-    if (!live || lane >= RPS * BR) return;
-    int64_t i = rowid[sl * RPS + cl];
     if (i < 0) return;
-    int64_t o = i * BR + lane % BR;
+    const int64_t o = i * BR + lane % BR;
     if (MODE == 0) y[o] = acc;
-    else if (MODE == 1) y[o] = b[o] - acc;
-    else if (MODE == 2) y[o] += acc;
-    else y[o] -= acc;
+    else if (MODE == 2) y[o] = old + acc;
+    else y[o] = old - acc;
 }
 
 // waves per slice: doubled while the matrix has fewer than 64K waves in all (256 per CU) and each
@@ -599,6 +600,52 @@ static int waves_per_slice(const DSell<T>& A) {
     return w;
 }
 
+// the 3*BC values of slot t of a lane (layout of rl_vidx): FP64 in 16-byte pairs, FP32 in 16-byte
+// quads, nontemporal
+template <typename T, int BC>
+__device__ __forceinline__ void rl_load(const T* __restrict__ v, int64_t t, int lane, T (&vv)[3 * BC]) {
+    constexpr int E = 3 * BC, Q = sizeof(T) == 8 ? 2 : 4;
+    typedef T VQ __attribute__((ext_vector_type(Q)));
+    const T* base = v + t * E * WAVE;
+#pragma unroll
+    for (int k = 0; k < E / Q; ++k) {
+        const VQ w = __builtin_nontemporal_load(reinterpret_cast<const VQ*>(base + k * Q * WAVE) + lane);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) vv[Q * k + q] = w[q];
+    }
+#pragma unroll
+    for (int e = E - E % Q; e < E; ++e) vv[e] = __builtin_nontemporal_load(base + e * WAVE + lane);
+}
+// r += block * x
+template <typename T, int BC>
+__device__ __forceinline__ void rl_fma(const T* vv, const T* xx, T r[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        T sum = vv[BC * q] * xx[0];
+#pragma unroll
+        for (int k = 1; k < BC; ++k) sum += vv[BC * q + k] * xx[k];
+        r[q] += sum;
+    }
+}
+
+// Wavefronts per slice of the block-row-lane kernels: doubled while the matrix has fewer than RL_WAVES
+// wavefronts in all (two per SIMD) and each keeps two slots or more.  With one wavefront per slice a
+// 7k-node tube puts 109 wavefronts on 1,024 SIMDs and each runs its 15 slots as eight dependent memory
+// round trips.  Measured, one FP64 V-cycle of AMG(A) with one wavefront per slice against this rule: 7k
+// nodes 189 -> 104 us, 22k 316 -> 222, 41k 501 -> 420 (FP32 138 -> 88, 222 -> 165, 345 -> 294).  Bounds
+// of 4,096 and 8,192 wavefronts were 3-5 % slower at 41k nodes, and a slice shared by two wavefronts 2-6 %
+// slower from 100k nodes on, where every SIMD has work without it.
+constexpr int64_t RL_WAVES = 2048;
+constexpr int RL_U = 2;     // slots per step of the shared form
+template <typename T>
+static int rl_waves_per_slice(const DSell<T>& A) {
+    if (A.nslices <= 0) return 1;
+    const int64_t avg = A.slots / A.nslices;
+    int w = 1;
+    while (w < 8 && A.nslices * w < RL_WAVES && avg >= 2 * (w * 2)) w *= 2;
+    return w;
+}
+
 // ---- block-row lanes (3xBC, BC = 3 or 6): r[0..2] = sum over the lane's slots of block * x[col]
 // Two slots per step (both slots' columns, then their values and x vectors are loaded before
 // use); FP32 3x6 takes one slot per step (18 values and an x 6-vector).  Measured on the refined
@@ -612,43 +659,6 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
                                              const T* __restrict__ v, const T* __restrict__ x, T r[3],
                                              int32_t irow = -1, T* dg = nullptr) {
     constexpr int U = (BC == 3 || sizeof(T) == 8) ? 2 : 1, E = 3 * BC;
-    // the E values of slot tt (layout of rl_vidx): FP64 in 16-byte pairs, FP32 in 16-byte quads,
-    // nontemporal
-    auto load_slot = [&](int64_t tt, T (&vv)[E]) {
-        if constexpr (sizeof(T) == 8) {
-            typedef T V2 __attribute__((ext_vector_type(2)));
-            const T* base = v + tt * E * WAVE;
-#pragma unroll
-            for (int k = 0; k < E / 2; ++k) {
-                const V2 w = __builtin_nontemporal_load(reinterpret_cast<const V2*>(base + k * 2 * WAVE) + lane);
-                vv[2 * k] = w.x;
-                vv[2 * k + 1] = w.y;
-            }
-            if constexpr (E % 2 == 1) vv[E - 1] = __builtin_nontemporal_load(base + (E - 1) * WAVE + lane);
-        } else {
-            typedef T V4 __attribute__((ext_vector_type(4)));
-            const T* base = v + tt * E * WAVE;
-#pragma unroll
-            for (int k = 0; k < E / 4; ++k) {
-                const V4 w = __builtin_nontemporal_load(reinterpret_cast<const V4*>(base + k * 4 * WAVE) + lane);
-                vv[4 * k] = w.x;
-                vv[4 * k + 1] = w.y;
-                vv[4 * k + 2] = w.z;
-                vv[4 * k + 3] = w.w;
-            }
-#pragma unroll
-            for (int e = E - E % 4; e < E; ++e) vv[e] = __builtin_nontemporal_load(base + e * WAVE + lane);
-        }
-    };
-    auto fma_block = [&](const T* vv, const T* xx) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            T sum = vv[BC * q] * xx[0];
-#pragma unroll
-            for (int k = 1; k < BC; ++k) sum += vv[BC * q + k] * xx[k];
-            r[q] += sum;
-        }
-    };
     r[0] = r[1] = r[2] = 0;
     bool got = false;
     (void)got;
@@ -673,9 +683,9 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
         }
         __builtin_amdgcn_sched_barrier(0);     // keep the gathers and indices ahead of the values
 #pragma unroll
-        for (int u = 0; u < U; ++u) load_slot(t + u, vv[u]);
+        for (int u = 0; u < U; ++u) rl_load<T, BC>(v, t + u, lane, vv[u]);
 #pragma unroll
-        for (int u = 0; u < U; ++u) fma_block(vv[u], xx[u]);
+        for (int u = 0; u < U; ++u) rl_fma<T, BC>(vv[u], xx[u], r);
         if constexpr (CAP) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -691,10 +701,10 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
     if (U > 1 && t < o1) {
         int64_t c = ci[t * WAVE + lane];
         T vv[E], xx[BC];
-        load_slot(t, vv);
+        rl_load<T, BC>(v, t, lane, vv);
 #pragma unroll
         for (int k = 0; k < BC; ++k) xx[k] = x[c * BC + k];
-        fma_block(vv, xx);
+        rl_fma<T, BC>(vv, xx, r);
         if constexpr (CAP) {
             if (c == irow && !got) {
 #pragma unroll
@@ -704,25 +714,98 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
     }
 }
 
-template <typename T, int BC, int MODE>
-__global__ void __launch_bounds__(256) sell_mv_rl3_k(int64_t nslices, const int32_t* __restrict__ off,
+// The same over one wavefront's part [t, o1) of a slice that several wavefronts share: U slots per
+// step, a last step that is not full repeats the part's last slot with zero values instead of running
+// slot by slot (each slot alone costs two dependent memory round trips).
+template <typename T, int BC, int U>
+__device__ __forceinline__ void rowlane3_dot_part(int64_t t, int64_t o1, int lane, const int32_t* __restrict__ ci,
+                                                  const T* __restrict__ v, const T* __restrict__ x, T r[3]) {
+    constexpr int E = 3 * BC;
+    r[0] = r[1] = r[2] = 0;
+    if (t >= o1) return;
+    int32_t c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = ci[(t + u < o1 ? t + u : o1 - 1) * WAVE + lane];
+    for (; t < o1; t += U) {
+        T vv[U][E], xx[U][BC];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < BC; ++k) xx[u][k] = x[(int64_t)c[u] * BC + k];
+        int32_t cn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * WAVE + lane];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = t + u < o1;
+            rl_load<T, BC>(v, in ? t + u : o1 - 1, lane, vv[u]);
+            if (u > 0 && !in) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) vv[u][e] = 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) rl_fma<T, BC>(vv[u], xx[u], r);
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = cn[u];
+    }
+}
+
+// Sums the parts of the WPS wavefronts of each slice (r, one 3-vector per lane) in the order of the
+// parts; true on the wavefront that holds the sum and finishes the slice.
+template <typename T, int WPS>
+__device__ __forceinline__ bool rl_reduce(int wv, int lane, T r[3]) {
+    __shared__ T red[SliceGroup<WPS>::SPB * WPS][3][WAVE];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) red[wv][q][lane] = r[q];
+    __syncthreads();
+    if (wv % WPS != 0) return false;
+#pragma unroll
+    for (int w = 1; w < WPS; ++w)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) r[q] += red[wv + w][q][lane];
+    return true;
+}
+
+template <typename T, int BC, int MODE, int WPS>
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_t nslices, const int32_t* __restrict__ off,
                                                      const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                      const T* __restrict__ v, const T* __restrict__ x,
                                                      const T* __restrict__ b, T* __restrict__ y) {
-    int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * 4 + threadIdx.x / WAVE;
-    if (sl >= nslices) return;
-    int lane = threadIdx.x & (WAVE - 1);
-    T r[3];
-    rowlane3_dot<T, BC>(off[sl], off[sl + 1], lane, ci, v, x, r);
-    int64_t i = rowid[sl * WAVE + lane];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    if (WPS == 1 && sl >= nslices) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const bool live = sl < nslices;
+    T r[3] = {0, 0, 0}, old[3];
+    int64_t i = -1;
+    if constexpr (WPS == 1) {
+        rowlane3_dot<T, BC>(off[sl], off[sl + 1], lane, ci, v, x, r);
+        i = rowid[sl * WAVE + lane];
+    } else {
+        if (live) {
+            // the finishing wavefront's row data are on their way while the slots stream
+            if (wv % WPS == 0) {
+                i = rowid[sl * WAVE + lane];
+                if (MODE != 0 && i >= 0)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) old[q] = MODE == 1 ? b[i * 3 + q] : y[i * 3 + q];
+            }
+            int64_t a, e;
+            slice_part<WPS>(off[sl], off[sl + 1], wv % WPS, a, e);
+            rowlane3_dot_part<T, BC, RL_U>(a, e, lane, ci, v, x, r);
+        }
+        if (!rl_reduce<T, WPS>(wv, lane, r) || !live) return;
+    }
     if (i < 0) return;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         int64_t o = i * 3 + q;
+        if (WPS == 1 && MODE != 0) old[q] = MODE == 1 ? b[o] : y[o];
         if (MODE == 0) y[o] = r[q];
-        else if (MODE == 1) y[o] = b[o] - r[q];
-        else if (MODE == 2) y[o] += r[q];
-        else y[o] -= r[q];
+        else if (MODE == 1 || MODE == 3) y[o] = old[q] - r[q];
+        else y[o] = old[q] + r[q];
     }
 }
 
@@ -756,17 +839,27 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
 template <typename T>
 void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
     if (A.rowlane) {
-        int64_t nblk = cdiv(A.nslices, 4);
-        if (nblk == 0) return;
-#define RL(BC)                                                                                                     \
-    switch (mode) {                                                                                                \
-        case 0: sell_mv_rl3_k<T, BC, 0><<<nblk, 256, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-        case 1: sell_mv_rl3_k<T, BC, 1><<<nblk, 256, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-        case 2: sell_mv_rl3_k<T, BC, 2><<<nblk, 256, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-        default: sell_mv_rl3_k<T, BC, 3><<<nblk, 256, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+        if (A.nslices == 0) return;
+        const int wps = rl_waves_per_slice(A);
+#define RLW(BC, W)                                                                                                  \
+    {                                                                                                               \
+        constexpr int W_ = W;                                                                                       \
+        dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W_>::SPB)), t(SliceGroup<W_>::THREADS);                         \
+        switch (mode) {                                                                                             \
+            case 0: sell_mv_rl3_k<T, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv_rl3_k<T, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv_rl3_k<T, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv_rl3_k<T, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+        }                                                                                                           \
     }
+#define RL(BC)               \
+    if (wps == 1) RLW(BC, 1) \
+    else if (wps == 2) RLW(BC, 2) \
+    else if (wps == 4) RLW(BC, 4) \
+    else RLW(BC, 8)
         if (A.bc == 3) { RL(3) } else { RL(6) }
 #undef RL
+#undef RLW
         check_launch("sell_mv");
         return;
     }
@@ -870,12 +963,27 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
                                                 const T* __restrict__ xin, T* __restrict__ d, T* __restrict__ xout,
                                                 T c1, T c2) {
     constexpr int RPS = WAVE / B;
-    int wv = threadIdx.x / WAVE;
-    int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
-    bool live = sl < nslices;
-    int lane = threadIdx.x & (WAVE - 1);
-    int cl = lane / B < RPS ? lane / B : RPS - 1;
-    T acc = 0;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const bool live = sl < nslices;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int cl = lane / B < RPS ? lane / B : RPS - 1;
+    const int r = lane % B;
+    T acc = 0, bi = 0, di = 0, xi = 0, Di[B];
+    int64_t i = -1;
+    if (live && wv % WPS == 0 && lane < RPS * B) i = rowid[sl * RPS + cl];
+    const bool valid = i >= 0;
+    const int64_t o = i * B + r;
+#pragma unroll
+    for (int k = 0; k < B; ++k) Di[k] = 0;
+    if (valid) {
+        // the finishing wavefront's row data are on their way while the slots stream
+        bi = b[o];
+        if (RD) di = d[o];
+        if (!ZERO) xi = xin[o];
+#pragma unroll
+        for (int k = 0; k < B; ++k) Di[k] = Dinv[o * B + k];
+    }
     if (!ZERO && live) {
         auto xat = [&](int64_t c, int k) { return xin[c * B + k]; };
         int64_t a, e;
@@ -887,57 +995,83 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
         red[wv][lane] = acc;
         __syncthreads();
         if (wv % WPS != 0) return;
+#pragma unroll
         for (int w = 1; w < WPS; ++w) acc += red[wv + w][lane];
     }
     if (!live) return;
-    int64_t i = rowid[sl * RPS + cl];
-    int r = lane % B;
-    bool valid = lane < RPS * B && i >= 0;
-    int64_t o = i * B + r;
-    T res = valid ? b[o] - acc : (T)0;
+    const T res = valid ? bi - acc : (T)0;
     T z = 0;
-    int base = lane - r;
+    const int base = lane - r;
 #pragma unroll
     for (int k = 0; k < B; ++k) {
-        T rk = B == 1 ? res : __shfl(res, base + k, WAVE);
-        if (valid) z += Dinv[o * B + k] * rk;
+        const T rk = B == 1 ? res : __shfl(res, base + k, WAVE);
+        z += Di[k] * rk;
     }
     if (!valid) return;
     T dn = c2 * z;
-    if (RD) dn += c1 * d[o];
+    if (RD) dn += c1 * di;
     if (WD) d[o] = dn;
-    xout[o] = ZERO ? dn : xin[o] + dn;
+    xout[o] = ZERO ? dn : xi + dn;
 }
 
-// block-row lanes (3x3): the lane holds its block row's whole residual, so D^-1 applies in-lane
-template <typename T, bool RD, bool WD, bool ZERO>
-__global__ void __launch_bounds__(256) smooth_rl3_k(int64_t nslices, const int32_t* __restrict__ off,
+// block-row lanes (3x3): the lane holds its block row's whole residual, so D^-1 applies in-lane.
+// WPS = 1 (large matrices): the diagonal block is captured while the row streams by and D^-1 is not
+// read (72 bytes per row less; measured on the refined tube: the FP64 steps 6-11 % faster, FP32 mixed
+// solves 1.6 %).  WPS > 1 (few slices): the wavefronts of a slice share its slots, and the finishing one
+// loads its rows' right-hand side, D^-1, x and d before the slots, so that the epilogue waits for no
+// memory.
+template <typename T, bool RD, bool WD, bool ZERO, int WPS>
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t nslices, const int32_t* __restrict__ off,
                                                     const int32_t* __restrict__ rowid,
                                                     const int32_t* __restrict__ ci, const T* __restrict__ v,
                                                     const T* __restrict__ Dinv, const T* __restrict__ b,
                                                     const T* __restrict__ xin, T* __restrict__ d, T* __restrict__ xout,
                                                     T c1, T c2) {
-    int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * 4 + threadIdx.x / WAVE;
-    if (sl >= nslices) return;
-    int lane = threadIdx.x & (WAVE - 1);
-    T r[3] = {0, 0, 0};
-    const int64_t i = rowid[sl * WAVE + lane];
-    // the diagonal block is captured while the row streams by and D^-1 is not read (72 bytes per
-    // row less; measured on the refined tube: the FP64 steps 6-11 % faster, FP32 mixed solves 1.6 %)
-    constexpr bool CAP = true;
-    T dg[9];
-    if (!ZERO) rowlane3_dot<T, 3, CAP>(off[sl], off[sl + 1], lane, ci, v, xin, r, (int32_t)i, dg);
-    if (i < 0) return;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    if (WPS == 1 && sl >= nslices) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const bool live = sl < nslices;
+    T r[3] = {0, 0, 0}, bi[3], di[3], xi[3], dg[9];
+    int64_t i = -1;
+    if (WPS == 1 || (live && wv % WPS == 0)) i = rowid[sl * WAVE + lane];
+    auto load_rows = [&]() {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            bi[q] = b[i * 3 + q];
+            if (RD) di[q] = d[i * 3 + q];
+            if (!ZERO) xi[q] = xin[i * 3 + q];
+        }
+    };
+    if constexpr (WPS == 1) {
+        if (!ZERO) rowlane3_dot<T, 3, true>(off[sl], off[sl + 1], lane, ci, v, xin, r, (int32_t)i, dg);
+        if (i < 0) return;
+        load_rows();
+    } else {
+        if (i >= 0) {
+            load_rows();
+#pragma unroll
+            for (int e = 0; e < 9; ++e) dg[e] = Dinv[i * 9 + e];
+        }
+        if (live) {
+            int64_t a, e;
+            slice_part<WPS>(off[sl], off[sl + 1], wv % WPS, a, e);
+            rowlane3_dot_part<T, 3, RL_U>(a, e, lane, ci, v, xin, r);
+        }
+        if (!rl_reduce<T, WPS>(wv, lane, r) || i < 0) return;
+    }
     T res[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) res[q] = b[i * 3 + q] - r[q];
-    // z = D^-1 res: the adjugate of the captured block over its determinant (the stored inverse in
-    // the first step, which has no matrix product)
+    for (int q = 0; q < 3; ++q) res[q] = bi[q] - r[q];
+    // z = D^-1 res: the adjugate of the captured block over its determinant, or the stored inverse
     T z[3];
-    if (ZERO || !CAP) {
-        const T* Di = Dinv + i * 9;
+    if (ZERO || WPS > 1) {
+        if (WPS == 1) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) z[q] = Di[3 * q] * res[0] + Di[3 * q + 1] * res[1] + Di[3 * q + 2] * res[2];
+            for (int e = 0; e < 9; ++e) dg[e] = Dinv[i * 9 + e];
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) z[q] = dg[3 * q] * res[0] + dg[3 * q + 1] * res[1] + dg[3 * q + 2] * res[2];
     } else {
         const T a0 = dg[4] * dg[8] - dg[5] * dg[7], a1 = dg[2] * dg[7] - dg[1] * dg[8], a2 = dg[1] * dg[5] - dg[2] * dg[4];
         const T a3 = dg[5] * dg[6] - dg[3] * dg[8], a4 = dg[0] * dg[8] - dg[2] * dg[6], a5 = dg[2] * dg[3] - dg[0] * dg[5];
@@ -949,37 +1083,46 @@ __global__ void __launch_bounds__(256) smooth_rl3_k(int64_t nslices, const int32
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        int64_t o = i * 3 + q;
+        const int64_t o = i * 3 + q;
         T dn = c2 * z[q];
-        if (RD) dn += c1 * d[o];
+        if (RD) dn += c1 * di[q];
         if (WD) d[o] = dn;
-        xout[o] = ZERO ? dn : xin[o] + dn;
+        xout[o] = ZERO ? dn : xi[q] + dn;
     }
 }
 
 template <typename T>
 static void smooth_rl3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, T c1, T c2,
                        bool rd, bool wd, bool zero, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    int64_t nblk = cdiv(A.nslices, 4);
-    if (nblk == 0) return;
-#define SK(RD, WD, Z)                                                                                              \
+    if (A.nslices == 0) return;
+    const int wps = zero ? 1 : rl_waves_per_slice(A);
+#define SKW(RD, WD, Z, W)                                                                                          \
     do {                                                                                                           \
+        dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), t(SliceGroup<W>::THREADS);                          \
         if (e0)                                                                                                    \
-            hipExtLaunchKernelGGL((smooth_rl3_k<T, RD, WD, Z>), dim3((unsigned)nblk), dim3(256), 0, s, e0, e1, 0,  \
+            hipExtLaunchKernelGGL((smooth_rl3_k<T, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0,                          \
                                   A.nslices, (const int32_t*)A.off, (const int32_t*)A.rowid, (const int32_t*)A.ci, \
                                   (const T*)A.v, Dinv, b, xin, d, xout, c1, c2);                                   \
         else                                                                                                       \
-            smooth_rl3_k<T, RD, WD, Z><<<nblk, 256, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, \
-                                                           xout, c1, c2);                                          \
+            smooth_rl3_k<T, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,   \
+                                                          xout, c1, c2);                                           \
+    } while (0)
+#define SK(RD, WD, Z)                           \
+    do {                                        \
+        if (wps == 1) SKW(RD, WD, Z, 1);        \
+        else if (wps == 2) SKW(RD, WD, Z, 2);   \
+        else if (wps == 4) SKW(RD, WD, Z, 4);   \
+        else SKW(RD, WD, Z, 8);                 \
     } while (0)
     if (zero) {
-        if (wd) SK(false, true, true); else SK(false, false, true);
+        if (wd) SKW(false, true, true, 1); else SKW(false, false, true, 1);
     } else if (rd) {
         if (wd) SK(true, true, false); else SK(true, false, false);
     } else {
         if (wd) SK(false, true, false); else SK(false, false, false);
     }
 #undef SK
+#undef SKW
     check_launch("smooth_step");
 }
 
