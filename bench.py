@@ -190,8 +190,13 @@ def _kt_bytes(levels):
     def add(key, grid, byts, where):
         shapes.setdefault(key, {}).setdefault(grid, (byts, where))
 
-    def slice_grid(nr, b, wps):
-        nsl = ceil(nr / (64 // b))
+    def slice_grid(nr, b, wps, nnz=0):
+        sl, avg, sp = ceil(nr / (64 // b)), nnz // nr, 1
+        if b == 6 and nnz:       # row positions per block row, as sell_parts of csrc/sparse.hip
+            sp = 5 if 2 * sl < 512 and avg >= 40 else 2 if sl < 512 and avg >= 16 else 1
+        while b == 1 and sp < 16 and sl * sp < 2048 and avg >= 32 * sp:
+            sp *= 2
+        nsl = ceil(nr / (64 // b // sp))
         spb = 1 if wps >= 4 else 4 // wps
         return ceil(nsl / spb) * spb * wps * 64
     for name, lv in H.items():
@@ -215,12 +220,12 @@ def _kt_bytes(levels):
                                 add(f"smooth_rl3_k<{tn},{rd},{wd},0,{w}>", slice_grid(nr, 1, w), byts, f"{name}{l}")
                             add(f"smooth_rl3_k<{tn},0,{wd},1,1>", slice_grid(nr, 1, 1), zero, f"{name}{l}")
                         for w in (1, 2, 4, 8, 16):
-                            add(f"smooth_k<{tn},{b},{rd},{wd},0,{w}>", slice_grid(nr, b, w), byts, f"{name}{l}")
-                            add(f"smooth_k<{tn},{b},0,{wd},1,{w}>", slice_grid(nr, b, w), zero, f"{name}{l}")
+                            add(f"smooth_k<{tn},{b},{rd},{wd},0,{w}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l}")
+                            add(f"smooth_k<{tn},{b},0,{wd},1,{w}>", slice_grid(nr, b, w, nnz), zero, f"{name}{l}")
                             if b == 1:
-                                add(f"smooth3_k<{tn},{rd},{wd},0,{w}>", slice_grid(nr, 1, w),
+                                add(f"smooth3_k<{tn},{rd},{wd},0,{w}>", slice_grid(nr, 1, w, nnz),
                                     nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * (3 + rd + wd)), f"{name}{l}")
-                                add(f"smooth3_k<{tn},0,{wd},1,{w}>", slice_grid(nr, 1, w), nr * (4.0 + 3 * tb * (2 + wd)),
+                                add(f"smooth3_k<{tn},0,{wd},1,{w}>", slice_grid(nr, 1, w, nnz), nr * (4.0 + 3 * tb * (2 + wd)),
                                     f"{name}{l}")
                 # products with A_l (residual y = b - A x: x, b read, y written)
                 for mode in (0, 1, 3):
@@ -230,9 +235,9 @@ def _kt_bytes(levels):
                         for w in (1, 2, 4, 8):
                             add(f"sell_mv_rl3_k<{tn},3,{mode},{w}>", slice_grid(nr, 1, w), byts, f"{name}{l} A")
                     for w in (1, 2, 4, 8, 16):
-                        add(f"sell_mv_k<{tn},{b},{b},{mode},{w}>", slice_grid(nr, b, w), byts, f"{name}{l} A")
+                        add(f"sell_mv_k<{tn},{b},{b},{mode},{w}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l} A")
                         if b == 1:
-                            add(f"sell_mv3_k<{tn},{mode},{w}>", slice_grid(nr, 1, w), nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * nv),
+                            add(f"sell_mv3_k<{tn},{mode},{w}>", slice_grid(nr, 1, w, nnz), nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * nv),
                                 f"{name}{l} A")
                 # prolongation y += P x (P: nr x nc blocks b x k; x coarse, y read and written)
                 nc, nnzp = L["nagg"], L["nnzP"]

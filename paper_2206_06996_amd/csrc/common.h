@@ -295,6 +295,9 @@ struct DBsr {
 // is needed.
 //   col of (slice s, slot t, block row j of the slice):   ci[(off[s] + t) * rps + j]
 //   entry k of lane l's row segment:                       v[((off[s] + t) * bc + k) * 64 + l]
+// On small 1x1 and 6x6 matrices sp neighbouring row positions share one block row: position j0 + p (p < sp)
+// holds its entries p, p + sp, ..., their sums are added across the lanes, and rowid names the block row
+// at the first of them (-1 at the others).
 //
 // Block-row lanes (3x3 blocks: the velocity block and its FP32 copy; 3x6: the prolongators of
 // AMG(A)).  A slice is one wavefront covering rps = 64 block rows, one per lane; the lane computes
@@ -315,7 +318,8 @@ template <typename T>
 struct DSell {
     int64_t nr = 0, nc = 0;
     int br = 0, bc = 0;
-    int rps = 0;                // block rows per slice
+    int rps = 0;                // row positions per slice (block rows, or their parts)
+    int sp = 1;                 // scalar-row lanes: neighbouring positions that share a block row
     bool rowlane = false;       // block-row lanes (3x3) instead of scalar-row lanes
     int64_t nslices = 0;
     int64_t slots = 0;          // sum over slices of the slice length

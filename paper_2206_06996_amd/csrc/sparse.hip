@@ -4,6 +4,8 @@
 // are not dense contractions).
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace scr {
@@ -166,7 +168,8 @@ void cast_f2d(const float* a, double* b, int64_t n, hipStream_t s) {
 
 // ============================================================== sliced ELL
 // rank of block row i within its window: rows ordered by decreasing length, ties by index
-__global__ void sell_rank_k(const int32_t* __restrict__ rp, int64_t nr, int64_t win, int32_t* __restrict__ rowid) {
+__global__ void sell_rank_k(const int32_t* __restrict__ rp, int64_t nr, int64_t win, int rps, int sp,
+                            int32_t* __restrict__ rowid) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nr) return;
     int64_t w0 = (i / win) * win, w1 = w0 + win < nr ? w0 + win : nr;
@@ -176,18 +179,19 @@ __global__ void sell_rank_k(const int32_t* __restrict__ rp, int64_t nr, int64_t 
         int32_t lj = rp[j + 1] - rp[j];
         rank += (lj > li) || (lj == li && j < i);
     }
-    rowid[w0 + rank] = (int32_t)i;
+    const int64_t rows = rps / sp, at = w0 + rank;     // block rows per slice
+    rowid[at / rows * rps + at % rows * sp] = (int32_t)i;
 }
 
 __global__ void sell_slice_len(const int32_t* __restrict__ rp, const int32_t* __restrict__ rowid, int rps,
-                               int64_t nslices, int grp, int32_t* __restrict__ len) {
+                               int64_t nslices, int grp, int sp, int32_t* __restrict__ len) {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= nslices) return;
     int32_t m = 0;
     for (int64_t j = s * rps; j < (s + 1) * rps; ++j) {
         int32_t i = rowid[j];
         if (i < 0) continue;
-        int32_t l = rp[i + 1] - rp[i];
+        int32_t l = (rp[i + 1] - rp[i] + sp - 1) / sp;
         m = l > m ? l : m;
     }
     len[s] = (m + grp - 1) / grp * grp;
@@ -226,8 +230,8 @@ __device__ __forceinline__ void sell_fill_part(int64_t g, int64_t& o0, int64_t e
 
 template <typename T>
 __global__ void sell_fill(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, const double* __restrict__ v,
-                          int br, int bc, int rps, const int32_t* __restrict__ rowid, const int32_t* __restrict__ off,
-                          int32_t* __restrict__ sci, T* __restrict__ sv, int64_t nslices) {
+                          int br, int bc, int rps, int sp, const int32_t* __restrict__ rowid,
+                          const int32_t* __restrict__ off, int32_t* __restrict__ sci, T* __restrict__ sv, int64_t nslices) {
     const bool grouped = br == 1 && bc == 1;
     int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t s = g / (SELL_FILL_PARTS * WAVE);
@@ -235,7 +239,8 @@ __global__ void sell_fill(const int32_t* __restrict__ rp, const int32_t* __restr
     int lane = (int)(g % WAVE);
     int j = lane / br;
     int r = lane % br;
-    int64_t i = j < rps ? rowid[s * rps + j] : -1;
+    const int part = j % sp;
+    int64_t i = j < rps ? rowid[s * rps + j - part] : -1;
     bool valid = i >= 0;
     int64_t o0 = off[s], o1, e1 = off[s + 1];
     sell_fill_part(g, o0, e1, o1);
@@ -245,7 +250,9 @@ __global__ void sell_fill(const int32_t* __restrict__ rp, const int32_t* __restr
         lo = rp[i]; hi = rp[i + 1];
         pad = hi > lo ? ci[hi - 1] : 0;
     }
-    const int64_t ob = off[s];   // first slot of the slice: slot t holds entry lo + (t - ob) of the row
+    // slot t of part `part` holds entry lo + (t - ob) sp + part of the row (ob: the slice's first slot)
+    const int64_t ob = off[s];
+    lo += part;
     if (grouped) {
         // whole groups of four slots (the slice's slot range and each part are multiples of four)
         typedef int32_t I4 __attribute__((ext_vector_type(4)));
@@ -255,7 +262,7 @@ __global__ void sell_fill(const int32_t* __restrict__ rp, const int32_t* __restr
             V4 vv;
 #pragma unroll
             for (int u = 0; u < SELL_G; ++u) {
-                const int64_t q = lo + (t + u - ob);
+                const int64_t q = lo + (t + u - ob) * sp;
                 const bool real = valid && q < hi;
                 cc[u] = real ? ci[q] : pad;
                 vv[u] = real ? (T)v[q] : (T)0;
@@ -268,7 +275,7 @@ __global__ void sell_fill(const int32_t* __restrict__ rp, const int32_t* __restr
     bool colwriter = j < rps && r == 0;
     const bool paired = sell_paired(bc, (int)sizeof(T));
     for (int64_t t = o0; t < o1; ++t) {
-        int64_t q = lo + (t - ob);
+        int64_t q = lo + (t - ob) * sp;
         bool real = valid && q < hi;
         if (colwriter) sci[t * rps + j] = real ? ci[q] : pad;
         for (int k = 0; k < bc; ++k)
@@ -316,21 +323,42 @@ __global__ void sell_fill_rowlane(const int32_t* __restrict__ rp, const int32_t*
     }
 }
 
+// Row positions that share a block row (1x1 and 6x6 matrices): doubled, or 2 and 5 of the ten positions of
+// a 6-wide slice, while the matrix has fewer than SP_SLICES slices and each position keeps two steps of
+// slots (8 slots a step for 1x1, 2 for 6x6, where four steps are kept).  Coarse levels have few, long rows:
+// 200 block rows of 200 blocks are 20 slices, which 16 wavefronts each leave most of the chip idle and
+// walk in a dozen dependent memory round trips; neighbouring lanes of a shared row also gather
+// neighbouring x.  Measured against one position per row, one V-cycle of AMG(S^) in FP64 / FP32: 22k
+// nodes 329 / 304 -> 198 / 188 us, 100k 707 / 606 -> 486 / 403, 300k 1544 / 1111 -> 1265 / 845, 700k 3305
+// / 2428 -> 2844 / 2061; of AMG(A) at 41k nodes 395 / 281 -> 346 / 259.  Bounds of 1,024 and 4,096 slices
+// were within 2 % of 2,048 for 1x1; 256 instead of 512 for 6x6 was 8 % slower at 41k nodes.
+constexpr int64_t SP_SLICES_1 = 2048, SP_SLICES_6 = 512;
+static int sell_parts(const DBsr& A) {
+    if (A.nr == 0 || A.br != A.bc || (A.br != 1 && A.br != 6)) return 1;
+    const int64_t avg = A.nnzb / A.nr, sl = cdiv(A.nr, WAVE / A.br);
+    if (A.br == 6) return 2 * sl < SP_SLICES_6 && avg >= 40 ? 5 : sl < SP_SLICES_6 && avg >= 16 ? 2 : 1;
+    int sp = 1;
+    while (sp < 16 && sl * sp < SP_SLICES_1 && avg >= 32 * sp) sp *= 2;
+    return sp;
+}
+
 template <typename T>
 DSell<T> sell_from_bsr(const DBsr& A, Arena& ar, hipStream_t s) {
     DSell<T> S;
     S.nr = A.nr; S.nc = A.nc; S.br = A.br; S.bc = A.bc; S.nnzb = A.nnzb;
     S.rowlane = A.br == 3 && (A.bc == 3 || A.bc == 6);
     S.rps = S.rowlane ? WAVE : WAVE / A.br;
-    S.nslices = cdiv(A.nr, S.rps);
+    S.sp = sell_parts(A);
+    const int rows = S.rps / S.sp;     // block rows per slice
+    S.nslices = cdiv(A.nr, rows);
     if (S.nslices == 0) return S;
     S.rowid = ar.make<int32_t>(S.nslices * S.rps);
     fill_i32(S.rowid, -1, S.nslices * S.rps, s);
-    int64_t win = (int64_t)(S.rowlane ? SELL_SIGMA_ROWLANE : SELL_SIGMA) * S.rps;
-    sell_rank_k<<<cdiv(A.nr, 256), 256, 0, s>>>(A.rp, A.nr, win, S.rowid);
+    int64_t win = (int64_t)(S.rowlane ? SELL_SIGMA_ROWLANE : SELL_SIGMA) * rows;
+    sell_rank_k<<<cdiv(A.nr, 256), 256, 0, s>>>(A.rp, A.nr, win, S.rps, S.sp, S.rowid);
     int32_t* len = ar.make<int32_t>(S.nslices);
     const int grp = (!S.rowlane && A.br == 1 && A.bc == 1) ? SELL_G : 1;
-    sell_slice_len<<<cdiv(S.nslices, 256), 256, 0, s>>>(A.rp, S.rowid, S.rps, S.nslices, grp, len);
+    sell_slice_len<<<cdiv(S.nslices, 256), 256, 0, s>>>(A.rp, S.rowid, S.rps, S.nslices, grp, S.sp, len);
     check_launch("sell_slice_len");
     S.off = ar.make<int32_t>(S.nslices + 1);
     S.slots = scan_i32(len, S.off, S.nslices, ar, s);
@@ -342,7 +370,7 @@ DSell<T> sell_from_bsr(const DBsr& A, Arena& ar, hipStream_t s) {
                                                                         S.ci, S.v, S.nslices);
     } else {
         S.v = ar.make<T>(S.slots * WAVE * A.bc + 1);
-        sell_fill<T><<<cdiv(S.nslices * SELL_FILL_PARTS * WAVE, 256), 256, 0, s>>>(A.rp, A.ci, A.v, A.br, A.bc, S.rps, S.rowid, S.off,
+        sell_fill<T><<<cdiv(S.nslices * SELL_FILL_PARTS * WAVE, 256), 256, 0, s>>>(A.rp, A.ci, A.v, A.br, A.bc, S.rps, S.sp, S.rowid, S.off,
                                                                 S.ci, S.v, S.nslices);
     }
     check_launch("sell_fill");
@@ -451,11 +479,10 @@ __device__ __forceinline__ T sell_row_dot_g(int64_t o0, int64_t o1, int lane, co
     T acc = 0;
     const int64_t g1 = o1 / SELL_G;
     int64_t g = o0 / SELL_G;
+    if (g >= g1) return acc;
     SellI4 c[2];
-    if (g + 2 <= g1) {
-        c[0] = sell_gidx(ci, g, lane);
-        c[1] = sell_gidx(ci, g + 1, lane);
-    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) c[u] = sell_gidx(ci, g + u < g1 ? g + u : g1 - 1, lane);
     for (; g + 2 <= g1; g += 2) {
         T xx[2][SELL_G], vv[2][SELL_G];
 #pragma unroll
@@ -475,12 +502,13 @@ __device__ __forceinline__ T sell_row_dot_g(int64_t o0, int64_t o1, int lane, co
 #pragma unroll
         for (int u = 0; u < 2; ++u) c[u] = cn[u];
     }
-    for (; g < g1; ++g) {
-        const SellI4 cc = sell_gidx(ci, g, lane);
-        T vv[SELL_G];
+    if (g < g1) {     // its indices are already here
+        T xx[SELL_G], vv[SELL_G];
+#pragma unroll
+        for (int j = 0; j < SELL_G; ++j) xx[j] = xat((int64_t)c[0][j], 0);
         sell_gvals<T>(v, g, lane, vv);
 #pragma unroll
-        for (int j = 0; j < SELL_G; ++j) acc += vv[j] * xat((int64_t)cc[j], 0);
+        for (int j = 0; j < SELL_G; ++j) acc += vv[j] * xx[j];
     }
     return acc;
 }
@@ -496,25 +524,27 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
     if (o0 >= o1) return acc;
     // software-pipelined as the block-row-lane loop: column indices one step ahead, x gathers and
     // the next indices issued before the values, one memory round trip per step; a last step that is
-    // not full repeats the last slot with zero values
+    // not full takes one slot alone (U = 2) or repeats the last slot with zero values
     int32_t c[U];     // int32 until used, so that no sign extension waits for the load
 #pragma unroll
     for (int u = 0; u < U; ++u) c[u] = ci[(o0 + u < o1 ? o0 + u : o1 - 1) * RPS + cl];
-    for (int64_t t = o0; t < o1; t += U) {
+    auto step = [&](int64_t t, auto full) {
         T xx[U][BC], vv[U][BC];
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < BC; ++k) xx[u][k] = xat((int64_t)c[u], k);
         int32_t cn[U];
+        if (full) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * RPS + cl];
+            for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * RPS + cl];
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = t + u < o1;
+            const bool in = full || t + u < o1;
             sell_vals<T, BC>(v, in ? t + u : o1 - 1, lane, vv[u]);
-            if (u > 0 && !in) {
+            if (!in) {
 #pragma unroll
                 for (int k = 0; k < BC; ++k) vv[u][k] = 0;
             }
@@ -523,8 +553,24 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < BC; ++k) acc += vv[u][k] * xx[u][k];
+        if (full) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = cn[u];
+            for (int u = 0; u < U; ++u) c[u] = cn[u];
+        }
+    };
+    int64_t t = o0;
+    for (; t + U <= o1; t += U) step(t, std::true_type{});
+    if constexpr (U == 2) {
+        if (t < o1) {     // its index is already here
+            T xx[BC], vv[BC];
+#pragma unroll
+            for (int k = 0; k < BC; ++k) xx[k] = xat((int64_t)c[0], k);
+            sell_vals<T, BC>(v, t, lane, vv);
+#pragma unroll
+            for (int k = 0; k < BC; ++k) acc += vv[k] * xx[k];
+        }
+    } else if (t < o1) {
+        step(t, std::false_type{});
     }
     return acc;
 }
@@ -545,8 +591,22 @@ __device__ __forceinline__ void slice_part(int64_t o0, int64_t o1, int part, int
     b = o0 + G * (len * (part + 1) / WPS);
 }
 
+// sum over the sp neighbouring row positions that share a block row, on the lanes of the first one
+// (every lane of the wavefront takes part)
+template <int BR, typename T>
+__device__ __forceinline__ T parts_sum(T acc, int lane, int sp) {
+    if constexpr (BR == 1) {
+        for (int o = 1; o < sp; o <<= 1) acc += __shfl_xor(acc, o, WAVE);
+        return acc;
+    } else {
+        T sum = acc;
+        for (int p = 1; p < sp; ++p) sum += __shfl(acc, lane + p * BR, WAVE);
+        return sum;
+    }
+}
+
 template <typename T, int BR, int BC, int MODE, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t nslices, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
                                                  const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ x,
                                                  const T* __restrict__ b, T* __restrict__ y) {
@@ -577,6 +637,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
 #pragma unroll
         for (int w = 1; w < WPS; ++w) acc += red[wv + w][lane];
     }
+    if (BR == BC) acc = parts_sum<BR>(acc, lane, sp);
     if (i < 0) return;
     const int64_t o = i * BR + lane % BR;
     if (MODE == 0) y[o] = acc;
@@ -586,15 +647,17 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
 
 // waves per slice: doubled while the matrix has fewer than 64K waves in all (256 per CU) and each
 // wave keeps at least 3 of the slice's average slots, up to 8 waves per slice; on small matrices
-// (fewer than 512 slices, where the time is the latency of each wave's chain of dependent loads)
-// at least 4 slots and up to 16 waves.  Measured on the refined tube (A/B on one box): a cap of 64K
+// (fewer than 512 slices, 2,048 for 6-wide rows, where the time is the latency of each wave's chain of
+// dependent loads) at least 4 slots (one step of 2 for 6-wide rows: AMG(A) in FP32 at 100k nodes 427 ->
+// 392 us a V-cycle, in FP64 at 41k 346 -> 334) and up to 16 waves.  Measured on the refined tube (A/B on one box): a cap of 64K
 // instead of 16K waves puts 8 waves on each slice of AMG(A)'s level 1 (55 slots) and 4 on AMG(S^)'s
 // level 0 and makes the FP64 solve 5 % faster; 16 waves per slice on level 1 is slower again.
 template <typename T>
 static int waves_per_slice(const DSell<T>& A) {
     if (A.nslices <= 0) return 1;
     int64_t avg = A.slots / A.nslices;
-    int wmax = A.nslices < 512 ? 16 : 8, per = A.nslices < 512 ? 4 : 3;
+    const bool few = A.nslices < (A.br == 6 ? 2048 : 512);
+    const int wmax = few ? 16 : 8, per = !few ? 3 : A.br == 6 ? 2 : 4;
     int w = 1;
     while (w < wmax && A.nslices * w < 65536 && avg >= per * (w * 2)) w *= 2;
     return w;
@@ -636,7 +699,6 @@ __device__ __forceinline__ void rl_fma(const T* vv, const T* xx, T r[3]) {
 // of 4,096 and 8,192 wavefronts were 3-5 % slower at 41k nodes, and a slice shared by two wavefronts 2-6 %
 // slower from 100k nodes on, where every SIMD has work without it.
 constexpr int64_t RL_WAVES = 2048;
-constexpr int RL_U = 2;     // slots per step of the shared form
 template <typename T>
 static int rl_waves_per_slice(const DSell<T>& A) {
     if (A.nslices <= 0) return 1;
@@ -714,41 +776,40 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
     }
 }
 
-// The same over one wavefront's part [t, o1) of a slice that several wavefronts share: U slots per
-// step, a last step that is not full repeats the part's last slot with zero values instead of running
-// slot by slot (each slot alone costs two dependent memory round trips).
-template <typename T, int BC, int U>
+// The same over one wavefront's part [t, o1) of a slice that several wavefronts share: two slots per
+// step; the index of a last single slot is here already, so that it costs one memory round trip.
+template <typename T, int BC>
 __device__ __forceinline__ void rowlane3_dot_part(int64_t t, int64_t o1, int lane, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x, T r[3]) {
     constexpr int E = 3 * BC;
     r[0] = r[1] = r[2] = 0;
     if (t >= o1) return;
-    int32_t c[U];
+    int32_t c[2];
 #pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = ci[(t + u < o1 ? t + u : o1 - 1) * WAVE + lane];
-    for (; t < o1; t += U) {
-        T vv[U][E], xx[U][BC];
+    for (int u = 0; u < 2; ++u) c[u] = ci[(t + u < o1 ? t + u : o1 - 1) * WAVE + lane];
+    for (; t + 2 <= o1; t += 2) {
+        T vv[2][E], xx[2][BC];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int k = 0; k < BC; ++k) xx[u][k] = x[(int64_t)c[u] * BC + k];
-        int32_t cn[U];
+        int32_t cn[2];
 #pragma unroll
-        for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * WAVE + lane];
+        for (int u = 0; u < 2; ++u) cn[u] = ci[(t + 2 + u < o1 ? t + 2 + u : o1 - 1) * WAVE + lane];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = t + u < o1;
-            rl_load<T, BC>(v, in ? t + u : o1 - 1, lane, vv[u]);
-            if (u > 0 && !in) {
+        for (int u = 0; u < 2; ++u) rl_load<T, BC>(v, t + u, lane, vv[u]);
 #pragma unroll
-                for (int e = 0; e < E; ++e) vv[u][e] = 0;
-            }
-        }
+        for (int u = 0; u < 2; ++u) rl_fma<T, BC>(vv[u], xx[u], r);
 #pragma unroll
-        for (int u = 0; u < U; ++u) rl_fma<T, BC>(vv[u], xx[u], r);
+        for (int u = 0; u < 2; ++u) c[u] = cn[u];
+    }
+    if (t < o1) {     // its index is already here
+        T vv[E], xx[BC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = cn[u];
+        for (int k = 0; k < BC; ++k) xx[k] = x[(int64_t)c[0] * BC + k];
+        rl_load<T, BC>(v, t, lane, vv);
+        rl_fma<T, BC>(vv, xx, r);
     }
 }
 
@@ -794,7 +855,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_
             }
             int64_t a, e;
             slice_part<WPS>(off[sl], off[sl + 1], wv % WPS, a, e);
-            rowlane3_dot_part<T, BC, RL_U>(a, e, lane, ci, v, x, r);
+            rowlane3_dot_part<T, BC>(a, e, lane, ci, v, x, r);
         }
         if (!rl_reduce<T, WPS>(wv, lane, r) || !live) return;
     }
@@ -811,8 +872,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_
 
 template <typename T, int BR, int BC>
 static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
-    // splitting slices only pays on the square coarse-level shapes (6x6 A levels, 1x1 S^/L levels)
-    constexpr bool SPLIT = (BR == 6 && BC == 6) || (BR == 1 && BC == 1);
+    constexpr bool SPLIT = true;
     int wps = SPLIT ? waves_per_slice(A) : 1;
     if (A.nslices == 0) return;
 #define MV(W)                                                                                                  \
@@ -821,10 +881,10 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
         int64_t nblk = cdiv(A.nslices, SliceGroup<W_>::SPB);                                                   \
         dim3 g((unsigned)nblk), t(SliceGroup<W_>::THREADS);                                                     \
         switch (mode) {                                                                                        \
-            case 0: sell_mv_k<T, BR, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv_k<T, BR, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv_k<T, BR, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv_k<T, BR, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv_k<T, BR, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv_k<T, BR, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv_k<T, BR, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv_k<T, BR, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                      \
     }
     if (!SPLIT || wps == 1) MV(1)
@@ -956,7 +1016,7 @@ template void bsrt_mv<float>(const DBsrT<float>&, const float*, float*, hipStrea
 // dn = c1*d + c2*Dinv*(b - A xin) ; xout = xin + dn.  One lane per scalar row; the block
 // residual of a block row is gathered from its B lanes with shuffles to apply Dinv.
 template <typename T, int B, bool RD, bool WD, bool ZERO, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nslices, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
                                                 const int32_t* __restrict__ rowid,
                                                 const int32_t* __restrict__ ci, const T* __restrict__ v,
                                                 const T* __restrict__ Dinv, const T* __restrict__ b,
@@ -999,6 +1059,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
         for (int w = 1; w < WPS; ++w) acc += red[wv + w][lane];
     }
     if (!live) return;
+    if (!ZERO) acc = parts_sum<B>(acc, lane, sp);
     const T res = valid ? bi - acc : (T)0;
     T z = 0;
     const int base = lane - r;
@@ -1056,7 +1117,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t
         if (live) {
             int64_t a, e;
             slice_part<WPS>(off[sl], off[sl + 1], wv % WPS, a, e);
-            rowlane3_dot_part<T, 3, RL_U>(a, e, lane, ci, v, xin, r);
+            rowlane3_dot_part<T, 3>(a, e, lane, ci, v, xin, r);
         }
         if (!rl_reduce<T, WPS>(wv, lane, r) || i < 0) return;
     }
@@ -1135,11 +1196,11 @@ static void smooth_dispatch(const DSell<T>& A, const T* Dinv, const T* b, const 
     do {                                                                                                           \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), t(SliceGroup<W>::THREADS);                          \
         if (e0)                                                                                                    \
-            hipExtLaunchKernelGGL((smooth_k<T, B, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0, A.nslices,                \
+            hipExtLaunchKernelGGL((smooth_k<T, B, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0, A.nslices, A.sp,          \
                                   (const int32_t*)A.off, (const int32_t*)A.rowid, (const int32_t*)A.ci,            \
                                   (const T*)A.v, Dinv, b, xin, d, xout, c1, c2);                                   \
         else                                                                                                       \
-            smooth_k<T, B, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,    \
+            smooth_k<T, B, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,    \
                                                         xout, c1, c2);                                             \
     } while (0)
 #define SK(RD, WD, Z)                                                                                              \
@@ -1196,11 +1257,10 @@ __device__ __forceinline__ void sell_row_dot3(int64_t o0, int64_t o1, int lane, 
     acc[0] = acc[1] = acc[2] = 0;
     const int64_t g1 = o1 / SELL_G;
     int64_t g = o0 / SELL_G;
+    if (g >= g1) return;
     SellI4 c[2];
-    if (g + 2 <= g1) {
-        c[0] = sell_gidx(ci, g, lane);
-        c[1] = sell_gidx(ci, g + 1, lane);
-    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) c[u] = sell_gidx(ci, g + u < g1 ? g + u : g1 - 1, lane);
     for (; g + 2 <= g1; g += 2) {
         T xx[2][SELL_G][3], vv[2][SELL_G];
 #pragma unroll
@@ -1224,27 +1284,38 @@ __device__ __forceinline__ void sell_row_dot3(int64_t o0, int64_t o1, int lane, 
 #pragma unroll
         for (int u = 0; u < 2; ++u) c[u] = cn[u];
     }
-    for (; g < g1; ++g) {
-        const SellI4 cc = sell_gidx(ci, g, lane);
-        T vv[SELL_G];
+    if (g < g1) {
+        T xx[SELL_G][3], vv[SELL_G];
+#pragma unroll
+        for (int j = 0; j < SELL_G; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) xx[j][k] = x[3 * (int64_t)c[0][j] + k];
         sell_gvals<T>(v, g, lane, vv);
 #pragma unroll
         for (int j = 0; j < SELL_G; ++j)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) acc[k] += vv[j] * x[3 * (int64_t)cc[j] + k];
+            for (int k = 0; k < 3; ++k) acc[k] += vv[j] * xx[j][k];
     }
 }
 template <typename T, int MODE, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t nslices, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
                                                   const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x,
                                                   const T* __restrict__ b, T* __restrict__ y) {
-    int wv = threadIdx.x / WAVE;
-    int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
-    int lane = threadIdx.x & (WAVE - 1);
-    bool live = sl < nslices;
-    T acc[3] = {0, 0, 0};
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const bool live = sl < nslices;
+    T acc[3] = {0, 0, 0}, old[3] = {0, 0, 0};
+    int64_t i = -1;
     if (live) {
+        // the finishing wavefront's row data are on their way while the slots stream
+        if (wv % WPS == 0) {
+            i = rowid[sl * WAVE + lane];
+            if (MODE != 0 && i >= 0)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) old[c] = MODE == 1 ? b[3 * i + c] : y[3 * i + c];
+        }
         int64_t a, e;
         slice_part<WPS, SELL_G>(off[sl], off[sl + 1], wv % WPS, a, e);
         sell_row_dot3<T>(a, e, lane, ci, v, x, acc);
@@ -1255,20 +1326,20 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t n
         for (int c = 0; c < 3; ++c) red[wv][c][lane] = acc[c];
         __syncthreads();
         if (wv % WPS != 0) return;
+#pragma unroll
         for (int w = 1; w < WPS; ++w)
 #pragma unroll
             for (int c = 0; c < 3; ++c) acc[c] += red[wv + w][c][lane];
     }
-    if (!live) return;
-    int64_t i = rowid[sl * WAVE + lane];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[c] = parts_sum<1>(acc[c], lane, sp);
     if (i < 0) return;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        int64_t o = 3 * i + c;
+        const int64_t o = 3 * i + c;
         if (MODE == 0) y[o] = acc[c];
-        else if (MODE == 1) y[o] = b[o] - acc[c];
-        else if (MODE == 2) y[o] += acc[c];
-        else y[o] -= acc[c];
+        else if (MODE == 2) y[o] = old[c] + acc[c];
+        else y[o] = old[c] - acc[c];
     }
 }
 
@@ -1282,10 +1353,10 @@ void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStre
         constexpr int W_ = W;                                                                                   \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W_>::SPB)), th(SliceGroup<W_>::THREADS);                    \
         switch (mode) {                                                                                         \
-            case 0: sell_mv3_k<T, 0, W_><<<g, th, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv3_k<T, 1, W_><<<g, th, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv3_k<T, 2, W_><<<g, th, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv3_k<T, 3, W_><<<g, th, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv3_k<T, 0, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv3_k<T, 1, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv3_k<T, 2, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv3_k<T, 3, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                       \
     }
     if (wps == 1) MV3(1)
@@ -1333,16 +1404,28 @@ template void bsrt_mv3<float>(const DBsrT<float>&, const float*, float*, hipStre
 
 // one smoothing step on three columns (1x1 blocks): as smooth_k with B = 1, per column
 template <typename T, bool RD, bool WD, bool ZERO, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t nslices, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
                                                  const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ Dinv,
                                                  const T* __restrict__ b, const T* __restrict__ xin, T* __restrict__ d,
                                                  T* __restrict__ xout, T c1, T c2) {
-    int wv = threadIdx.x / WAVE;
-    int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
-    bool live = sl < nslices;
-    int lane = threadIdx.x & (WAVE - 1);
-    T acc[3] = {0, 0, 0};
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const bool live = sl < nslices;
+    const int lane = threadIdx.x & (WAVE - 1);
+    T acc[3] = {0, 0, 0}, bi[3], dold[3], xi[3], di = 0;
+    int64_t i = -1;
+    if (live && wv % WPS == 0) i = rowid[sl * WAVE + lane];
+    if (i >= 0) {
+        // the finishing wavefront's row data are on their way while the slots stream
+        di = Dinv[i];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            bi[c] = b[3 * i + c];
+            if (RD) dold[c] = d[3 * i + c];
+            if (!ZERO) xi[c] = xin[3 * i + c];
+        }
+    }
     if (!ZERO && live) {
         int64_t a, e;
         slice_part<WPS, SELL_G>(off[sl], off[sl + 1], wv % WPS, a, e);
@@ -1354,24 +1437,26 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t ns
         for (int c = 0; c < 3; ++c) red[wv][c][lane] = acc[c];
         __syncthreads();
         if (wv % WPS != 0) return;
+#pragma unroll
         for (int w = 1; w < WPS; ++w)
 #pragma unroll
             for (int c = 0; c < 3; ++c) acc[c] += red[wv + w][c][lane];
     }
-    if (!live) return;
-    int64_t i = rowid[sl * WAVE + lane];
+    if (!ZERO) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] = parts_sum<1>(acc[c], lane, sp);
+    }
     if (i < 0) return;
-    const T di = Dinv[i];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const int64_t o = 3 * i + c;
-        const T res = b[o] - acc[c];
+        const T res = bi[c] - acc[c];
         T z = 0;
         z += di * res;
         T dn = c2 * z;
-        if (RD) dn += c1 * d[o];
+        if (RD) dn += c1 * dold[c];
         if (WD) d[o] = dn;
-        xout[o] = ZERO ? dn : xin[o] + dn;
+        xout[o] = ZERO ? dn : xi[c] + dn;
     }
 }
 
@@ -1385,7 +1470,7 @@ void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T*
 #define S3W(RD, WD, Z, W)                                                                                        \
     do {                                                                                                         \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), th(SliceGroup<W>::THREADS);                        \
-        smooth3_k<T, RD, WD, Z, W><<<g, th, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, xout,  \
+        smooth3_k<T, RD, WD, Z, W><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, xout,  \
                                                    C1, C2);                                                      \
     } while (0)
 #define S3(RD, WD, Z)                                                                                            \

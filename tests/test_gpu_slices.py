@@ -1,6 +1,6 @@
 """Sliced-ELL kernels over the sizes at which their split of a slice's work changes: wavefronts per slice
 (block-row lanes: 8 from 209 slices, 4 at 395, 2 at about 1,550, 1 above 2,048) and, on the coarse levels,
-the lanes that share a row.
+the row positions that share a row (1 to 16 of a 1x1 slice, 1, 2 and 5 of a 6x6 one).
 
 Against the FP64 oracle with the bars of the other parity tests: products within 1e-13 of the largest entry
 (rows of at most 30 blocks, FMA against unfused rounding), FP64 V-cycles within 1e-10, FP32 ones within 1e-4."""
