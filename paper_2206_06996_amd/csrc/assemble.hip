@@ -2,12 +2,9 @@
 // 3.2 and 3.5: the linearised unified-continuum VMS tangent, divided by alpha_f gamma dt) into a
 // fixed 4x4 block pattern.
 //
-// One thread per stored 4x4 block.  Each block row keeps its incident (element, local vertex)
-// pairs sorted by element, so every entry is the sum of its element contributions in ascending
-// element order: the result does not depend on scheduling (no atomics in the value pass).  A
-// thread recomputes the geometry, tau and the advective quantities of each element that couples
-// its row and column (an element is seen by the 16 blocks of its vertex pairs, more on the
-// fluid/solid interface); the values are accumulated in registers and written once.
+// One wavefront per block row.  Each block row keeps its incident (element, local vertex) pairs sorted
+// by element, so every entry is the sum of its element contributions in ascending element order: the
+// result does not depend on scheduling (no atomics in the value pass).
 #include <climits>
 #include <cmath>
 #include <memory>
@@ -21,7 +18,6 @@ struct scr_assembler {
     int64_t n_tets = 0, nb = 0, nnzb = 0, n_inc = 0;
     int32_t *tv = nullptr, *tp = nullptr, *rp = nullptr, *ci = nullptr, *inc_off = nullptr;
     int64_t* inc = nullptr;       // per block row, sorted: ((4 e + a) << 2) | role
-    int32_t* rowof = nullptr;     // block row of each stored block
     uint8_t *solid = nullptr, *mask = nullptr;
     double* xyz = nullptr;
     scr_tangent_params p{};
@@ -35,7 +31,8 @@ namespace {
 // by alpha_f gamma dt; the other forms are the parts of the linear(ised) semi-discrete residual that
 // act on the rates, on the state and on the solid displacement, see OperatorForm)
 struct TanPrm {
-    double rho_f, mu_f, rho_s, ct, visc_s, kappa, dt;
+    double rho_f, mu_f, rho_s, ct, visc_s, kappa;
+    double tau_t, tau_v;    // 4 / dt^2 and 36 (mu_f / rho_f)^2, the constant parts of tau_M
     int terms, dtc;
     double c_mass;          // times rho M (both media)
     double c_visc_f;        // fluid viscous coefficient (mu_f or 0)
@@ -53,7 +50,9 @@ TanPrm tan_prm(const scr_tangent_params& p, int form = FORM_TANGENT) {
     const double am = 0.5 * (3.0 - p.rho_inf) / (1.0 + p.rho_inf);
     const double af = 1.0 / (1.0 + p.rho_inf), g = 1.0 / (1.0 + p.rho_inf);
     TanPrm t;
-    t.rho_f = p.rho_f; t.mu_f = p.mu_f; t.rho_s = p.rho_s; t.dt = p.dt;
+    t.rho_f = p.rho_f; t.mu_f = p.mu_f; t.rho_s = p.rho_s;
+    const double nu = p.mu_f / p.rho_f;
+    t.tau_t = 4.0 / (p.dt * p.dt); t.tau_v = 36.0 * nu * nu;
     t.ct = am / (af * g * p.dt);
     const double mu_s = p.E_s / (2.0 * (1.0 + p.nu_s));
     t.visc_s = (af * g * p.dt / am) * mu_s;
@@ -139,8 +138,7 @@ __device__ __forceinline__ void fluid_tau(const double (&dN)[4][3], const double
             uGu += ub[i] * G[i][j] * ub[j];
         }
     }
-    const double nu = P.mu_f / P.rho_f;
-    tauM = 1.0 / (P.rho_f * sqrt(4.0 / (P.dt * P.dt) + uGu + 36.0 * nu * nu * GG));
+    tauM = 1.0 / (P.rho_f * sqrt(P.tau_t + uGu + P.tau_v * GG));
     tauC = 1.0 / (tauM * trG);
 }
 
@@ -248,154 +246,232 @@ __global__ void inc_sort_k(int64_t nb, const int32_t* __restrict__ off, int64_t*
 //   C    =  tau_M L_ab (fluid),  (c_t/kappa) M_ab (solid)                          (bit 16)
 // visc = mu_f for fluid, (alpha_f gamma dt/alpha_m) mu_s for solid.  The A and G rows go to block
 // row tv[a] (role 1), the D and C row to tp[a] (role 2); columns tv[b] (A, D) and tp[b] (G, C).
-// One thread per stored block (r, c): it walks row r's incidence list (ascending elements), skips
-// the elements that do not hold c as a velocity or pressure column, and accumulates the 16 entries
-// of the block in registers; each block is written once (consecutive threads write consecutive
-// blocks), then the Dirichlet elimination is applied to it.
-__global__ void __launch_bounds__(256) tangent_blocks_k(int64_t nnzb, const int32_t* __restrict__ rowof,
-                                                        const int32_t* __restrict__ ci, const int32_t* __restrict__ ioff,
-                                                        const int64_t* __restrict__ inc, const int32_t* __restrict__ tv,
-                                                        const int32_t* __restrict__ tp, const uint8_t* __restrict__ solid,
-                                                        const double* __restrict__ xyz, const double* __restrict__ u,
-                                                        const uint8_t* __restrict__ mask, TanPrm P,
-                                                        double* __restrict__ val) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nnzb) return;
-    const int32_t r = rowof[q], c = ci[q];
-    double acc[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) acc[t] = 0.0;
+//
+// One wavefront per block row, in three parts per 64 entries of the row's incidence list:
+//   1. lane k computes the geometry, tau and advective quantities of the k-th element once (they stay in
+//      its registers; the lanes of part 2 fetch them with shuffles);
+//   2. 16 elements at a time, lane 4 k + b computes the 4x4 contribution of element k's column vertex b
+//      into LDS, entry by entry;
+//   3. element by element, lane (b, e) adds entry e of column vertex b to its block's sum with an LDS
+//      atomic: the lanes of one instruction add to distinct entries and LDS serves a wavefront's
+//      instructions in order, so every entry is summed in ascending element order.
+// The sums are written at the end, 512 contiguous bytes per store.  Rows of more than ASM_BLK blocks
+// repeat the list for the next ASM_BLK.
+// One thread per stored block walked its row's whole list and ran all the arithmetic of the elements that
+// hold its column with a quarter of the lanes: 2.20 ms for 5.05M blocks of 1.71M advective tetrahedra, this
+// form 1.06 (0.92 at rest); bound by the FP64 arithmetic and the LDS exchange in about equal parts (each
+// near 0.45 ms) at three wavefronts per SIMD, not by the 0.9 GB it moves.
+constexpr int ASM_EL = 16;              // elements per chunk of part 2 (times 4 column vertices = the lanes)
+constexpr int ASM_BLK = 32;             // blocks whose sums LDS holds
+constexpr int ASM_LD = 68;              // LDS stride of an entry (the 16 entries of part 3 in different banks)
+// orders the LDS accesses of a wavefront's lanes (LDS serves a wavefront's instructions in order)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+struct AsmLds {
+    double c[16 * ASM_LD];
+    double sum[ASM_BLK * 16];
+    int32_t pos[WAVE];
+};
+__global__ void __launch_bounds__(256, 3) tangent_rows_k(int64_t nb, int per, const int32_t* __restrict__ rp,
+                                                      const int32_t* __restrict__ ci, const int32_t* __restrict__ ioff,
+                                                      const int64_t* __restrict__ inc, const int32_t* __restrict__ tv,
+                                                      const int32_t* __restrict__ tp, const uint8_t* __restrict__ solid,
+                                                      const double* __restrict__ xyz, const double* __restrict__ u,
+                                                      const uint8_t* __restrict__ mask, TanPrm P,
+                                                      double* __restrict__ val) {
+    __shared__ AsmLds lds[256 / WAVE];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t first = (xcd_tile(blockIdx.x, gridDim.x) * (256 / WAVE) + w) * per;
+    const int64_t last = first + per < nb ? first + per : nb;
+    const int lane = threadIdx.x & (WAVE - 1);
+    AsmLds& S = lds[w];
     const bool t_mass = P.terms & 1, t_visc = P.terms & 2, t_gd = P.terms & 4, t_gdiv = (P.terms & 8) && P.c_gdiv != 0.0,
-               t_c = P.terms & 16;
-    for (int32_t k = ioff[r]; k < ioff[r + 1]; ++k) {
-        const int64_t key = inc[k];
-        const int64_t e = key >> 4;
-        const int a = (int)((key >> 2) & 3);
-        const int role = (int)(key & 3);
-        typedef int I4 __attribute__((ext_vector_type(4)));
-        const I4 va = *reinterpret_cast<const I4*>(tv + 4 * e);
-        const I4 pa = *reinterpret_cast<const I4*>(tp + 4 * e);
-        // the column vertex b of c (velocity and pressure columns; at most one b each)
-        int bv = -1, bq = -1;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            if (va[b] == c) bv = b;
-            if (pa[b] == c) bq = b;
+               t_c = P.terms & 16, t_dtc = (P.terms & 8) && P.dtc, t_conv = u != nullptr && (P.terms & 32) && P.conv;
+    const int b = lane & 3;                                // part 2: column vertex
+    const int b3 = lane >> 4, e3 = lane & 15;              // part 3: column vertex and entry
+    const int kind = (e3 & 3) == 3 ? 16 : 0;               // pressure columns: the upper half of pos
+    typedef int I4 __attribute__((ext_vector_type(4)));
+    // what the first sweep of a row needs first, loaded while the previous row is worked on
+    struct Head { int32_t q0, nblk, k0, k1, col; uint32_t mc; int64_t key; I4 va, pa; uint8_t sol; };
+    auto element = [&](Head& h, int32_t kc) {      // the lane's element of the list from kc on
+        if (kc + lane < h.k1) {
+            h.key = inc[kc + lane];
+            const int64_t el = h.key >> 4;
+            h.va = *reinterpret_cast<const I4*>(tv + 4 * el);
+            h.pa = *reinterpret_cast<const I4*>(tp + 4 * el);
+            h.sol = solid[el];
         }
-        if (bv < 0 && bq < 0) continue;
-        double x[4][3];
+    };
+    auto columns = [&](Head& h, int32_t g0) {      // the lane's column of the blocks from g0 on, and its Dirichlet flags
+        h.col = INT32_MAX;
+        h.mc = 0;
+        if (lane < ASM_BLK && g0 + lane < h.nblk) {
+            h.col = ci[h.q0 + g0 + lane];
+            h.mc = *reinterpret_cast<const uint32_t*>(mask + 4 * (int64_t)h.col);
+        }
+    };
+    auto head = [&](int64_t r) {
+        Head h{};
+        h.q0 = rp[r]; h.nblk = rp[r + 1] - h.q0;
+        h.k0 = ioff[r]; h.k1 = ioff[r + 1];
+        element(h, h.k0);
+        columns(h, 0);
+        return h;
+    };
+    if (first >= last) return;
+    Head next = head(first);
+    for (int64_t r = first; r < last; ++r) {
+        Head h = next;
+        if (r + 1 < last) next = head(r + 1);
+        const int32_t q0 = h.q0, nblk = h.nblk, k0 = h.k0, k1 = h.k1;
+        const uint32_t mr = *reinterpret_cast<const uint32_t*>(mask + 4 * r);
+        for (int32_t g0 = 0; g0 < nblk; g0 += ASM_BLK) {
+            const int32_t g1 = g0 + ASM_BLK < nblk ? g0 + ASM_BLK : nblk;
+            if (g0 > 0) columns(h, g0);
+            for (int t = lane; t < 16 * (g1 - g0); t += WAVE) S.sum[t] = 0.0;
+            for (int32_t kc = k0; kc < k1; kc += WAVE) {
+                if (kc > k0 || g0 > 0) element(h, kc);
+                // ---- part 1
+                const int32_t nel = k1 - kc < WAVE ? k1 - kc : WAVE;
+                const I4 va = h.va, pa = h.pa;
+                double dN[4][3] = {}, V = 0.0, tauM = 0.0, gd = 0.0, ub[3] = {0.0, 0.0, 0.0}, gu[3][3] = {};
+                bool sol = false;
+                if (lane < nel) {
+                    sol = h.sol != 0;
+                    double x[4][3];
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+                    for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int i = 0; i < 3; ++i) x[b][i] = xyz[3 * (int64_t)va[b] + i];
-        double dN[4][3];
-        const double V = fabs(tet_shape(x, dN)) / 6.0;
-        const bool sol = solid[e] != 0;
-        const bool conv = !sol && u != nullptr && (P.terms & 32) && P.conv;
-        double ub[3] = {0.0, 0.0, 0.0}, gu[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-        if (conv) {
+                        for (int i = 0; i < 3; ++i) x[v][i] = xyz[3 * (int64_t)va[v] + i];
+                    V = fabs(tet_shape(x, dN)) * (1.0 / 6.0);
+                    if (t_conv && !sol) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+                        for (int v = 0; v < 4; ++v)
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const double ui = u[3 * (int64_t)va[b] + i];
-                    ub[i] += 0.25 * ui;
+                            for (int i = 0; i < 3; ++i) {
+                                const double ui = u[3 * (int64_t)va[v] + i];
+                                ub[i] += 0.25 * ui;
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) gu[i][j] += ui * dN[b][j];
+                                for (int j = 0; j < 3; ++j) gu[i][j] += ui * dN[v][j];
+                            }
+                    }
+                    if (!sol) {
+                        double tauC;
+                        fluid_tau(dN, ub, P, tauM, tauC);
+                        if (t_gd) gd = P.c_gd * tauC;
+                    }
                 }
-        }
-        double tauM = 0.0, tauC = 0.0, rho, visc;
-        if (!sol) {
-            fluid_tau(dN, ub, P, tauM, tauC);
-            rho = P.rho_f;
-            visc = P.c_visc_f;
-        } else {
-            rho = P.rho_s;
-            visc = P.c_visc_s;
-        }
-        const double gd = sol ? 0.0 : P.c_gd * tauC;
-        double dNa[3];
+                const int meta = (int)(h.key & 15) | (sol ? 16 : 0);     // role, local vertex, medium
+                for (int32_t kk = 0; kk < nel; kk += ASM_EL) {
+                    // ---- part 2
+                    const int src = kk + (lane >> 2);      // the element's lane
+                    const int mt = __shfl(meta, src, WAVE);
+                    const int a = (mt >> 2) & 3, role = mt & 3;
+                    const bool so = (mt & 16) != 0, in = src < nel;
+                    int cv = 0, cp = 0;
+                    double dNa[3] = {}, dNb[3] = {}, uv[3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) dNa[i] = a == 0 ? dN[0][i] : a == 1 ? dN[1][i] : a == 2 ? dN[2][i] : dN[3][i];
-        const double ua = ub[0] * dNa[0] + ub[1] * dNa[1] + ub[2] * dNa[2];
-        if (bv >= 0) {
-            double dNb[3];
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = __shfl(va[v], src, WAVE), p = __shfl(pa[v], src, WAVE);
+                        if (b == v) { cv = c; cp = p; }
 #pragma unroll
-            for (int i = 0; i < 3; ++i) dNb[i] = bv == 0 ? dN[0][i] : bv == 1 ? dN[1][i] : bv == 2 ? dN[2][i] : dN[3][i];
-            const double Mab = V * (a == bv ? 2.0 : 1.0) / 20.0;
-            const double Lab = V * (dNa[0] * dNb[0] + dNa[1] * dNb[1] + dNa[2] * dNb[2]);
-            const double uB = ub[0] * dNb[0] + ub[1] * dNb[1] + ub[2] * dNb[2];
-            if (role & 1) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        double v = 0.0;
-                        if (t_mass && i == j) v += rho * P.c_mass * Mab;
-                        if (t_visc)
-                            v += visc * ((i == j ? Lab : 0.0) + V * dNa[j] * dNb[i] - (2.0 / 3.0) * V * dNa[i] * dNb[j]);
-                        if (t_gd) v += gd * V * dNa[i] * dNb[j];
-                        if (conv) {
-                            if (i == j) v += rho * (V / 4.0) * uB + tauM * rho * rho * ua * (P.ct * (V / 4.0) + V * uB);
-                            v += rho * Mab * gu[i][j];
+                        for (int i = 0; i < 3; ++i) {
+                            const double g = __shfl(dN[v][i], src, WAVE);
+                            if (a == v) dNa[i] = g;
+                            if (b == v) dNb[i] = g;
                         }
-                        acc[4 * i + j] += v;
                     }
-            }
-            if (role & 2) {
+                    const double Ve = __shfl(V, src, WAVE), tm = __shfl(tauM, src, WAVE), ge = __shfl(gd, src, WAVE);
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    double d = 0.0;
-                    if (P.terms & 8) {
-                        if (t_gdiv) d = (V / 4.0) * dNb[j];
-                        if (!sol && P.dtc) d += P.c_dtc * rho * tauM * (V / 4.0) * dNa[j];
+                    for (int i = 0; i < 3; ++i) uv[i] = t_conv ? __shfl(ub[i], src, WAVE) : 0.0;
+                    // positions of the columns among this sweep's blocks (ascending, one per lane)
+                    int pv = 0, pp = 0;
+#pragma unroll
+                    for (int step = ASM_BLK / 2; step > 0; step >>= 1) {
+                        if (__shfl(h.col, pv + step - 1, WAVE) < cv) pv += step;
+                        if (__shfl(h.col, pp + step - 1, WAVE) < cp) pp += step;
                     }
-                    if (conv) d += tauM * rho * V * dNa[j] * uB;
-                    acc[12 + j] += d;
+                    // every lane takes part in the shuffles: an element's lanes read the columns of lanes beyond the list
+                    const int colv = __shfl(h.col, pv, WAVE), colp = __shfl(h.col, pp, WAVE);
+                    if (!in || colv != cv) pv = -1;
+                    if (!in || colp != cp) pp = -1;
+                    S.pos[lane] = (pv & 0xffff) | (pp << 16);
+                    const double rho = so ? P.rho_s : P.rho_f, visc = t_visc ? (so ? P.c_visc_s : P.c_visc_f) : 0.0;
+                    const double V4 = Ve * 0.25, Mab = Ve * (a == b ? 0.1 : 0.05);
+                    const double Lab = Ve * (dNa[0] * dNb[0] + dNa[1] * dNb[1] + dNa[2] * dNb[2]);
+                    const double ua = uv[0] * dNa[0] + uv[1] * dNa[1] + uv[2] * dNa[2];
+                    const double uB = uv[0] * dNb[0] + uv[1] * dNb[1] + uv[2] * dNb[2];
+                    double diag = visc * Lab;
+                    if (t_mass) diag += rho * P.c_mass * Mab;
+                    if (t_conv) diag += rho * V4 * uB + tm * rho * rho * ua * (P.ct * V4 + Ve * uB);
+                    const double cs = ge - (2.0 / 3.0) * visc;
+                    const bool rv = (role & 1) && in, rq = (role & 2) && in;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) {
+                            double v = visc * (Ve * dNa[j] * dNb[i]) + cs * (Ve * dNa[i] * dNb[j]);
+                            if (i == j) v += diag;
+                            if (t_conv) v += rho * Mab * __shfl(gu[i][j], src, WAVE);
+                            S.c[(4 * i + j) * ASM_LD + lane] = rv ? v : 0.0;
+                        }
+                        double g = t_gdiv ? -V4 * dNa[i] : 0.0;
+                        if (t_conv) g += tm * rho * Ve * ua * dNb[i];
+                        S.c[(4 * i + 3) * ASM_LD + lane] = rv ? g : 0.0;
+                        double d = t_gdiv ? V4 * dNb[i] : 0.0;
+                        if (t_dtc && !so) d += P.c_dtc * rho * tm * V4 * dNa[i];
+                        if (t_conv) d += tm * rho * Ve * dNa[i] * uB;
+                        S.c[(12 + i) * ASM_LD + lane] = rq ? d : 0.0;
+                    }
+                    S.c[15 * ASM_LD + lane] = rq && t_c ? (so ? P.c_cs * Mab : P.c_cf * tm * Lab) : 0.0;
+                    wave_sync();
+                    // ---- part 3
+                    const int nk = nel - kk < ASM_EL ? nel - kk : ASM_EL;
+                    for (int k = 0; k < nk; k += 4) {
+                        int p[4];
+                        double v[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {      // beyond nk: no position, so nothing is added
+                            p[t] = (int)(int16_t)(S.pos[4 * (k + t) + b3] >> kind);
+                            v[t] = S.c[e3 * ASM_LD + 4 * (k + t) + b3];
+                        }
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if (p[t] >= 0)
+                                (void)__hip_atomic_fetch_add(&S.sum[16 * p[t] + e3], v[t], __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    }
+                    wave_sync();
                 }
             }
-        }
-        if (bq >= 0) {
-            double dNb[3];
+            // Dirichlet elimination: rows and columns of constrained dofs zeroed, unit diagonal
+            wave_sync();
+            const bool gone = (mr >> (8 * (e3 >> 2))) & 0xff;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) dNb[i] = bq == 0 ? dN[0][i] : bq == 1 ? dN[1][i] : bq == 2 ? dN[2][i] : dN[3][i];
-            if (role & 1) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    double g = t_gdiv ? -(V / 4.0) * dNa[i] : 0.0;
-                    if (conv) g += tauM * rho * V * ua * dNb[i];
-                    acc[4 * i + 3] += g;
-                }
+            for (int j = 0; j < ASM_BLK / 4; ++j) {
+                if (g0 + 4 * j >= g1) break;
+                const int p = 4 * j + b3;
+                const int c = __shfl(h.col, p, WAVE);
+                const bool mc = ((uint32_t)__shfl((int)h.mc, p, WAVE) >> (8 * (e3 & 3))) & 0xff;
+                if (g0 + p < g1)
+                    val[16 * (int64_t)(q0 + g0 + p) + e3] =
+                        (gone || mc) ? ((c == r && (e3 >> 2) == (e3 & 3) && P.unit_diag) ? 1.0 : 0.0) : S.sum[16 * p + e3];
             }
-            if ((role & 2) && t_c) {
-                const double Mab = V * (a == bq ? 2.0 : 1.0) / 20.0;
-                const double Lab = V * (dNa[0] * dNb[0] + dNa[1] * dNb[1] + dNa[2] * dNb[2]);
-                acc[15] += sol ? P.c_cs * Mab : P.c_cf * tauM * Lab;
-            }
+            wave_sync();
         }
-    }
-    // Dirichlet elimination: rows and columns of constrained dofs zeroed, unit diagonal
-    typedef double D2 __attribute__((ext_vector_type(2)));
-    D2* out = reinterpret_cast<D2*>(val + 16 * q);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint8_t mr = mask[4 * (int64_t)r + i];
-        double w[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint8_t mc = mask[4 * (int64_t)c + j];
-            w[j] = (mr || mc) ? ((c == r && i == j && P.unit_diag) ? 1.0 : 0.0) : acc[4 * i + j];
-        }
-        out[2 * i] = D2{w[0], w[1]};
-        out[2 * i + 1] = D2{w[2], w[3]};
     }
 }
 
-// block row of every stored block
-__global__ void row_of_k(int64_t nb, const int32_t* __restrict__ rp, int32_t* __restrict__ rowof) {
-    int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nb) return;
-    for (int32_t q = rp[r]; q < rp[r + 1]; ++q) rowof[q] = (int32_t)r;
+void tangent_run(const scr_assembler* A, const double* u, const TanPrm& P, double* val, hipStream_t s) {
+    // two rows per wavefront, the second one's lists on their way during the first, once the chip's 3,072
+    // resident wavefronts (LDS: 12 per CU) have several rounds of rows (1.11 -> 1.06 ms at 324k rows; at 7k
+    // rows 48 -> 53 us)
+    const int per = A->nb >= 4 * 3072 ? 2 : 1;
+    tangent_rows_k<<<(unsigned)cdiv(A->nb, per * (256 / WAVE)), 256, 0, s>>>(A->nb, per, A->rp, A->ci, A->inc_off, A->inc,
+                                                                             A->tv, A->tp, A->solid, A->xyz, u, A->mask, P, val);
+    check_launch("tangent_rows");
 }
 
 scr_status asm_fail(const std::exception& e) { return status_of(e); }
@@ -480,9 +556,6 @@ scr_status scr_assembler_create(scr_ctx* ctx, int64_t n_tets, const int32_t* tv,
         check_launch("inc_fill");
         inc_sort_k<<<cdiv(n_brows, 256), 256, 0, s>>>(n_brows, A->inc_off, A->inc);
         check_launch("inc_sort");
-        A->rowof = ar.make<int32_t>(A->nnzb);
-        row_of_k<<<cdiv(n_brows, 256), 256, 0, s>>>(n_brows, A->rp, A->rowof);
-        check_launch("row_of");
         ar.free(cnt);
         ar.free(err);
         HIPCHK(hipStreamSynchronize(s));
@@ -502,10 +575,7 @@ void assemble_form(scr_assembler* A, int form, double dt, const double* u, doubl
     scr_tangent_params p = A->p;
     p.dt = dt;
     const TanPrm P = tan_prm(p, form);
-    tangent_blocks_k<<<cdiv(A->nnzb, 256), 256, 0, s>>>(A->nnzb, A->rowof, A->ci, A->inc_off, A->inc, A->tv, A->tp,
-                                                         A->solid, A->xyz, form == FORM_TANGENT ? u : nullptr,
-                                                         A->mask, P, val);
-    check_launch("tangent_blocks");
+    tangent_run(A, form == FORM_TANGENT ? u : nullptr, P, val, s);
 }
 double asmb_rho_inf(const scr_assembler* A) { return A->p.rho_inf; }
 void asmb_pattern(const scr_assembler* A, int32_t* rp, int32_t* ci, hipStream_t s) {
@@ -520,9 +590,7 @@ scr_status scr_assemble_tangent(scr_assembler* A, const double* u, double* val, 
         if (!A || !val) throw Error(SCR_E_INVALID, "NULL assembler or val");
         if (reinterpret_cast<uintptr_t>(val) % 16 != 0) throw Error(SCR_E_INVALID, "val must be 16-byte aligned");
         HIPCHK(hipSetDevice(A->ctx->device));
-        tangent_blocks_k<<<cdiv(A->nnzb, 256), 256, 0, s>>>(A->nnzb, A->rowof, A->ci, A->inc_off, A->inc, A->tv, A->tp,
-                                                             A->solid, A->xyz, u, A->mask, tan_prm(A->p), val);
-        check_launch("tangent_blocks");
+        tangent_run(A, u, tan_prm(A->p), val, s);
         HIPCHK(hipStreamSynchronize(s));
         return SCR_OK;
     } catch (const std::exception& e) {

@@ -201,3 +201,46 @@ def test_cfg1_full_size(scr, ctx, cfg1):
     ref = asm.tangent(s.tv, s.tp, s.tsolid, s.xyz, s.rp, s.ci, s.mask, asm.params_of(p), u=s.uadv, rows=rows)
     assert row_rel_err(s, got, ref, rows=rows) <= 1e-12
     a.destroy()
+
+
+@pytest.mark.parametrize("fan", [5, 15, 16, 33, 64, 70])
+def test_rows_of_any_incidence_and_width(scr, ctx, fan):
+    # `fan` tetrahedra around one edge: its two end rows have `fan` incident elements and fan + 2 blocks, on
+    # both sides of the 16 and 64 elements and the 32 blocks that the kernel takes at a time; the first third
+    # is solid, with its own pressure rows.  Against the element matrices of the generator, summed on the host.
+    p = synth.default_params(mode=0, m_core=2, n_bl=0, n_wall=0, nz=2, u_max=1.0)
+    ang = 2 * np.pi * np.arange(fan) / fan
+    xyz = np.concatenate([[[0, 0, -1.0], [0, 0, 1.0]], np.stack([np.cos(ang), np.sin(ang), 0.1 * np.sin(3 * ang)], 1)])
+    n = fan + 2
+    tv = np.array([[0, 1, 2 + k, 2 + (k + 1) % fan] for k in range(fan)], np.int32)
+    solid = (np.arange(fan) < fan // 3).astype(np.uint8)
+    tp = np.where(solid[:, None] != 0, tv + n, tv).astype(np.int32)     # pressure rows of the solid
+    nb = 2 * n
+    xyz = np.concatenate([xyz, xyz])
+    u = np.random.default_rng(fan).uniform(-1, 1, (nb, 3))
+    blocks = {}
+    for r in range(nb):
+        blocks[(r, r)] = np.zeros((4, 4))
+    for e in range(fan):
+        Ke, _ = synth.element(xyz[tv[e]], p, bool(solid[e]), u[tv[e]])
+        Ke = Ke.reshape(4, 4, 4, 4)                                      # vertex a, entry i, vertex b, entry j
+        for a in range(4):
+            for b in range(4):
+                for rows, ri in ((tv[e, a], slice(0, 3)), (tp[e, a], slice(3, 4))):
+                    for cols, cj in ((tv[e, b], slice(0, 3)), (tp[e, b], slice(3, 4))):
+                        blk = blocks.setdefault((int(rows), int(cols)), np.zeros((4, 4)))
+                        blk[ri, cj] += Ke[a, ri, b, cj]
+    keys = sorted(blocks)
+    rp = np.searchsorted([k[0] for k in keys], np.arange(nb + 1)).astype(np.int32)
+    ci = np.array([k[1] for k in keys], np.int32)
+    ref = np.array([blocks[k] for k in keys])
+    a = scr.scr_assembler_create(ctx, dev(tv), dev(tp), dev(solid), dev(rp), dev(ci), dev(xyz), dev(np.zeros(4 * nb, np.uint8)),
+                                 tparams(scr, p))
+    val = torch.empty(16 * ci.size, dtype=torch.float64, device="cuda")
+    scr.scr_assemble_tangent(a, dev(u), val)
+    got = host(val).reshape(-1, 4, 4)
+    # sums of at most `fan` terms per entry in the same order, each within a few roundings of its largest part
+    big = np.array([np.abs(ref[rp[r]:rp[r + 1]]).max() for r in range(nb)])
+    err = np.abs(got - ref).max((1, 2)) / np.maximum(big[np.repeat(np.arange(nb), np.diff(rp))], 1e-300)
+    assert err.max() <= 1e-12, err.max()
+    a.destroy()
