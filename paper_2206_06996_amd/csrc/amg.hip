@@ -12,6 +12,7 @@
 // evaluated as written, without fused multiply-adds.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "solver.h"
 
@@ -91,22 +92,21 @@ void split_blocks(const DBsr& K, DBsr& A, DBsr& G, DBsr& D, DBsr& C, Arena& ar, 
     check_launch("split");
 }
 
-// ====================================================================== generic SpGEMM (one wave per row)
-constexpr int HS_MAX = 8192;       // largest LDS hash table per row
-constexpr int HMAX = HS_MAX / 2;   // unique columns allowed per row
-constexpr int HS_COUNT = 2048;     // first hash table of the counting pass (x4 on each overflow)
-constexpr int SPG_NW_BOUND = 2048; // mean candidates per row from which rows take four wavefronts
-
-// returns 1 if newly inserted (table of hs slots, hs a power of two, never more than half full)
-__device__ __forceinline__ int hash_insert(int* t, int hs, int key) {
-    unsigned h = ((unsigned)key * 2654435761u) & (unsigned)(hs - 1);
-    for (;;) {
-        int prev = atomicCAS(&t[h], -1, key);
-        if (prev == -1) return 1;
-        if (prev == key) return 0;
-        h = (h + 1) & (unsigned)(hs - 1);
-    }
-}
+// ====================================================================== generic SpGEMM
+// C = X Y row by row.  A row's columns lie in a window [first, last] of Y's columns (the smallest first and
+// the largest last column of the Y rows that it meets), narrow on a mesh whose numbering is local, so LDS
+// holds the row's columns as flags over its window: the distinct columns of a row are its set flags,
+// their number a population count, in ascending order without a sort, and the place of a column in the
+// row a prefix count plus a population count within one word.  Windows of more than SPG_SEG columns are
+// taken SPG_SEG columns at a time, the candidates read again for each.  Against LDS hash tables with a rank
+// sort (pattern) and serial read-add-write steps per X entry (numeric), over all products of one set-up at
+// 324k rows: pattern 11.4 -> 8.3 ms, scalar products 9.1 -> 5.1, block products 6.4 -> 7.0; one host
+// synchronisation per product instead of three.  Bound by the latency of the gathers of Y's rows: each
+// wavefront keeps four steps of loads in flight.
+constexpr int HMAX = 4096;         // unique columns allowed per row
+constexpr int SPG_SEG = 32768;     // columns of one map
+constexpr int SPG_WIDE = 2048;     // mean candidates per row from which a row takes four wavefronts
+constexpr int SPG_LONG = 24;       // mean length of the Y rows from which one X entry takes a wavefront
 
 // Maximum over a 256-thread workgroup, folded into *out by one atomic (every thread must call it).
 // A same-address atomic per row serialises at one L2 channel: 324k of them cost about 3.5 ms.
@@ -127,131 +127,246 @@ __device__ __forceinline__ void block_max_to(T v, T* out) {
     }
 }
 
-// upper bound of the candidates of each row of X*Y (sum of the lengths of the Y rows it meets):
-// its maximum over the rows into *maxub, its sum into *sumub.  A wavefront per row (grid-stride over
-// the rows, at most SPG_BOUND_BLOCKS workgroups), one atomic of each kind per workgroup.
-constexpr int SPG_BOUND_BLOCKS = 4096;
-__global__ void __launch_bounds__(256) spg_bound_k(int64_t nr, const int32_t* __restrict__ xrp,
-                                                   const int32_t* __restrict__ xci, const int32_t* __restrict__ yrp,
-                                                   int* __restrict__ maxub, unsigned long long* __restrict__ sumub) {
-    __shared__ int64_t redm[256 / WAVE];
-    __shared__ unsigned long long reds[256 / WAVE];
-    const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    int64_t mx = 0;
-    unsigned long long sm = 0;
-    for (int64_t i = (int64_t)blockIdx.x * (256 / WAVE) + w; i < nr; i += (int64_t)gridDim.x * (256 / WAVE)) {
-        int64_t ub = 0;
-        for (int32_t q = xrp[i] + lane; q < xrp[i + 1]; q += WAVE) {
-            const int32_t k = xci[q];
-            ub += yrp[k + 1] - yrp[k];
-        }
-#pragma unroll
-        for (int o = WAVE / 2; o > 0; o >>= 1) ub += __shfl_xor(ub, o, WAVE);
-        mx = ub > mx ? ub : mx;
-        sm += (unsigned long long)ub;
+// largest of n counts, and of the n window sizes win[2 i + 1] (one atomic of each kind per workgroup)
+__global__ void __launch_bounds__(256) spg_max_k(int64_t n, const int32_t* __restrict__ cnt, const int32_t* __restrict__ win,
+                                                 int* __restrict__ wmax, int* __restrict__ maxwin) {
+    int m = 0, w = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        m = cnt[i] > m ? cnt[i] : m;
+        w = win[2 * i + 1] > w ? win[2 * i + 1] : w;
     }
-    if (lane == 0) { redm[w] = mx; reds[w] = sm; }
+    block_max_to(m, wmax);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int v = 1; v < 256 / WAVE; ++v) { mx = redm[v] > mx ? redm[v] : mx; sm += reds[v]; }
-        atomicMax(maxub, (int)(mx < (1 << 30) ? mx : (1 << 30)));
-        atomicAdd(sumub, sm);
-    }
+    block_max_to(w, maxwin);
 }
 
-// largest of n counts (one atomic per workgroup)
-__global__ void __launch_bounds__(256) max_i32_k(int64_t n, const int32_t* __restrict__ a, int* __restrict__ out) {
-    int m = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) m = a[i] > m ? a[i] : m;
-    block_max_to(m, out);
-}
-
-// count (phase 0) or emit sorted (phase 1) the structural pattern of row i of X*Y, NW wavefronts
-// per row sharing one LDS hash table (NW = 4 for products whose rows meet thousands of candidates:
-// the table's LDS then serves four wavefronts instead of one).  In the counting pass a row whose
-// unique columns overflow the table gets cnt = -1 and raises the overflow flag; a retry pass
-// (retry = 1, larger table) recounts only those rows.
-// Dynamic LDS: hs hash slots, then hs/2 + NW * 64 list entries.
-template <int PHASE, int NW>
-__global__ void __launch_bounds__(NW * WAVE) spg_symbolic(int64_t nr, int hs, int retry, const int32_t* __restrict__ xrp,
-                                                          const int32_t* __restrict__ xci, const int32_t* __restrict__ yrp,
-                                                          const int32_t* __restrict__ yci, const uint8_t* __restrict__ rowmask,
-                                                          int32_t* __restrict__ cnt, const int32_t* __restrict__ crp,
-                                                          int32_t* __restrict__ cci, int* __restrict__ overflow) {
-    extern __shared__ int smem[];
-    int* table = smem;
-    int* list = smem + hs;
-    __shared__ int nuniq;
-    const int hmax = hs / 2;
-    int64_t i = blockIdx.x;
-    if (i >= nr) return;
-    const int tid = threadIdx.x;
-    const int lane = tid & (WAVE - 1);
-    if (PHASE == 0 && retry && cnt[i] >= 0) return;
-    if (rowmask && !rowmask[i]) {
-        if (PHASE == 0 && tid == 0) cnt[i] = 0;
-        return;
-    }
-    for (int t = tid; t < hs; t += NW * WAVE) table[t] = -1;
-    if (tid == 0) nuniq = 0;
-    __syncthreads();
-    // The candidates (X entry q, Y entry t) of up to 64 X entries at a time are spread over the
-    // lanes of one wavefront (wavefront w takes chunks w, w + NW, ...): lane l holds the Y row of
-    // X entry q0 + l, an inclusive prefix of their lengths maps a candidate number to its (l, t) by
-    // a binary search over the prefix (every lane takes part in the shuffles).  Only a set is
-    // built here, so the order of insertion does not matter.
-    const int32_t x0 = xrp[i], x1 = xrp[i + 1];
-    for (int32_t q0 = x0 + (tid / WAVE) * WAVE; q0 < x1; q0 += NW * WAVE) {
-        int st = 0, len = 0;
-        if (q0 + lane < x1) {
-            int32_t k = xci[q0 + lane];
+// The candidates (X entry, Y entry) of 64 consecutive X entries as one list in (X entry, Y entry) order,
+// spread over the lanes of a wavefront: lane l holds X entry q0 + l, `incl` the number of candidates of the
+// entries up to its own and `off` the Y index of its first candidate minus the candidates before it.
+struct SpgList {
+    int st, len, incl, off, total, nq;
+    __device__ __forceinline__ SpgList(int32_t q0, int32_t x1, int lane, const int32_t* __restrict__ xci,
+                                       const int32_t* __restrict__ yrp) {
+        st = len = 0;
+        nq = x1 - q0 < WAVE ? x1 - q0 : WAVE;
+        if (lane < nq) {
+            const int32_t k = xci[q0 + lane];
             st = yrp[k];
             len = yrp[k + 1] - st;
         }
-        int incl = len;
+        incl = len;
+#pragma unroll
         for (int o = 1; o < WAVE; o <<= 1) {
-            int v = __shfl_up(incl, o, WAVE);
+            const int v = __shfl_up(incl, o, WAVE);
             if (lane >= o) incl += v;
         }
-        const int total = __shfl(incl, WAVE - 1, WAVE);
-        for (int base = 0; base < total; base += WAVE) {
-            if (nuniq >= hmax) break;
-            const int cidx = base + lane;
-            int l = 0;     // number of lanes whose inclusive prefix is <= cidx
-            for (int step = WAVE / 2; step > 0; step >>= 1) {
-                int v = __shfl(incl, l + step - 1, WAVE);
-                if (v <= cidx) l += step;
-            }
-            const int stl = __shfl(st, l, WAVE);
-            const int excl = __shfl(incl, l, WAVE) - __shfl(len, l, WAVE);
-            if (cidx < total) {
-                int c = yci[stl + (cidx - excl)];
-                if (hash_insert(table, hs, c)) {
-                    int pos = atomicAdd(&nuniq, 1);
-                    if (pos < hmax + NW * WAVE) list[pos] = c;
+        total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+        off = st - (incl - len);
+    }
+    // long Y rows: one X entry per step, its Y row over the lanes
+    __device__ __forceinline__ bool is_long() const { return total >= SPG_LONG * nq; }
+    // one candidate per X entry at most: the lane's own
+    __device__ __forceinline__ bool single() const { return !__any(len > 1); }
+    // X entry (its lane) and Y index of candidate c, the last one for c beyond the list (every lane takes
+    // part; the list is not empty)
+    __device__ __forceinline__ void get(int c, int& l, int32_t& t) const {
+        c = c < total ? c : total - 1;
+        l = 0;     // number of lanes whose inclusive count is <= c
+#pragma unroll
+        for (int step = WAVE / 2; step > 0; step >>= 1) {
+            const int v = __shfl(incl, l + step - 1, WAVE);
+            if (v <= c) l += step;
+        }
+        t = __shfl(off, l, WAVE) + c;
+    }
+};
+// walks the X entries of a list in steps of up to 64 candidates of one entry
+struct SpgWalk {
+    const SpgList& list;
+    int j = -1, o = 0, n = 0, s = 0;
+    __device__ __forceinline__ explicit SpgWalk(const SpgList& l) : list(l) { entry(); }
+    __device__ __forceinline__ void entry() {
+        do {
+            ++j;
+            n = j < list.nq ? __builtin_amdgcn_readlane(list.len, j) : 0;
+        } while (j < list.nq && n == 0);
+        if (j < list.nq) s = __builtin_amdgcn_readlane(list.st, j);
+        o = 0;
+    }
+    __device__ __forceinline__ bool more() const { return j < list.nq; }
+    // the step's X entry, the lane's Y index (the entry's last one beyond it) and whether the lane has one
+    __device__ __forceinline__ void take(int lane, int& l, int32_t& t, bool& in) {
+        l = j;
+        in = o + lane < n;
+        t = s + (in ? o + lane : n - 1);
+        o += WAVE;
+        if (o >= n) entry();
+    }
+};
+constexpr int SPG_PASS = 4;        // steps of a wavefront over the list whose loads are in flight together
+// calls f(first candidate, number of steps) for a list of `total` candidates, `per` of them a step, up to
+// SPG_PASS steps at a time
+template <typename F>
+__device__ __forceinline__ void spg_steps(int total, int per, F f) {
+    int base = 0;
+    for (; total - base > 2 * per; base += SPG_PASS * per) f(base, std::integral_constant<int, SPG_PASS>{});
+    if (total - base > per) f(base, std::integral_constant<int, 2>{});
+    else if (total > base) f(base, std::integral_constant<int, 1>{});
+}
+
+// Pattern of row i of X*Y: count (PHASE 0) or columns in ascending order (PHASE 1), NW wavefronts per row
+// (NW = 4 where a row meets thousands of candidates; they take 64 X entries in turn) and 4 / NW rows per
+// workgroup.  The candidates' columns set their flags, a byte each (the same column may be set by many
+// lanes at once: plain byte stores, where bits would need atomics that neighbouring columns serialise:
+// 8.8 -> 6.0 ms over the products of a 324k-row set-up).  PHASE 0 finds the row's window and leaves it in
+// win for PHASE 1; flags of masked rows stay empty.  Dynamic LDS: 4 / NW maps of `seg` bytes.
+constexpr int SPG_PSEG = 8192;     // columns of one map of flags
+template <int PHASE, int NW>
+__global__ void __launch_bounds__(256) spg_pattern_k(int64_t nr, int seg, const int32_t* __restrict__ xrp,
+                                                     const int32_t* __restrict__ xci, const int32_t* __restrict__ yrp,
+                                                     const int32_t* __restrict__ yci, const uint8_t* __restrict__ rowmask,
+                                                     int32_t* __restrict__ win, int32_t* __restrict__ cnt,
+                                                     const int32_t* __restrict__ crp,
+                                                     int32_t* __restrict__ cci) {
+    extern __shared__ uint32_t flagw[];
+    __shared__ int red[2][256 / WAVE];
+    constexpr int NT = NW * WAVE, ROWS = 256 / NT;
+    const int row = threadIdx.x / NT, tid = threadIdx.x % NT, lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const int64_t i = (int64_t)blockIdx.x * ROWS + row;
+    uint32_t* fw = flagw + row * (seg / 4);
+    uint8_t* fb = reinterpret_cast<uint8_t*>(fw);
+    const bool live = i < nr && (!rowmask || rowmask[i]);
+    const int32_t x0 = live ? xrp[i] : 0, x1 = live ? xrp[i + 1] : 0;
+    int32_t c0 = 0;
+    int n = 0;
+    if (PHASE == 0) {
+        int lo = INT32_MAX, hi = -1;
+        for (int32_t q = x0 + tid; q < x1; q += NT) {
+            const int32_t k = xci[q];
+            const int32_t s = yrp[k], e = yrp[k + 1];
+            if (e <= s) continue;
+            const int f = yci[s], l = yci[e - 1];
+            lo = f < lo ? f : lo;
+            hi = l > hi ? l : hi;
+        }
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) {
+            const int a = __shfl_xor(lo, o, WAVE), b = __shfl_xor(hi, o, WAVE);
+            lo = a < lo ? a : lo;
+            hi = b > hi ? b : hi;
+        }
+        if (lane == 0) { red[0][w] = lo; red[1][w] = hi; }
+        __syncthreads();
+        for (int v = row * NW; v < (row + 1) * NW; ++v) {
+            lo = red[0][v] < lo ? red[0][v] : lo;
+            hi = red[1][v] > hi ? red[1][v] : hi;
+        }
+        n = hi >= lo ? hi - lo + 1 : 0;
+        c0 = n ? lo : 0;
+        if (tid == 0 && i < nr) {
+            win[2 * i] = c0;
+            win[2 * i + 1] = n;
+        }
+        __syncthreads();
+    } else if (i < nr) {
+        c0 = win[2 * i];
+        n = win[2 * i + 1];
+    }
+    // (the workgroup's rows may need different numbers of segments: every thread joins each barrier)
+    if (lane == 0) red[0][w] = n;
+    __syncthreads();
+    int most = 0;
+    for (int v = 0; v < 256 / WAVE; ++v) most = red[0][v] > most ? red[0][v] : most;
+    int count = 0;
+    for (int at0 = 0; at0 < most; at0 += seg) {
+        const int32_t s0 = c0 + at0;
+        const int sn = n - at0 < seg ? (n > at0 ? n - at0 : 0) : seg;     // the row's columns of this segment
+        const int sw = (sn + 3) / 4;
+        for (int t = tid; t < sw; t += NT) fw[t] = 0;
+        __syncthreads();
+        if (sn > 0)
+            for (int32_t q0 = x0 + tid / WAVE * WAVE; q0 < x1; q0 += NT) {
+                const SpgList list(q0, x1, lane, xci, yrp);
+                auto mark = [&](int32_t c) {
+                    const unsigned at = (unsigned)(c - s0);
+                    if (at < (unsigned)sn) fb[at] = 1;
+                };
+                if (list.is_long()) {
+                    SpgWalk walk(list);
+                    while (walk.more()) {
+                        int32_t t[SPG_PASS], c[SPG_PASS];
+                        int l;
+                        bool in;
+#pragma unroll
+                        for (int u = 0; u < SPG_PASS; ++u) {
+                            t[u] = u ? t[0] : 0;
+                            if (walk.more()) walk.take(lane, l, t[u], in);
+                        }
+#pragma unroll
+                        for (int u = 0; u < SPG_PASS; ++u) c[u] = yci[t[u]];
+#pragma unroll
+                        for (int u = 0; u < SPG_PASS; ++u) mark(c[u]);
+                    }
+                } else if (list.single()) {
+                    if (list.len) mark(yci[list.st]);
+                } else {
+                    // beyond the list the last candidate again, so that no load waits behind a branch
+                    spg_steps(list.total, WAVE, [&](int base, auto steps) {
+                        constexpr int U = decltype(steps)::value;
+                        int32_t t[U], c[U];
+                        int l;
+#pragma unroll
+                        for (int u = 0; u < U; ++u) list.get(base + u * WAVE + lane, l, t[u]);
+#pragma unroll
+                        for (int u = 0; u < U; ++u) c[u] = yci[t[u]];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) mark(c[u]);
+                    });
                 }
             }
+        __syncthreads();
+        if (PHASE == 0) {
+            for (int t = tid; t < sw; t += NT) count += __popc(fw[t]);
+        } else if (tid < WAVE && sn > 0) {
+            // one wavefront emits the columns, 16 of the map per lane: a prefix of the lanes' counts
+            int32_t base = crp[i] + count;
+            for (int t0 = 0; t0 < sw; t0 += 4 * WAVE) {
+                uint32_t v[4];
+                int own = 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int t = t0 + 4 * lane + u;
+                    v[u] = t < sw ? fw[t] : 0;
+                    own += __popc(v[u]);
+                }
+                int incl = own;
+#pragma unroll
+                for (int o = 1; o < WAVE; o <<= 1) {
+                    const int u = __shfl_up(incl, o, WAVE);
+                    if (lane >= o) incl += u;
+                }
+                int32_t at = base + incl - own;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    for (uint32_t m = v[u]; m; m &= m - 1) cci[at++] = s0 + (t0 + 4 * lane + u) * 4 + (__builtin_ctz(m) >> 3);
+                const int all = __shfl(incl, WAVE - 1, WAVE);
+                base += all;
+                count += all;
+            }
         }
-    }
-    __syncthreads();
-    int w = nuniq;
-    if (w >= hmax) {
-        if (tid == 0) {
-            if (PHASE == 0) cnt[i] = -1;
-            atomicOr(overflow, 1);
-        }
-        return;
+        if (at0 + seg < most) __syncthreads();
     }
     if (PHASE == 0) {
-        if (tid == 0) cnt[i] = w;
-        return;
-    }
-    // rank sort of the unique columns
-    int32_t base = crp[i];
-    for (int a = tid; a < w; a += NW * WAVE) {
-        int key = list[a], rank = 0;
-        for (int b = 0; b < w; ++b) rank += list[b] < key;
-        cci[base + rank] = key;
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) count += __shfl_xor(count, o, WAVE);
+        if (NW > 1) {
+            __syncthreads();
+            if (lane == 0) red[1][w] = count;
+            __syncthreads();
+            count = red[1][0];
+            for (int v = 1; v < NW; ++v) count += red[1][v];
+        }
+        if (tid == 0 && i < nr) cnt[i] = count;
     }
 }
 
@@ -287,200 +402,257 @@ __global__ void __launch_bounds__(256) spg_numeric(int64_t nr, const int32_t* __
     }
 }
 
-// numeric phase, one wave per output row: the row's output columns go into an LDS hash (column ->
-// position).  The candidates (X entry q, Y entry t) of up to 64 X entries at a time are spread over
-// all lanes as in the symbolic phase, each lane forms its block product X_iq * Y_kt in registers,
-// and the products are added to their LDS accumulators in rounds: in each round the lowest pending
-// lane of every accumulator (an LDS atomic minimum over lane ids) adds its product.  Lanes hold
-// candidates in (q, t) order and a row of Y holds a column once, so every accumulator receives the
-// same terms in the same order (q ascending) as in the pull kernel above and the results are
-// identical; a round count is the largest number of candidates of one pass that meet one output
-// column, instead of one serial step per X entry.  Where the rows of Y of a chunk of 64 X entries
-// average SPG_STEP_LEN entries or more, the chunk instead takes one X entry per step with its row
-// of Y over the lanes (the same order again), which costs less than packing rows that already fill
-// the wave.
-// Dynamic LDS: hs keys, hs positions, wmax * M * P doubles, then wmax owner slots.
-constexpr int SPG_STEP_LEN = 32;
-constexpr int SPG_PF = 4;
-template <int M, int N, int P>
-__global__ void __launch_bounds__(WAVE) spg_numeric_lds(int64_t nr, int hs, int wmax, const int32_t* __restrict__ xrp,
-                                                        const int32_t* __restrict__ xci, const double* __restrict__ xv,
-                                                        const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
-                                                        const double* __restrict__ yv, const int32_t* __restrict__ crp,
-                                                        const int32_t* __restrict__ cci, double* __restrict__ cv) {
-    extern __shared__ int smem[];
-    int* keys = smem;
-    int* pos = smem + hs;
-    double* acc = reinterpret_cast<double*>(smem + 2 * hs);
-    constexpr int MP = M * P;
-    int* owner = reinterpret_cast<int*>(acc + (size_t)wmax * MP);
-    int64_t i = blockIdx.x;
-    if (i >= nr) return;
-    int lane = threadIdx.x;
-    int32_t c0 = crp[i];
-    int w = crp[i + 1] - c0;
-    if (w == 0) return;
-    for (int t = lane; t < hs; t += WAVE) keys[t] = -1;
+// ---- numeric phase with the row's sums in LDS.  Every entry of C sums its products in the order of X's row
+// (q ascending), as the pull kernel above, so the values are identical: the candidates are taken in list
+// order, and products are added to their sums by LDS atomics without return, one X entry per instruction
+// (its Y row has distinct columns; spg_add_in_order); LDS serves a wavefront's instructions in order.
+// Nothing waits for a sum, so the loads of SPG_PASS passes are in flight.
+// The row's columns as {bits, columns before the word} of each 32 columns of the window (or of a segment of
+// it, see SPG_SEG): a column's place is one 8-byte LDS read and a population count.
+struct SpgWord { uint32_t bits; int32_t before; };
+// fills map[0 .. ceil(sn / 32)) for the columns [s0, s0 + sn) of cci[lo, hi) (the NT threads of a workgroup)
+template <int NT = WAVE>
+__device__ __forceinline__ void spg_map(SpgWord* map, int32_t s0, int sn, const int32_t* __restrict__ cci, int32_t lo,
+                                        int32_t hi, int before, int tid) {
+    const int sw = (sn + 31) / 32, lane = tid & (WAVE - 1);
+    for (int t = tid; t < sw; t += NT) map[t].bits = 0;
     __syncthreads();
-    for (int p = lane; p < w; p += WAVE) {
-        int c = cci[c0 + p];
-        unsigned h = ((unsigned)c * 2654435761u) & (unsigned)(hs - 1);
-        while (atomicCAS(&keys[h], -1, c) != -1) h = (h + 1) & (unsigned)(hs - 1);
-        pos[h] = p;
-        owner[p] = WAVE;
-        for (int e = 0; e < MP; ++e) acc[p * MP + e] = 0.0;
+    for (int32_t p = lo + tid; p < hi; p += NT) {
+        const unsigned at = (unsigned)(cci[p] - s0);
+        if (at < (unsigned)sn) atomicOr(&map[at >> 5].bits, 1u << (at & 31));
     }
     __syncthreads();
-    const int32_t x0 = xrp[i], x1 = xrp[i + 1];
-    for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
-        int st = 0, len = 0;
-        if (q0 + lane < x1) {
-            int32_t k = xci[q0 + lane];
-            st = yrp[k];
-            len = yrp[k + 1] - st;
-        }
-        int incl = len;
-        for (int o = 1; o < WAVE; o <<= 1) {
-            int v = __shfl_up(incl, o, WAVE);
-            if (lane >= o) incl += v;
-        }
-        const int total = __shfl(incl, WAVE - 1, WAVE);
-        const int nq = x1 - q0 < WAVE ? x1 - q0 : WAVE;
-        if (total >= SPG_STEP_LEN * nq) {
-            // long rows of Y: one X entry per step, its row of Y over the lanes
-            if constexpr (M == 1 && N == 1 && P == 1) {
-                // scalar: the first 64 entries of the Y rows of SPG_PF steps are loaded together
-                // before those steps run in order (the same terms, order and arithmetic as below)
-                const double xl = lane < nq ? xv[q0 + lane] : 0.0;
-                for (int j0 = 0; j0 < nq; j0 += SPG_PF) {
-                    int cpf[SPG_PF];
-                    double ypf[SPG_PF];
+    if (tid < WAVE)
+        for (int t0 = 0; t0 < sw; t0 += WAVE) {
+            const int own = t0 + lane < sw ? __popc(map[t0 + lane].bits) : 0;
+            int incl = own;
 #pragma unroll
-                    for (int u = 0; u < SPG_PF; ++u) {
-                        cpf[u] = -1;
-                        ypf[u] = 0.0;
-                        if (j0 + u < nq) {
-                            const int stj = __builtin_amdgcn_readlane(st, j0 + u);
-                            if (lane < __builtin_amdgcn_readlane(len, j0 + u)) {
-                                cpf[u] = yci[stj + lane];
-                                ypf[u] = yv[stj + lane];
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < SPG_PF; ++u) {
-                        const int j = j0 + u;
-                        if (j >= nq) break;
-                        const double xj = __shfl(xl, j, WAVE);
-                        const int stj = __builtin_amdgcn_readlane(st, j);
-                        const int enj = stj + __builtin_amdgcn_readlane(len, j);
-                        for (int32_t t = stj + lane; t < enj; t += WAVE) {
-                            const int c = t == stj + lane ? cpf[u] : yci[t];
-                            const double y = t == stj + lane ? ypf[u] : yv[t];
-                            unsigned h = ((unsigned)c * 2654435761u) & (unsigned)(hs - 1);
-                            for (int g = 0; g < hs && keys[h] != c; ++g) h = (h + 1) & (unsigned)(hs - 1);
-                            if (keys[h] != c) continue;   // not reached: every column met is in the pattern
-                            double sum = 0.0;
-                            sum += xj * y;
-                            acc[pos[h]] += sum;
-                        }
-                        __syncthreads();
-                    }
-                }
-                continue;
+            for (int o = 1; o < WAVE; o <<= 1) {
+                const int u = __shfl_up(incl, o, WAVE);
+                if (lane >= o) incl += u;
             }
-            for (int j = 0; j < nq; ++j) {
-                const int stj = __builtin_amdgcn_readlane(st, j);
-                const int enj = stj + __builtin_amdgcn_readlane(len, j);
-                const double* xb = xv + (int64_t)(q0 + j) * M * N;
-                for (int t = stj + lane; t < enj; t += WAVE) {
-                    const int c = yci[t];
-                    unsigned h = ((unsigned)c * 2654435761u) & (unsigned)(hs - 1);
-                    for (int g = 0; g < hs && keys[h] != c; ++g) h = (h + 1) & (unsigned)(hs - 1);
-                    if (keys[h] != c) continue;       // not reached: every column met is in the pattern
-                    double* a = acc + pos[h] * MP;
-                    const double* yb = yv + (int64_t)t * N * P;
-                    for (int r = 0; r < M; ++r)
-                        for (int cc = 0; cc < P; ++cc) {
-                            double sum = 0.0;
-                            for (int k = 0; k < N; ++k) sum += xb[r * N + k] * yb[k * P + cc];
-                            a[r * P + cc] += sum;
-                        }
-                }
-                __syncthreads();
-            }
-            continue;
+            if (t0 + lane < sw) map[t0 + lane].before = before + incl - own;
+            before += __shfl(incl, WAVE - 1, WAVE);
         }
-        for (int base = 0; base < total; base += WAVE) {
-            const int cidx = base + lane;
-            int l = 0;     // number of lanes whose inclusive prefix is <= cidx
-            for (int step = WAVE / 2; step > 0; step >>= 1) {
-                int v = __shfl(incl, l + step - 1, WAVE);
-                if (v <= cidx) l += step;
-            }
-            const int stl = __shfl(st, l, WAVE);
-            const int excl = __shfl(incl, l, WAVE) - __shfl(len, l, WAVE);
-            bool todo = false;
-            int p = 0;
-            double prod[MP];
-            if (cidx < total) {
-                const int32_t t = stl + (cidx - excl);
-                const int c = yci[t];
-                unsigned h = ((unsigned)c * 2654435761u) & (unsigned)(hs - 1);
-                for (int g = 0; g < hs && keys[h] != c; ++g) h = (h + 1) & (unsigned)(hs - 1);
-                todo = keys[h] == c;       // always: every column met is in the pattern
-                p = pos[h];
-                const double* xb = xv + (int64_t)(q0 + l) * M * N;
-                const double* yb = yv + (int64_t)t * N * P;
-                for (int r = 0; r < M; ++r)
-                    for (int cc = 0; cc < P; ++cc) {
-                        double sum = 0.0;
-                        for (int k = 0; k < N; ++k) sum += xb[r * N + k] * yb[k * P + cc];
-                        prod[r * P + cc] = sum;
-                    }
-            }
-            while (__ballot(todo)) {
-                if (todo) atomicMin(&owner[p], lane);
-                __syncthreads();
-                if (todo && owner[p] == lane) {
-                    for (int e = 0; e < MP; ++e) acc[p * MP + e] += prod[e];
-                    owner[p] = WAVE;
-                    todo = false;
-                }
-                __syncthreads();
-            }
-        }
-    }
-    for (int p = lane; p < w; p += WAVE)
-        for (int e = 0; e < MP; ++e) cv[(int64_t)(c0 + p) * MP + e] = acc[p * MP + e];
+    __syncthreads();
+}
+// place of column c of the segment in the row, -1 if it lies outside the segment (every column met inside it
+// is in the pattern)
+__device__ __forceinline__ int spg_place(const SpgWord* map, int32_t s0, int sn, int32_t c) {
+    const unsigned at = (unsigned)(c - s0);
+    const bool in = at < (unsigned)sn;
+    const SpgWord w = map[in ? at >> 5 : 0];
+    return in ? w.before + __popc(w.bits & ((1u << (at & 31)) - 1)) : -1;
+}
+__device__ __forceinline__ void spg_add(double* p, double v) {
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
-// numeric phase of C = X Y into C's pattern (wmax = longest row of C): the LDS form when its
-// accumulators fit, else the pull form
-static void spgemm_numeric_run(const DBsr& X, const DBsr& Y, DBsr& C, int wmax, hipStream_t s) {
-    int64_t nb = cdiv(X.nr, 4);
-    int key = X.br * 100 + X.bc * 10 + Y.bc;
-    int hsn = 64;
-    while (hsn < 2 * wmax) hsn <<= 1;
-    size_t lds_n = (size_t)2 * hsn * sizeof(int) + (size_t)wmax * (C.br * C.bc * sizeof(double) + sizeof(int));
-    if (X.nr > 0 && lds_n <= 64 * 1024) {
-#define SPL(m, n, p)                                                                                          \
-    spg_numeric_lds<m, n, p><<<X.nr, WAVE, lds_n, s>>>(X.nr, hsn, wmax, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, \
-                                                       C.v)
+// adds v to sums[p] on the lanes with p >= 0, X entry after X entry (l ascends over the lanes)
+__device__ __forceinline__ void spg_add_in_order(double* sums, int p, double v, int l) {
+    uint64_t todo = __ballot(p >= 0);
+    while (todo) {
+        const int lead = __builtin_amdgcn_readlane(l, __builtin_ctzll(todo));
+        const bool mine = p >= 0 && l == lead;
+        if (mine) spg_add(sums + p, v);
+        todo &= ~__ballot(mine);
+    }
+}
+
+// scalar rows of C (M = P = 1, inner dimension N), one wavefront per row.  Dynamic LDS: wmax sums, then the
+// map.
+template <int N>
+__global__ void __launch_bounds__(WAVE) spg_scalar_k(int64_t nr, int wmax, const int32_t* __restrict__ xrp,
+                                                     const int32_t* __restrict__ xci, const double* __restrict__ xv,
+                                                     const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
+                                                     const double* __restrict__ yv, const int32_t* __restrict__ crp,
+                                                     const int32_t* __restrict__ cci, double* __restrict__ cv) {
+    extern __shared__ double sums[];
+    SpgWord* map = reinterpret_cast<SpgWord*>(sums + wmax);
+    const int64_t i = blockIdx.x;
+    if (i >= nr) return;
+    const int lane = threadIdx.x;
+    const int32_t lo = crp[i], hi = crp[i + 1];
+    if (hi <= lo) return;
+    for (int p = lane; p < hi - lo; p += WAVE) sums[p] = 0.0;
+    const int32_t c0 = cci[lo];
+    const int n = cci[hi - 1] - c0 + 1;
+    const int32_t x0 = xrp[i], x1 = xrp[i + 1];
+    for (int seg = 0; seg < n; seg += SPG_SEG) {
+        const int32_t s0 = c0 + seg;
+        const int sn = n - seg < SPG_SEG ? n - seg : SPG_SEG;
+        spg_map(map, s0, sn, cci, lo, hi, seg == 0 ? 0 : lower_col(cci, lo, hi, s0) - lo, lane);
+        for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
+            double x[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) x[k] = q0 + lane < x1 ? xv[(int64_t)(q0 + lane) * N + k] : 0.0;
+            const SpgList list(q0, x1, lane, xci, yrp);
+            if (list.is_long()) {
+                SpgWalk walk(list);
+                while (walk.more()) {
+                    int l[SPG_PASS];
+                    int32_t t[SPG_PASS], c[SPG_PASS];
+                    bool in[SPG_PASS];
+                    double y[SPG_PASS][N];
+#pragma unroll
+                    for (int u = 0; u < SPG_PASS; ++u) {
+                        l[u] = 0;
+                        t[u] = u ? t[0] : 0;
+                        in[u] = false;
+                        if (walk.more()) walk.take(lane, l[u], t[u], in[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < SPG_PASS; ++u) {
+                        c[u] = yci[t[u]];
+#pragma unroll
+                        for (int k = 0; k < N; ++k) y[u][k] = yv[(int64_t)t[u] * N + k];
+                    }
+#pragma unroll
+                    for (int u = 0; u < SPG_PASS; ++u) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int k = 0; k < N; ++k) sum += __shfl(x[k], l[u], WAVE) * y[u][k];
+                        const int p = spg_place(map, s0, sn, c[u]);
+                        if (in[u] && p >= 0) spg_add(sums + p, sum);
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+            } else if (list.single()) {
+                const bool in = list.len != 0;
+                const int32_t t = in ? list.st : 0;
+                const int32_t c = yci[t];
+                double sum = 0.0;
+#pragma unroll
+                for (int k = 0; k < N; ++k) sum += x[k] * yv[(int64_t)t * N + k];
+                spg_add_in_order(sums, in ? spg_place(map, s0, sn, c) : -1, sum, lane);
+            } else {
+                spg_steps(list.total, WAVE, [&](int base, auto steps) {
+                    constexpr int U = decltype(steps)::value;
+                    int l[U];
+                    int32_t t[U], c[U];
+                    double y[U][N];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) list.get(base + u * WAVE + lane, l[u], t[u]);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        c[u] = yci[t[u]];
+#pragma unroll
+                        for (int k = 0; k < N; ++k) y[u][k] = yv[(int64_t)t[u] * N + k];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int k = 0; k < N; ++k) sum += __shfl(x[k], l[u], WAVE) * y[u][k];
+                        const bool in = base + u * WAVE + lane < list.total;
+                        spg_add_in_order(sums, in ? spg_place(map, s0, sn, c[u]) : -1, sum, l[u]);
+                    }
+                });
+            }
+        }
+        __syncthreads();
+    }
+    for (int p = lane; p < hi - lo; p += WAVE) cv[lo + p] = sums[p];
+}
+
+// block rows (M x P blocks of C, inner dimension N), MP / 9 wavefronts per row: each owns 9 entries of every
+// block, so that each sum has one owner and the sums in LDS (18 or 36 doubles per block
+// column, which bound the rows in flight) serve 2 or 4 wavefronts; a pass takes 7 candidates, one lane
+// per entry.  Dynamic LDS: wmax * M * P sums, then the map.
+constexpr int SPG_E = 9;
+struct SpgCand { int32_t t, lp; };     // Y index; X entry (bits 24-29) and place in the row (bits 0-23)
+template <int M, int N, int P>
+__global__ void __launch_bounds__(M* P / SPG_E* WAVE)
+    spg_block_k(int64_t nr, int wmax, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci,
+                const double* __restrict__ xv, const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
+                const double* __restrict__ yv, const int32_t* __restrict__ crp, const int32_t* __restrict__ cci,
+                double* __restrict__ cv) {
+    constexpr int MP = M * P, E = SPG_E, NW = MP / E, CPP = WAVE / E, NT = NW * WAVE;
+    extern __shared__ double sums[];
+    __shared__ SpgCand batch[NT];
+    SpgWord* map = reinterpret_cast<SpgWord*>(sums + (size_t)wmax * MP);
+    const int64_t i = blockIdx.x;
+    if (i >= nr) return;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int32_t lo = crp[i], hi = crp[i + 1];
+    if (hi <= lo) return;
+    for (int p = tid; p < (hi - lo) * MP; p += NT) sums[p] = 0.0;
+    const int32_t c0 = cci[lo];
+    const int n = cci[hi - 1] - c0 + 1;
+    const int32_t x0 = xrp[i], x1 = xrp[i + 1];
+    const int slot = lane / E;                  // lane 63 holds no candidate (slot 7)
+    const int en = w * E + lane % E, r = en / P, cc = en % P;
+    for (int seg = 0; seg < n; seg += SPG_SEG) {
+        const int32_t s0 = c0 + seg;
+        const int sn = n - seg < SPG_SEG ? n - seg : SPG_SEG;
+        spg_map<NT>(map, s0, sn, cci, lo, hi, seg == 0 ? 0 : lower_col(cci, lo, hi, s0) - lo, tid);
+        for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
+            const SpgList list(q0, x1, lane, xci, yrp);
+            for (int base = 0; base < list.total; base += NT) {
+                // a batch: each thread finds one candidate and its place, for the wavefronts to share
+                int l;
+                int32_t t;
+                list.get(base + tid, l, t);
+                const int32_t col = yci[t];
+                __syncthreads();
+                batch[tid].t = t;
+                batch[tid].lp = base + tid < list.total ? (l << 24 | (spg_place(map, s0, sn, col) & 0xffffff)) : -1;
+                __syncthreads();
+                const int left = list.total - base < NT ? list.total - base : NT;
+                spg_steps(left, CPP, [&](int b0, auto steps) {
+                    constexpr int U = decltype(steps)::value;
+                    int lu[U], p[U];
+                    double x[U][N], y[U][N];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int at = b0 + u * CPP + slot;
+                        const bool in = slot < CPP && at < left;
+                        const SpgCand c = batch[in ? at : b0];
+                        lu[u] = (c.lp >> 24) & 63;
+                        p[u] = in ? (c.lp << 8) >> 8 : -1;      // -1: outside the segment
+#pragma unroll
+                        for (int k = 0; k < N; ++k) {
+                            x[u][k] = xv[((int64_t)(q0 + lu[u]) * M + r) * N + k];
+                            y[u][k] = yv[((int64_t)c.t * N + k) * P + cc];
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int k = 0; k < N; ++k) sum += x[u][k] * y[u][k];
+                        spg_add_in_order(sums, p[u] >= 0 ? p[u] * MP + en : -1, sum, lu[u]);
+                    }
+                });
+            }
+        }
+        __syncthreads();
+    }
+    for (int p = tid; p < (hi - lo) * MP; p += NT) cv[(int64_t)lo * MP + p] = sums[p];
+}
+
+// numeric phase of C = X Y into C's pattern: the sums in LDS when the widest row's fit, else the pull form
+static void spgemm_numeric(const DBsr& X, const DBsr& Y, DBsr& C, hipStream_t s) {
+    if (X.nr <= 0) return;
+    const int key = X.br * 100 + X.bc * 10 + Y.bc;
+    const int words = (std::min(C.wmax_cols, SPG_SEG) + 31) / 32;
+    const size_t lds = (size_t)C.wmax * C.br * C.bc * sizeof(double) + (size_t)words * sizeof(SpgWord);
+    const unsigned nb = (unsigned)cdiv(X.nr, 4);
+    if (lds <= 64 * 1024) {
+#define SPS(n) spg_scalar_k<n><<<(unsigned)X.nr, WAVE, lds, s>>>(X.nr, C.wmax, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v)
+#define SPB(m, n, p) spg_block_k<m, n, p><<<(unsigned)X.nr, m * p / SPG_E * WAVE, lds, s>>>(X.nr, C.wmax, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v)
         switch (key) {
-            case 111: SPL(1, 1, 1); break;
-            case 131: SPL(1, 3, 1); break;
-            case 336: SPL(3, 3, 6); break;
-            case 636: SPL(6, 3, 6); break;
-            case 666: SPL(6, 6, 6); break;
+            case 111: SPS(1); break;
+            case 131: SPS(3); break;
+            case 336: SPB(3, 3, 6); break;
+            case 636: SPB(6, 3, 6); break;
+            case 666: SPB(6, 6, 6); break;
             default: throw Error(SCR_E_UNIMPLEMENTED, "spgemm block shape " + std::to_string(key));
         }
-#undef SPL
-        check_launch("spg_numeric");
-        return;
-    }
+#undef SPS
+#undef SPB
+    } else {
 #define SPN(m, n, p) spg_numeric<m, n, p><<<nb, 256, 0, s>>>(X.nr, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v)
-    if (nb > 0) {
         switch (key) {
             case 111: SPN(1, 1, 1); break;
             case 131: SPN(1, 3, 1); break;
@@ -489,8 +661,8 @@ static void spgemm_numeric_run(const DBsr& X, const DBsr& Y, DBsr& C, int wmax, 
             case 666: SPN(6, 6, 6); break;
             default: throw Error(SCR_E_UNIMPLEMENTED, "spgemm block shape " + std::to_string(key));
         }
-    }
 #undef SPN
+    }
     check_launch("spg_numeric");
 }
 
@@ -499,89 +671,47 @@ DBsr spgemm(const DBsr& X, const DBsr& Y, const uint8_t* rowmask, Arena& ar, hip
     C.nr = X.nr; C.nc = Y.nc; C.br = X.br; C.bc = Y.bc;
     C.rp = ar.make<int32_t>(X.nr + 1);
     int32_t* cnt = ar.make<int32_t>(X.nr + 1);
-    int* flags = ar.make<int>(3);      // [overflow, max candidate bound, max output row length]
-    unsigned long long* csum = ar.make<unsigned long long>(1);   // candidates over all rows
-    zero_dev(flags, 3 * sizeof(int), s);
-    zero_dev(csum, sizeof(unsigned long long), s);
+    int32_t* win = ar.make<int32_t>(2 * X.nr + 1);
+    struct Head { int maxwin, wmax; };     // widest window, longest row
+    Head* head = ar.make<Head>(1);
+    Head h{};
+    zero_dev(head, sizeof(Head), s);
+    // rows that meet SPG_WIDE candidates or more (by the mean lengths of both factors) take four wavefronts
+    const bool wide = X.nr > 0 && Y.nr > 0 &&
+                      (double)X.nnzb * (double)Y.nnzb >= (double)SPG_WIDE * (double)X.nr * (double)Y.nr;
+    const int seg = (int)(std::min<int64_t>(Y.nc > 0 ? Y.nc : 1, SPG_PSEG) + 3) / 4 * 4;
+    const unsigned grid = (unsigned)cdiv(X.nr, wide ? 1 : 4);
+    const size_t lds = (size_t)seg * (wide ? 1 : 4);
+#define SPP(ph)                                                                                                    \
+    if (X.nr > 0 && wide)                                                                                          \
+        spg_pattern_k<ph, 4><<<grid, 256, lds, s>>>(X.nr, seg, X.rp, X.ci, Y.rp, Y.ci, rowmask, win, cnt,          \
+                                                    C.rp, C.ci);                                    \
+    else if (X.nr > 0)                                                                                             \
+        spg_pattern_k<ph, 1><<<grid, 256, lds, s>>>(X.nr, seg, X.rp, X.ci, Y.rp, Y.ci, rowmask, win, cnt,          \
+                                                    C.rp, C.ci)
+    SPP(0);
     if (X.nr > 0)
-        spg_bound_k<<<(unsigned)std::min<int64_t>(cdiv(X.nr, 256 / WAVE), SPG_BOUND_BLOCKS), 256, 0, s>>>(
-            X.nr, X.rp, X.ci, Y.rp, flags + 1, csum);
-    int hflags[2] = {0, 0};
-    unsigned long long hsum = 0;
-    HIPCHK(hipMemcpyAsync(hflags, flags, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&hsum, csum, sizeof(hsum), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    ar.free(csum);
-    // hash table of the counting pass: twice the candidate bound, but at most HS_COUNT slots (the
-    // unique columns of a row are far fewer than its candidates); the rows that overflow it are
-    // counted again with a table four times larger.  The result does not depend on the table size.
-    // Products whose rows meet SPG_NW_BOUND candidates or more on average take four wavefronts
-    // per row.
-    const bool wide = X.nr > 0 && hsum >= (unsigned long long)SPG_NW_BOUND * (unsigned long long)X.nr;
-    int need = 2 * (hflags[1] < HMAX ? hflags[1] : HMAX) + 2;
-    int hs = 64;
-    while (hs < need && hs < HS_COUNT) hs <<= 1;
-    int hf[3] = {0, 0, 0};
-    for (int retry = 0;; retry = 1) {
-        if (X.nr > 0) {
-            if (wide)
-                spg_symbolic<0, 4><<<X.nr, 4 * WAVE, (size_t)(hs + hs / 2 + 4 * WAVE) * sizeof(int), s>>>(
-                    X.nr, hs, retry, X.rp, X.ci, Y.rp, Y.ci, rowmask, cnt, nullptr, nullptr, flags);
-            else
-                spg_symbolic<0, 1><<<X.nr, WAVE, (size_t)(hs + hs / 2 + WAVE) * sizeof(int), s>>>(
-                    X.nr, hs, retry, X.rp, X.ci, Y.rp, Y.ci, rowmask, cnt, nullptr, nullptr, flags);
-        }
-        check_launch("spg_count");
-        HIPCHK(hipMemcpyAsync(hf, flags, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        if (!hf[0]) break;
-        if (hs >= HS_MAX) throw Error(SCR_E_INVALID, "Galerkin product row wider than " + std::to_string(HMAX) + " blocks");
-        hs = std::min(4 * hs, HS_MAX);
-        zero_dev(flags, sizeof(int), s);
-    }
-    // widest output row (flags[2] is still zero: the counting pass does not touch it)
-    if (X.nr > 0) max_i32_k<<<(unsigned)std::min<int64_t>(cdiv(X.nr, 256), 1024), 256, 0, s>>>(X.nr, cnt, flags + 2);
-    check_launch("max_i32");
-    HIPCHK(hipMemcpyAsync(&hf[2], flags + 2, sizeof(int), hipMemcpyDeviceToHost, s));
-    C.nnzb = scan_i32(cnt, C.rp, X.nr, ar, s);
-    HIPCHK(hipStreamSynchronize(s));
-    const int wmax = hf[2];
-    ar.free(cnt);
+        spg_max_k<<<(unsigned)std::min<int64_t>(cdiv(X.nr, 256), 256), 256, 0, s>>>(X.nr, cnt, win, &head->wmax,
+                                                                                    &head->maxwin);
+    check_launch("spg_count");
+    HIPCHK(hipMemcpyAsync(&h, head, sizeof(Head), hipMemcpyDeviceToHost, s));
+    C.nnzb = scan_i32(cnt, C.rp, X.nr, ar, s);      // synchronises
+    if (h.wmax >= HMAX) throw Error(SCR_E_INVALID, "Galerkin product row wider than " + std::to_string(HMAX) + " blocks");
+    C.wmax = h.wmax;
+    C.wmax_cols = h.maxwin;
     C.ci = ar.make<int32_t>(C.nnzb > 0 ? C.nnzb : 1);
     C.v = ar.make<double>((C.nnzb > 0 ? C.nnzb : 1) * C.br * C.bc);
-    // the filling pass knows the widest row exactly
-    int hs1 = 64;
-    while (hs1 < 2 * wmax + 2) hs1 <<= 1;
-    if (X.nr > 0) {
-        if (wide)
-            spg_symbolic<1, 4><<<X.nr, 4 * WAVE, (size_t)(hs1 + hs1 / 2 + 4 * WAVE) * sizeof(int), s>>>(
-                X.nr, hs1, 0, X.rp, X.ci, Y.rp, Y.ci, rowmask, nullptr, C.rp, C.ci, flags);
-        else
-            spg_symbolic<1, 1><<<X.nr, WAVE, (size_t)(hs1 + hs1 / 2 + WAVE) * sizeof(int), s>>>(
-                X.nr, hs1, 0, X.rp, X.ci, Y.rp, Y.ci, rowmask, nullptr, C.rp, C.ci, flags);
-    }
+    SPP(1);
+#undef SPP
     check_launch("spg_fill");
-    ar.free(flags);
-    spgemm_numeric_run(X, Y, C, wmax, s);
+    ar.free(cnt); ar.free(win); ar.free(head);
+    spgemm_numeric(X, Y, C, s);
     return C;
 }
 
-// max row length of a pattern
 __global__ void __launch_bounds__(256) rowlen_max_k(int64_t nr, const int32_t* __restrict__ rp, int* __restrict__ out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     block_max_to(i < nr ? rp[i + 1] - rp[i] : 0, out);
-}
-
-// numeric phase only, into the existing pattern of C (same terms and order as a full product)
-static void spgemm_numeric(const DBsr& X, const DBsr& Y, DBsr& C, Arena& ar, hipStream_t s) {
-    int* d = ar.make<int>(1);
-    zero_dev(d, sizeof(int), s);
-    if (C.nr > 0) rowlen_max_k<<<cdiv(C.nr, 256), 256, 0, s>>>(C.nr, C.rp, d);
-    int wmax = 0;
-    HIPCHK(hipMemcpyAsync(&wmax, d, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    ar.free(d);
-    spgemm_numeric_run(X, Y, C, wmax, s);
 }
 
 // ---------------------------------------------------------------------- S^ = C - D d^-1 G
@@ -1968,7 +2098,7 @@ void update_hierarchy(Hierarchy& H, const double* vals0, const double* B0, Arena
         ptent_fill_k<<<g, 256, 0, s>>>(nr, b * kk, L.agg, Pt.rp, Q, Pt.ci, Pt.v);
         check_launch("ptent");
         // smoothed prolongator into its kept pattern
-        spgemm_numeric(L.A, Pt, L.P, ar, s);
+        spgemm_numeric(L.A, Pt, L.P, s);
         bsr_release(Pt, ar);
         double omega = 4.0 / (3.0 * L.lam);
         if (b == 1 && kk == 1) smooth_p_k<1, 1><<<g, 256, 0, s>>>(nr, L.P.rp, L.P.ci, L.P.v, L.Dinv, L.agg, Q, omega);
@@ -1981,8 +2111,8 @@ void update_hierarchy(Hierarchy& H, const double* vals0, const double* B0, Arena
         L.R = transpose(L.P, ar, s);
         // Galerkin product into the kept patterns of A P and A_{l+1}
         L.AP.v = ar.make<double>((L.AP.nnzb > 0 ? L.AP.nnzb : 1) * L.AP.br * L.AP.bc);
-        spgemm_numeric(L.A, L.P, L.AP, ar, s);
-        spgemm_numeric(L.R, L.AP, N.A, ar, s);
+        spgemm_numeric(L.A, L.P, L.AP, s);
+        spgemm_numeric(L.R, L.AP, N.A, s);
         ar.free(L.AP.v);
         L.AP.v = nullptr;
         if (na) dead_diag_k<<<cdiv(na, 256), 256, 0, s>>>(na, kk, N.A.rp, N.A.ci, N.A.v, L.dead);

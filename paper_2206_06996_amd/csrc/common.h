@@ -283,6 +283,7 @@ struct DBsr {
     int32_t* rp = nullptr;
     int32_t* ci = nullptr;
     double* v = nullptr;
+    int wmax = 0, wmax_cols = 0;     // results of spgemm: the longest row, and the widest (last - first column + 1)
 };
 
 // Sliced ELL, two lane mappings.

@@ -50,3 +50,34 @@ def test_products_and_vcycles_at_every_split(scr, nodes):
                 assert np.abs(d).max() <= 1e-13 * np.abs(yo).max(), (op, precision)
         h.destroy()
     ctx.destroy()
+
+
+def test_setup_products_on_a_shuffled_numbering(scr):
+    """Rows renumbered at random: the columns of a product's row then span the whole matrix (about 42,000
+    columns), beyond the 8,192 and 32,768 that its maps hold at a time.  Patterns, aggregates and strength
+    flags bit-exact against the oracle, values within the bars of the hierarchy tests."""
+    from tests.test_gpu_parity import _compare_hierarchy
+    s = synth.generate(synth.tube_params(40e3, 1.0, 5.0))
+    n = s.n_b
+    assert n > 32768
+    new = np.random.default_rng(1).permutation(n)                # new index of each row
+    rows = np.repeat(np.arange(n), np.diff(s.rp))
+    r, c = new[rows], new[s.ci]
+    order = np.lexsort((c, r))
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(np.bincount(r, minlength=n))
+    ci, val = c[order].astype(np.int32), s.val[order]
+    xyz = np.empty_like(s.xyz)
+    xyz[new] = s.xyz
+    ctx = scr.Context(0)
+    print(f"[gpu] shuffled setup n_b={n}", flush=True)
+    h = scr.amg_setup(ctx, scr.SCR_SYSTEM, dev(rp), dev(ci), dev(val.reshape(-1)), dev(xyz.reshape(-1)))
+    o = oracle.Scr(rp, ci, val, xyz)
+    grp, gci, gv = h.matrix_copy("Shat")
+    orp, oci, ov = o.matrix("Shat")
+    assert np.array_equal(grp, orp) and np.array_equal(gci, oci)
+    assert np.abs(gv - ov).max() <= 1e-13 * np.abs(ov).max()
+    _compare_hierarchy(h, 0, o.amgA)
+    _compare_hierarchy(h, 1, o.amgS)
+    h.destroy()
+    ctx.destroy()
