@@ -410,9 +410,10 @@ __global__ void __launch_bounds__(256) spg_numeric(int64_t nr, const int32_t* __
 // The row's columns as {bits, columns before the word} of each 32 columns of the window (or of a segment of
 // it, see SPG_SEG): a column's place is one 8-byte LDS read and a population count.
 struct SpgWord { uint32_t bits; int32_t before; };
-// fills map[0 .. ceil(sn / 32)) for the columns [s0, s0 + sn) of cci[lo, hi) (the NT threads of a workgroup)
+// fills map[0 .. ceil(sn / 32)) for the columns [s0, s0 + sn) of cci[lo, hi) (the NT threads of a workgroup);
+// returns the columns up to the segment's end on the first wavefront
 template <int NT = WAVE>
-__device__ __forceinline__ void spg_map(SpgWord* map, int32_t s0, int sn, const int32_t* __restrict__ cci, int32_t lo,
+__device__ __forceinline__ int spg_map(SpgWord* map, int32_t s0, int sn, const int32_t* __restrict__ cci, int32_t lo,
                                         int32_t hi, int before, int tid) {
     const int sw = (sn + 31) / 32, lane = tid & (WAVE - 1);
     for (int t = tid; t < sw; t += NT) map[t].bits = 0;
@@ -435,6 +436,7 @@ __device__ __forceinline__ void spg_map(SpgWord* map, int32_t s0, int sn, const 
             before += __shfl(incl, WAVE - 1, WAVE);
         }
     __syncthreads();
+    return before;
 }
 // place of column c of the segment in the row, -1 if it lies outside the segment (every column met inside it
 // is in the pattern)
@@ -795,14 +797,14 @@ __global__ void __launch_bounds__(256) merge_sub_k(int64_t nr, const int32_t* __
     }
 }
 
-DBsr schur_approx(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, Arena& ar,
+DBsr schur_approx(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, DBsr& DG, Arena& ar,
                   hipStream_t s) {
     DBsr X = D;
     X.v = ar.make<double>(D.nnzb * 3);
     if (A.nr > 0) schur_diag_k<<<cdiv(A.nr, 256), 256, 0, s>>>(A.nr, mode, A.rp, A.ci, A.v, d);
     if (D.nr > 0) diag_scale_D<<<cdiv(D.nr, 256), 256, 0, s>>>(D.nr, D.rp, D.ci, d, D.v, X.v);
     check_launch("diag_scale_D");
-    DBsr DG = spgemm(X, G, nullptr, ar, s);
+    DG = spgemm(X, G, nullptr, ar, s);
     ar.free(X.v);
     DBsr S;
     S.nr = C.nr; S.nc = C.nc; S.br = 1; S.bc = 1;
@@ -816,23 +818,26 @@ DBsr schur_approx(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, in
     S.v = ar.make<double>(S.nnzb);
     if (nw) merge_sub_k<1><<<nw, 256, 0, s>>>(C.nr, C.rp, C.ci, C.v, DG.rp, DG.ci, DG.v, nullptr, S.rp, S.ci, S.v);
     check_launch("merge_sub");
-    bsr_release(DG, ar);
+    ar.free(DG.v);
+    DG.v = nullptr;
     return S;
 }
 
-void schur_update(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, DBsr& S, Arena& ar,
-                  hipStream_t s) {
+void schur_update(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, DBsr& DG, DBsr& S,
+                  Arena& ar, hipStream_t s) {
     DBsr X = D;
     X.v = ar.make<double>(D.nnzb * 3);
     if (A.nr > 0) schur_diag_k<<<cdiv(A.nr, 256), 256, 0, s>>>(A.nr, mode, A.rp, A.ci, A.v, d);
     if (D.nr > 0) diag_scale_D<<<cdiv(D.nr, 256), 256, 0, s>>>(D.nr, D.rp, D.ci, d, D.v, X.v);
     check_launch("diag_scale_D");
-    DBsr DG = spgemm(X, G, nullptr, ar, s);
+    DG.v = ar.make<double>(DG.nnzb > 0 ? DG.nnzb : 1);
+    spgemm_numeric(X, G, DG, s);
     ar.free(X.v);
     int64_t nw = cdiv(C.nr, 256 / WAVE);
     if (nw) merge_sub_k<1><<<nw, 256, 0, s>>>(C.nr, C.rp, C.ci, C.v, DG.rp, DG.ci, DG.v, nullptr, S.rp, S.ci, S.v);
     check_launch("merge_sub");
-    bsr_release(DG, ar);
+    ar.free(DG.v);
+    DG.v = nullptr;
 }
 
 // ---------------------------------------------------------------------- rigid-body modes
@@ -878,52 +883,65 @@ void rigid_modes(int64_t nb, const double* xyz, double* B, Arena& ar, hipStream_
 }
 
 // ====================================================================== strength and MIS-2
-__device__ __forceinline__ double block_f(const double* __restrict__ v, int bb) {
-    double f = 0.0;
-    for (int e = 0; e < bb; ++e) f = f + v[e] * v[e];
-    return f;
+// squared Frobenius norm of every block, its entries added in order.  A workgroup takes 64 blocks: their
+// values come coalesced through LDS (36 values a block read by one thread each kept 64 lines per load busy:
+// the strength pass over 1.35M 6x6 blocks took 970 us)
+__global__ void __launch_bounds__(256) block_f_k(int64_t nnzb, int bb, const double* __restrict__ v, double* __restrict__ f) {
+    extern __shared__ double stage[];        // 64 blocks of bb values, bb + 1 apart
+    const int64_t q0 = (int64_t)blockIdx.x * WAVE;
+    const int n = nnzb - q0 < WAVE ? (int)(nnzb - q0) : WAVE;
+    for (int t = threadIdx.x; t < n * bb; t += 256) {
+        const int q = t / bb;
+        stage[q * (bb + 1) + t - q * bb] = v[q0 * bb + t];
+    }
+    __syncthreads();
+    if ((int)threadIdx.x >= n) return;
+    double sum = 0.0;
+    for (int e = 0; e < bb; ++e) {
+        const double x = stage[threadIdx.x * (bb + 1) + e];
+        sum = sum + x * x;
+    }
+    f[q0 + threadIdx.x] = sum;
 }
-__global__ void fdiag_k(int64_t nr, int bb, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                        const double* __restrict__ v, double* __restrict__ fd) {
+__global__ void fdiag_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, const double* __restrict__ f,
+                        double* __restrict__ fd) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nr) return;
     int32_t q = find_col(ci, rp[i], rp[i + 1], (int32_t)i);
-    fd[i] = q >= 0 ? block_f(v + (int64_t)q * bb, bb) : 0.0;
+    fd[i] = q >= 0 ? f[q] : 0.0;
 }
-// strength of the coupling at entry q = (i, j) of row i, symmetrised with (j, i)
-__device__ __forceinline__ uint8_t strong_entry(int64_t i, int32_t q, int bb, const int32_t* __restrict__ rp,
-                                                const int32_t* __restrict__ ci, const double* __restrict__ v,
+// strength of the coupling at entry q = (i, j) of row i, symmetrised with (j, i), which is looked up only
+// where (i, j) alone is not strong
+__device__ __forceinline__ uint8_t strong_entry(int64_t i, int32_t q, const int32_t* __restrict__ rp,
+                                                const int32_t* __restrict__ ci, const double* __restrict__ f,
                                                 const double* __restrict__ fd, double th4) {
-    int32_t j = ci[q];
+    const int32_t j = ci[q];
     if (j == i) return 0;
-    double fij = block_f(v + (int64_t)q * bb, bb);
-    bool s1 = (fij * fij) >= ((th4 * fd[i]) * fd[j]);
-    bool s2 = false;
-    int32_t t = find_col(ci, rp[j], rp[j + 1], (int32_t)i);
-    if (t >= 0) {
-        double fji = block_f(v + (int64_t)t * bb, bb);
-        s2 = (fji * fji) >= ((th4 * fd[j]) * fd[i]);
-    }
-    return (s1 || s2) ? 1 : 0;
+    const double fij = f[q];
+    if ((fij * fij) >= ((th4 * fd[i]) * fd[j])) return 1;
+    const int32_t t = find_col(ci, rp[j], rp[j + 1], (int32_t)i);
+    if (t < 0) return 0;
+    const double fji = f[t];
+    return (fji * fji) >= ((th4 * fd[j]) * fd[i]) ? 1 : 0;
 }
 
-__global__ void strength_k(int64_t nr, int bb, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                           const double* __restrict__ v, const double* __restrict__ fd, double th4,
+__global__ void strength_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                           const double* __restrict__ f, const double* __restrict__ fd, double th4,
                            uint8_t* __restrict__ flags, uint8_t* __restrict__ iso) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nr) return;
     uint8_t any = 0;
     for (int32_t q = rp[i]; q < rp[i + 1]; ++q) {
-        const uint8_t f = strong_entry(i, q, bb, rp, ci, v, fd, th4);
-        flags[q] = f;
-        any |= f;
+        const uint8_t st = strong_entry(i, q, rp, ci, f, fd, th4);
+        flags[q] = st;
+        any |= st;
     }
     iso[i] = any ? 0 : 1;
 }
 
 // the same with one wavefront per row, lanes over its entries (levels with long rows)
-__global__ void __launch_bounds__(256) strength_wave_k(int64_t nr, int bb, const int32_t* __restrict__ rp,
-                                                       const int32_t* __restrict__ ci, const double* __restrict__ v,
+__global__ void __launch_bounds__(256) strength_wave_k(int64_t nr, const int32_t* __restrict__ rp,
+                                                       const int32_t* __restrict__ ci, const double* __restrict__ f,
                                                        const double* __restrict__ fd, double th4,
                                                        uint8_t* __restrict__ flags, uint8_t* __restrict__ iso) {
     const int64_t i = (int64_t)blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE;
@@ -931,9 +949,9 @@ __global__ void __launch_bounds__(256) strength_wave_k(int64_t nr, int bb, const
     if (i >= nr) return;
     int any = 0;
     for (int32_t q = rp[i] + lane; q < rp[i + 1]; q += WAVE) {
-        const uint8_t f = strong_entry(i, q, bb, rp, ci, v, fd, th4);
-        flags[q] = f;
-        any |= f;
+        const uint8_t st = strong_entry(i, q, rp, ci, f, fd, th4);
+        flags[q] = st;
+        any |= st;
     }
     const uint64_t b = __ballot(any);
     if (lane == 0) iso[i] = b ? 0 : 1;
@@ -1012,39 +1030,57 @@ __global__ void agg_roots_k(int64_t nr, const uint64_t* __restrict__ st, const i
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nr) agg[i] = (st[i] >> 62) == 2 ? rid[i] : -1;
 }
-__global__ void agg_dist1_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                            const uint8_t* __restrict__ flags, const uint8_t* __restrict__ iso, const uint64_t* __restrict__ st,
-                            const int32_t* __restrict__ rid, int32_t* __restrict__ agg, uint8_t* __restrict__ step1) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// (a wavefront per row; the first strong IN neighbour, and the strong neighbour of largest key, as a walk over
+// the row in order finds them)
+__global__ void __launch_bounds__(256) agg_dist1_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                                                   const uint8_t* __restrict__ flags, const uint8_t* __restrict__ iso,
+                                                   const uint64_t* __restrict__ st, const int32_t* __restrict__ rid,
+                                                   int32_t* __restrict__ agg, uint8_t* __restrict__ step1) {
+    const int64_t i = (int64_t)blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE;
     if (i >= nr) return;
-    step1[i] = 0;
-    if (iso[i] || (st[i] >> 62) == 2) return;
-    for (int32_t q = rp[i]; q < rp[i + 1]; ++q) {
-        int32_t j = ci[q];
-        if (flags[q] && (st[j] >> 62) == 2) {
-            agg[i] = rid[j];
-            step1[i] = 1;
+    const int lane = threadIdx.x & (WAVE - 1);
+    if (iso[i] || (st[i] >> 62) == 2) {
+        if (lane == 0) step1[i] = 0;
+        return;
+    }
+    for (int32_t q0 = rp[i]; q0 < rp[i + 1]; q0 += WAVE) {
+        const int32_t q = q0 + lane;
+        const bool in = q < rp[i + 1];
+        const int32_t j = in ? ci[q] : 0;
+        const uint64_t hit = __ballot(in && flags[q] && (st[j] >> 62) == 2);
+        if (hit) {
+            if (lane == __builtin_ctzll(hit)) {
+                agg[i] = rid[j];
+                step1[i] = 1;
+            }
             return;
         }
     }
+    if (lane == 0) step1[i] = 0;
 }
-__global__ void agg_dist2_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                            const uint8_t* __restrict__ flags, const uint8_t* __restrict__ iso,
-                            const uint8_t* __restrict__ step1, uint64_t seed, int level, int32_t* __restrict__ agg,
-                            int* __restrict__ err) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) agg_dist2_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                                                   const uint8_t* __restrict__ flags, const uint8_t* __restrict__ iso,
+                                                   const uint8_t* __restrict__ step1, uint64_t seed, int level,
+                                                   int32_t* __restrict__ agg, int* __restrict__ err) {
+    const int64_t i = (int64_t)blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE;
     if (i >= nr) return;
+    const int lane = threadIdx.x & (WAVE - 1);
     if (iso[i] || agg[i] >= 0) return;
-    uint64_t best = 0;
-    int32_t bj = -1;
-    for (int32_t q = rp[i]; q < rp[i + 1]; ++q) {
-        int32_t j = ci[q];
+    uint64_t best = 0;       // key + 1 (keys hold the index: no two are equal)
+    for (int32_t q = rp[i] + lane; q < rp[i + 1]; q += WAVE) {
+        const int32_t j = ci[q];
         if (!flags[q] || !step1[j]) continue;
-        uint64_t kj = mis_key(seed, level, j);
-        if (bj < 0 || kj > best) { best = kj; bj = j; }
+        const uint64_t kj = mis_key(seed, level, j) + 1;
+        best = kj > best ? kj : best;
     }
-    if (bj < 0) { atomicOr(err, 1); return; }
-    agg[i] = agg[bj];   // bj joined in the distance-1 step: its aggregate is final
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        const uint64_t k = __shfl_xor(best, o, WAVE);
+        best = k > best ? k : best;
+    }
+    if (lane != 0) return;
+    if (best == 0) { atomicOr(err, 1); return; }
+    agg[i] = agg[(uint32_t)(best - 1)];   // it joined in the distance-1 step: its aggregate is final
 }
 
 // ====================================================================== tentative prolongator
@@ -1057,15 +1093,16 @@ __global__ void agg_fill_k(int64_t nr, const int32_t* __restrict__ agg, const in
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nr && agg[i] >= 0) mem[mrp[agg[i]] + atomicAdd(&fillc[agg[i]], 1)] = (int32_t)i;
 }
-__global__ void agg_sort_k(int64_t na, const int32_t* __restrict__ mrp, int32_t* __restrict__ mem) {
-    int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= na) return;
-    int32_t lo = mrp[a], hi = mrp[a + 1];
-    for (int32_t t = lo + 1; t < hi; ++t) {
-        int32_t v = mem[t], u = t - 1;
-        while (u >= lo && mem[u] > v) { mem[u + 1] = mem[u]; --u; }
-        mem[u + 1] = v;
-    }
+// members of each aggregate in ascending order: every member goes to its rank in its aggregate's list
+__global__ void agg_sort_k(int64_t nm, const int32_t* __restrict__ agg, const int32_t* __restrict__ mrp,
+                           const int32_t* __restrict__ mem, int32_t* __restrict__ out) {
+    int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= nm) return;
+    const int32_t i = mem[m];
+    const int32_t lo = mrp[agg[i]], hi = mrp[agg[i] + 1];
+    int32_t rank = 0;
+    for (int32_t t = lo; t < hi; ++t) rank += mem[t] < i;
+    out[lo + rank] = i;
 }
 
 // Gram-Schmidt (two modified-GS passes) of B restricted to the aggregate's rows (members in
@@ -1126,17 +1163,29 @@ __global__ void tentative_k(int64_t na, int b, int k, const int32_t* __restrict_
     }
 }
 
-// The same factorisation with one wavefront per aggregate and the aggregate's rows of Q in LDS
-// (rows in member order, k columns).  Every sum is taken by lane 0 in that row order, so the
-// rounding is that of tentative_k; the element-wise updates run on all lanes.
-__global__ void __launch_bounds__(WAVE) tentative_lds_k(int64_t na, int b, int k, const int32_t* __restrict__ mrp,
+// The same factorisation with one wavefront per aggregate and the aggregate's rows of Q in LDS (rows in member
+// order, k columns).  The products of a dot go to LDS from all lanes, and every lane then adds them in row
+// order (the rounding is that of tentative_k, and no lane waits for another's result); the element-wise
+// updates run on all lanes.  Dynamic LDS: nmax b k values of Q, then nmax b products.
+__device__ __forceinline__ double ordered_sum(const double* p, int n) {
+    double sum = 0.0;
+    int t = 0;
+    for (; t + 8 <= n; t += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = p[t + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += x[u];
+    }
+    for (; t < n; ++t) sum += p[t];
+    return sum;
+}
+__global__ void __launch_bounds__(WAVE) tentative_lds_k(int64_t na, int b, int k, int nmax, const int32_t* __restrict__ mrp,
                                                         const int32_t* __restrict__ mem, const double* __restrict__ B,
                                                         double* __restrict__ Q, double* __restrict__ Bc,
                                                         uint8_t* __restrict__ dead) {
     extern __shared__ double q[];
-    __shared__ double bc[2];
-    __shared__ double rk[64];      // R of the aggregate (k <= 8)
-    __shared__ uint8_t dl[8];
+    double* prod = q + (size_t)nmax * b * k;
     const int64_t a = blockIdx.x;
     if (a >= na) return;
     const int lane = threadIdx.x;
@@ -1147,41 +1196,40 @@ __global__ void __launch_bounds__(WAVE) tentative_lds_k(int64_t na, int b, int k
         const int t = rr / b, r = rr - t * b;
         q[e] = B[((int64_t)mem[lo + t] * b + r) * k + c];
     }
-    for (int e = lane; e < k * k; e += WAVE) rk[e] = 0.0;
+    for (int e = lane; e < k * k; e += WAVE) Bc[a * k * k + e] = 0.0;
     __syncthreads();
+    auto dot = [&](int i, int j) {
+        for (int rr = lane; rr < nrow; rr += WAVE) prod[rr] = q[rr * k + i] * q[rr * k + j];
+        __syncthreads();
+        const double c = ordered_sum(prod, nrow);
+        __syncthreads();
+        return c;
+    };
+    unsigned gone = 0;       // dead columns (k <= 8)
     for (int j = 0; j < k; ++j) {
-        double nb = 0.0;
-        if (lane == 0) {
-            for (int rr = 0; rr < nrow; ++rr) nb += q[rr * k + j] * q[rr * k + j];
-            nb = sqrt(nb);
-        }
+        const double nb = sqrt(dot(j, j));
+        double rij[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rij[i] = 0.0;
         for (int pass = 0; pass < 2; ++pass)
-            for (int i = 0; i < j; ++i) {
-                if (dl[i]) continue;           // written and synchronised when column i finished
-                if (lane == 0) {
-                    double c = 0.0;
-                    for (int rr = 0; rr < nrow; ++rr) c += q[rr * k + i] * q[rr * k + j];
-                    bc[0] = c;
-                    rk[i * k + j] += c;
-                }
-                __syncthreads();
-                const double c = bc[0];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (i >= j || (gone >> i) & 1) continue;
+                const double c = dot(i, j);
+                rij[i] += c;
                 for (int rr = lane; rr < nrow; rr += WAVE) q[rr * k + j] -= c * q[rr * k + i];
                 __syncthreads();
             }
+        const double nv = sqrt(dot(j, j));
+        const bool isdead = (nb == 0.0) || (nv <= 1e-10 * nb);
+        if (isdead) gone |= 1u << j;
         if (lane == 0) {
-            double nv = 0.0;
-            for (int rr = 0; rr < nrow; ++rr) nv += q[rr * k + j] * q[rr * k + j];
-            nv = sqrt(nv);
-            const bool isdead = (nb == 0.0) || (nv <= 1e-10 * nb);
-            dl[j] = isdead ? 1 : 0;
             dead[a * k + j] = isdead ? 1 : 0;
-            rk[j * k + j] = isdead ? 0.0 : nv;
-            bc[1] = nv;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i < j) Bc[a * k * k + i * k + j] = rij[i];
+            Bc[a * k * k + j * k + j] = isdead ? 0.0 : nv;
         }
-        __syncthreads();
-        const double nv = bc[1];
-        const bool isdead = dl[j] != 0;
         for (int rr = lane; rr < nrow; rr += WAVE) q[rr * k + j] = isdead ? 0.0 : q[rr * k + j] / nv;
         __syncthreads();
     }
@@ -1190,7 +1238,6 @@ __global__ void __launch_bounds__(WAVE) tentative_lds_k(int64_t na, int b, int k
         const int t = rr / b, r = rr - t * b;
         Q[((int64_t)mem[lo + t] * b + r) * k + c] = q[e];
     }
-    for (int e = lane; e < k * k; e += WAVE) Bc[a * k * k + e] = rk[e];
 }
 
 // tentative prolongator of all aggregates: the LDS form when the largest aggregate fits
@@ -1205,8 +1252,8 @@ static void tentative_run(int64_t na, int b, int k, const int32_t* mrp, const in
     HIPCHK(hipMemcpyAsync(&hm, mx, sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     ar.free(mx);
-    const size_t lds = (size_t)hm * b * k * sizeof(double);
-    if (k <= 8 && lds <= 48 * 1024) tentative_lds_k<<<(unsigned)na, WAVE, lds, s>>>(na, b, k, mrp, mem, B, Q, Bc, dead);
+    const size_t lds = (size_t)hm * b * (k + 1) * sizeof(double);
+    if (k <= 8 && lds <= 56 * 1024) tentative_lds_k<<<(unsigned)na, WAVE, lds, s>>>(na, b, k, hm, mrp, mem, B, Q, Bc, dead);
     else tentative_k<<<cdiv(na, 64), 64, 0, s>>>(na, b, k, mrp, mem, B, Q, Bc, dead);
     check_launch("tentative");
 }
@@ -1256,31 +1303,49 @@ __device__ bool invert_small(const double* __restrict__ a, double* __restrict__ 
 }
 
 template <int B>
-__global__ void __launch_bounds__(256) dinv_lambda_k(int64_t nr, const int32_t* __restrict__ rp,
-                                                     const int32_t* __restrict__ ci, const double* __restrict__ v,
-                                                     double* __restrict__ Dinv, unsigned long long* __restrict__ lam,
-                                                     int* __restrict__ err) {
+__global__ void __launch_bounds__(256) dinv_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                                              const double* __restrict__ v, double* __restrict__ Dinv, int* __restrict__ err) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double m = 0.0;     // max absolute row sum of D^-1 A over the block row (0 for idle threads)
-    if (i < nr) {
-        int32_t q = find_col(ci, rp[i], rp[i + 1], (int32_t)i);
-        double Di[B * B];
-        if (q < 0 || !invert_small<B>(v + (int64_t)q * B * B, Di)) {
-            atomicOr(err, 1);
-        } else {
-            for (int e = 0; e < B * B; ++e) Dinv[i * B * B + e] = Di[e];
-            double rs[B];
-            for (int r = 0; r < B; ++r) rs[r] = 0.0;
-            for (int32_t t = rp[i]; t < rp[i + 1]; ++t) {
-                const double* blk = v + (int64_t)t * B * B;
-                for (int r = 0; r < B; ++r)
-                    for (int c = 0; c < B; ++c) {
-                        double sum = 0.0;
-                        for (int l = 0; l < B; ++l) sum += Di[r * B + l] * blk[l * B + c];
-                        rs[r] += fabs(sum);
-                    }
-            }
-            for (int r = 0; r < B; ++r) m = rs[r] > m ? rs[r] : m;
+    if (i >= nr) return;
+    const int32_t q = find_col(ci, rp[i], rp[i + 1], (int32_t)i);
+    double Di[B * B];
+    const bool ok = q >= 0 && invert_small<B>(v + (int64_t)q * B * B, Di);
+    if (!ok) atomicOr(err, 1);
+    for (int e = 0; e < B * B; ++e) Dinv[i * B * B + e] = ok ? Di[e] : 0.0;
+}
+// lam = max over the rows of the absolute row sums of D^-1 A: a wavefront per block row (grid-stride), its
+// blocks over the lanes (one thread per row left rows of 50 and more blocks to one lane: 6x6 blocks at
+// 24,500 rows 650 us)
+constexpr int LAMBDA_BLOCKS = 2048;
+template <int B>
+__global__ void __launch_bounds__(256) lambda_k(int64_t nr, const int32_t* __restrict__ rp, const double* __restrict__ v,
+                                                const double* __restrict__ Dinv, unsigned long long* __restrict__ lam) {
+    const int lane = threadIdx.x & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    double m = 0.0;     // max absolute row sum of D^-1 A over the rows taken
+    for (int64_t i = (int64_t)blockIdx.x * (256 / WAVE) + w; i < nr; i += (int64_t)gridDim.x * (256 / WAVE)) {
+        double Di[B * B], rs[B];
+#pragma unroll
+        for (int e = 0; e < B * B; ++e) Di[e] = Dinv[i * B * B + e];
+#pragma unroll
+        for (int r = 0; r < B; ++r) rs[r] = 0.0;
+        for (int32_t t = rp[i] + lane; t < rp[i + 1]; t += WAVE) {
+            double blk[B * B];
+#pragma unroll
+            for (int e = 0; e < B * B; ++e) blk[e] = v[(int64_t)t * B * B + e];
+#pragma unroll
+            for (int r = 0; r < B; ++r)
+#pragma unroll
+                for (int c = 0; c < B; ++c) {
+                    double sum = 0.0;
+#pragma unroll
+                    for (int l = 0; l < B; ++l) sum += Di[r * B + l] * blk[l * B + c];
+                    rs[r] += fabs(sum);
+                }
+        }
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            const double sum = wave_sum(rs[r]);
+            m = sum > m ? sum : m;
         }
     }
     // nonnegative doubles order as their bit patterns
@@ -1327,30 +1392,59 @@ __global__ void tr_fill_k(int64_t nr, const int32_t* __restrict__ rp, const int3
         src[pos] = q;
     }
 }
-// place each entry of a transposed row at its rank (source rows are unique within a row)
-__global__ void tr_rank_k(int64_t nnz, int64_t ntr, const int32_t* __restrict__ trp, const int32_t* __restrict__ tci,
-                          const int32_t* __restrict__ src, const double* __restrict__ v, int br, int bc,
-                          int32_t* __restrict__ oci, double* __restrict__ ov, const int32_t* __restrict__ rowof) {
-    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nnz) return;
-    int32_t r = rowof[p];
-    int32_t lo = trp[r], hi = trp[r + 1];
-    int32_t key = tci[p], rank = 0;
-    for (int32_t u = lo; u < hi; ++u) rank += tci[u] < key;
-    int64_t dst = lo + rank;
-    oci[dst] = key;
-    const double* s = v + (int64_t)src[p] * br * bc;
-    double* d = ov + dst * br * bc;
-    for (int r0 = 0; r0 < br; ++r0)
-        for (int c0 = 0; c0 < bc; ++c0) d[c0 * br + r0] = s[r0 * bc + c0];
+// the entries of each transposed row in ascending order (source rows are unique within a row): a wavefront per
+// row, the place of an entry from the prefix counts of a map of the row's keys (TR_SEG keys of its window at
+// a time), as in the products above; rows of a thousand entries cost no more per entry than short ones
+constexpr int TR_SEG = 8192;
+__global__ void __launch_bounds__(WAVE) tr_sort_k(int64_t ntr, const int32_t* __restrict__ trp, const int32_t* __restrict__ tci,
+                                                  const int32_t* __restrict__ src, int32_t* __restrict__ oci,
+                                                  int32_t* __restrict__ osrc) {
+    __shared__ SpgWord map[TR_SEG / 32];
+    const int64_t r = blockIdx.x;
+    if (r >= ntr) return;
+    const int lane = threadIdx.x;
+    const int32_t lo = trp[r], hi = trp[r + 1];
+    if (hi <= lo) return;
+    int k0 = INT32_MAX, k1 = -1;
+    for (int32_t p = lo + lane; p < hi; p += WAVE) {
+        const int k = tci[p];
+        k0 = k < k0 ? k : k0;
+        k1 = k > k1 ? k : k1;
+    }
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        const int a = __shfl_xor(k0, o, WAVE), b = __shfl_xor(k1, o, WAVE);
+        k0 = a < k0 ? a : k0;
+        k1 = b > k1 ? b : k1;
+    }
+    int before = 0;
+    for (int64_t s0 = k0; s0 <= k1; s0 += TR_SEG) {
+        const int sn = k1 + 1 - s0 < TR_SEG ? (int)(k1 + 1 - s0) : TR_SEG;
+        before = spg_map(map, (int32_t)s0, sn, tci, lo, hi, before, lane);
+        for (int32_t p = lo + lane; p < hi; p += WAVE) {
+            const int32_t k = tci[p];
+            const int at = spg_place(map, (int32_t)s0, sn, k);
+            if (at >= 0) {
+                oci[lo + at] = k;
+                osrc[lo + at] = src[p];
+            }
+        }
+        __syncthreads();
+    }
 }
-__global__ void row_of_k(int64_t nr, const int32_t* __restrict__ rp, int32_t* __restrict__ rowof) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nr) return;
-    for (int32_t q = rp[i]; q < rp[i + 1]; ++q) rowof[q] = (int32_t)i;
+// values of the transpose from those of the matrix: thread per value, in the order they are written
+__global__ void tr_values_k(int64_t nv, int br, int bc, const int32_t* __restrict__ src, const double* __restrict__ v,
+                            double* __restrict__ ov) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= nv) return;
+    const int bb = br * bc;
+    const int64_t p = t / bb;
+    const int e = (int)(t - p * bb), c = e / br, r = e - c * br;
+    ov[t] = v[(int64_t)src[p] * bb + r * bc + c];
 }
 
-DBsr transpose(const DBsr& M, Arena& ar, hipStream_t s) {
+// M^T; src (if not NULL) receives the index in M of each of its entries, for transpose_values
+DBsr transpose(const DBsr& M, Arena& ar, hipStream_t s, int32_t** src_out) {
     DBsr T;
     T.nr = M.nc; T.nc = M.nr; T.br = M.bc; T.bc = M.br; T.nnzb = M.nnzb;
     int32_t* cnt = ar.make<int32_t>(M.nc + 1);
@@ -1362,15 +1456,21 @@ DBsr transpose(const DBsr& M, Arena& ar, hipStream_t s) {
     int32_t* tci = ar.make<int32_t>(M.nnzb + 1);
     int32_t* src = ar.make<int32_t>(M.nnzb + 1);
     if (M.nr) tr_fill_k<<<cdiv(M.nr, 256), 256, 0, s>>>(M.nr, M.rp, M.ci, T.rp, cnt, tci, src);
-    int32_t* rowof = ar.make<int32_t>(M.nnzb + 1);
-    if (T.nr) row_of_k<<<cdiv(T.nr, 256), 256, 0, s>>>(T.nr, T.rp, rowof);
     T.ci = ar.make<int32_t>(M.nnzb + 1);
     T.v = ar.make<double>((M.nnzb + 1) * M.br * M.bc);
-    if (M.nnzb)
-        tr_rank_k<<<cdiv(M.nnzb, 256), 256, 0, s>>>(M.nnzb, T.nr, T.rp, tci, src, M.v, M.br, M.bc, T.ci, T.v, rowof);
+    int32_t* osrc = ar.make<int32_t>(M.nnzb + 1);
+    if (T.nr) tr_sort_k<<<(unsigned)T.nr, WAVE, 0, s>>>(T.nr, T.rp, tci, src, T.ci, osrc);
     check_launch("transpose");
-    ar.free(cnt); ar.free(tci); ar.free(src); ar.free(rowof);
+    ar.free(cnt); ar.free(tci); ar.free(src);
+    transpose_values(M, T, osrc, s);
+    if (src_out) *src_out = osrc;
+    else ar.free(osrc);
     return T;
+}
+void transpose_values(const DBsr& M, DBsr& T, const int32_t* src, hipStream_t s) {
+    const int64_t nv = M.nnzb * M.br * M.bc;
+    if (nv) tr_values_k<<<cdiv(nv, 256), 256, 0, s>>>(nv, M.br, M.bc, src, M.v, T.v);
+    check_launch("transpose values");
 }
 
 __global__ void dead_diag_k(int64_t na, int k, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
@@ -1640,44 +1740,50 @@ class HierT : public Hierarchy {
             q.A = sell_from_bsr<T>(ls.A, a, s);
             q.P = sell_from_bsr<T>(ls.P, a, s);
             q.R = bsrt_from_bsr<T>(ls.R, a, s);
-            int64_t bb = (int64_t)ls.A.nr * ls.b * ls.b;
-            q.Dinv = a.make<T>(bb);
-            if (std::is_same<T, double>::value) copy_d(bb, ls.Dinv, (double*)q.Dinv, s);
-            else cast_d2f(ls.Dinv, (float*)q.Dinv, bb, s);
+            q.Dinv = a.make<T>((int64_t)ls.A.nr * ls.b * ls.b);
             q.w = a.make<T>(n); q.t1 = a.make<T>(n); q.t2 = a.make<T>(n); q.d = a.make<T>(n); q.r = a.make<T>(n);
             if (three) {
                 q.w3 = a.make<T>(3 * n); q.t13 = a.make<T>(3 * n); q.t23 = a.make<T>(3 * n);
                 q.d3 = a.make<T>(3 * n); q.r3 = a.make<T>(3 * n);
             }
-            // smoothing coefficients: step t computes dn = c1[t] d + c2[t] Dinv (b - A x)
-            if (opts.smoother == SCR_SMOOTH_CHEBYSHEV) {
-                q.cheb = true;
-                double lmax = ls.lam, lmin = ls.lam / opts.cheb_ratio;
-                double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin);
-                double sigma = theta / delta, rho_prev = 1.0 / sigma;
-                q.c1.push_back(0.0); q.c2.push_back(1.0 / theta);
-                for (int t = 1; t < opts.cheb_degree; ++t) {
-                    double rho = 1.0 / (2.0 * sigma - rho_prev);
-                    q.c1.push_back(rho * rho_prev); q.c2.push_back(2.0 * rho / delta);
-                    rho_prev = rho;
-                }
-            } else {
-                double w = 4.0 / (3.0 * ls.lam);
-                for (int t = 0; t < opts.jacobi_sweeps; ++t) { q.c1.push_back(0.0); q.c2.push_back(w); }
+            smoother(l, s);
+        }
+    }
+    // D^-1 in T and the smoothing coefficients of level l from its set-up data:
+    // step t computes dn = c1[t] d + c2[t] Dinv (b - A x)
+    void smoother(size_t l, hipStream_t s) {
+        LevelSetup& ls = L[l];
+        LS& q = S[l];
+        const int64_t bb = (int64_t)ls.A.nr * ls.b * ls.b;
+        if (std::is_same<T, double>::value) copy_d(bb, ls.Dinv, (double*)q.Dinv, s);
+        else cast_d2f(ls.Dinv, (float*)q.Dinv, bb, s);
+        q.c1.clear();
+        q.c2.clear();
+        if (opts.smoother == SCR_SMOOTH_CHEBYSHEV) {
+            q.cheb = true;
+            double lmax = ls.lam, lmin = ls.lam / opts.cheb_ratio;
+            double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin);
+            double sigma = theta / delta, rho_prev = 1.0 / sigma;
+            q.c1.push_back(0.0); q.c2.push_back(1.0 / theta);
+            for (int t = 1; t < opts.cheb_degree; ++t) {
+                double rho = 1.0 / (2.0 * sigma - rho_prev);
+                q.c1.push_back(rho * rho_prev); q.c2.push_back(2.0 * rho / delta);
+                rho_prev = rho;
             }
+        } else {
+            double w = 4.0 / (3.0 * ls.lam);
+            for (int t = 0; t < opts.jacobi_sweeps; ++t) { q.c1.push_back(0.0); q.c2.push_back(w); }
         }
     }
 
-    void refresh(Arena& a, hipStream_t s) override {
-        for (auto& q : S) {
-            sell_free(q.A, a);
-            sell_free(q.P, a);
-            a.free(q.R.v);
-            for (T* p : {q.Dinv, q.b, q.x, q.w, q.t1, q.t2, q.d, q.r}) a.free(p);
-            for (T* p : {q.b3, q.x3, q.w3, q.t13, q.t23, q.d3, q.r3}) a.free(p);
+    // the patterns are kept: new values into the same slices, vectors and index arrays untouched
+    void refresh(Arena&, hipStream_t s) override {
+        for (size_t l = 0; l + 1 < L.size(); ++l) {
+            sell_refill(L[l].A, S[l].A, s);
+            sell_refill(L[l].P, S[l].P, s);
+            bsrt_refill(L[l].R, S[l].R, s);
+            smoother(l, s);
         }
-        S.clear();
-        prepare(a, s);
     }
 
     // algorithmic bytes of one smoother step with a matrix product: every stored block (values
@@ -1768,6 +1874,10 @@ class HierT : public Hierarchy {
         if (!std::is_same<T, float>::value || S.size() < 2) return nullptr;
         return (const DSell<float>*)&S[0].A;
     }
+    const DSell<double>* level0_d() const override {
+        if (!std::is_same<T, double>::value || S.size() < 2) return nullptr;
+        return (const DSell<double>*)&S[0].A;
+    }
 
     void vcycle(const double* x, double* y, hipStream_t s) override {
         ++vcycles;
@@ -1803,10 +1913,17 @@ void level_diag(LevelSetup& L, int l, int* err, unsigned long long* lamd, hipStr
     zero_dev(err, sizeof(int), s);
     zero_dev(lamd, sizeof(unsigned long long), s);
     if (g) {
-        if (b == 1) dinv_lambda_k<1><<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.A.v, L.Dinv, lamd, err);
-        else if (b == 3) dinv_lambda_k<3><<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.A.v, L.Dinv, lamd, err);
-        else if (b == 6) dinv_lambda_k<6><<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.A.v, L.Dinv, lamd, err);
+        const unsigned gl = (unsigned)std::min<int64_t>(cdiv(nr, 256 / WAVE), LAMBDA_BLOCKS);
+#define DL(B)                                                                     \
+    {                                                                             \
+        dinv_k<B><<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.A.v, L.Dinv, err);      \
+        lambda_k<B><<<gl, 256, 0, s>>>(nr, L.A.rp, L.A.v, L.Dinv, lamd);          \
+    }
+        if (b == 1) DL(1)
+        else if (b == 3) DL(3)
+        else if (b == 6) DL(6)
         else throw Error(SCR_E_UNIMPLEMENTED, "AMG block size");
+#undef DL
     }
     check_launch("dinv_lambda");
     unsigned long long hl = 0;
@@ -1938,15 +2055,21 @@ std::unique_ptr<Hierarchy> build_hierarchy(const DBsr& A0, const double* B0, int
         double* fd = ar.make<double>(nr);
         L.strong = ar.make<uint8_t>(L.A.nnzb > 0 ? L.A.nnzb : 1);
         uint8_t* iso = ar.make<uint8_t>(nr);
-        fdiag_k<<<g, 256, 0, s>>>(nr, bb, L.A.rp, L.A.ci, L.A.v, fd);
+        double* f = ar.make<double>(L.A.nnzb > 0 ? L.A.nnzb : 1);
+        if (L.A.nnzb > 0)
+            block_f_k<<<(unsigned)cdiv(L.A.nnzb, WAVE), 256, (size_t)WAVE * (bb + 1) * sizeof(double), s>>>(L.A.nnzb, bb, L.A.v, f);
+        fdiag_k<<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, f, fd);
         double theta = std::ldexp(o.theta, -l);
         double th4 = ((theta * theta) * theta) * theta;
-        // rows of 16 or more entries on average: one wavefront per row (same flags)
+        // rows of 16 or more entries on average: one wavefront per row (same flags); of 8 or more for the
+        // strength (1,030 -> 430 us at 324k rows of 15.6 blocks)
         const bool wide = L.A.nnzb >= 16 * nr;
-        if (wide) strength_wave_k<<<cdiv(nr, 256 / WAVE), 256, 0, s>>>(nr, bb, L.A.rp, L.A.ci, L.A.v, fd, th4, L.strong, iso);
-        else strength_k<<<g, 256, 0, s>>>(nr, bb, L.A.rp, L.A.ci, L.A.v, fd, th4, L.strong, iso);
+        if (L.A.nnzb >= 8 * nr)
+            strength_wave_k<<<cdiv(nr, 256 / WAVE), 256, 0, s>>>(nr, L.A.rp, L.A.ci, f, fd, th4, L.strong, iso);
+        else strength_k<<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, f, fd, th4, L.strong, iso);
         check_launch("strength");
         ar.free(fd);
+        ar.free(f);
         // MIS-2 rounds
         uint64_t* st = ar.make<uint64_t>(nr);
         uint64_t* m1 = ar.make<uint64_t>(nr);
@@ -1981,9 +2104,9 @@ std::unique_ptr<Hierarchy> build_hierarchy(const DBsr& A0, const double* B0, int
         L.agg = ar.make<int32_t>(nr);
         uint8_t* step1 = ar.make<uint8_t>(nr);
         agg_roots_k<<<g, 256, 0, s>>>(nr, st, rid, L.agg);
-        agg_dist1_k<<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.strong, iso, st, rid, L.agg, step1);
+        agg_dist1_k<<<cdiv(nr, 256 / WAVE), 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.strong, iso, st, rid, L.agg, step1);
         zero_dev(err, sizeof(int), s);
-        agg_dist2_k<<<g, 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.strong, iso, step1, o.seed, l, L.agg, err);
+        agg_dist2_k<<<cdiv(nr, 256 / WAVE), 256, 0, s>>>(nr, L.A.rp, L.A.ci, L.strong, iso, step1, o.seed, l, L.agg, err);
         check_launch("aggregate");
         HIPCHK(hipMemcpyAsync(&he, err, sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
@@ -2004,8 +2127,10 @@ std::unique_ptr<Hierarchy> build_hierarchy(const DBsr& A0, const double* B0, int
         int64_t nmem = scan_i32(mcnt, mrp, na, ar, s);
         zero_dev(mcnt, (na + 1) * sizeof(int32_t), s);
         int32_t* mem = ar.make<int32_t>(nmem + 1);
-        agg_fill_k<<<g, 256, 0, s>>>(nr, L.agg, mrp, mcnt, mem);
-        agg_sort_k<<<cdiv(na, 64), 64, 0, s>>>(na, mrp, mem);
+        int32_t* unsorted = ar.make<int32_t>(nmem + 1);
+        agg_fill_k<<<g, 256, 0, s>>>(nr, L.agg, mrp, mcnt, unsorted);
+        if (nmem > 0) agg_sort_k<<<cdiv(nmem, 256), 256, 0, s>>>(nmem, L.agg, mrp, unsorted, mem);
+        ar.free(unsorted);
         // tentative prolongator and coarse near-null space
         double* Q = ar.make<double>(nr * b * kk);
         zero_dev(Q, nr * b * kk * sizeof(double), s);
@@ -2043,7 +2168,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(const DBsr& A0, const double* B0, int
         check_launch("smooth_p");
         ar.free(Q);
         L.P = P;
-        L.R = transpose(L.P, ar, s);
+        L.R = transpose(L.P, ar, s, &L.rsrc);
         // Galerkin product A_c = R (A P) on structural patterns; dead coarse dofs get a unit diagonal
         DBsr AP = spgemm(L.A, L.P, nullptr, ar, s);
         N.A = spgemm(L.R, AP, nullptr, ar, s);
@@ -2107,8 +2232,7 @@ void update_hierarchy(Hierarchy& H, const double* vals0, const double* B0, Arena
         else throw Error(SCR_E_UNIMPLEMENTED, "prolongator block shape");
         check_launch("smooth_p");
         ar.free(Q);
-        bsr_release(L.R, ar);
-        L.R = transpose(L.P, ar, s);
+        transpose_values(L.P, L.R, L.rsrc, s);
         // Galerkin product into the kept patterns of A P and A_{l+1}
         L.AP.v = ar.make<double>((L.AP.nnzb > 0 ? L.AP.nnzb : 1) * L.AP.br * L.AP.bc);
         spgemm_numeric(L.A, L.P, L.AP, s);

@@ -19,6 +19,8 @@ void cast_f2d(const float* a, double* b, int64_t n, hipStream_t s);
 
 // ---------------------------------------------------------------- sparse (sparse.hip)
 template <typename T> DSell<T> sell_from_bsr(const DBsr& A, Arena& ar, hipStream_t s);
+// the entries of A again into its sliced form (new values on the same pattern)
+template <typename T> void sell_refill(const DBsr& A, DSell<T>& S, hipStream_t s);
 template <typename T> void sell_free(DSell<T>& A, Arena& ar);
 // Block CSR with values in T (row-wave kernels for wide rows, e.g. restriction)
 template <typename T>
@@ -31,6 +33,7 @@ struct DBsrT {
     T* v = nullptr;
 };
 template <typename T> DBsrT<T> bsrt_from_bsr(const DBsr& A, Arena& ar, hipStream_t s);
+template <typename T> void bsrt_refill(const DBsr& A, DBsrT<T>& R, hipStream_t s);   // new values, same pattern
 
 // y = A x (mode 0), y = b - A x (mode 1), y += A x (mode 2), y -= A x (mode 3)
 template <typename T> void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s);

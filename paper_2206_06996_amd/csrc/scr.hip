@@ -50,7 +50,12 @@ struct scr_handle {
     int64_t nb = 0;
     // SCR system (FP64 setup form; A, G, D, C share K's index arrays)
     DBsr K, A, G, D, C, Sh;
-    DSell<double> Ks, As, Gs, Ds, Cs, Ls, Shs;   // Shs: S^ for SIMPLE, built on first use
+    DBsr DG;                                      // pattern of D d^-1 G (for amg_update; no values)
+    // As, Ls: only where level 0 of an FP64 hierarchy does not hold the same (a_sell, l_sell); Shs: S^ for
+    // SIMPLE, built on first use
+    DSell<double> Ks, As, Gs, Ds, Cs, Ls, Shs;
+    const DSell<double>& a_sell() const { return hA->level0_d() ? *hA->level0_d() : As; }
+    const DSell<double>& l_sell() const { return hL->level0_d() ? *hL->level0_d() : Ls; }
     double* B = nullptr;
     double* dvec = nullptr;                       // the diagonal d used in S^ (3n)
     std::unique_ptr<Hierarchy> hA, hS, hL;
@@ -149,7 +154,7 @@ struct AOp : Op {
     const scr_handle* h;
     explicit AOp(const scr_handle* hh) : h(hh) {}
     void apply(const double* x, double* y, hipStream_t s) override {
-        sell_mv<double>(h->As, x, nullptr, y, 0, s);
+        sell_mv<double>(h->a_sell(), x, nullptr, y, 0, s);
         apply_outlets(h, x, y, s);
     }
 };
@@ -309,7 +314,7 @@ void ensure_workspaces(scr_handle* h, const scr_solve_opts& o, hipStream_t s) {
 // hierarchy or on request) with one product with L and one V-cycle of AMG(L) per iteration for all
 // three columns; ws holds Pcg3::workspace_doubles(n) doubles.  Fills the handle's stats.
 bool mesh_solve_run(scr_handle* h, const double* b, double* x, const scr_solve_opts& o, double* ws, hipStream_t s) {
-    MatOp3 lop(&h->Ls);
+    MatOp3 lop(&h->l_sell());
     VOp3 pl(h->hL.get());
     const bool flexible = o.flexible_cg || h->opts.precision != SCR_FP64;
     const int64_t v0 = h->hL->vcycles;
@@ -528,7 +533,7 @@ scr_status amg_setup(scr_ctx* ctx, int kind, const scr_bsr* K, const double* coo
             if (o.schur_diag != SCR_DIAG_A && o.schur_diag != SCR_DIAG_ABSROWSUM)
                 throw Error(SCR_E_INVALID, "schur_diag must be SCR_DIAG_A or SCR_DIAG_ABSROWSUM");
             h->dvec = ar.make<double>(3 * nb);
-            h->Sh = schur_approx(h->A, h->G, h->D, h->C, o.schur_diag, h->dvec, ar, s);
+            h->Sh = schur_approx(h->A, h->G, h->D, h->C, o.schur_diag, h->dvec, h->DG, ar, s);
             double* xyz = ar.make<double>(nb * 3);
             copy_dev(xyz, coords, nb * 3 * sizeof(double), s);
             h->B = ar.make<double>(nb * 18);
@@ -547,7 +552,7 @@ scr_status amg_setup(scr_ctx* ctx, int kind, const scr_bsr* K, const double* coo
             h->hS = build_hierarchy(h->Sh, ones, 1, oS, ar, s);
             ar.free(ones);
             h->Ks = sell_from_bsr<double>(Km, ar, s);
-            h->As = sell_from_bsr<double>(h->A, ar, s);
+            if (!h->hA->level0_d()) h->As = sell_from_bsr<double>(h->A, ar, s);
             h->Gs = sell_from_bsr<double>(h->G, ar, s);
             h->Ds = sell_from_bsr<double>(h->D, ar, s);
             h->Cs = sell_from_bsr<double>(h->C, ar, s);
@@ -563,7 +568,7 @@ scr_status amg_setup(scr_ctx* ctx, int kind, const scr_bsr* K, const double* coo
             fill<double>(ones, 1.0, nb, s);
             h->hL = build_hierarchy(Km, ones, 1, o, ar, s, nullptr, true);
             ar.free(ones);
-            h->Ls = sell_from_bsr<double>(Km, ar, s);
+            if (!h->hL->level0_d()) h->Ls = sell_from_bsr<double>(Km, ar, s);
             h->mslot.h = ctx->c.pinned.get();
             h->mslot.d = PinnedPool::device_ptr(h->mslot.h);
             h->mslot.h[15] = 0.0;
@@ -620,7 +625,7 @@ scr_status amg_update(scr_handle* h, const scr_bsr* K, const double* coords, voi
         copy_dev(Km.v, K->val, Km.nnzb * Km.br * Km.bc * sizeof(double), s);
         if (h->kind == SCR_SYSTEM) {
             split_values(Km, h->A, h->G, h->D, h->C, s);
-            schur_update(h->A, h->G, h->D, h->C, h->opts.schur_diag, h->dvec, h->Sh, ar, s);
+            schur_update(h->A, h->G, h->D, h->C, h->opts.schur_diag, h->dvec, h->DG, h->Sh, ar, s);
             if (coords) {
                 double* xyz = ar.make<double>(nb * 3);
                 copy_dev(xyz, coords, nb * 3 * sizeof(double), s);
@@ -629,20 +634,15 @@ scr_status amg_update(scr_handle* h, const scr_bsr* K, const double* coords, voi
             }
             update_hierarchy(*h->hA, h->A.v, coords ? h->B : nullptr, ar, s);
             update_hierarchy(*h->hS, h->Sh.v, nullptr, ar, s);
-            for (DSell<double>* M : {&h->Ks, &h->As, &h->Gs, &h->Ds, &h->Cs}) sell_free(*M, ar);
-            h->Ks = sell_from_bsr<double>(Km, ar, s);
-            h->As = sell_from_bsr<double>(h->A, ar, s);
-            h->Gs = sell_from_bsr<double>(h->G, ar, s);
-            h->Ds = sell_from_bsr<double>(h->D, ar, s);
-            h->Cs = sell_from_bsr<double>(h->C, ar, s);
-            if (h->Shs.nslices) {
-                sell_free(h->Shs, ar);
-                h->Shs = sell_from_bsr<double>(h->Sh, ar, s);
-            }
+            sell_refill(Km, h->Ks, s);
+            sell_refill(h->A, h->As, s);
+            sell_refill(h->G, h->Gs, s);
+            sell_refill(h->D, h->Ds, s);
+            sell_refill(h->C, h->Cs, s);
+            sell_refill(h->Sh, h->Shs, s);     // nothing unless SIMPLE has set it up
         } else {
             update_hierarchy(*h->hL, Km.v, nullptr, ar, s);
-            sell_free(h->Ls, ar);
-            h->Ls = sell_from_bsr<double>(Km, ar, s);
+            sell_refill(Km, h->Ls, s);
         }
         HIPCHK(hipStreamSynchronize(s));
         h->broken = false;
@@ -999,7 +999,7 @@ scr_status scr_apply(scr_handle* h, int op, const double* x, double* y, const sc
                 sell_free(S, *h->ar);
                 break;
             }
-            case 10: sell_mv<double>(h->Ls, x, nullptr, y, 0, s); break;
+            case 10: sell_mv<double>(h->l_sell(), x, nullptr, y, 0, s); break;
             case 11: h->hL->vcycle(x, y, s); break;
             case 12: { ensure_simple(h, s); SimplePrec p(h); p.apply(x, y, s); break; }
             case 13: copy_d(3 * h->nb, h->dvec, y, s); break;

@@ -111,8 +111,10 @@ struct LevelSetup {
     uint8_t* func = nullptr;         // classical AMG: the function (unknown) of each scalar row
     double* ell = nullptr;           // classical AMG, l1 smoother: the l1 term of each row's diagonal
     double lam = 0.0;
-    // kept for the numeric re-setup: aggregate member lists and the pattern of A P (no values)
+    // kept for the numeric re-setup: aggregate member lists, the order of R's entries and the pattern of A P
+    // (no values)
     int32_t *mrp = nullptr, *mem = nullptr;
+    int32_t* rsrc = nullptr;         // entry of P behind each entry of R
     DBsr AP;
 };
 
@@ -131,6 +133,8 @@ class Hierarchy {
     virtual void vcycle3(const double* x, double* y, hipStream_t s) = 0;
     bool three = false;
     virtual const DSell<float>* level0_f() const = 0;
+    // FP64 hierarchies: the sliced-ELL copy of the level-0 matrix, where the hierarchy keeps one in blocks
+    virtual const DSell<double>* level0_d() const { return nullptr; }
     std::vector<LevelSetup> L;
     double* cinv = nullptr;          // dense inverse of the coarsest matrix (FP64)
     int64_t ncoarse = 0;
@@ -151,8 +155,8 @@ std::unique_ptr<Hierarchy> build_hierarchy(const DBsr& A0, const double* B0, int
 void update_hierarchy(Hierarchy& H, const double* vals0, const double* B0, Arena& ar, hipStream_t s);
 
 // new values of S^ = C - D d^-1 G into its existing pattern (the patterns of A, G, D, C unchanged)
-void schur_update(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, DBsr& S, Arena& ar,
-                  hipStream_t s);
+void schur_update(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, DBsr& DG, DBsr& S,
+                  Arena& ar, hipStream_t s);
 
 // values of the split of K into A, G, D, C (patterns already set up by split_blocks)
 void split_values(const DBsr& K, DBsr& A, DBsr& G, DBsr& D, DBsr& C, hipStream_t s);
@@ -169,7 +173,9 @@ void bsr_release(DBsr& M, Arena& ar);
 // C = X Y on the structural pattern (rows with rowmask[i] == 0 left empty when rowmask is given);
 // each entry sums its products in the order of X's row
 DBsr spgemm(const DBsr& X, const DBsr& Y, const uint8_t* rowmask, Arena& ar, hipStream_t s);
-DBsr transpose(const DBsr& M, Arena& ar, hipStream_t s);
+DBsr transpose(const DBsr& M, Arena& ar, hipStream_t s, int32_t** src_out = nullptr);
+// new values of T = M^T on its kept pattern (src: transpose's map)
+void transpose_values(const DBsr& M, DBsr& T, const int32_t* src, hipStream_t s);
 // D^-1 and lambda_hat of a level (err, lamd: one-element device scratch)
 void level_diag(LevelSetup& L, int l, int* err, unsigned long long* lamd, hipStream_t s);
 // explicit inverse of the coarsest level into H.cinv (fast, with a pivoted fallback)
@@ -181,7 +187,8 @@ void rigid_modes(int64_t nb, const double* xyz, double* B, Arena& ar, hipStream_
 // split K (4x4) into A (3x3), G (3x1), D (1x3), C (1x1) and build S^ = C - D diag(A)^-1 G
 void split_blocks(const DBsr& K, DBsr& A, DBsr& G, DBsr& D, DBsr& C, Arena& ar, hipStream_t s);
 // S^ = C - D d^-1 G; d (3n, written) = diag(A) (mode 0) or the absolute row sums of A (mode 1)
-DBsr schur_approx(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, Arena& ar,
+// (DG receives the pattern of D d^-1 G for schur_update)
+DBsr schur_approx(const DBsr& A, const DBsr& G, const DBsr& D, const DBsr& C, int mode, double* d, DBsr& DG, Arena& ar,
                   hipStream_t s);
 
 }  // namespace scr

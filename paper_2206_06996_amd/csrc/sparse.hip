@@ -56,27 +56,33 @@ __global__ void scan_sums(int64_t* __restrict__ sums, int64_t nt) {
     if (threadIdx.x == 0) sums[nt] = carry;
 }
 
-__global__ void scan_tiles(const int32_t* __restrict__ in, int64_t n, const int64_t* __restrict__ sums,
-                           int32_t* __restrict__ out) {
-    __shared__ int64_t buf[SCAN_TILE];
-    int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
+// each thread sums SCAN_PER consecutive entries, the wavefronts scan the threads' sums with shuffles and the
+// wavefront sums are added through LDS (one thread walking the 1,024 entries of a tile took 14 us)
+__global__ void __launch_bounds__(SCAN_TPB) scan_tiles(const int32_t* __restrict__ in, int64_t n,
+                                                       const int64_t* __restrict__ sums, int32_t* __restrict__ out) {
+    __shared__ int64_t red[SCAN_TPB / WAVE];
+    const int64_t i0 = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_PER;
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    int64_t v[SCAN_PER], own = 0;
+#pragma unroll
     for (int k = 0; k < SCAN_PER; ++k) {
-        int64_t i = base + k * SCAN_TPB + threadIdx.x;
-        buf[k * SCAN_TPB + threadIdx.x] = i < n ? in[i] : 0;
+        v[k] = i0 + k < n ? in[i0 + k] : 0;
+        own += v[k];
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = sums[blockIdx.x];
-        for (int t = 0; t < SCAN_TILE; ++t) {
-            int64_t v = buf[t];
-            buf[t] = run;
-            run += v;
-        }
+    int64_t incl = own;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int64_t u = __shfl_up(incl, o, WAVE);
+        if (lane >= o) incl += u;
     }
+    if (lane == WAVE - 1) red[w] = incl;
     __syncthreads();
+    int64_t run = sums[blockIdx.x] + incl - own;
+    for (int q = 0; q < w; ++q) run += red[q];
+#pragma unroll
     for (int k = 0; k < SCAN_PER; ++k) {
-        int64_t i = base + k * SCAN_TPB + threadIdx.x;
-        if (i < n) out[i] = (int32_t)buf[k * SCAN_TPB + threadIdx.x];
+        if (i0 + k < n) out[i0 + k] = (int32_t)run;
+        run += v[k];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = (int32_t)sums[gridDim.x];
 }
@@ -167,20 +173,35 @@ void cast_f2d(const float* a, double* b, int64_t n, hipStream_t s) {
 }
 
 // ============================================================== sliced ELL
-// rank of block row i within its window: rows ordered by decreasing length, ties by index
-__global__ void sell_rank_k(const int32_t* __restrict__ rp, int64_t nr, int64_t win, int rps, int sp,
-                            int32_t* __restrict__ rowid) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nr) return;
-    int64_t w0 = (i / win) * win, w1 = w0 + win < nr ? w0 + win : nr;
-    int32_t li = rp[i + 1] - rp[i];
-    int64_t rank = 0;
-    for (int64_t j = w0; j < w1; ++j) {
-        int32_t lj = rp[j + 1] - rp[j];
-        rank += (lj > li) || (lj == li && j < i);
+// places of the block rows of a window: by decreasing length, ties by index.  One workgroup per window of at
+// most SELL_WIN rows sorts the pairs (length, index) in LDS (a bitonic network; comparing every row with
+// every other took 65-130 us a matrix)
+constexpr int SELL_WIN = SELL_SIGMA * WAVE;
+static_assert(SELL_SIGMA_ROWLANE * WAVE <= SELL_WIN, "window of the block-row lanes");
+__global__ void __launch_bounds__(256) sell_rank_k(const int32_t* __restrict__ rp, int64_t nr, int win, int rps, int sp,
+                                                   int32_t* __restrict__ rowid) {
+    __shared__ uint64_t key[SELL_WIN];
+    const int64_t w0 = (int64_t)blockIdx.x * win;
+    const int n = nr - w0 < win ? (int)(nr - w0) : win;
+    int size = 64;
+    while (size < n) size <<= 1;
+    for (int j = threadIdx.x; j < size; j += 256)
+        key[j] = j < n ? (uint64_t)(uint32_t)(INT32_MAX - (rp[w0 + j + 1] - rp[w0 + j])) << 32 | (uint32_t)j : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= size; k <<= 1)
+        for (int h = k >> 1; h > 0; h >>= 1) {
+            for (int t = threadIdx.x; t < size / 2; t += 256) {
+                const int i = 2 * h * (t / h) + t % h, j = i + h;
+                const uint64_t a = key[i], b = key[j];
+                if ((a > b) == ((i & k) == 0)) { key[i] = b; key[j] = a; }
+            }
+            __syncthreads();
+        }
+    const int rows = rps / sp;     // block rows per slice
+    for (int j = threadIdx.x; j < n; j += 256) {
+        const int64_t at = w0 + j;
+        rowid[at / rows * rps + at % rows * sp] = (int32_t)(w0 + (uint32_t)key[j]);
     }
-    const int64_t rows = rps / sp, at = w0 + rank;     // block rows per slice
-    rowid[at / rows * rps + at % rows * sp] = (int32_t)i;
 }
 
 __global__ void sell_slice_len(const int32_t* __restrict__ rp, const int32_t* __restrict__ rowid, int rps,
@@ -354,8 +375,8 @@ DSell<T> sell_from_bsr(const DBsr& A, Arena& ar, hipStream_t s) {
     if (S.nslices == 0) return S;
     S.rowid = ar.make<int32_t>(S.nslices * S.rps);
     fill_i32(S.rowid, -1, S.nslices * S.rps, s);
-    int64_t win = (int64_t)(S.rowlane ? SELL_SIGMA_ROWLANE : SELL_SIGMA) * rows;
-    sell_rank_k<<<cdiv(A.nr, 256), 256, 0, s>>>(A.rp, A.nr, win, S.rps, S.sp, S.rowid);
+    const int win = (S.rowlane ? SELL_SIGMA_ROWLANE : SELL_SIGMA) * rows;
+    sell_rank_k<<<cdiv(A.nr, win), 256, 0, s>>>(A.rp, A.nr, win, S.rps, S.sp, S.rowid);
     int32_t* len = ar.make<int32_t>(S.nslices);
     const int grp = (!S.rowlane && A.br == 1 && A.bc == 1) ? SELL_G : 1;
     sell_slice_len<<<cdiv(S.nslices, 256), 256, 0, s>>>(A.rp, S.rowid, S.rps, S.nslices, grp, S.sp, len);
@@ -364,17 +385,19 @@ DSell<T> sell_from_bsr(const DBsr& A, Arena& ar, hipStream_t s) {
     S.slots = scan_i32(len, S.off, S.nslices, ar, s);
     ar.free(len);
     S.ci = ar.make<int32_t>(S.slots * S.rps + 1);
-    if (S.rowlane) {
-        S.v = ar.make<T>(S.slots * WAVE * A.br * A.bc + 1);
-        sell_fill_rowlane<T><<<cdiv(S.nslices * SELL_FILL_PARTS * WAVE, 256), 256, 0, s>>>(A.rp, A.ci, A.v, A.br * A.bc, S.rowid, S.off,
-                                                                        S.ci, S.v, S.nslices);
-    } else {
-        S.v = ar.make<T>(S.slots * WAVE * A.bc + 1);
-        sell_fill<T><<<cdiv(S.nslices * SELL_FILL_PARTS * WAVE, 256), 256, 0, s>>>(A.rp, A.ci, A.v, A.br, A.bc, S.rps, S.sp, S.rowid, S.off,
-                                                                S.ci, S.v, S.nslices);
-    }
-    check_launch("sell_fill");
+    S.v = ar.make<T>(S.slots * WAVE * (S.rowlane ? A.br : 1) * A.bc + 1);
+    sell_refill(A, S, s);
     return S;
+}
+template <typename T>
+void sell_refill(const DBsr& A, DSell<T>& S, hipStream_t s) {
+    if (S.nslices == 0) return;
+    const unsigned g = (unsigned)cdiv(S.nslices * SELL_FILL_PARTS * WAVE, 256);
+    if (S.rowlane)
+        sell_fill_rowlane<T><<<g, 256, 0, s>>>(A.rp, A.ci, A.v, A.br * A.bc, S.rowid, S.off, S.ci, S.v, S.nslices);
+    else
+        sell_fill<T><<<g, 256, 0, s>>>(A.rp, A.ci, A.v, A.br, A.bc, S.rps, S.sp, S.rowid, S.off, S.ci, S.v, S.nslices);
+    check_launch("sell_fill");
 }
 template <typename T>
 void sell_free(DSell<T>& A, Arena& ar) {
@@ -383,6 +406,8 @@ void sell_free(DSell<T>& A, Arena& ar) {
 }
 template DSell<double> sell_from_bsr<double>(const DBsr&, Arena&, hipStream_t);
 template DSell<float> sell_from_bsr<float>(const DBsr&, Arena&, hipStream_t);
+template void sell_refill<double>(const DBsr&, DSell<double>&, hipStream_t);
+template void sell_refill<float>(const DBsr&, DSell<float>&, hipStream_t);
 template void sell_free<double>(DSell<double>&, Arena&);
 template void sell_free<float>(DSell<float>&, Arena&);
 
@@ -405,10 +430,16 @@ DBsrT<T> bsrt_from_bsr(const DBsr& A, Arena& ar, hipStream_t s) {
     R.rp = A.rp; R.ci = A.ci;   // shares the index arrays of the FP64 matrix
     int64_t nv = A.nnzb * A.br * A.bc;
     R.v = ar.make<T>(nv > 0 ? nv : 1);
-    if (nv > 0) bsrt_fill_k<T><<<cdiv(A.nr, 4), 256, 0, s>>>(A.nr, A.br * A.bc, A.rp, A.v, R.v);
-    check_launch("bsrt_from_bsr");
+    bsrt_refill(A, R, s);
     return R;
 }
+template <typename T>
+void bsrt_refill(const DBsr& A, DBsrT<T>& R, hipStream_t s) {
+    if (A.nnzb > 0) bsrt_fill_k<T><<<cdiv(A.nr, 4), 256, 0, s>>>(A.nr, A.br * A.bc, A.rp, A.v, R.v);
+    check_launch("bsrt_fill");
+}
+template void bsrt_refill<double>(const DBsr&, DBsrT<double>&, hipStream_t);
+template void bsrt_refill<float>(const DBsr&, DBsrT<float>&, hipStream_t);
 template DBsrT<double> bsrt_from_bsr<double>(const DBsr&, Arena&, hipStream_t);
 template DBsrT<float> bsrt_from_bsr<float>(const DBsr&, Arena&, hipStream_t);
 
