@@ -723,7 +723,9 @@ __device__ __forceinline__ void rl_fma(const T* vv, const T* xx, T r[3]) {
 }
 
 // Wavefronts per slice of the block-row-lane kernels: doubled while the matrix has fewer than RL_WAVES
-// wavefronts in all (two per SIMD) and each keeps two slots or more.  With one wavefront per slice a
+// wavefronts in all (two per SIMD) and each keeps two slots or more (one of the twice as large 3x6 blocks:
+// the three slots of a prolongator's slice are a chain of eight round trips, 19.1 us for one wavefront at 7k
+// nodes and 5.0 for four).  With one wavefront per slice a
 // 7k-node tube puts 109 wavefronts on 1,024 SIMDs and each runs its 15 slots as eight dependent memory
 // round trips.  Measured, one FP64 V-cycle of AMG(A) with one wavefront per slice against this rule: 7k
 // nodes 189 -> 104 us, 22k 316 -> 222, 41k 501 -> 420 (FP32 138 -> 88, 222 -> 165, 345 -> 294).  Bounds
@@ -733,9 +735,9 @@ constexpr int64_t RL_WAVES = 2048;
 template <typename T>
 static int rl_waves_per_slice(const DSell<T>& A) {
     if (A.nslices <= 0) return 1;
-    const int64_t avg = A.slots / A.nslices;
+    const int64_t avg = cdiv(A.slots, A.nslices), least = A.bc == 6 ? 1 : 2;
     int w = 1;
-    while (w < 8 && A.nslices * w < RL_WAVES && avg >= 2 * (w * 2)) w *= 2;
+    while (w < 8 && A.nslices * w < RL_WAVES && avg >= least * (w * 2)) w *= 2;
     return w;
 }
 
@@ -999,45 +1001,74 @@ void sell_mv_split4(const DSell<double>& K, const double* x, const double* b, do
 }
 
 // ---------------------------------------------------------------- restriction (row per wave)
-// Values in row-entry-major order (bsrt_fill_k); lane j of the wave takes blocks j, j+64, ...
-template <typename T, int BR, int BC>
+// Values in row-entry-major order (bsrt_fill_k); lane j of the row's WPR wavefronts takes blocks j,
+// j + 64 WPR, ...  Fewer than BSRT_ROWS rows that are longer than one pass of a wavefront leave most SIMDs
+// idle and each wavefront with two or more dependent round trips: four wavefronts share a row there (246
+// rows of 90 3x6 blocks: 9.0 -> 4.9 us; 2,393 rows and more are no faster that way).
+template <typename T, int BR, int BC, int WPR>
 __global__ void __launch_bounds__(256) bsrt_mv_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ x, T* __restrict__ y) {
-    int64_t row = xcd_tile(blockIdx.x, gridDim.x) * 4 + (threadIdx.x / WAVE);
-    if (row >= nr) return;
-    int lane = threadIdx.x & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t row = xcd_tile(blockIdx.x, gridDim.x) * (4 / WPR) + wv / WPR;
+    if (WPR == 1 && row >= nr) return;
+    const int lane = threadIdx.x & (WAVE - 1);
     T acc[BR];
 #pragma unroll
     for (int r = 0; r < BR; ++r) acc[r] = 0;
-    int64_t q0 = rp[row], len = rp[row + 1] - q0;
-    for (int64_t j = lane; j < len; j += WAVE) {
-        int64_t c = ci[q0 + j];
-        const T* vb = v + q0 * (BR * BC) + j;
-        T xx[BC];
+    if (row < nr) {
+        const int64_t q0 = rp[row], len = rp[row + 1] - q0;
+        for (int64_t j = wv % WPR * WAVE + lane; j < len; j += WPR * WAVE) {
+            int64_t c = ci[q0 + j];
+            const T* vb = v + q0 * (BR * BC) + j;
+            T xx[BC], vv[BR * BC];
 #pragma unroll
-        for (int k = 0; k < BC; ++k) xx[k] = x[c * BC + k];
+            for (int e = 0; e < BR * BC; ++e) vv[e] = ld_stream<BC>(vb + e * len);
 #pragma unroll
-        for (int r = 0; r < BR; ++r)
+            for (int k = 0; k < BC; ++k) xx[k] = x[c * BC + k];
 #pragma unroll
-            for (int k = 0; k < BC; ++k) acc[r] += ld_stream<BC>(vb + (r * BC + k) * len) * xx[k];
+            for (int r = 0; r < BR; ++r)
+#pragma unroll
+                for (int k = 0; k < BC; ++k) acc[r] += vv[r * BC + k] * xx[k];
+        }
     }
+    if constexpr (WPR == 1) {
 #pragma unroll
-    for (int r = 0; r < BR; ++r) {
-        T sum = wave_sum(acc[r]);
-        if (lane == 0) y[row * BR + r] = sum;
+        for (int r = 0; r < BR; ++r) {
+            T sum = wave_sum(acc[r]);
+            if (lane == 0) y[row * BR + r] = sum;
+        }
+    } else {
+        __shared__ T part[4][BR];
+#pragma unroll
+        for (int r = 0; r < BR; ++r) {
+            const T sum = wave_sum(acc[r]);
+            if (lane == 0) part[wv][r] = sum;
+        }
+        __syncthreads();
+        if (row >= nr || wv % WPR != 0 || lane >= BR) return;
+        T sum = part[wv][lane];
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) sum += part[wv + w][lane];
+        y[row * BR + lane] = sum;
     }
 }
+constexpr int64_t BSRT_ROWS = 2048;
 template <typename T>
 void bsrt_mv(const DBsrT<T>& R, const T* x, T* y, hipStream_t s) {
-    int64_t nblk = cdiv(R.nr, 4);
-    if (nblk == 0) return;
-    int key = R.br * 10 + R.bc;
+    if (R.nr == 0) return;
+    const int key = R.br * 10 + R.bc;
+    const bool wide = R.nr < BSRT_ROWS && R.nnzb >= WAVE * R.nr;
+    const unsigned g = (unsigned)(wide ? R.nr : cdiv(R.nr, 4));
+#define BMV(BR, BC)                                                                                   \
+    if (wide) bsrt_mv_k<T, BR, BC, 4><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);                 \
+    else bsrt_mv_k<T, BR, BC, 1><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y)
     switch (key) {
-        case 11: bsrt_mv_k<T, 1, 1><<<nblk, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y); break;
-        case 63: bsrt_mv_k<T, 6, 3><<<nblk, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y); break;
-        case 66: bsrt_mv_k<T, 6, 6><<<nblk, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y); break;
+        case 11: BMV(1, 1); break;
+        case 63: BMV(6, 3); break;
+        case 66: BMV(6, 6); break;
         default: throw Error(SCR_E_UNIMPLEMENTED, "bsrt_mv: block shape");
     }
+#undef BMV
     check_launch("bsrt_mv");
 }
 template void bsrt_mv<double>(const DBsrT<double>&, const double*, double*, hipStream_t);
@@ -1564,7 +1595,30 @@ __global__ void __launch_bounds__(256) dense_mv_k(int64_t n, const double* __res
     if (row >= n) return;
     int lane = threadIdx.x & (WAVE - 1);
     double acc = 0.0;
-    for (int64_t c = lane; c < n; c += WAVE) acc += M[row * n + c] * (double)b[c];
+    // U loads in flight per lane: one at a time, 1,476 columns were 23 round trips (9.0 -> 5.9 us)
+    constexpr int U = 8;
+    int64_t c = lane;
+    for (; c + (U - 1) * WAVE < n; c += U * WAVE) {
+        double m[U], bb[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            m[u] = M[row * n + c + u * WAVE];
+            bb[u] = (double)b[c + u * WAVE];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += m[u] * bb[u];
+    }
+    if (c < n) {
+        double m[U], bb[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = c + u * WAVE < n ? c + u * WAVE : n - 1;
+            m[u] = M[row * n + q];
+            bb[u] = (double)b[q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += c + u * WAVE < n ? m[u] * bb[u] : 0.0;
+    }
     acc = wave_sum(acc);
     if (lane == 0) x[row] = (T)acc;
 }
