@@ -1797,8 +1797,10 @@ class HierT : public Hierarchy {
         return (double)q.A.nnzb * (b * b * t + 4.0) + rows * (4.0 + b * t * (3.0 + (rd ? 1.0 : 0.0) + (wd ? 1.0 : 0.0)));
     }
 
-    // smoothing sweeps from xin (nullptr = zero) into dst
-    void smooth(size_t l, LS& q, const T* b, const T* xin, T* dst, hipStream_t s) {
+    // smoothing sweeps from xin (nullptr = zero) into dst.  Passes over a level's matrix alternate in
+    // direction (down), so that each starts with what the one before left in the caches; the last sweep
+    // runs down, and the product with the system matrix that follows in a Krylov step runs up.
+    void smooth(size_t l, LS& q, const T* b, const T* xin, T* dst, bool& down, hipStream_t s) {
         int ns = (int)q.c1.size();
         const T* cur = xin;
         for (int t = 0; t < ns; ++t) {
@@ -1807,7 +1809,8 @@ class HierT : public Hierarchy {
             bool timed = prof && l == 0 && !zero;
             hipEvent_t e0 = nullptr, e1 = nullptr;
             if (timed) { e0 = prof->get(); e1 = prof->get(); }
-            smooth_step<T>(q.A, q.Dinv, b, cur, q.d, out, q.c1[t], q.c2[t], rd, wd, zero, s, e0, e1);
+            smooth_step<T>(q.A, q.Dinv, b, cur, q.d, out, q.c1[t], q.c2[t], rd, wd, zero, down, s, e0, e1);
+            if (!zero) down = !down;
             if (timed) prof->push(e0, e1, step_bytes(q, rd, wd));
             cur = out;
         }
@@ -1819,23 +1822,26 @@ class HierT : public Hierarchy {
             return;
         }
         LS& q = S[l];
-        smooth(l, q, b, nullptr, q.w, s);
-        sell_mv<T>(q.A, q.w, b, q.r, 1, s);
+        bool down = true;
+        smooth(l, q, b, nullptr, q.w, down, s);
+        sell_mv<T>(q.A, q.w, b, q.r, 1, down, s);
         bsrt_mv<T>(q.R, q.r, S[l + 1].b, s);
         cycle(l + 1, S[l + 1].b, S[l + 1].x, s);
         sell_mv<T>(q.P, S[l + 1].x, nullptr, q.w, 2, s);
-        smooth(l, q, b, q.w, x, s);
+        down = false;
+        smooth(l, q, b, q.w, x, down, s);
     }
 
     // the V-cycle on three interleaved columns: every kernel passes over its matrix once for all
     // three, and each column's result is bitwise the one-column V-cycle's
-    void smooth3(LS& q, const T* b, const T* xin, T* dst, hipStream_t s) {
+    void smooth3(LS& q, const T* b, const T* xin, T* dst, bool& down, hipStream_t s) {
         int ns = (int)q.c1.size();
         const T* cur = xin;
         for (int t = 0; t < ns; ++t) {
             T* out = (t == ns - 1) ? dst : ((t % 2 == 0) ? q.t13 : q.t23);
             bool rd = q.cheb && t > 0, wd = q.cheb && t + 1 < ns, zero = cur == nullptr;
-            smooth_step3<T>(q.A, q.Dinv, b, cur, q.d3, out, q.c1[t], q.c2[t], rd, wd, zero, s);
+            smooth_step3<T>(q.A, q.Dinv, b, cur, q.d3, out, q.c1[t], q.c2[t], rd, wd, zero, down, s);
+            if (!zero) down = !down;
             cur = out;
         }
     }
@@ -1845,12 +1851,14 @@ class HierT : public Hierarchy {
             return;
         }
         LS& q = S[l];
-        smooth3(q, b, nullptr, q.w3, s);
-        sell_mv3<T>(q.A, q.w3, b, q.r3, 1, s);
+        bool down = true;
+        smooth3(q, b, nullptr, q.w3, down, s);
+        sell_mv3<T>(q.A, q.w3, b, q.r3, 1, down, s);
         bsrt_mv3<T>(q.R, q.r3, S[l + 1].b3, s);
         cycle3(l + 1, S[l + 1].b3, S[l + 1].x3, s);
         sell_mv3<T>(q.P, S[l + 1].x3, nullptr, q.w3, 2, s);
-        smooth3(q, b, q.w3, x, s);
+        down = false;
+        smooth3(q, b, q.w3, x, down, s);
     }
     void vcycle3(const double* x, double* y, hipStream_t s) override {
         if (!three) throw Error(SCR_E_INVALID, "three-column V-cycle on a hierarchy built without it");

@@ -341,6 +341,12 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nb) {
     int64_t x = b % NXCD, k = b / NXCD;
     return x * q + (x < r ? x : r) + k;
 }
+// the same with each XCD's tiles in descending order
+__device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nb, bool down) {
+    const int64_t q = nb / NXCD, r = nb % NXCD;
+    const int64_t x = b % NXCD, k = b / NXCD, n = q + (x < r);
+    return x * q + (x < r ? x : r) + (down ? n - 1 - k : k);
+}
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {

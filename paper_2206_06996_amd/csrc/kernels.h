@@ -35,8 +35,13 @@ struct DBsrT {
 template <typename T> DBsrT<T> bsrt_from_bsr(const DBsr& A, Arena& ar, hipStream_t s);
 template <typename T> void bsrt_refill(const DBsr& A, DBsrT<T>& R, hipStream_t s);   // new values, same pattern
 
-// y = A x (mode 0), y = b - A x (mode 1), y += A x (mode 2), y -= A x (mode 3)
-template <typename T> void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s);
+// y = A x (mode 0), y = b - A x (mode 1), y += A x (mode 2), y -= A x (mode 3); down: the slices in descending
+// order (same result)
+template <typename T> void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down,
+                                   hipStream_t s);
+template <typename T> inline void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
+    sell_mv<T>(A, x, b, y, mode, false, s);
+}
 // Same for the 4x4 FP64 system matrix on split vectors [v (3n); p (n)]
 void sell_mv_split4(const DSell<double>& K, const double* x, const double* b, double* y, int mode, hipStream_t s);
 // y = R x with a row-wave kernel (rows of R are long)
@@ -46,17 +51,20 @@ template <typename T> void bsrt_mv(const DBsrT<T>& R, const T* x, T* y, hipStrea
 // e0/e1 (optional): events recorded by the kernel's own dispatch packet (kernel time only).
 template <typename T>
 void smooth_step(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, double c1,
-                 double c2, bool read_d, bool write_d, bool zero_in, hipStream_t s, hipEvent_t e0 = nullptr,
+                 double c2, bool read_d, bool write_d, bool zero_in, bool down, hipStream_t s, hipEvent_t e0 = nullptr,
                  hipEvent_t e1 = nullptr);
 // x = M b for a dense row-major n x n FP64 matrix M (coarsest-level inverse)
 template <typename T> void dense_mv(int64_t n, const double* M, const T* b, T* x, hipStream_t s);
 // The same four operations for 1x1 matrices on three node-interleaved columns (entry 3 i + c), one
 // pass over the matrix; per column bitwise the one-column result
-template <typename T> void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s);
+template <typename T> void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s);
+template <typename T> inline void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
+    sell_mv3<T>(A, x, b, y, mode, false, s);
+}
 template <typename T> void bsrt_mv3(const DBsrT<T>& R, const T* x, T* y, hipStream_t s);
 template <typename T>
 void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, double c1, double c2,
-                  bool read_d, bool write_d, bool zero_in, hipStream_t s);
+                  bool read_d, bool write_d, bool zero_in, bool down, hipStream_t s);
 template <typename T> void dense_mv3(int64_t n, const double* M, const T* b, T* x, hipStream_t s);
 // validate a square BSR (device); returns error bits (synchronises)
 int validate_bsr(int64_t nr, int bs, int64_t nnzb, const int32_t* rp, const int32_t* ci, const double* v,

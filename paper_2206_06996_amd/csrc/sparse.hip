@@ -445,26 +445,52 @@ template DBsrT<float> bsrt_from_bsr<float>(const DBsr&, Arena&, hipStream_t);
 
 // ============================================================== SpMV family (one lane per scalar row)
 // Unrolled slot loop: U slots' columns, then their values and x segments, are loaded before use.
-// Matrix values are read once per call: nontemporal loads keep them from evicting the gathered
-// x entries and the per-row vectors from the caches.
-// (measured: a gain for 3- and 6-wide FP64 row segments, a loss for scalar entries)
-template <int BC, typename T>
+//
+// Which matrix values go through the caches.  A sweep of the smoother reads its matrix 4 times before and 4
+// times after the coarse levels, with nothing large in between, so what of it stays in the 256 MB memory-side
+// cache is read from there; but a matrix larger than that cache, read from end to end, evicts itself.
+//   * Square block matrices: KEEP_BYTES of the values are loaded through the caches, the rest with
+//     nontemporal loads, which leave the cached part (and the gathered x) alone.  The cached slices are
+//     spread evenly (k of every KEEP_PARTS), so that both kinds are in flight at all times.  One V-cycle of
+//     AMG(A), all nontemporal -> this: 22k nodes FP64 188 -> 152 us, 41k 319 -> 277, 100k 588 -> 538, 300k
+//     1,427 -> 1,337 (through the caches: 1,530), 700k 3,022 -> 2,950 (3,312); FP32 41k 235 -> 192, 100k
+//     370 -> 326, 300k 812 -> 755, 700k 1,684 -> 1,551.  96 to 192 MB are within 2 %.
+//   * 1x1 matrices always use the caches: two 16-byte loads share each line (nontemporal: 300k nodes FP64
+//     V-cycle of AMG(S^) 1,160 -> 1,570 us).
+//     Consecutive sweeps run in opposite directions (xcd_tile), so that each starts with what the last one
+//     left in the caches: that V-cycle 1,285 -> 1,120 us, of AMG(A) 1,366 -> 1,342, at 41k nodes 300 -> 282.
+//   * Prolongators and restrictions are read once a cycle: FP64 segments of three or more values nontemporal.
+constexpr int KEEP_PARTS = 16;
+constexpr double KEEP_BYTES = 160.0 * (1 << 20);
+__device__ __forceinline__ bool keep_slice(int64_t sl, int keep) { return (int)(sl % KEEP_PARTS) < keep; }
+template <typename T>
+static int keep_of(const DSell<T>& A) {
+    const double slot = A.rowlane ? WAVE * (3.0 * A.bc * sizeof(T) + 4.0) : WAVE * (double)A.bc * sizeof(T) + A.rps * 4.0;
+    const double bytes = slot * (double)A.slots;
+    return bytes <= KEEP_BYTES ? KEEP_PARTS : (int)(KEEP_PARTS * KEEP_BYTES / bytes);
+}
+// (Keep: whether the size decides, and the choice where it does not)
+template <typename T, int BR, int BC> struct Keep {
+    static constexpr bool BY_SIZE = BR == BC && BR > 1;
+    static constexpr bool ALWAYS = BC < 3 || sizeof(T) == 4;
+};
+template <bool KEEP, typename T>
 __device__ __forceinline__ T ld_stream(const T* p) {
-    if (BC >= 3 && sizeof(T) == 8) return __builtin_nontemporal_load(p);
-    return *p;
+    if constexpr (KEEP) return *p;
+    else return __builtin_nontemporal_load(p);
 }
 // (6-wide rows: four slots per step measured 5 % slower per FP64 V-cycle at 300k nodes, 1-2 % in FP32)
 template <int BC> struct Unroll { static constexpr int U = BC == 1 ? 8 : (BC <= 4 ? 4 : 2); };
 
 // the BC values of slot t of a lane (layout of sell_vidx)
-template <typename T, int BC>
+template <typename T, int BC, bool KEEP>
 __device__ __forceinline__ void sell_vals(const T* __restrict__ v, int64_t t, int lane, T (&vv)[BC]) {
     if constexpr (BC == 6 && sizeof(T) == 8) {
         typedef T V2 __attribute__((ext_vector_type(2)));
         const V2* vp = reinterpret_cast<const V2*>(v);
 #pragma unroll
         for (int kk = 0; kk < 3; ++kk) {
-            const V2 w = __builtin_nontemporal_load(vp + (t * 3 + kk) * WAVE + lane);
+            const V2 w = ld_stream<KEEP>(vp + (t * 3 + kk) * WAVE + lane);
             vv[2 * kk] = w.x;
             vv[2 * kk + 1] = w.y;
         }
@@ -472,13 +498,13 @@ __device__ __forceinline__ void sell_vals(const T* __restrict__ v, int64_t t, in
         typedef T V4 __attribute__((ext_vector_type(4)));
         typedef T V2 __attribute__((ext_vector_type(2)));
         const T* base = v + t * 6 * WAVE;
-        const V4 a = __builtin_nontemporal_load(reinterpret_cast<const V4*>(base) + lane);
-        const V2 c = __builtin_nontemporal_load(reinterpret_cast<const V2*>(base + 4 * WAVE) + lane);
+        const V4 a = ld_stream<KEEP>(reinterpret_cast<const V4*>(base) + lane);
+        const V2 c = ld_stream<KEEP>(reinterpret_cast<const V2*>(base + 4 * WAVE) + lane);
         vv[0] = a.x; vv[1] = a.y; vv[2] = a.z; vv[3] = a.w;
         vv[4] = c.x; vv[5] = c.y;
     } else {
 #pragma unroll
-        for (int k = 0; k < BC; ++k) vv[k] = ld_stream<BC>(v + (t * BC + k) * WAVE + lane);
+        for (int k = 0; k < BC; ++k) vv[k] = ld_stream<KEEP>(v + (t * BC + k) * WAVE + lane);
     }
 }
 
@@ -546,7 +572,7 @@ __device__ __forceinline__ T sell_row_dot_g(int64_t o0, int64_t o1, int lane, co
 
 // acc = sum over the lane's row segments of v . x[col*BC : col*BC+BC]; cl = the lane's block row
 // within the slice (column indices are stored once per block row, RPS per slot)
-template <typename T, int BC, int RPS, typename XF>
+template <typename T, int BC, int RPS, bool KEEP, typename XF>
 __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int cl, const int32_t* __restrict__ ci,
                                           const T* __restrict__ v, XF xat) {
     if constexpr (BC == 1 && RPS == WAVE) return sell_row_dot_g<T>(o0, o1, lane, ci, v, xat);
@@ -574,7 +600,7 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool in = full || t + u < o1;
-            sell_vals<T, BC>(v, in ? t + u : o1 - 1, lane, vv[u]);
+            sell_vals<T, BC, KEEP>(v, in ? t + u : o1 - 1, lane, vv[u]);
             if (!in) {
 #pragma unroll
                 for (int k = 0; k < BC; ++k) vv[u][k] = 0;
@@ -596,7 +622,7 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
             T xx[BC], vv[BC];
 #pragma unroll
             for (int k = 0; k < BC; ++k) xx[k] = xat((int64_t)c[0], k);
-            sell_vals<T, BC>(v, t, lane, vv);
+            sell_vals<T, BC, KEEP>(v, t, lane, vv);
 #pragma unroll
             for (int k = 0; k < BC; ++k) acc += vv[k] * xx[k];
         }
@@ -637,13 +663,13 @@ __device__ __forceinline__ T parts_sum(T acc, int lane, int sp) {
 }
 
 template <typename T, int BR, int BC, int MODE, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t nslices, bool down, int keep, int sp, const int32_t* __restrict__ off,
                                                  const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ x,
                                                  const T* __restrict__ b, T* __restrict__ y) {
     constexpr int RPS = WAVE / BR;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
     auto xat = [&](int64_t c, int k) { return x[c * BC + k]; };
@@ -658,7 +684,10 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
         }
         int64_t a, e;
         slice_part<WPS, (BR == 1 && BC == 1) ? SELL_G : 1>(off[sl], off[sl + 1], wv % WPS, a, e);
-        acc = sell_row_dot<T, BC, RPS>(a, e, lane, cl, ci, v, xat);
+        using K = Keep<T, BR, BC>;
+        if constexpr (!K::BY_SIZE) acc = sell_row_dot<T, BC, RPS, K::ALWAYS>(a, e, lane, cl, ci, v, xat);
+        else acc = keep_slice(sl, keep) ? sell_row_dot<T, BC, RPS, true>(a, e, lane, cl, ci, v, xat)
+                                        : sell_row_dot<T, BC, RPS, false>(a, e, lane, cl, ci, v, xat);
     }
     if (WPS > 1) {
         __shared__ T red[SliceGroup<WPS>::SPB * WPS][WAVE];
@@ -696,19 +725,19 @@ static int waves_per_slice(const DSell<T>& A) {
 
 // the 3*BC values of slot t of a lane (layout of rl_vidx): FP64 in 16-byte pairs, FP32 in 16-byte
 // quads, nontemporal
-template <typename T, int BC>
+template <typename T, int BC, bool KEEP>
 __device__ __forceinline__ void rl_load(const T* __restrict__ v, int64_t t, int lane, T (&vv)[3 * BC]) {
     constexpr int E = 3 * BC, Q = sizeof(T) == 8 ? 2 : 4;
     typedef T VQ __attribute__((ext_vector_type(Q)));
     const T* base = v + t * E * WAVE;
 #pragma unroll
     for (int k = 0; k < E / Q; ++k) {
-        const VQ w = __builtin_nontemporal_load(reinterpret_cast<const VQ*>(base + k * Q * WAVE) + lane);
+        const VQ w = ld_stream<KEEP>(reinterpret_cast<const VQ*>(base + k * Q * WAVE) + lane);
 #pragma unroll
         for (int q = 0; q < Q; ++q) vv[Q * k + q] = w[q];
     }
 #pragma unroll
-    for (int e = E - E % Q; e < E; ++e) vv[e] = __builtin_nontemporal_load(base + e * WAVE + lane);
+    for (int e = E - E % Q; e < E; ++e) vv[e] = ld_stream<KEEP>(base + e * WAVE + lane);
 }
 // r += block * x
 template <typename T, int BC>
@@ -749,7 +778,7 @@ static int rl_waves_per_slice(const DSell<T>& A) {
 // CAP: also copy the 3x3 block of column irow (the diagonal block of the lane's row) into dg; the
 // first match is the stored block (padding slots that repeat the row's last column hold zeros and
 // come after it)
-template <typename T, int BC, bool CAP = false>
+template <typename T, int BC, bool KEEP, bool CAP = false>
 __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, const int32_t* __restrict__ ci,
                                              const T* __restrict__ v, const T* __restrict__ x, T r[3],
                                              int32_t irow = -1, T* dg = nullptr) {
@@ -778,7 +807,7 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
         }
         __builtin_amdgcn_sched_barrier(0);     // keep the gathers and indices ahead of the values
 #pragma unroll
-        for (int u = 0; u < U; ++u) rl_load<T, BC>(v, t + u, lane, vv[u]);
+        for (int u = 0; u < U; ++u) rl_load<T, BC, KEEP>(v, t + u, lane, vv[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u) rl_fma<T, BC>(vv[u], xx[u], r);
         if constexpr (CAP) {
@@ -796,7 +825,7 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
     if (U > 1 && t < o1) {
         int64_t c = ci[t * WAVE + lane];
         T vv[E], xx[BC];
-        rl_load<T, BC>(v, t, lane, vv);
+        rl_load<T, BC, KEEP>(v, t, lane, vv);
 #pragma unroll
         for (int k = 0; k < BC; ++k) xx[k] = x[c * BC + k];
         rl_fma<T, BC>(vv, xx, r);
@@ -811,7 +840,7 @@ __device__ __forceinline__ void rowlane3_dot(int64_t t, int64_t o1, int lane, co
 
 // The same over one wavefront's part [t, o1) of a slice that several wavefronts share: two slots per
 // step; the index of a last single slot is here already, so that it costs one memory round trip.
-template <typename T, int BC>
+template <typename T, int BC, bool KEEP>
 __device__ __forceinline__ void rowlane3_dot_part(int64_t t, int64_t o1, int lane, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x, T r[3]) {
     constexpr int E = 3 * BC;
@@ -831,7 +860,7 @@ __device__ __forceinline__ void rowlane3_dot_part(int64_t t, int64_t o1, int lan
         for (int u = 0; u < 2; ++u) cn[u] = ci[(t + 2 + u < o1 ? t + 2 + u : o1 - 1) * WAVE + lane];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) rl_load<T, BC>(v, t + u, lane, vv[u]);
+        for (int u = 0; u < 2; ++u) rl_load<T, BC, KEEP>(v, t + u, lane, vv[u]);
 #pragma unroll
         for (int u = 0; u < 2; ++u) rl_fma<T, BC>(vv[u], xx[u], r);
 #pragma unroll
@@ -841,7 +870,7 @@ __device__ __forceinline__ void rowlane3_dot_part(int64_t t, int64_t o1, int lan
         T vv[E], xx[BC];
 #pragma unroll
         for (int k = 0; k < BC; ++k) xx[k] = x[(int64_t)c[0] * BC + k];
-        rl_load<T, BC>(v, t, lane, vv);
+        rl_load<T, BC, KEEP>(v, t, lane, vv);
         rl_fma<T, BC>(vv, xx, r);
     }
 }
@@ -863,19 +892,20 @@ __device__ __forceinline__ bool rl_reduce(int wv, int lane, T r[3]) {
 }
 
 template <typename T, int BC, int MODE, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_t nslices, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_t nslices, bool down, int keep, const int32_t* __restrict__ off,
                                                      const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                      const T* __restrict__ v, const T* __restrict__ x,
                                                      const T* __restrict__ b, T* __restrict__ y) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     if (WPS == 1 && sl >= nslices) return;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
     T r[3] = {0, 0, 0}, old[3];
     int64_t i = -1;
     if constexpr (WPS == 1) {
-        rowlane3_dot<T, BC>(off[sl], off[sl + 1], lane, ci, v, x, r);
+        if (BC == 3 && keep_slice(sl, keep)) rowlane3_dot<T, BC, true>(off[sl], off[sl + 1], lane, ci, v, x, r);
+        else rowlane3_dot<T, BC, false>(off[sl], off[sl + 1], lane, ci, v, x, r);
         i = rowid[sl * WAVE + lane];
     } else {
         if (live) {
@@ -888,7 +918,8 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_
             }
             int64_t a, e;
             slice_part<WPS>(off[sl], off[sl + 1], wv % WPS, a, e);
-            rowlane3_dot_part<T, BC>(a, e, lane, ci, v, x, r);
+            if (BC == 3 && keep_slice(sl, keep)) rowlane3_dot_part<T, BC, true>(a, e, lane, ci, v, x, r);
+            else rowlane3_dot_part<T, BC, false>(a, e, lane, ci, v, x, r);
         }
         if (!rl_reduce<T, WPS>(wv, lane, r) || !live) return;
     }
@@ -904,9 +935,9 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_
 }
 
 template <typename T, int BR, int BC>
-static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
+static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
     constexpr bool SPLIT = true;
-    int wps = SPLIT ? waves_per_slice(A) : 1;
+    const int wps = SPLIT ? waves_per_slice(A) : 1, keep = keep_of(A);
     if (A.nslices == 0) return;
 #define MV(W)                                                                                                  \
     {                                                                                                          \
@@ -914,10 +945,10 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
         int64_t nblk = cdiv(A.nslices, SliceGroup<W_>::SPB);                                                   \
         dim3 g((unsigned)nblk), t(SliceGroup<W_>::THREADS);                                                     \
         switch (mode) {                                                                                        \
-            case 0: sell_mv_k<T, BR, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv_k<T, BR, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv_k<T, BR, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv_k<T, BR, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv_k<T, BR, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv_k<T, BR, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv_k<T, BR, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv_k<T, BR, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                      \
     }
     if (!SPLIT || wps == 1) MV(1)
@@ -930,19 +961,19 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
 }
 
 template <typename T>
-void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
+void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
     if (A.rowlane) {
         if (A.nslices == 0) return;
-        const int wps = rl_waves_per_slice(A);
+        const int wps = rl_waves_per_slice(A), keep = keep_of(A);
 #define RLW(BC, W)                                                                                                  \
     {                                                                                                               \
         constexpr int W_ = W;                                                                                       \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W_>::SPB)), t(SliceGroup<W_>::THREADS);                         \
         switch (mode) {                                                                                             \
-            case 0: sell_mv_rl3_k<T, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv_rl3_k<T, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv_rl3_k<T, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv_rl3_k<T, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv_rl3_k<T, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv_rl3_k<T, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv_rl3_k<T, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv_rl3_k<T, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                           \
     }
 #define RL(BC)               \
@@ -958,18 +989,18 @@ void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStrea
     }
     int key = A.br * 10 + A.bc;
     switch (key) {
-        case 11: sell_mv_dispatch_mode<T, 1, 1>(A, x, b, y, mode, s); break;
-        case 33: sell_mv_dispatch_mode<T, 3, 3>(A, x, b, y, mode, s); break;
-        case 66: sell_mv_dispatch_mode<T, 6, 6>(A, x, b, y, mode, s); break;
-        case 31: sell_mv_dispatch_mode<T, 3, 1>(A, x, b, y, mode, s); break;
-        case 13: sell_mv_dispatch_mode<T, 1, 3>(A, x, b, y, mode, s); break;
-        case 36: sell_mv_dispatch_mode<T, 3, 6>(A, x, b, y, mode, s); break;
-        case 44: sell_mv_dispatch_mode<T, 4, 4>(A, x, b, y, mode, s); break;
+        case 11: sell_mv_dispatch_mode<T, 1, 1>(A, x, b, y, mode, down, s); break;
+        case 33: sell_mv_dispatch_mode<T, 3, 3>(A, x, b, y, mode, down, s); break;
+        case 66: sell_mv_dispatch_mode<T, 6, 6>(A, x, b, y, mode, down, s); break;
+        case 31: sell_mv_dispatch_mode<T, 3, 1>(A, x, b, y, mode, down, s); break;
+        case 13: sell_mv_dispatch_mode<T, 1, 3>(A, x, b, y, mode, down, s); break;
+        case 36: sell_mv_dispatch_mode<T, 3, 6>(A, x, b, y, mode, down, s); break;
+        case 44: sell_mv_dispatch_mode<T, 4, 4>(A, x, b, y, mode, down, s); break;
         default: throw Error(SCR_E_UNIMPLEMENTED, "sell_mv: block shape " + std::to_string(A.br) + "x" + std::to_string(A.bc));
     }
 }
-template void sell_mv<double>(const DSell<double>&, const double*, const double*, double*, int, hipStream_t);
-template void sell_mv<float>(const DSell<float>&, const float*, const float*, float*, int, hipStream_t);
+template void sell_mv<double>(const DSell<double>&, const double*, const double*, double*, int, bool, hipStream_t);
+template void sell_mv<float>(const DSell<float>&, const float*, const float*, float*, int, bool, hipStream_t);
 
 // 4x4 system matrix on split vectors [x_v (3n); x_p (n)]
 template <int MODE>
@@ -984,7 +1015,7 @@ __global__ void __launch_bounds__(256) sell_mv_split4_k(int64_t nr, int64_t nsli
     int lane = threadIdx.x & (WAVE - 1);
     const double* xp = x + 3 * nr;
     auto xat = [&](int64_t c, int k) { return k < 3 ? x[3 * c + k] : xp[c]; };
-    double acc = sell_row_dot<double, 4, RPS>(off[sl], off[sl + 1], lane, lane / 4, ci, v, xat);
+    double acc = sell_row_dot<double, 4, RPS, false>(off[sl], off[sl + 1], lane, lane / 4, ci, v, xat);
     int64_t i = rowid[sl * RPS + lane / 4];
     if (i < 0) return;
     int r = lane & 3;
@@ -1022,7 +1053,7 @@ __global__ void __launch_bounds__(256) bsrt_mv_k(int64_t nr, const int32_t* __re
             const T* vb = v + q0 * (BR * BC) + j;
             T xx[BC], vv[BR * BC];
 #pragma unroll
-            for (int e = 0; e < BR * BC; ++e) vv[e] = ld_stream<BC>(vb + e * len);
+            for (int e = 0; e < BR * BC; ++e) vv[e] = ld_stream<Keep<T, 1, BC>::ALWAYS>(vb + e * len);
 #pragma unroll
             for (int k = 0; k < BC; ++k) xx[k] = x[c * BC + k];
 #pragma unroll
@@ -1078,7 +1109,7 @@ template void bsrt_mv<float>(const DBsrT<float>&, const float*, float*, hipStrea
 // dn = c1*d + c2*Dinv*(b - A xin) ; xout = xin + dn.  One lane per scalar row; the block
 // residual of a block row is gathered from its B lanes with shuffles to apply Dinv.
 template <typename T, int B, bool RD, bool WD, bool ZERO, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nslices, bool down, int keep, int sp, const int32_t* __restrict__ off,
                                                 const int32_t* __restrict__ rowid,
                                                 const int32_t* __restrict__ ci, const T* __restrict__ v,
                                                 const T* __restrict__ Dinv, const T* __restrict__ b,
@@ -1086,7 +1117,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
                                                 T c1, T c2) {
     constexpr int RPS = WAVE / B;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const bool live = sl < nslices;
     const int lane = threadIdx.x & (WAVE - 1);
     const int cl = lane / B < RPS ? lane / B : RPS - 1;
@@ -1110,7 +1141,9 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
         auto xat = [&](int64_t c, int k) { return xin[c * B + k]; };
         int64_t a, e;
         slice_part<WPS, B == 1 ? SELL_G : 1>(off[sl], off[sl + 1], wv % WPS, a, e);
-        acc = sell_row_dot<T, B, RPS>(a, e, lane, cl, ci, v, xat);
+        if constexpr (B == 1) acc = sell_row_dot<T, B, RPS, true>(a, e, lane, cl, ci, v, xat);
+        else acc = keep_slice(sl, keep) ? sell_row_dot<T, B, RPS, true>(a, e, lane, cl, ci, v, xat)
+                                        : sell_row_dot<T, B, RPS, false>(a, e, lane, cl, ci, v, xat);
     }
     if (WPS > 1) {
         __shared__ T red[SliceGroup<WPS>::SPB * WPS][WAVE];
@@ -1144,14 +1177,14 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
 // loads its rows' right-hand side, D^-1, x and d before the slots, so that the epilogue waits for no
 // memory.
 template <typename T, bool RD, bool WD, bool ZERO, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t nslices, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t nslices, bool down, int keep, const int32_t* __restrict__ off,
                                                     const int32_t* __restrict__ rowid,
                                                     const int32_t* __restrict__ ci, const T* __restrict__ v,
                                                     const T* __restrict__ Dinv, const T* __restrict__ b,
                                                     const T* __restrict__ xin, T* __restrict__ d, T* __restrict__ xout,
                                                     T c1, T c2) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     if (WPS == 1 && sl >= nslices) return;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
@@ -1167,7 +1200,10 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t
         }
     };
     if constexpr (WPS == 1) {
-        if (!ZERO) rowlane3_dot<T, 3, true>(off[sl], off[sl + 1], lane, ci, v, xin, r, (int32_t)i, dg);
+        if (!ZERO) {
+            if (keep_slice(sl, keep)) rowlane3_dot<T, 3, true, true>(off[sl], off[sl + 1], lane, ci, v, xin, r, (int32_t)i, dg);
+            else rowlane3_dot<T, 3, false, true>(off[sl], off[sl + 1], lane, ci, v, xin, r, (int32_t)i, dg);
+        }
         if (i < 0) return;
         load_rows();
     } else {
@@ -1179,7 +1215,8 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t
         if (live) {
             int64_t a, e;
             slice_part<WPS>(off[sl], off[sl + 1], wv % WPS, a, e);
-            rowlane3_dot_part<T, 3>(a, e, lane, ci, v, xin, r);
+            if (keep_slice(sl, keep)) rowlane3_dot_part<T, 3, true>(a, e, lane, ci, v, xin, r);
+            else rowlane3_dot_part<T, 3, false>(a, e, lane, ci, v, xin, r);
         }
         if (!rl_reduce<T, WPS>(wv, lane, r) || i < 0) return;
     }
@@ -1216,18 +1253,18 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_rl3_k(int64_t
 
 template <typename T>
 static void smooth_rl3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, T c1, T c2,
-                       bool rd, bool wd, bool zero, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                       bool rd, bool wd, bool zero, bool down, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (A.nslices == 0) return;
-    const int wps = zero ? 1 : rl_waves_per_slice(A);
+    const int wps = zero ? 1 : rl_waves_per_slice(A), keep = keep_of(A);
 #define SKW(RD, WD, Z, W)                                                                                          \
     do {                                                                                                           \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), t(SliceGroup<W>::THREADS);                          \
         if (e0)                                                                                                    \
             hipExtLaunchKernelGGL((smooth_rl3_k<T, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0,                          \
-                                  A.nslices, (const int32_t*)A.off, (const int32_t*)A.rowid, (const int32_t*)A.ci, \
+                                  A.nslices, down, keep, (const int32_t*)A.off, (const int32_t*)A.rowid, (const int32_t*)A.ci, \
                                   (const T*)A.v, Dinv, b, xin, d, xout, c1, c2);                                   \
         else                                                                                                       \
-            smooth_rl3_k<T, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,   \
+            smooth_rl3_k<T, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, down, keep, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,   \
                                                           xout, c1, c2);                                           \
     } while (0)
 #define SK(RD, WD, Z)                           \
@@ -1251,18 +1288,18 @@ static void smooth_rl3(const DSell<T>& A, const T* Dinv, const T* b, const T* xi
 
 template <typename T, int B>
 static void smooth_dispatch(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, T c1, T c2,
-                            bool rd, bool wd, bool zero, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    int wps = zero ? 1 : waves_per_slice(A);
+                            bool rd, bool wd, bool zero, bool down, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const int wps = zero ? 1 : waves_per_slice(A), keep = keep_of(A);
     if (A.nslices == 0) return;
 #define SKW(RD, WD, Z, W)                                                                                          \
     do {                                                                                                           \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), t(SliceGroup<W>::THREADS);                          \
         if (e0)                                                                                                    \
-            hipExtLaunchKernelGGL((smooth_k<T, B, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0, A.nslices, A.sp,          \
+            hipExtLaunchKernelGGL((smooth_k<T, B, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0, A.nslices, down, keep, A.sp,          \
                                   (const int32_t*)A.off, (const int32_t*)A.rowid, (const int32_t*)A.ci,            \
                                   (const T*)A.v, Dinv, b, xin, d, xout, c1, c2);                                   \
         else                                                                                                       \
-            smooth_k<T, B, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,    \
+            smooth_k<T, B, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,    \
                                                         xout, c1, c2);                                             \
     } while (0)
 #define SK(RD, WD, Z)                                                                                              \
@@ -1287,21 +1324,21 @@ static void smooth_dispatch(const DSell<T>& A, const T* Dinv, const T* b, const 
 
 template <typename T>
 void smooth_step(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, double c1, double c2,
-                 bool read_d, bool write_d, bool zero_in, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                 bool read_d, bool write_d, bool zero_in, bool down, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     switch (A.br) {
-        case 1: smooth_dispatch<T, 1>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, s, e0, e1); break;
+        case 1: smooth_dispatch<T, 1>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1); break;
         case 3:
-            if (A.rowlane) smooth_rl3<T>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, s, e0, e1);
-            else smooth_dispatch<T, 3>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, s, e0, e1);
+            if (A.rowlane) smooth_rl3<T>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1);
+            else smooth_dispatch<T, 3>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1);
             break;
-        case 6: smooth_dispatch<T, 6>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, s, e0, e1); break;
+        case 6: smooth_dispatch<T, 6>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1); break;
         default: throw Error(SCR_E_UNIMPLEMENTED, "smooth_step: block size");
     }
 }
 template void smooth_step<double>(const DSell<double>&, const double*, const double*, const double*, double*, double*,
-                                  double, double, bool, bool, bool, hipStream_t, hipEvent_t, hipEvent_t);
+                                  double, double, bool, bool, bool, bool, hipStream_t, hipEvent_t, hipEvent_t);
 template void smooth_step<float>(const DSell<float>&, const float*, const float*, const float*, float*, float*,
-                                 double, double, bool, bool, bool, hipStream_t, hipEvent_t, hipEvent_t);
+                                 double, double, bool, bool, bool, bool, hipStream_t, hipEvent_t, hipEvent_t);
 
 // ---------------------------------------------------------------- three interleaved columns (1x1 blocks)
 // The scalar mesh Laplacian acts on x, y and z alike (Sec. 5.2.2): its products, smoother steps,
@@ -1360,12 +1397,12 @@ __device__ __forceinline__ void sell_row_dot3(int64_t o0, int64_t o1, int lane, 
     }
 }
 template <typename T, int MODE, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t nslices, bool down, int sp, const int32_t* __restrict__ off,
                                                   const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x,
                                                   const T* __restrict__ b, T* __restrict__ y) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
     T acc[3] = {0, 0, 0}, old[3] = {0, 0, 0};
@@ -1406,7 +1443,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t n
 }
 
 template <typename T>
-void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStream_t s) {
+void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
     if (A.br != 1 || A.bc != 1 || A.rowlane) throw Error(SCR_E_UNIMPLEMENTED, "sell_mv3: 1x1 blocks only");
     if (A.nslices == 0) return;
     int wps = waves_per_slice(A);
@@ -1415,10 +1452,10 @@ void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStre
         constexpr int W_ = W;                                                                                   \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W_>::SPB)), th(SliceGroup<W_>::THREADS);                    \
         switch (mode) {                                                                                         \
-            case 0: sell_mv3_k<T, 0, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv3_k<T, 1, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv3_k<T, 2, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv3_k<T, 3, W_><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv3_k<T, 0, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv3_k<T, 1, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv3_k<T, 2, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv3_k<T, 3, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                       \
     }
     if (wps == 1) MV3(1)
@@ -1429,8 +1466,8 @@ void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, hipStre
 #undef MV3
     check_launch("sell_mv3");
 }
-template void sell_mv3<double>(const DSell<double>&, const double*, const double*, double*, int, hipStream_t);
-template void sell_mv3<float>(const DSell<float>&, const float*, const float*, float*, int, hipStream_t);
+template void sell_mv3<double>(const DSell<double>&, const double*, const double*, double*, int, bool, hipStream_t);
+template void sell_mv3<float>(const DSell<float>&, const float*, const float*, float*, int, bool, hipStream_t);
 
 // y = R x for 1x1 R (rows of R are long; one row per wavefront, the lane tree of bsrt_mv_k)
 template <typename T>
@@ -1466,13 +1503,13 @@ template void bsrt_mv3<float>(const DBsrT<float>&, const float*, float*, hipStre
 
 // one smoothing step on three columns (1x1 blocks): as smooth_k with B = 1, per column
 template <typename T, bool RD, bool WD, bool ZERO, int WPS>
-__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t nslices, int sp, const int32_t* __restrict__ off,
+__global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t nslices, bool down, int sp, const int32_t* __restrict__ off,
                                                  const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ Dinv,
                                                  const T* __restrict__ b, const T* __restrict__ xin, T* __restrict__ d,
                                                  T* __restrict__ xout, T c1, T c2) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x) * SliceGroup<WPS>::SPB + wv / WPS;
+    const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const bool live = sl < nslices;
     const int lane = threadIdx.x & (WAVE - 1);
     T acc[3] = {0, 0, 0}, bi[3], dold[3], xi[3], di = 0;
@@ -1524,7 +1561,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t ns
 
 template <typename T>
 void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, double c1, double c2,
-                  bool read_d, bool write_d, bool zero_in, hipStream_t s) {
+                  bool read_d, bool write_d, bool zero_in, bool down, hipStream_t s) {
     if (A.br != 1 || A.bc != 1 || A.rowlane) throw Error(SCR_E_UNIMPLEMENTED, "smooth_step3: 1x1 blocks only");
     if (A.nslices == 0) return;
     const T C1 = (T)c1, C2 = (T)c2;
@@ -1532,7 +1569,7 @@ void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T*
 #define S3W(RD, WD, Z, W)                                                                                        \
     do {                                                                                                         \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), th(SliceGroup<W>::THREADS);                        \
-        smooth3_k<T, RD, WD, Z, W><<<g, th, 0, s>>>(A.nslices, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, xout,  \
+        smooth3_k<T, RD, WD, Z, W><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, xout,  \
                                                    C1, C2);                                                      \
     } while (0)
 #define S3(RD, WD, Z)                                                                                            \
@@ -1555,9 +1592,9 @@ void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T*
     check_launch("smooth_step3");
 }
 template void smooth_step3<double>(const DSell<double>&, const double*, const double*, const double*, double*,
-                                   double*, double, double, bool, bool, bool, hipStream_t);
+                                   double*, double, double, bool, bool, bool, bool, hipStream_t);
 template void smooth_step3<float>(const DSell<float>&, const float*, const float*, const float*, float*, float*,
-                                  double, double, bool, bool, bool, hipStream_t);
+                                  double, double, bool, bool, bool, bool, hipStream_t);
 
 // x = M b on three columns (the lane tree of dense_mv_k, per column)
 template <typename T>
