@@ -48,11 +48,21 @@ void split_to_interleaved(int64_t nb, const double* sv, double* a, hipStream_t s
     check_launch("s2i");
 }
 // ------------------------------------------------------------------ reduction machinery
+// Workgroups of the vector kernels that end in partial sums: one element a thread up to FUSE_GRID workgroups,
+// beyond that four, up to 1,024.  Up to FUSE_GRID workgroups the kernel after the partials adds them itself,
+// each workgroup for itself (the same order, so the same bits); a launch of its own for the sums, which at
+// 7k nodes takes 2.2 us of a kernel and the gap before it, is left to longer vectors, where 1,024 workgroups
+// would read 1,024 partials each.
+constexpr int FUSE_GRID = 256;
+static int reduce_grid(int64_t n) {
+    const int64_t one = cdiv(n, RTPB), four = cdiv(n, 4 * RTPB);
+    const int64_t g = four > FUSE_GRID ? (four > 1024 ? 1024 : four) : one > FUSE_GRID ? FUSE_GRID : one;
+    return (int)(g < 1 ? 1 : g);
+}
 void Reducer::init(int64_t n_, Arena& ar, hipStream_t s) {
     n = n_;
-    int64_t g = cdiv(n, 4 * RTPB);
-    grid = (int)(g < 1 ? 1 : (g > 1024 ? 1024 : g));
-    partials = ar.make<double>((size_t)grid * RMAXJ);
+    grid = reduce_grid(n);
+    partials = ar.make<double>((size_t)grid * RMAXJ * 2);
     out = ar.make<double>(RMAXJ);
 }
 
@@ -207,11 +217,44 @@ __global__ void __launch_bounds__(RTPB) gm_init_fin_k(const double* __restrict__
     }
 }
 
+// v = b * s (v == b: in place)
 template <typename T>
-__global__ void scale_by_k(int64_t n, T* __restrict__ v, const double* __restrict__ s) {
+__global__ void scale_from_k(int64_t n, const T* b, T* v, const double* __restrict__ s) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double f = *s;
-    if (i < n) v[i] = (T)((double)v[i] * f);
+    if (i < n) v[i] = (T)((double)b[i] * f);
+}
+
+// The basis columns of an element.  J <= 8 is the number of columns itself; above, jn <= J columns in groups
+// of four (one branch a group: with one a column, every load waited for the one before it), the places beyond
+// jn repeating the last column.
+template <int J, typename T>
+__device__ __forceinline__ void basis_row(const T* __restrict__ V, int64_t ld, int64_t e, int jn, double (&v)[J]) {
+    constexpr int U = J <= 8 ? J : 4;
+#pragma unroll
+    for (int j0 = 0; j0 < J; j0 += U)
+        if (J <= 8 || j0 < jn) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[j0 + u] = (double)V[(int64_t)(J <= 8 || j0 + u < jn ? j0 + u : jn - 1) * ld + e];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[j0 + u] = 0.0;
+        }
+}
+// Coefficients of an update: the sums of the partials of the kernel before (nprev > 0; workgroup 0 stores them
+// in h), or h as an earlier launch left it.  Zeros from jn to J.
+template <int J>
+__device__ __forceinline__ void update_coeffs(const double* __restrict__ prev, int nprev, int jn, double* __restrict__ h,
+                                              double (&hs)[J]) {
+    for (int j = jn + threadIdx.x; j < J; j += RTPB) hs[j] = 0.0;
+    if (nprev > 0) {
+        final_sums<J>(prev, nprev, jn, hs);
+        if (blockIdx.x == 0)
+            for (int j = threadIdx.x; j < jn; j += RTPB) h[j] = hs[j];
+    } else {
+        for (int j = threadIdx.x; j < jn; j += RTPB) hs[j] = h[j];
+        __syncthreads();
+    }
 }
 
 // partials of V_i . w  (i < jn)
@@ -222,10 +265,11 @@ __global__ void __launch_bounds__(RTPB) mdot_k(int64_t n, int jn, const T* __res
 #pragma unroll
     for (int j = 0; j < J; ++j) acc[j] = 0.0;
     for (int64_t e = (int64_t)blockIdx.x * RTPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * RTPB) {
-        double we = w[e];
+        const double we = w[e];
+        double v[J];
+        basis_row<J>(V, ld, e, jn, v);
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-            if (j < jn) acc[j] += (double)V[j * ld + e] * we;
+        for (int j = 0; j < J; ++j) acc[j] += v[j] * we;
     }
     block_partials<J>(acc, jn, partials);
 }
@@ -233,28 +277,23 @@ __global__ void __launch_bounds__(RTPB) mdot_k(int64_t n, int jn, const T* __res
 // w -= sum_i h_i V_i ;  partials of V_i . w
 template <int J, typename T>
 __global__ void __launch_bounds__(RTPB) upd_dot_k(int64_t n, int jn, const T* __restrict__ V, int64_t ld,
-                                                  T* __restrict__ w, const double* __restrict__ h,
-                                                  double* __restrict__ partials) {
+                                                  T* __restrict__ w, const double* __restrict__ prev, int nprev,
+                                                  double* __restrict__ h, double* __restrict__ partials) {
     __shared__ double hs[J];
-    for (int j = threadIdx.x; j < jn; j += RTPB) hs[j] = h[j];
-    __syncthreads();
+    update_coeffs<J>(prev, nprev, jn, h, hs);
     double acc[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) acc[j] = 0.0;
     for (int64_t e = (int64_t)blockIdx.x * RTPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * RTPB) {
         double v[J];
         double we = w[e];
+        basis_row<J>(V, ld, e, jn, v);
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-            if (j < jn) {
-                v[j] = V[j * ld + e];
-                we -= hs[j] * v[j];
-            }
+        for (int j = 0; j < J; ++j) we -= hs[j] * v[j];
         const T wr = (T)we;     // the stored value enters the dot products
         w[e] = wr;
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-            if (j < jn) acc[j] += v[j] * (double)wr;
+        for (int j = 0; j < J; ++j) acc[j] += v[j] * (double)wr;
     }
     block_partials<J>(acc, jn, partials);
 }
@@ -262,17 +301,17 @@ __global__ void __launch_bounds__(RTPB) upd_dot_k(int64_t n, int jn, const T* __
 // w -= sum_i h2_i V_i ; partials of ||w||^2
 template <int J, typename T>
 __global__ void __launch_bounds__(RTPB) upd_norm_k(int64_t n, int jn, const T* __restrict__ V, int64_t ld,
-                                                   T* __restrict__ w, const double* __restrict__ h2,
-                                                   double* __restrict__ partials) {
+                                                   T* __restrict__ w, const double* __restrict__ prev, int nprev,
+                                                   double* __restrict__ h2, double* __restrict__ partials) {
     __shared__ double hs[J];
-    for (int t = threadIdx.x; t < jn; t += RTPB) hs[t] = h2[t];
-    __syncthreads();
+    update_coeffs<J>(prev, nprev, jn, h2, hs);
     double acc[1] = {0.0};
     for (int64_t e = (int64_t)blockIdx.x * RTPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * RTPB) {
+        double v[J];
         double we = w[e];
+        basis_row<J>(V, ld, e, jn, v);
 #pragma unroll
-        for (int t = 0; t < J; ++t)
-            if (t < jn) we -= hs[t] * (double)V[t * ld + e];
+        for (int t = 0; t < J; ++t) we -= hs[t] * v[t];
         const T wr = (T)we;
         w[e] = wr;
         acc[0] += (double)wr * (double)wr;
@@ -280,42 +319,61 @@ __global__ void __launch_bounds__(RTPB) upd_norm_k(int64_t n, int jn, const T* _
     block_partials<1>(acc, 1, partials);
 }
 
-// Arnoldi column j (one block): ||w||, H[:,j] = h1 + h2, H[j+1,j] = ||w||, previous rotations,
-// new rotation, g update, estimate |g[j+1]|, 1/||w|| for the normalisation.
-__global__ void __launch_bounds__(RTPB) arnoldi_fin_k(const double* __restrict__ partials, int nblk,
-                                                      double* __restrict__ st, int m, int j, double* __restrict__ hslot,
-                                                      double seq) {
+// Arnoldi column j, one workgroup: H[:,j] = h1 + h2, H[j+1,j] = hn = ||w||, previous rotations, new rotation,
+// g update, estimate |g[j+1]|, 1/||w|| for the normalisation; published to the host.
+__device__ __forceinline__ void arnoldi_column(double hn, double* __restrict__ st, int m, int j, double* __restrict__ hslot,
+                                               double seq) {
     GLay L{m};
-    double* sc = st + L.scal();
-    final_sums<1>(partials, nblk, 1, sc + S_HN);
-    if (threadIdx.x != 0) return;
-    double* H = st + L.H();
-    double* cs = st + L.cs();
-    double* sn = st + L.sn();
-    double* g = st + L.g();
-    const double* h1 = st + L.h1();
-    const double* h2 = st + L.h2();
-    double hn = sqrt(sc[S_HN]);
-    for (int i = 0; i <= j; ++i) H[i * m + j] = h1[i] + h2[i];
-    H[(j + 1) * m + j] = hn;
-    for (int i = 0; i < j; ++i) {
-        double a = H[i * m + j], c = H[(i + 1) * m + j];
-        H[i * m + j] = cs[i] * a + sn[i] * c;
-        H[(i + 1) * m + j] = -sn[i] * a + cs[i] * c;
+    __shared__ double hc[RMAXJ], cc[RMAXJ], ss[RMAXJ];
+    for (int i = threadIdx.x; i <= j; i += RTPB) {
+        hc[i] = st[L.h1() + i] + st[L.h2() + i];
+        cc[i] = st[L.cs() + i];
+        ss[i] = st[L.sn() + i];
     }
-    double a = H[j * m + j], c = H[(j + 1) * m + j];
-    double rr = sqrt(a * a + c * c);
-    cs[j] = rr == 0.0 ? 1.0 : a / rr;
-    sn[j] = rr == 0.0 ? 0.0 : c / rr;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double* sc = st + L.scal();
+    double* H = st + L.H();
+    double* g = st + L.g();
+    double a = hc[0];
+    for (int i = 0; i < j; ++i) {
+        const double c = hc[i + 1];
+        H[i * m + j] = cc[i] * a + ss[i] * c;
+        a = -ss[i] * a + cc[i] * c;
+    }
+    const double rr = sqrt(a * a + hn * hn);
+    const double cj = rr == 0.0 ? 1.0 : a / rr, sj = rr == 0.0 ? 0.0 : hn / rr;
+    const double gj = g[j];
+    st[L.cs() + j] = cj;
+    st[L.sn() + j] = sj;
     H[j * m + j] = rr;
     H[(j + 1) * m + j] = 0.0;
-    g[j + 1] = -sn[j] * g[j];
-    g[j] = cs[j] * g[j];
+    g[j + 1] = -sj * gj;
+    g[j] = cj * gj;
     sc[S_HN] = hn;
-    sc[S_EST] = fabs(g[j + 1]);
+    sc[S_EST] = fabs(-sj * gj);
     sc[S_INV] = hn > 0.0 ? 1.0 / hn : 0.0;
     sc[S_FLAG] = (isfinite(hn) && isfinite(sc[S_EST]) && isfinite(rr)) ? 0.0 : 1.0;
     publish(hslot, sc, 8, seq);
+}
+__global__ void __launch_bounds__(RTPB) arnoldi_fin_k(const double* __restrict__ partials, int nblk,
+                                                      double* __restrict__ st, int m, int j, double* __restrict__ hslot,
+                                                      double seq) {
+    __shared__ double hn2;
+    final_sums<1>(partials, nblk, 1, &hn2);
+    arnoldi_column(sqrt(hn2), st, m, j, hslot, seq);
+}
+// the same and the normalisation w /= ||w|| in one launch: workgroup 0 finishes the column first
+template <typename T>
+__global__ void __launch_bounds__(RTPB) arnoldi_scale_k(int64_t n, T* __restrict__ w, const double* __restrict__ partials,
+                                                        int nblk, double* __restrict__ st, int m, int j,
+                                                        double* __restrict__ hslot, double seq) {
+    __shared__ double hn2;
+    final_sums<1>(partials, nblk, 1, &hn2);
+    const double hn = sqrt(hn2), f = hn > 0.0 ? 1.0 / hn : 0.0;
+    if (blockIdx.x == 0) arnoldi_column(hn, st, m, j, hslot, seq);
+    for (int64_t i = (int64_t)blockIdx.x * RTPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * RTPB)
+        w[i] = (T)((double)w[i] * f);
 }
 
 // back substitution of the j x j upper triangle: y = R^-1 g
@@ -332,27 +390,46 @@ __global__ void ysolve_k(double* __restrict__ st, int m, int j) {
     }
 }
 
-// x += sum_i y_i Z_i
+// x += sum_i y_i Z_i (fresh: x = sum)
 template <typename T>
 __global__ void __launch_bounds__(RTPB) maxpy_k(int64_t n, int jn, const T* __restrict__ Z, int64_t ld,
-                                                const double* __restrict__ y, T* __restrict__ x) {
+                                                const double* __restrict__ y, int fresh, T* __restrict__ x) {
     __shared__ double ys[RMAXJ];
     for (int j = threadIdx.x; j < jn; j += RTPB) ys[j] = y[j];
     __syncthreads();
     int64_t e = (int64_t)blockIdx.x * RTPB + threadIdx.x;
     if (e >= n) return;
-    double xe = x[e];
+    double xe = fresh ? 0.0 : (double)x[e];
+#pragma unroll 4
     for (int j = 0; j < jn; ++j) xe += ys[j] * (double)Z[j * ld + e];
     x[e] = (T)xe;
 }
 
 #define JDISPATCH(jn, KERNEL, ...)                                         \
     do {                                                                   \
-        if ((jn) <= 4) KERNEL<4>__VA_ARGS__;                               \
-        else if ((jn) <= 8) KERNEL<8>__VA_ARGS__;                          \
-        else if ((jn) <= 16) KERNEL<16>__VA_ARGS__;                        \
-        else if ((jn) <= 32) KERNEL<32>__VA_ARGS__;                        \
-        else KERNEL<64>__VA_ARGS__;                                        \
+        switch (jn) {                                                      \
+            case 1: KERNEL<1>__VA_ARGS__; break;                           \
+            case 2: KERNEL<2>__VA_ARGS__; break;                           \
+            case 3: KERNEL<3>__VA_ARGS__; break;                           \
+            case 4: KERNEL<4>__VA_ARGS__; break;                           \
+            case 5: KERNEL<5>__VA_ARGS__; break;                           \
+            case 6: KERNEL<6>__VA_ARGS__; break;                           \
+            case 7: KERNEL<7>__VA_ARGS__; break;                           \
+            case 8: KERNEL<8>__VA_ARGS__; break;                           \
+            default:                                                       \
+                if ((jn) <= 16) KERNEL<16>__VA_ARGS__;                     \
+                else if ((jn) <= 32) KERNEL<32>__VA_ARGS__;                \
+                else KERNEL<64>__VA_ARGS__;                                \
+        }                                                                  \
+    } while (0)
+
+#define SDISPATCH(jn, ...)                                                 \
+    do {                                                                   \
+        if ((jn) <= 4) sum_k<4><<<1, RTPB, 0, s>>>__VA_ARGS__;             \
+        else if ((jn) <= 8) sum_k<8><<<1, RTPB, 0, s>>>__VA_ARGS__;        \
+        else if ((jn) <= 16) sum_k<16><<<1, RTPB, 0, s>>>__VA_ARGS__;      \
+        else if ((jn) <= 32) sum_k<32><<<1, RTPB, 0, s>>>__VA_ARGS__;      \
+        else sum_k<64><<<1, RTPB, 0, s>>>__VA_ARGS__;                      \
     } while (0)
 
 template <typename T>
@@ -382,38 +459,51 @@ KStat GmresT<T>::solve(OpT<T>& A, OpT<T>& M, const T* b, T* x, double tol, int m
     const int m = m_;
     const int G = red_.grid;
     double* part = red_.partials;
+    double* part2 = part + (int64_t)G * RMAXJ;
+    const bool fuse = G <= FUSE_GRID;
     GLay L{m};
-    double bn = device_norm(b, n, red_, slot_, s);
-    if (!use_x0 || bn == 0.0) zero_dev(x, n * sizeof(T), s);
+    const double* host_ = slot_.h;
+    // A start from zero takes the first residual's norm from the right-hand side's, and x is written (not
+    // added to) by the first update: `fresh` until then, and every way out before it clears x.
+    bool fresh = !use_x0;
+    double bn;
+    if (fresh) {
+        dot_part_k<T><<<G, RTPB, 0, s>>>(n, b, b, part);
+        gm_init_fin_k<<<1, RTPB, 0, s>>>(part, G, st_, m, slot_.d, slot_.next());
+        check_launch("gm_init");
+        slot_.wait(s);
+        bn = host_[S_BETA];
+    } else {
+        bn = device_norm(b, n, red_, slot_, s);
+    }
     if (bn == 0.0) {
+        zero_dev(x, n * sizeof(T), s);
         st.converged = true;
         return st;
     }
-    if (!std::isfinite(bn)) throw Error(SCR_E_BREAKDOWN, "non-finite right-hand side");
-    bool first = true;
+    if (!std::isfinite(bn)) {
+        if (fresh) zero_dev(x, n * sizeof(T), s);
+        throw Error(SCR_E_BREAKDOWN, "non-finite right-hand side");
+    }
     double est = INFINITY;
     int64_t nblk = cdiv(n, 256);
     for (;;) {
         T* V0 = V_;
-        if (first && !use_x0) {
-            copy_dev(V0, b, n * sizeof(T), s);
-        } else {
+        if (!fresh) {
             A.apply(x, V0, s);
             axpby_t_k<T><<<nblk, 256, 0, s>>>(n, 1.0, b, -1.0, V0);
+            dot_part_k<T><<<G, RTPB, 0, s>>>(n, V0, V0, part);
+            gm_init_fin_k<<<1, RTPB, 0, s>>>(part, G, st_, m, slot_.d, slot_.next());
+            check_launch("gm_init");
+            slot_.wait(s);
         }
-        first = false;
-        dot_part_k<T><<<G, RTPB, 0, s>>>(n, V0, V0, part);
-        gm_init_fin_k<<<1, RTPB, 0, s>>>(part, G, st_, m, slot_.d, slot_.next());
-        check_launch("gm_init");
-        slot_.wait(s);
-        const double* host_ = slot_.h;
         double beta = host_[S_BETA];
         if (host_[S_FLAG] != 0.0) throw Error(SCR_E_BREAKDOWN, "non-finite residual in GMRES");
         st.rel_res = beta / bn;
         if (beta <= tol * bn) { st.converged = true; break; }
         if (!check_true && est <= tol * bn) { st.converged = true; break; }
         if (st.iters >= maxit) break;
-        scale_by_k<<<nblk, 256, 0, s>>>(n, V0, st_ + L.scal() + S_INV);
+        scale_from_k<<<nblk, 256, 0, s>>>(n, fresh ? b : (const T*)V0, V0, st_ + L.scal() + S_INV);
         int j = 0;
         while (j < m) {
             T* Vj = V_ + (int64_t)j * n;
@@ -424,30 +514,39 @@ KStat GmresT<T>::solve(OpT<T>& A, OpT<T>& M, const T* b, T* x, double tol, int m
             int jn = j + 1;
             // CGS2: h1 = V^T w; w -= V h1, h2 = V^T w; w -= V h2; ||w||
             JDISPATCH(jn, mdot_k, <<<G, RTPB, 0, s>>>(n, jn, V_, n, w, part));
-            JDISPATCH(jn, sum_k, <<<1, RTPB, 0, s>>>(part, G, jn, st_ + L.h1()));
-            JDISPATCH(jn, upd_dot_k, <<<G, RTPB, 0, s>>>(n, jn, V_, n, w, st_ + L.h1(), part));
-            JDISPATCH(jn, sum_k, <<<1, RTPB, 0, s>>>(part, G, jn, st_ + L.h2()));
-            JDISPATCH(jn, upd_norm_k, <<<G, RTPB, 0, s>>>(n, jn, V_, n, w, st_ + L.h2(), part));
-            arnoldi_fin_k<<<1, RTPB, 0, s>>>(part, G, st_, m, j, slot_.d, slot_.next());
+            if (!fuse) SDISPATCH(jn, (part, G, jn, st_ + L.h1()));
+            JDISPATCH(jn, upd_dot_k, <<<G, RTPB, 0, s>>>(n, jn, V_, n, w, part, fuse ? G : 0, st_ + L.h1(), part2));
+            if (!fuse) SDISPATCH(jn, (part2, G, jn, st_ + L.h2()));
+            JDISPATCH(jn, upd_norm_k, <<<G, RTPB, 0, s>>>(n, jn, V_, n, w, part2, fuse ? G : 0, st_ + L.h2(), part));
+            if (fuse) {
+                arnoldi_scale_k<T><<<G, RTPB, 0, s>>>(n, w, part, G, st_, m, j, slot_.d, slot_.next());
+            } else {
+                arnoldi_fin_k<<<1, RTPB, 0, s>>>(part, G, st_, m, j, slot_.d, slot_.next());
+                scale_from_k<<<nblk, 256, 0, s>>>(n, w, w, st_ + L.scal() + S_INV);
+            }
             check_launch("cgs2");
-            scale_by_k<<<nblk, 256, 0, s>>>(n, w, st_ + L.scal() + S_INV);
             slot_.wait(s);
             ++st.iters;
             ++j;
-            if (host_[S_FLAG] != 0.0) throw Error(SCR_E_BREAKDOWN, "non-finite value in the Arnoldi process");
+            if (host_[S_FLAG] != 0.0) {
+                if (fresh) zero_dev(x, n * sizeof(T), s);
+                throw Error(SCR_E_BREAKDOWN, "non-finite value in the Arnoldi process");
+            }
             est = host_[S_EST];
             if (host_[S_HN] == 0.0) break;   // happy breakdown: the Krylov space is invariant
             if (est <= tol * bn || st.iters >= maxit) break;
         }
         ysolve_k<<<1, 64, 0, s>>>(st_, m, j);
-        maxpy_k<<<nblk, RTPB, 0, s>>>(n, j, Z_, n, st_ + L.y(), x);
+        maxpy_k<<<nblk, RTPB, 0, s>>>(n, j, Z_, n, st_ + L.y(), fresh ? 1 : 0, x);
         check_launch("gmres update");
+        fresh = false;
         st.rel_res = est / bn;
         if (!check_true && (est <= tol * bn || st.iters >= maxit)) {
             st.converged = est <= tol * bn;
             break;
         }
     }
+    if (fresh) zero_dev(x, n * sizeof(T), s);
     return st;
 }
 
@@ -455,14 +554,9 @@ template class GmresT<double>;
 template class GmresT<float>;
 
 // ------------------------------------------------------------------ CG on three columns
-// Per-column state (doubles): RZ[3] | ALPHA[3] | BETA[3] | PQ[3] | DONE[3] | RN2[3] | spare
-enum { C3_RZ = 0, C3_ALPHA = 3, C3_BETA = 6, C3_PQ = 9, C3_DONE = 12, C3_RN2 = 15, C3_SIZE = 32 };
-
-// the reduction grid of a vector length (as Reducer::init)
-static int reduce_grid(int64_t n) {
-    int64_t g = cdiv(n, 4 * RTPB);
-    return (int)(g < 1 ? 1 : (g > 1024 ? 1024 : g));
-}
+// Per-column state (doubles): RZ[3] | ALPHA[3] | BETA[3] | PQ[3] | DONE[3] | RN2[3] | RZ of odd steps[3] | spare
+// (r.z of a step is written beside the one before it, which other workgroups may still be reading)
+enum { C3_RZ = 0, C3_ALPHA = 3, C3_BETA = 6, C3_PQ = 9, C3_DONE = 12, C3_RN2 = 15, C3_RZ_ODD = 18, C3_SIZE = 32 };
 
 // partials of x_c . y_c per column (the element order of dot_part_k, per column)
 __global__ void __launch_bounds__(RTPB) dot3_part_k(int64_t n, const double* __restrict__ x, const double* __restrict__ y,
@@ -479,33 +573,49 @@ __global__ void __launch_bounds__(RTPB) sum3_pub_k(const double* __restrict__ pa
     if (threadIdx.x == 0) publish(hslot, out, 3, seq);
 }
 // ALPHA_c = RZ_c / PQ_c for the columns still running
-__global__ void __launch_bounds__(RTPB) cg3_alpha_fin_k(const double* __restrict__ partials, int nblk, double* __restrict__ st) {
+__global__ void __launch_bounds__(RTPB) cg3_alpha_fin_k(const double* __restrict__ partials, int nblk, int rz,
+                                                        double* __restrict__ st) {
     final_sums<3>(partials, nblk, 3, st + C3_PQ);
     if (threadIdx.x == 0)
-        for (int c = 0; c < 3; ++c) st[C3_ALPHA + c] = st[C3_DONE + c] != 0.0 ? 0.0 : st[C3_RZ + c] / st[C3_PQ + c];
+        for (int c = 0; c < 3; ++c) st[C3_ALPHA + c] = st[C3_DONE + c] != 0.0 ? 0.0 : st[rz + c] / st[C3_PQ + c];
 }
-// per running column: (rold = r;) x += alpha p; r -= alpha q; partials of r . r
+// per running column: (rold = r;) x += alpha p; r -= alpha q; partials of r . r.  nprev > 0: alpha from the
+// partials of p . q, each workgroup for itself; otherwise as cg3_alpha_fin_k left it
 __global__ void __launch_bounds__(RTPB) cg3_update_k(int64_t n, double* __restrict__ x, const double* __restrict__ p,
                                                      double* __restrict__ r, const double* __restrict__ q,
                                                      double* __restrict__ rold, const double* __restrict__ st,
+                                                     const double* __restrict__ prev, int nprev, int rz,
                                                      double* __restrict__ partials) {
+    __shared__ double pq[3];
+    if (nprev > 0) final_sums<3>(prev, nprev, 3, pq);
     double alpha[3];
     bool run[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { alpha[c] = st[C3_ALPHA + c]; run[c] = st[C3_DONE + c] == 0.0; }
+    for (int c = 0; c < 3; ++c) {
+        run[c] = st[C3_DONE + c] == 0.0;
+        alpha[c] = nprev > 0 ? st[rz + c] / pq[c] : st[C3_ALPHA + c];
+    }
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * RTPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * RTPB)
+    for (int64_t i = (int64_t)blockIdx.x * RTPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * RTPB) {
+        double xc[3], pc[3], rc[3], qc[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            rc[c] = r[3 * i + c];
+            xc[c] = x[3 * i + c];
+            pc[c] = p[3 * i + c];
+            qc[c] = q[3 * i + c];
+        }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             if (!run[c]) continue;
             const int64_t o = 3 * i + c;
-            double ri = r[o];
-            if (rold) rold[o] = ri;
-            x[o] += alpha[c] * p[o];
-            ri -= alpha[c] * q[o];
+            if (rold) rold[o] = rc[c];
+            x[o] = xc[c] + alpha[c] * pc[c];
+            const double ri = rc[c] - alpha[c] * qc[c];
             r[o] = ri;
             acc[c] += ri * ri;
         }
+    }
     block_partials<3>(acc, 3, partials);
 }
 // partials of r_c . z_c and (flexible) z_c . (r_c - rold_c)
@@ -521,16 +631,16 @@ __global__ void __launch_bounds__(RTPB) cg3_rz_k(int64_t n, const double* __rest
         }
     block_partials<6>(acc, 6, partials);
 }
-// BETA_c = (flex ? num_c : rz_new_c) / RZ_c; RZ_c = rz_new_c   (init: only RZ)
+// BETA_c = (flex ? num_c : rz_new_c) / RZ_c; the new RZ goes to rz_new   (init: only RZ)
 __global__ void __launch_bounds__(RTPB) cg3_beta_fin_k(const double* __restrict__ partials, int nblk, int flexible,
-                                                       int init, double* __restrict__ st) {
+                                                       int init, int rz, int rz_new, double* __restrict__ st) {
     __shared__ double res[6];
     final_sums<6>(partials, nblk, 6, res);
     if (threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) {
             if (st[C3_DONE + c] != 0.0) continue;
-            if (!init) st[C3_BETA + c] = (flexible ? res[3 + c] : res[c]) / st[C3_RZ + c];
-            st[C3_RZ + c] = res[c];
+            if (!init) st[C3_BETA + c] = (flexible ? res[3 + c] : res[c]) / st[rz + c];
+            st[rz_new + c] = res[c];
         }
 }
 __global__ void cg3_p_k(int64_t n3, double* __restrict__ p, const double* __restrict__ z, const double* __restrict__ st) {
@@ -539,6 +649,27 @@ __global__ void cg3_p_k(int64_t n3, double* __restrict__ p, const double* __rest
     const int c = (int)(o % 3);
     p[o] = st[C3_DONE + c] != 0.0 ? 0.0 : z[o] + st[C3_BETA + c] * p[o];
 }
+// the two in one launch (each workgroup adds the partials for itself, workgroup 0 stores the new RZ)
+__global__ void __launch_bounds__(RTPB) cg3_beta_p_k(int64_t n3, double* __restrict__ p, const double* __restrict__ z,
+                                                     const double* __restrict__ partials, int nblk, int flexible, int rz,
+                                                     int rz_new, double* __restrict__ st) {
+    __shared__ double res[6];
+    final_sums<6>(partials, nblk, 6, res);
+    double beta[3];
+    bool run[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        run[c] = st[C3_DONE + c] == 0.0;
+        beta[c] = (flexible ? res[3 + c] : res[c]) / st[rz + c];
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 3 && st[C3_DONE + threadIdx.x] == 0.0) st[rz_new + threadIdx.x] = res[threadIdx.x];
+    for (int64_t o = (int64_t)blockIdx.x * RTPB + threadIdx.x; o < n3; o += (int64_t)gridDim.x * RTPB) {
+        const int c = (int)(o % 3);
+        const double bc = c == 0 ? beta[0] : c == 1 ? beta[1] : beta[2];
+        const bool rc = c == 0 ? run[0] : c == 1 ? run[1] : run[2];
+        p[o] = rc ? z[o] + bc * p[o] : 0.0;
+    }
+}
 __global__ void cg3_set_done_k(double* __restrict__ st, double d0, double d1, double d2) {
     if (threadIdx.x == 0) { st[C3_DONE] = d0; st[C3_DONE + 1] = d1; st[C3_DONE + 2] = d2; }
 }
@@ -546,15 +677,18 @@ __global__ void cg3_init_k(double* __restrict__ st) {
     for (int e = threadIdx.x; e < C3_SIZE; e += blockDim.x) st[e] = 0.0;
 }
 
+// (a second set of partials only where the next kernel adds them, which is far below any limit on the size)
 int64_t Pcg3::workspace_doubles(int64_t n) {
-    return 15 * n + C3_SIZE + (int64_t)reduce_grid(n) * RMAXJ + RMAXJ;
+    const int64_t g = reduce_grid(n);
+    return 15 * n + C3_SIZE + (g <= FUSE_GRID ? 2 : 1) * g * RMAXJ + RMAXJ;
 }
 
 Pcg3::Pcg3(int64_t n, double* ws, StatusSlot* slot) : n_(n), grid_(reduce_grid(n)), slot_(slot) {
     r_ = ws; z_ = r_ + 3 * n; p_ = z_ + 3 * n; q_ = p_ + 3 * n; rold_ = q_ + 3 * n;
     st_ = rold_ + 3 * n;
     part_ = st_ + C3_SIZE;
-    out_ = part_ + (int64_t)grid_ * RMAXJ;
+    part2_ = grid_ <= FUSE_GRID ? part_ + (int64_t)grid_ * RMAXJ : part_;
+    out_ = part2_ + (int64_t)grid_ * RMAXJ;
 }
 
 Pcg3::Result Pcg3::solve(Op& A, Op& M, const double* b, double* x, double tol, int maxit, bool flexible,
@@ -583,14 +717,16 @@ Pcg3::Result Pcg3::solve(Op& A, Op& M, const double* b, double* x, double tol, i
     M.apply(r_, z_, s);
     copy_d(3 * n, z_, p_, s);
     cg3_rz_k<<<G, RTPB, 0, s>>>(n, r_, z_, nullptr, part_);
-    cg3_beta_fin_k<<<1, RTPB, 0, s>>>(part_, G, 0, 1, st_);
+    int rz = C3_RZ, rz_new = C3_RZ_ODD;
+    cg3_beta_fin_k<<<1, RTPB, 0, s>>>(part_, G, 0, 1, rz, rz, st_);
     double* rold = flexible ? rold_ : nullptr;
+    const bool fuse = G <= FUSE_GRID;
     for (;;) {
         A.apply(p_, q_, s);
         dot3_part_k<<<G, RTPB, 0, s>>>(n, p_, q_, part_);
-        cg3_alpha_fin_k<<<1, RTPB, 0, s>>>(part_, G, st_);
-        cg3_update_k<<<G, RTPB, 0, s>>>(n, x, p_, r_, q_, rold, st_, part_);
-        sum3_pub_k<<<1, RTPB, 0, s>>>(part_, G, st_ + C3_RN2, slot_->d, slot_->next());
+        if (!fuse) cg3_alpha_fin_k<<<1, RTPB, 0, s>>>(part_, G, rz, st_);
+        cg3_update_k<<<G, RTPB, 0, s>>>(n, x, p_, r_, q_, rold, st_, part_, fuse ? G : 0, rz, part2_);
+        sum3_pub_k<<<1, RTPB, 0, s>>>(part2_, G, st_ + C3_RN2, slot_->d, slot_->next());
         check_launch("cg3");
         slot_->wait(s);
         bool changed = false;
@@ -608,8 +744,13 @@ Pcg3::Result Pcg3::solve(Op& A, Op& M, const double* b, double* x, double tol, i
             cg3_set_done_k<<<1, 64, 0, s>>>(st_, done[0] ? 1.0 : 0.0, done[1] ? 1.0 : 0.0, done[2] ? 1.0 : 0.0);
         M.apply(r_, z_, s);
         cg3_rz_k<<<G, RTPB, 0, s>>>(n, r_, z_, rold, part_);
-        cg3_beta_fin_k<<<1, RTPB, 0, s>>>(part_, G, flexible ? 1 : 0, 0, st_);
-        cg3_p_k<<<nblk3, 256, 0, s>>>(3 * n, p_, z_, st_);
+        if (fuse) {
+            cg3_beta_p_k<<<3 * G, RTPB, 0, s>>>(3 * n, p_, z_, part_, G, flexible ? 1 : 0, rz, rz_new, st_);
+        } else {
+            cg3_beta_fin_k<<<1, RTPB, 0, s>>>(part_, G, flexible ? 1 : 0, 0, rz, rz_new, st_);
+            cg3_p_k<<<nblk3, 256, 0, s>>>(3 * n, p_, z_, st_);
+        }
+        std::swap(rz, rz_new);
         check_launch("cg3");
     }
     return res;

@@ -26,7 +26,7 @@ struct KStat {
 struct Reducer {
     int64_t n = 0;
     int grid = 0;
-    double* partials = nullptr;      // grid * 64
+    double* partials = nullptr;      // grid * 64, twice (a kernel may add one set while it writes the other)
     double* out = nullptr;           // 64 results
     void init(int64_t n_, Arena& ar, hipStream_t s);
     void release(Arena& ar) {
@@ -91,7 +91,7 @@ class Pcg3 {
    private:
     int64_t n_;
     int grid_;
-    double *r_, *z_, *p_, *q_, *rold_, *st_, *part_, *out_;
+    double *r_, *z_, *p_, *q_, *rold_, *st_, *part_, *part2_, *out_;
     StatusSlot* slot_;
 };
 

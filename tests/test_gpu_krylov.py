@@ -1,0 +1,65 @@
+"""GMRES and CG where their vector kernels change: the number of basis columns a kernel takes (1 to 8, then up
+to 16, 32 and 64), one and four elements a thread (65,536 unknowns), and the sums of the partials added by the
+next kernel or by a launch of their own (262,144 unknowns).
+
+A wrong coefficient spoils the orthogonality of the basis, and the estimate of the residual then parts from the
+residual: the solves must stop at the oracle's iteration (+-1: the order of the sums differs), and the
+residual, computed here in FP64, must meet the tolerance with 1 % for its own rounding."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def scr():
+    import paper_2206_06996_amd.scr as m
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def residual(s, b, x):
+    rows = np.repeat(np.arange(s.n_b), np.diff(s.rp))
+    y = np.zeros((s.n_b, 4))
+    np.add.at(y, rows, np.einsum("eij,ej->ei", s.val.reshape(-1, 4, 4), x.reshape(-1, 4)[s.ci]))
+    return np.linalg.norm(b - y.reshape(-1)) / np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("nodes,precond,restart", [(700, 1, 63), (700, 1, 20), (700, 0, 9),
+                                                   (18e3, 0, 30), (95e3, 0, 30)])
+def test_gmres_at_every_kernel_width(scr, nodes, precond, restart):
+    s = synth.generate(synth.tube_params(nodes, 1.0, 5.0))
+    print(f"[gpu] gmres n_b={s.n_b} precond={precond} restart={restart}", flush=True)
+    ctx = scr.Context(0)
+    h = scr.amg_setup(ctx, scr.SCR_SYSTEM, dev(s.rp), dev(s.ci), dev(s.val.reshape(-1)), dev(s.xyz.reshape(-1)))
+    b = synth.rhs(3, 4 * s.n_b, s.mask)
+    kw = dict(tol=1e-9, precond=precond, restart=restart, restart_inner=63, tol_A=1e-12, tol_S=1e-12, max_it_A=80, max_it_S=80)
+    x = torch.full((4 * s.n_b,), float("nan"), dtype=torch.float64, device="cuda")   # written, not added to
+    rc, st = scr.scr_solve(h, dev(b), x, scr.solve_opts(**kw))
+    xs = x.cpu().numpy()
+    print(f"[gpu] outer {st['outer_it']} its_A {st['its_A']}/{st['calls_A']} its_S {st['its_S']}/{st['calls_S']}", flush=True)
+    assert rc == 0 and np.isfinite(xs).all()
+    assert residual(s, b, xs) <= 1.01e-9
+    if nodes < 1e3:
+        o = oracle.Scr(s.rp, s.ci, s.val, s.xyz)
+        _, rco, sto = o.solve(b, oracle.solve_opts(**kw))
+        assert rco == 0 and abs(st["outer_it"] - sto["outer_it"]) <= 1
+    # a tolerance that zero meets, and a right-hand side of zero: x is zero
+    x.fill_(float("nan"))
+    scr.scr_solve(h, dev(b), x, scr.solve_opts(tol=2.0))
+    assert not x.any()
+    x.fill_(float("nan"))
+    rc, st = scr.scr_solve(h, torch.zeros_like(x), x)
+    assert rc == 0 and not x.any()
+    h.destroy()
+    ctx.destroy()
