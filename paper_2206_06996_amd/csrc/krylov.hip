@@ -48,15 +48,16 @@ void split_to_interleaved(int64_t nb, const double* sv, double* a, hipStream_t s
     check_launch("s2i");
 }
 // ------------------------------------------------------------------ reduction machinery
-// Workgroups of the vector kernels that end in partial sums: one element a thread up to FUSE_GRID workgroups,
+// Workgroups of the vector kernels that end in partial sums: one element a thread up to ONE_GRID workgroups,
 // beyond that four, up to 1,024.  Up to FUSE_GRID workgroups the kernel after the partials adds them itself,
 // each workgroup for itself (the same order, so the same bits); a launch of its own for the sums, which at
-// 7k nodes takes 2.2 us of a kernel and the gap before it, is left to longer vectors, where 1,024 workgroups
-// would read 1,024 partials each.
-constexpr int FUSE_GRID = 256;
+// 7k nodes takes 2.2 us of a kernel and the gap before it, is left to longer vectors, where every workgroup
+// would read up to 1,024 partials.  FUSE_GRID 256, 512 and 1,024: solve at 100k nodes (323 workgroups) 238,
+// 232 and 232 ms, at 300k (949) 989, 989 and 1,007.  ONE_GRID 512: 41k corrector 120 ms against 118.
+constexpr int FUSE_GRID = 512, ONE_GRID = 256;
 static int reduce_grid(int64_t n) {
     const int64_t one = cdiv(n, RTPB), four = cdiv(n, 4 * RTPB);
-    const int64_t g = four > FUSE_GRID ? (four > 1024 ? 1024 : four) : one > FUSE_GRID ? FUSE_GRID : one;
+    const int64_t g = four > ONE_GRID ? (four > 1024 ? 1024 : four) : one > ONE_GRID ? ONE_GRID : one;
     return (int)(g < 1 ? 1 : g);
 }
 void Reducer::init(int64_t n_, Arena& ar, hipStream_t s) {

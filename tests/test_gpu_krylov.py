@@ -1,6 +1,6 @@
 """GMRES and CG where their vector kernels change: the number of basis columns a kernel takes (1 to 8, then up
 to 16, 32 and 64), one and four elements a thread (65,536 unknowns), and the sums of the partials added by the
-next kernel or by a launch of their own (262,144 unknowns).
+next kernel or by a launch of their own (524,288 unknowns).
 
 A wrong coefficient spoils the orthogonality of the basis, and the estimate of the residual then parts from the
 residual: the solves must stop at the oracle's iteration (+-1: the order of the sums differs), and the
@@ -36,7 +36,7 @@ def residual(s, b, x):
 
 
 @pytest.mark.parametrize("nodes,precond,restart", [(700, 1, 63), (700, 1, 20), (700, 0, 9),
-                                                   (18e3, 0, 30), (95e3, 0, 30)])
+                                                   (18e3, 0, 30), (140e3, 0, 30)])
 def test_gmres_at_every_kernel_width(scr, nodes, precond, restart):
     s = synth.generate(synth.tube_params(nodes, 1.0, 5.0))
     print(f"[gpu] gmres n_b={s.n_b} precond={precond} restart={restart}", flush=True)
