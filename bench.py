@@ -253,8 +253,10 @@ def _kt_bytes(levels):
                 # restriction y = R x (R: nc x nr blocks k x b)
                 rbytes = L["nnzR"] * (k * b * tb + 4.0) + nr * b * tb + nc * (4.0 + k * tb)
                 add(f"bsrt_mv_k<{tn},{k},{b},1>", ceil(nc / 4) * 256, rbytes, f"{name}{l} R")
-                add(f"bsrt_mv_k<{tn},{k},{b},4>", nc * 256, rbytes, f"{name}{l} R")
-                if b == 1:
+                if b > 1:
+                    add(f"bsrt_rows_k<{tn},{k},{b}>", nc * 384, rbytes, f"{name}{l} R")
+                else:
+                    add(f"bsrt_mv_k<{tn},1,1,4>", nc * 256, rbytes, f"{name}{l} R")
                     add(f"bsrt_mv3_k<{tn}>", ceil(nc / 4) * 256, L["nnzR"] * (tb + 4.0) + nr * 3 * tb + nc * (4.0 + 3 * tb), f"{name}{l} R")
     nb, nnzb = levels["n_b"], levels["nnzb"]
     for mode in (0, 1):

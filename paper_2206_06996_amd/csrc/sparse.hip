@@ -1033,9 +1033,8 @@ void sell_mv_split4(const DSell<double>& K, const double* x, const double* b, do
 
 // ---------------------------------------------------------------- restriction (row per wave)
 // Values in row-entry-major order (bsrt_fill_k); lane j of the row's WPR wavefronts takes blocks j,
-// j + 64 WPR, ...  Fewer than BSRT_ROWS rows that are longer than one pass of a wavefront leave most SIMDs
-// idle and each wavefront with two or more dependent round trips: four wavefronts share a row there (246
-// rows of 90 3x6 blocks: 9.0 -> 4.9 us; 2,393 rows and more are no faster that way).
+// j + 64 WPR, ...  (WPR = 4 for fewer than BSRT_ROWS rows of 1x1 blocks that are longer than one pass of a
+// wavefront.)
 template <typename T, int BR, int BC, int WPR>
 __global__ void __launch_bounds__(256) bsrt_mv_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ x, T* __restrict__ y) {
@@ -1083,23 +1082,67 @@ __global__ void __launch_bounds__(256) bsrt_mv_k(int64_t nr, const int32_t* __re
         y[row * BR + lane] = sum;
     }
 }
+// Few rows of 6-wide blocks: one workgroup per row, one wavefront per scalar row (each gathers the row's x),
+// two entries per lane in flight; the sums are those of bsrt_mv_k with one wavefront.  Bound by latency: one
+// wavefront for the block row issues 18 or 36 strided loads per pass and adds six sums across its lanes.
+// FP64, one wavefront -> this: 110 rows of 6x6 10.6 -> 4.0 us, 246 of 6x3 9.0 -> 3.8, 1,776 of 6x3 8.7 -> 7.1;
+// from 3,200 rows of 6x3 on the gathers of x by six wavefronts cost more than they hide (8,600 rows: 20.3
+// against 26.9 us), hence BSRT_ROWS.
+template <typename T, int BR, int BC>
+__global__ void __launch_bounds__(BR * WAVE) bsrt_rows_k(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                                                         const T* __restrict__ v, const T* __restrict__ x, T* __restrict__ y) {
+    const int64_t row = blockIdx.x;
+    const int r = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
+    const int64_t q0 = rp[row];
+    const int len = (int)(rp[row + 1] - q0);
+    const T* vr = v + q0 * (BR * BC) + (int64_t)(r * BC) * len;
+    T acc = 0;
+    for (int j = lane; j < len; j += 2 * WAVE) {
+        const int j2 = j + WAVE < len ? j + WAVE : j;     // the second entry, or the first again with weight 0
+        const int64_t c0 = ci[q0 + j], c1 = ci[q0 + j2];
+        T v0[BC], v1[BC], x0[BC], x1[BC];
+#pragma unroll
+        for (int k = 0; k < BC; ++k) {
+            v0[k] = vr[(int64_t)k * len + j];
+            v1[k] = vr[(int64_t)k * len + j2];
+        }
+#pragma unroll
+        for (int k = 0; k < BC; ++k) {
+            x0[k] = x[c0 * BC + k];
+            x1[k] = x[c1 * BC + k];
+        }
+#pragma unroll
+        for (int k = 0; k < BC; ++k) acc += v0[k] * x0[k];
+        if (j2 != j)
+#pragma unroll
+            for (int k = 0; k < BC; ++k) acc += v1[k] * x1[k];
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) y[row * BR + r] = acc;
+}
+
 constexpr int64_t BSRT_ROWS = 2048;
 template <typename T>
 void bsrt_mv(const DBsrT<T>& R, const T* x, T* y, hipStream_t s) {
     if (R.nr == 0) return;
     const int key = R.br * 10 + R.bc;
-    const bool wide = R.nr < BSRT_ROWS && R.nnzb >= WAVE * R.nr;
-    const unsigned g = (unsigned)(wide ? R.nr : cdiv(R.nr, 4));
-#define BMV(BR, BC)                                                                                   \
-    if (wide) bsrt_mv_k<T, BR, BC, 4><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);                 \
-    else bsrt_mv_k<T, BR, BC, 1><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y)
+    const bool few = R.nr < BSRT_ROWS;
+    const unsigned g = (unsigned)cdiv(R.nr, 4), gr = (unsigned)R.nr;
     switch (key) {
-        case 11: BMV(1, 1); break;
-        case 63: BMV(6, 3); break;
-        case 66: BMV(6, 6); break;
+        case 11:
+            if (few && R.nnzb >= WAVE * R.nr) bsrt_mv_k<T, 1, 1, 4><<<gr, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+            else bsrt_mv_k<T, 1, 1, 1><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+            break;
+        case 63:
+            if (few) bsrt_rows_k<T, 6, 3><<<gr, 6 * WAVE, 0, s>>>(R.rp, R.ci, R.v, x, y);
+            else bsrt_mv_k<T, 6, 3, 1><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+            break;
+        case 66:
+            if (few) bsrt_rows_k<T, 6, 6><<<gr, 6 * WAVE, 0, s>>>(R.rp, R.ci, R.v, x, y);
+            else bsrt_mv_k<T, 6, 6, 1><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+            break;
         default: throw Error(SCR_E_UNIMPLEMENTED, "bsrt_mv: block shape");
     }
-#undef BMV
     check_launch("bsrt_mv");
 }
 template void bsrt_mv<double>(const DBsrT<double>&, const double*, double*, hipStream_t);
