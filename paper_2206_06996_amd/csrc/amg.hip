@@ -97,14 +97,14 @@ void split_blocks(const DBsr& K, DBsr& A, DBsr& G, DBsr& D, DBsr& C, Arena& ar, 
 // the largest last column of the Y rows that it meets), narrow on a mesh whose numbering is local, so LDS
 // holds the row's columns as flags over its window: the distinct columns of a row are its set flags,
 // their number a population count, in ascending order without a sort, and the place of a column in the
-// row a prefix count plus a population count within one word.  Windows of more than SPG_SEG columns are
-// taken SPG_SEG columns at a time, the candidates read again for each.  Against LDS hash tables with a rank
+// row a prefix count plus a population count within one word.  Against LDS hash tables with a rank
 // sort (pattern) and serial read-add-write steps per X entry (numeric), over all products of one set-up at
 // 324k rows: pattern 11.4 -> 8.3 ms, scalar products 9.1 -> 5.1, block products 6.4 -> 7.0; one host
 // synchronisation per product instead of three.  Bound by the latency of the gathers of Y's rows: each
 // wavefront keeps four steps of loads in flight.
+// Rows whose window is wider than a map take hash tables instead, whose cost follows the candidates and not the
+// numbering (SPG_WIN, SPG_SEG).
 constexpr int HMAX = 4096;         // unique columns allowed per row
-constexpr int SPG_SEG = 32768;     // columns of one map
 constexpr int SPG_WIDE = 2048;     // mean candidates per row from which a row takes four wavefronts
 constexpr int SPG_LONG = 24;       // mean length of the Y rows from which one X entry takes a wavefront
 
@@ -214,13 +214,55 @@ __device__ __forceinline__ void spg_steps(int total, int per, F f) {
     else if (total > base) f(base, std::integral_constant<int, 1>{});
 }
 
+// calls f(column) for every candidate of the list, some of them more than once (beyond the list the last
+// candidate again, so that no load waits behind a branch)
+template <typename F>
+__device__ __forceinline__ void spg_columns(const SpgList& list, int lane, const int32_t* __restrict__ yci, F f) {
+    if (list.is_long()) {
+        SpgWalk walk(list);
+        while (walk.more()) {
+            int32_t t[SPG_PASS], c[SPG_PASS];
+            int l;
+            bool in;
+#pragma unroll
+            for (int u = 0; u < SPG_PASS; ++u) {
+                t[u] = u ? t[0] : 0;
+                if (walk.more()) walk.take(lane, l, t[u], in);
+            }
+#pragma unroll
+            for (int u = 0; u < SPG_PASS; ++u) c[u] = yci[t[u]];
+#pragma unroll
+            for (int u = 0; u < SPG_PASS; ++u) f(c[u]);
+        }
+    } else if (list.single()) {
+        if (list.len) f(yci[list.st]);
+    } else {
+        spg_steps(list.total, WAVE, [&](int base, auto steps) {
+            constexpr int U = decltype(steps)::value;
+            int32_t t[U], c[U];
+            int l;
+#pragma unroll
+            for (int u = 0; u < U; ++u) list.get(base + u * WAVE + lane, l, t[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) c[u] = yci[t[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) f(c[u]);
+        });
+    }
+}
+
 // Pattern of row i of X*Y: count (PHASE 0) or columns in ascending order (PHASE 1), NW wavefronts per row
 // (NW = 4 where a row meets thousands of candidates; they take 64 X entries in turn) and 4 / NW rows per
 // workgroup.  The candidates' columns set their flags, a byte each (the same column may be set by many
 // lanes at once: plain byte stores, where bits would need atomics that neighbouring columns serialise:
 // 8.8 -> 6.0 ms over the products of a 324k-row set-up).  PHASE 0 finds the row's window and leaves it in
-// win for PHASE 1; flags of masked rows stay empty.  Dynamic LDS: 4 / NW maps of `seg` bytes.
-constexpr int SPG_PSEG = 8192;     // columns of one map of flags
+// win; flags of masked rows stay empty, and rows whose window exceeds SPG_WIN are left to spg_hash_k.
+// Dynamic LDS: 4 / NW maps of `seg` bytes.
+// SPG_WIN, the columns of one map (four of them in a workgroup's LDS): against every candidate read once per
+// map of the window, set-up of a 324k-row tube renumbered at random 110 -> 52 ms (in layers 41), with rows moved
+// by up to 20,000 places 47.0 -> 43.7, of a Y bifurcation of 892k rows 96.9 -> 92.4; windows of up to two and four
+// maps read so, the rest hashed: shuffled 53.9 and 65.3, the Y 94.3 and 95.8.
+constexpr int SPG_WIN = 8192;
 template <int PHASE, int NW>
 __global__ void __launch_bounds__(256) spg_pattern_k(int64_t nr, int seg, const int32_t* __restrict__ xrp,
                                                      const int32_t* __restrict__ xci, const int32_t* __restrict__ yrp,
@@ -272,89 +314,43 @@ __global__ void __launch_bounds__(256) spg_pattern_k(int64_t nr, int seg, const 
         c0 = win[2 * i];
         n = win[2 * i + 1];
     }
-    // (the workgroup's rows may need different numbers of segments: every thread joins each barrier)
-    if (lane == 0) red[0][w] = n;
+    if (n > SPG_WIN) n = 0;
+    const int words = (n + 3) / 4;
+    for (int t = tid; t < words; t += NT) fw[t] = 0;
     __syncthreads();
-    int most = 0;
-    for (int v = 0; v < 256 / WAVE; ++v) most = red[0][v] > most ? red[0][v] : most;
-    int count = 0;
-    for (int at0 = 0; at0 < most; at0 += seg) {
-        const int32_t s0 = c0 + at0;
-        const int sn = n - at0 < seg ? (n > at0 ? n - at0 : 0) : seg;     // the row's columns of this segment
-        const int sw = (sn + 3) / 4;
-        for (int t = tid; t < sw; t += NT) fw[t] = 0;
-        __syncthreads();
-        if (sn > 0)
-            for (int32_t q0 = x0 + tid / WAVE * WAVE; q0 < x1; q0 += NT) {
-                const SpgList list(q0, x1, lane, xci, yrp);
-                auto mark = [&](int32_t c) {
-                    const unsigned at = (unsigned)(c - s0);
-                    if (at < (unsigned)sn) fb[at] = 1;
-                };
-                if (list.is_long()) {
-                    SpgWalk walk(list);
-                    while (walk.more()) {
-                        int32_t t[SPG_PASS], c[SPG_PASS];
-                        int l;
-                        bool in;
-#pragma unroll
-                        for (int u = 0; u < SPG_PASS; ++u) {
-                            t[u] = u ? t[0] : 0;
-                            if (walk.more()) walk.take(lane, l, t[u], in);
-                        }
-#pragma unroll
-                        for (int u = 0; u < SPG_PASS; ++u) c[u] = yci[t[u]];
-#pragma unroll
-                        for (int u = 0; u < SPG_PASS; ++u) mark(c[u]);
-                    }
-                } else if (list.single()) {
-                    if (list.len) mark(yci[list.st]);
-                } else {
-                    // beyond the list the last candidate again, so that no load waits behind a branch
-                    spg_steps(list.total, WAVE, [&](int base, auto steps) {
-                        constexpr int U = decltype(steps)::value;
-                        int32_t t[U], c[U];
-                        int l;
-#pragma unroll
-                        for (int u = 0; u < U; ++u) list.get(base + u * WAVE + lane, l, t[u]);
-#pragma unroll
-                        for (int u = 0; u < U; ++u) c[u] = yci[t[u]];
-#pragma unroll
-                        for (int u = 0; u < U; ++u) mark(c[u]);
-                    });
-                }
-            }
-        __syncthreads();
-        if (PHASE == 0) {
-            for (int t = tid; t < sw; t += NT) count += __popc(fw[t]);
-        } else if (tid < WAVE && sn > 0) {
-            // one wavefront emits the columns, 16 of the map per lane: a prefix of the lanes' counts
-            int32_t base = crp[i] + count;
-            for (int t0 = 0; t0 < sw; t0 += 4 * WAVE) {
-                uint32_t v[4];
-                int own = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int t = t0 + 4 * lane + u;
-                    v[u] = t < sw ? fw[t] : 0;
-                    own += __popc(v[u]);
-                }
-                int incl = own;
-#pragma unroll
-                for (int o = 1; o < WAVE; o <<= 1) {
-                    const int u = __shfl_up(incl, o, WAVE);
-                    if (lane >= o) incl += u;
-                }
-                int32_t at = base + incl - own;
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    for (uint32_t m = v[u]; m; m &= m - 1) cci[at++] = s0 + (t0 + 4 * lane + u) * 4 + (__builtin_ctz(m) >> 3);
-                const int all = __shfl(incl, WAVE - 1, WAVE);
-                base += all;
-                count += all;
-            }
+    if (n > 0)
+        for (int32_t q0 = x0 + tid / WAVE * WAVE; q0 < x1; q0 += NT) {
+            const SpgList list(q0, x1, lane, xci, yrp);
+            spg_columns(list, lane, yci, [&](int32_t c) { fb[c - c0] = 1; });
         }
-        if (at0 + seg < most) __syncthreads();
+    __syncthreads();
+    int count = 0;
+    if (PHASE == 0) {
+        for (int t = tid; t < words; t += NT) count += __popc(fw[t]);
+    } else if (tid < WAVE && n > 0) {
+        // one wavefront emits the columns, 16 of the map per lane: a prefix of the lanes' counts
+        int32_t base = crp[i];
+        for (int t0 = 0; t0 < words; t0 += 4 * WAVE) {
+            uint32_t v[4];
+            int own = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = t0 + 4 * lane + u;
+                v[u] = t < words ? fw[t] : 0;
+                own += __popc(v[u]);
+            }
+            int incl = own;
+#pragma unroll
+            for (int o = 1; o < WAVE; o <<= 1) {
+                const int u = __shfl_up(incl, o, WAVE);
+                if (lane >= o) incl += u;
+            }
+            int32_t at = base + incl - own;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                for (uint32_t m = v[u]; m; m &= m - 1) cci[at++] = c0 + (t0 + 4 * lane + u) * 4 + (__builtin_ctz(m) >> 3);
+            base += __shfl(incl, WAVE - 1, WAVE);
+        }
     }
     if (PHASE == 0) {
 #pragma unroll
@@ -370,15 +366,97 @@ __global__ void __launch_bounds__(256) spg_pattern_k(int64_t nr, int seg, const 
     }
 }
 
-// numeric phase: lane owns output blocks; accumulates X_iq * Y_kc over q in ascending order
+// The same for the rows whose window exceeds SPG_WIN, NW wavefronts and one workgroup per row: the columns go
+// into a hash table in LDS.  PHASE 0: a table of twice the row's candidates, `hs` slots (a power of two, 512 NW
+// or more) at the most; a row whose columns fill half of those gets cnt = -1 and raises *overflow, and a
+// later pass (retry) with a larger table counts such rows again.  PHASE 1: a table of twice the row's
+// columns, which go to their ranks.  Dynamic LDS: hs slots, in PHASE 1 the longest row's columns after them.
+constexpr int HS_COUNT = 2048;     // first table of PHASE 0 (x4 on each overflow)
+constexpr int HS_MAX = 2 * HMAX;
+__device__ __forceinline__ unsigned hash_slot(int key, int hs) { return ((unsigned)key * 2654435761u) & (unsigned)(hs - 1); }
+// true if newly inserted (a table that is never full)
+__device__ __forceinline__ bool hash_insert(int* t, int hs, int key) {
+    unsigned h = hash_slot(key, hs);
+    for (;;) {
+        const int prev = atomicCAS(&t[h], -1, key);
+        if (prev == -1) return true;
+        if (prev == key) return false;
+        h = (h + 1) & (unsigned)(hs - 1);
+    }
+}
+template <int PHASE, int NW>
+__global__ void __launch_bounds__(NW * WAVE) spg_hash_k(int64_t nr, int hs, int retry, const int32_t* __restrict__ xrp,
+                                                        const int32_t* __restrict__ xci, const int32_t* __restrict__ yrp,
+                                                        const int32_t* __restrict__ yci, const int32_t* __restrict__ win,
+                                                        int32_t* __restrict__ cnt, const int32_t* __restrict__ crp,
+                                                        int32_t* __restrict__ cci, int* __restrict__ overflow) {
+    extern __shared__ int table[];
+    __shared__ unsigned long long cand;     // candidates of the row
+    __shared__ int nuniq;
+    constexpr int NT = NW * WAVE;
+    const int64_t i = blockIdx.x;
+    if (i >= nr || win[2 * i + 1] <= SPG_WIN || (PHASE == 0 && retry && cnt[i] >= 0)) return;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int32_t x0 = xrp[i], x1 = xrp[i + 1];
+    if (tid == 0) { cand = 0; nuniq = 0; }
+    __syncthreads();
+    uint64_t want;
+    if (PHASE == 0) {
+        uint64_t own = 0;
+        for (int32_t q = x0 + tid; q < x1; q += NT) {
+            const int32_t k = xci[q];
+            own += (uint64_t)(yrp[k + 1] - yrp[k]);
+        }
+        own = wave_sum(own);
+        if (lane == 0) atomicAdd(&cand, (unsigned long long)own);
+        __syncthreads();
+        want = 2 * cand;
+    } else {
+        want = 2 * (uint64_t)(crp[i + 1] - crp[i]);
+    }
+    int size = WAVE;
+    while (size < hs && (uint64_t)size < want) size <<= 1;
+    // half a table at the most, plus what the wavefronts insert between two looks at the number
+    const int limit = PHASE == 0 && (uint64_t)size < want ? size / 2 : INT32_MAX;
+    int32_t* cols = table + hs;
+    for (int t = tid; t < size; t += NT) table[t] = -1;
+    __syncthreads();
+    for (int32_t q0 = x0 + tid / WAVE * WAVE; q0 < x1; q0 += NT) {
+        const SpgList list(q0, x1, lane, xci, yrp);
+        spg_columns(list, lane, yci, [&](int32_t c) {
+            if (*(volatile int*)&nuniq >= limit) return;
+            if (!hash_insert(table, size, c)) return;
+            const int at = atomicAdd(&nuniq, 1);
+            if (PHASE == 1) cols[at] = c;
+        });
+    }
+    __syncthreads();
+    const int w = nuniq;
+    if (PHASE == 0) {
+        if (tid == 0) {
+            cnt[i] = w < limit ? w : -1;
+            if (w >= limit) atomicOr(overflow, 1);
+        }
+    } else {
+        for (int a = tid; a < w; a += NT) {
+            const int key = cols[a];
+            int rank = 0;
+            for (int b = 0; b < w; ++b) rank += cols[b] < key;
+            cci[crp[i] + rank] = key;
+        }
+    }
+}
+
+// numeric phase of the rows whose columns span more than `above`: lane owns output blocks; accumulates
+// X_iq * Y_kc over q in ascending order
 template <int M, int N, int P>
-__global__ void __launch_bounds__(256) spg_numeric(int64_t nr, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci,
-                                                   const double* __restrict__ xv, const int32_t* __restrict__ yrp,
+__global__ void __launch_bounds__(256) spg_numeric(int64_t nr, int above, const int32_t* __restrict__ xrp,
+                                                   const int32_t* __restrict__ xci, const double* __restrict__ xv, const int32_t* __restrict__ yrp,
                                                    const int32_t* __restrict__ yci, const double* __restrict__ yv,
                                                    const int32_t* __restrict__ crp, const int32_t* __restrict__ cci,
                                                    double* __restrict__ cv) {
     int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
-    if (i >= nr) return;
+    if (i >= nr || crp[i + 1] <= crp[i] || cci[crp[i + 1] - 1] - cci[crp[i]] < above) return;
     int lane = threadIdx.x & (WAVE - 1);
     for (int32_t p = crp[i] + lane; p < crp[i + 1]; p += WAVE) {
         int32_t c = cci[p];
@@ -407,11 +485,12 @@ __global__ void __launch_bounds__(256) spg_numeric(int64_t nr, const int32_t* __
 // order, and products are added to their sums by LDS atomics without return, one X entry per instruction
 // (its Y row has distinct columns; spg_add_in_order); LDS serves a wavefront's instructions in order.
 // Nothing waits for a sum, so the loads of SPG_PASS passes are in flight.
-// The row's columns as {bits, columns before the word} of each 32 columns of the window (or of a segment of
-// it, see SPG_SEG): a column's place is one 8-byte LDS read and a population count.
+// The row's columns as {bits, columns before the word} of each 32 columns of the window: a column's place is
+// one 8-byte LDS read and a population count.  Rows that span more than SPG_SEG columns: a hash table.
+constexpr int SPG_SEG = 32768;
 struct SpgWord { uint32_t bits; int32_t before; };
-// fills map[0 .. ceil(sn / 32)) for the columns [s0, s0 + sn) of cci[lo, hi) (the NT threads of a workgroup);
-// returns the columns up to the segment's end on the first wavefront
+// fills map[0 .. ceil(sn / 32)) for the columns [s0, s0 + sn) of cci[lo, hi), `before` of which come before s0
+// (the NT threads of a workgroup); returns the columns up to the segment's end on the first wavefront
 template <int NT = WAVE>
 __device__ __forceinline__ int spg_map(SpgWord* map, int32_t s0, int sn, const int32_t* __restrict__ cci, int32_t lo,
                                         int32_t hi, int before, int tid) {
@@ -438,14 +517,52 @@ __device__ __forceinline__ int spg_map(SpgWord* map, int32_t s0, int sn, const i
     __syncthreads();
     return before;
 }
-// place of column c of the segment in the row, -1 if it lies outside the segment (every column met inside it
-// is in the pattern)
+// place of column c in the row, -1 if it lies outside [s0, s0 + sn) (c is one of the row's columns)
 __device__ __forceinline__ int spg_place(const SpgWord* map, int32_t s0, int sn, int32_t c) {
     const unsigned at = (unsigned)(c - s0);
     const bool in = at < (unsigned)sn;
     const SpgWord w = map[in ? at >> 5 : 0];
     return in ? w.before + __popc(w.bits & ((1u << (at & 31)) - 1)) : -1;
 }
+// the places of the columns of cci[lo, hi) in one form or the other; table: a power of two of slots, twice the
+// columns or more (its words hold {column, place})
+template <bool HASH, int NT>
+struct SpgPlaces {
+    SpgWord* map;
+    int32_t c0;
+    int n;       // columns spanned, or slots
+    __device__ __forceinline__ SpgPlaces(SpgWord* m, const int32_t* __restrict__ cci, int32_t lo, int32_t hi, int tid) : map(m) {
+        if constexpr (HASH) {
+            for (n = WAVE; n < 2 * (hi - lo); n <<= 1) {}
+            for (int t = tid; t < n; t += NT) map[t].bits = ~0u;
+            __syncthreads();
+            for (int32_t p = lo + tid; p < hi; p += NT) {
+                const int c = cci[p];
+                unsigned h = hash_slot(c, n);
+                while (atomicCAS(&map[h].bits, ~0u, (uint32_t)c) != ~0u) h = (h + 1) & (unsigned)(n - 1);
+                map[h].before = p - lo;
+            }
+            __syncthreads();
+        } else {
+            c0 = cci[lo];
+            n = cci[hi - 1] - c0 + 1;
+            spg_map<NT>(map, c0, n, cci, lo, hi, 0, tid);
+        }
+    }
+    __device__ __forceinline__ int operator()(int32_t c) const {
+        if constexpr (HASH) {
+            unsigned h = hash_slot(c, n);
+            for (;;) {
+                const SpgWord w = map[h];
+                if (w.bits == (uint32_t)c) return w.before;
+                if (w.bits == ~0u) return -1;      // not reached: every column met is in the pattern
+                h = (h + 1) & (unsigned)(n - 1);
+            }
+        } else {
+            return spg_place(map, c0, n, c);
+        }
+    }
+};
 __device__ __forceinline__ void spg_add(double* p, double v) {
     (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
@@ -461,9 +578,9 @@ __device__ __forceinline__ void spg_add_in_order(double* sums, int p, double v, 
     }
 }
 
-// scalar rows of C (M = P = 1, inner dimension N), one wavefront per row.  Dynamic LDS: wmax sums, then the
-// map.
-template <int N>
+// scalar rows of C (M = P = 1, inner dimension N), one wavefront per row; the rows that span more than SPG_SEG
+// columns (HASH) or the others.  Dynamic LDS: wmax sums, then the map or table.
+template <int N, bool HASH>
 __global__ void __launch_bounds__(WAVE) spg_scalar_k(int64_t nr, int wmax, const int32_t* __restrict__ xrp,
                                                      const int32_t* __restrict__ xci, const double* __restrict__ xv,
                                                      const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
@@ -476,94 +593,89 @@ __global__ void __launch_bounds__(WAVE) spg_scalar_k(int64_t nr, int wmax, const
     const int lane = threadIdx.x;
     const int32_t lo = crp[i], hi = crp[i + 1];
     if (hi <= lo) return;
+    if ((cci[hi - 1] - cci[lo] >= SPG_SEG) != HASH) return;
     for (int p = lane; p < hi - lo; p += WAVE) sums[p] = 0.0;
-    const int32_t c0 = cci[lo];
-    const int n = cci[hi - 1] - c0 + 1;
     const int32_t x0 = xrp[i], x1 = xrp[i + 1];
-    for (int seg = 0; seg < n; seg += SPG_SEG) {
-        const int32_t s0 = c0 + seg;
-        const int sn = n - seg < SPG_SEG ? n - seg : SPG_SEG;
-        spg_map(map, s0, sn, cci, lo, hi, seg == 0 ? 0 : lower_col(cci, lo, hi, s0) - lo, lane);
-        for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
-            double x[N];
+    const SpgPlaces<HASH, WAVE> place(map, cci, lo, hi, lane);
+    for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
+        double x[N];
 #pragma unroll
-            for (int k = 0; k < N; ++k) x[k] = q0 + lane < x1 ? xv[(int64_t)(q0 + lane) * N + k] : 0.0;
-            const SpgList list(q0, x1, lane, xci, yrp);
-            if (list.is_long()) {
-                SpgWalk walk(list);
-                while (walk.more()) {
-                    int l[SPG_PASS];
-                    int32_t t[SPG_PASS], c[SPG_PASS];
-                    bool in[SPG_PASS];
-                    double y[SPG_PASS][N];
+        for (int k = 0; k < N; ++k) x[k] = q0 + lane < x1 ? xv[(int64_t)(q0 + lane) * N + k] : 0.0;
+        const SpgList list(q0, x1, lane, xci, yrp);
+        if (list.is_long()) {
+            SpgWalk walk(list);
+            while (walk.more()) {
+                int l[SPG_PASS];
+                int32_t t[SPG_PASS], c[SPG_PASS];
+                bool in[SPG_PASS];
+                double y[SPG_PASS][N];
 #pragma unroll
-                    for (int u = 0; u < SPG_PASS; ++u) {
-                        l[u] = 0;
-                        t[u] = u ? t[0] : 0;
-                        in[u] = false;
-                        if (walk.more()) walk.take(lane, l[u], t[u], in[u]);
-                    }
-#pragma unroll
-                    for (int u = 0; u < SPG_PASS; ++u) {
-                        c[u] = yci[t[u]];
-#pragma unroll
-                        for (int k = 0; k < N; ++k) y[u][k] = yv[(int64_t)t[u] * N + k];
-                    }
-#pragma unroll
-                    for (int u = 0; u < SPG_PASS; ++u) {
-                        double sum = 0.0;
-#pragma unroll
-                        for (int k = 0; k < N; ++k) sum += __shfl(x[k], l[u], WAVE) * y[u][k];
-                        const int p = spg_place(map, s0, sn, c[u]);
-                        if (in[u] && p >= 0) spg_add(sums + p, sum);
-                        __builtin_amdgcn_wave_barrier();
-                    }
+                for (int u = 0; u < SPG_PASS; ++u) {
+                    l[u] = 0;
+                    t[u] = u ? t[0] : 0;
+                    in[u] = false;
+                    if (walk.more()) walk.take(lane, l[u], t[u], in[u]);
                 }
-            } else if (list.single()) {
-                const bool in = list.len != 0;
-                const int32_t t = in ? list.st : 0;
-                const int32_t c = yci[t];
-                double sum = 0.0;
 #pragma unroll
-                for (int k = 0; k < N; ++k) sum += x[k] * yv[(int64_t)t * N + k];
-                spg_add_in_order(sums, in ? spg_place(map, s0, sn, c) : -1, sum, lane);
-            } else {
-                spg_steps(list.total, WAVE, [&](int base, auto steps) {
-                    constexpr int U = decltype(steps)::value;
-                    int l[U];
-                    int32_t t[U], c[U];
-                    double y[U][N];
+                for (int u = 0; u < SPG_PASS; ++u) {
+                    c[u] = yci[t[u]];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) list.get(base + u * WAVE + lane, l[u], t[u]);
+                    for (int k = 0; k < N; ++k) y[u][k] = yv[(int64_t)t[u] * N + k];
+                }
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        c[u] = yci[t[u]];
+                for (int u = 0; u < SPG_PASS; ++u) {
+                    double sum = 0.0;
 #pragma unroll
-                        for (int k = 0; k < N; ++k) y[u][k] = yv[(int64_t)t[u] * N + k];
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        double sum = 0.0;
-#pragma unroll
-                        for (int k = 0; k < N; ++k) sum += __shfl(x[k], l[u], WAVE) * y[u][k];
-                        const bool in = base + u * WAVE + lane < list.total;
-                        spg_add_in_order(sums, in ? spg_place(map, s0, sn, c[u]) : -1, sum, l[u]);
-                    }
-                });
+                    for (int k = 0; k < N; ++k) sum += __shfl(x[k], l[u], WAVE) * y[u][k];
+                    const int p = place(c[u]);
+                    if (in[u] && p >= 0) spg_add(sums + p, sum);
+                    __builtin_amdgcn_wave_barrier();
+                }
             }
+        } else if (list.single()) {
+            const bool in = list.len != 0;
+            const int32_t t = in ? list.st : 0;
+            const int32_t c = yci[t];
+            double sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < N; ++k) sum += x[k] * yv[(int64_t)t * N + k];
+            spg_add_in_order(sums, in ? place(c) : -1, sum, lane);
+        } else {
+            spg_steps(list.total, WAVE, [&](int base, auto steps) {
+                constexpr int U = decltype(steps)::value;
+                int l[U];
+                int32_t t[U], c[U];
+                double y[U][N];
+#pragma unroll
+                for (int u = 0; u < U; ++u) list.get(base + u * WAVE + lane, l[u], t[u]);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    c[u] = yci[t[u]];
+#pragma unroll
+                    for (int k = 0; k < N; ++k) y[u][k] = yv[(int64_t)t[u] * N + k];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    double sum = 0.0;
+#pragma unroll
+                    for (int k = 0; k < N; ++k) sum += __shfl(x[k], l[u], WAVE) * y[u][k];
+                    const bool in = base + u * WAVE + lane < list.total;
+                    spg_add_in_order(sums, in ? place(c[u]) : -1, sum, l[u]);
+                }
+            });
         }
-        __syncthreads();
     }
+    __syncthreads();
     for (int p = lane; p < hi - lo; p += WAVE) cv[lo + p] = sums[p];
 }
 
 // block rows (M x P blocks of C, inner dimension N), MP / 9 wavefronts per row: each owns 9 entries of every
 // block, so that each sum has one owner and the sums in LDS (18 or 36 doubles per block
 // column, which bound the rows in flight) serve 2 or 4 wavefronts; a pass takes 7 candidates, one lane
-// per entry.  Dynamic LDS: wmax * M * P sums, then the map.
+// per entry.  Rows and dynamic LDS as above (wmax * M * P sums).
 constexpr int SPG_E = 9;
 struct SpgCand { int32_t t, lp; };     // Y index; X entry (bits 24-29) and place in the row (bits 0-23)
-template <int M, int N, int P>
+template <int M, int N, int P, bool HASH>
 __global__ void __launch_bounds__(M* P / SPG_E* WAVE)
     spg_block_k(int64_t nr, int wmax, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci,
                 const double* __restrict__ xv, const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
@@ -578,93 +690,97 @@ __global__ void __launch_bounds__(M* P / SPG_E* WAVE)
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int32_t lo = crp[i], hi = crp[i + 1];
     if (hi <= lo) return;
+    if ((cci[hi - 1] - cci[lo] >= SPG_SEG) != HASH) return;
     for (int p = tid; p < (hi - lo) * MP; p += NT) sums[p] = 0.0;
-    const int32_t c0 = cci[lo];
-    const int n = cci[hi - 1] - c0 + 1;
     const int32_t x0 = xrp[i], x1 = xrp[i + 1];
     const int slot = lane / E;                  // lane 63 holds no candidate (slot 7)
     const int en = w * E + lane % E, r = en / P, cc = en % P;
-    for (int seg = 0; seg < n; seg += SPG_SEG) {
-        const int32_t s0 = c0 + seg;
-        const int sn = n - seg < SPG_SEG ? n - seg : SPG_SEG;
-        spg_map<NT>(map, s0, sn, cci, lo, hi, seg == 0 ? 0 : lower_col(cci, lo, hi, s0) - lo, tid);
-        for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
-            const SpgList list(q0, x1, lane, xci, yrp);
-            for (int base = 0; base < list.total; base += NT) {
-                // a batch: each thread finds one candidate and its place, for the wavefronts to share
-                int l;
-                int32_t t;
-                list.get(base + tid, l, t);
-                const int32_t col = yci[t];
-                __syncthreads();
-                batch[tid].t = t;
-                batch[tid].lp = base + tid < list.total ? (l << 24 | (spg_place(map, s0, sn, col) & 0xffffff)) : -1;
-                __syncthreads();
-                const int left = list.total - base < NT ? list.total - base : NT;
-                spg_steps(left, CPP, [&](int b0, auto steps) {
-                    constexpr int U = decltype(steps)::value;
-                    int lu[U], p[U];
-                    double x[U][N], y[U][N];
+    const SpgPlaces<HASH, NT> place(map, cci, lo, hi, tid);
+    for (int32_t q0 = x0; q0 < x1; q0 += WAVE) {
+        const SpgList list(q0, x1, lane, xci, yrp);
+        for (int base = 0; base < list.total; base += NT) {
+            // a batch: each thread finds one candidate and its place, for the wavefronts to share
+            int l;
+            int32_t t;
+            list.get(base + tid, l, t);
+            const int32_t col = yci[t];
+            __syncthreads();
+            batch[tid].t = t;
+            batch[tid].lp = base + tid < list.total ? (l << 24 | (place(col) & 0xffffff)) : -1;
+            __syncthreads();
+            const int left = list.total - base < NT ? list.total - base : NT;
+            spg_steps(left, CPP, [&](int b0, auto steps) {
+                constexpr int U = decltype(steps)::value;
+                int lu[U], p[U];
+                double x[U][N], y[U][N];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int at = b0 + u * CPP + slot;
-                        const bool in = slot < CPP && at < left;
-                        const SpgCand c = batch[in ? at : b0];
-                        lu[u] = (c.lp >> 24) & 63;
-                        p[u] = in ? (c.lp << 8) >> 8 : -1;      // -1: outside the segment
+                for (int u = 0; u < U; ++u) {
+                    const int at = b0 + u * CPP + slot;
+                    const bool in = slot < CPP && at < left;
+                    const SpgCand c = batch[in ? at : b0];
+                    lu[u] = (c.lp >> 24) & 63;
+                    p[u] = in ? (c.lp << 8) >> 8 : -1;
 #pragma unroll
-                        for (int k = 0; k < N; ++k) {
-                            x[u][k] = xv[((int64_t)(q0 + lu[u]) * M + r) * N + k];
-                            y[u][k] = yv[((int64_t)c.t * N + k) * P + cc];
-                        }
+                    for (int k = 0; k < N; ++k) {
+                        x[u][k] = xv[((int64_t)(q0 + lu[u]) * M + r) * N + k];
+                        y[u][k] = yv[((int64_t)c.t * N + k) * P + cc];
                     }
+                }
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        double sum = 0.0;
+                for (int u = 0; u < U; ++u) {
+                    double sum = 0.0;
 #pragma unroll
-                        for (int k = 0; k < N; ++k) sum += x[u][k] * y[u][k];
-                        spg_add_in_order(sums, p[u] >= 0 ? p[u] * MP + en : -1, sum, lu[u]);
-                    }
-                });
-            }
+                    for (int k = 0; k < N; ++k) sum += x[u][k] * y[u][k];
+                    spg_add_in_order(sums, p[u] >= 0 ? p[u] * MP + en : -1, sum, lu[u]);
+                }
+            });
         }
-        __syncthreads();
     }
+    __syncthreads();
     for (int p = tid; p < (hi - lo) * MP; p += NT) cv[(int64_t)lo * MP + p] = sums[p];
 }
 
-// numeric phase of C = X Y into C's pattern: the sums in LDS when the widest row's fit, else the pull form
+// numeric phase of C = X Y into C's pattern: the sums in LDS where the longest row's fit, else the pull form;
+// rows that span more than SPG_SEG columns apart (SPG_LDS: two workgroups a CU)
+constexpr size_t SPG_LDS = 68 * 1024;
 static void spgemm_numeric(const DBsr& X, const DBsr& Y, DBsr& C, hipStream_t s) {
     if (X.nr <= 0) return;
     const int key = X.br * 100 + X.bc * 10 + Y.bc;
-    const int words = (std::min(C.wmax_cols, SPG_SEG) + 31) / 32;
-    const size_t lds = (size_t)C.wmax * C.br * C.bc * sizeof(double) + (size_t)words * sizeof(SpgWord);
+    const size_t sums = (size_t)C.wmax * C.br * C.bc * sizeof(double);
+    const bool wide = C.wmax_cols > SPG_SEG;
+    const size_t lds = sums + (size_t)(std::min(C.wmax_cols, SPG_SEG) + 31) / 32 * sizeof(SpgWord);
+    size_t slots = WAVE;
+    while (slots < 2 * (size_t)C.wmax) slots <<= 1;
+    const size_t ldsh = sums + slots * sizeof(SpgWord);
+    const size_t most = SPG_LDS - (C.br * C.bc > 1 ? C.br * C.bc / SPG_E * WAVE * sizeof(SpgCand) : 0);
+    const bool map = lds <= most, hash = map && wide && ldsh <= most, pull = !map || (wide && !hash);
     const unsigned nb = (unsigned)cdiv(X.nr, 4);
-    if (lds <= 64 * 1024) {
-#define SPS(n) spg_scalar_k<n><<<(unsigned)X.nr, WAVE, lds, s>>>(X.nr, C.wmax, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v)
-#define SPB(m, n, p) spg_block_k<m, n, p><<<(unsigned)X.nr, m * p / SPG_E * WAVE, lds, s>>>(X.nr, C.wmax, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v)
-        switch (key) {
-            case 111: SPS(1); break;
-            case 131: SPS(3); break;
-            case 336: SPB(3, 3, 6); break;
-            case 636: SPB(6, 3, 6); break;
-            case 666: SPB(6, 6, 6); break;
-            default: throw Error(SCR_E_UNIMPLEMENTED, "spgemm block shape " + std::to_string(key));
-        }
+    const int above = map ? SPG_SEG : 0;
+#define SPG_ARGS X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v
+#define SPS(n)                                                                                                  \
+    {                                                                                                           \
+        if (map) spg_scalar_k<n, false><<<(unsigned)X.nr, WAVE, lds, s>>>(X.nr, C.wmax, SPG_ARGS);              \
+        if (hash) spg_scalar_k<n, true><<<(unsigned)X.nr, WAVE, ldsh, s>>>(X.nr, C.wmax, SPG_ARGS);             \
+        if (pull) spg_numeric<1, n, 1><<<nb, 256, 0, s>>>(X.nr, above, SPG_ARGS);                               \
+    }
+#define SPB(m, n, p)                                                                                            \
+    {                                                                                                           \
+        constexpr int T = m * p / SPG_E * WAVE;                                                                 \
+        if (map) spg_block_k<m, n, p, false><<<(unsigned)X.nr, T, lds, s>>>(X.nr, C.wmax, SPG_ARGS);            \
+        if (hash) spg_block_k<m, n, p, true><<<(unsigned)X.nr, T, ldsh, s>>>(X.nr, C.wmax, SPG_ARGS);           \
+        if (pull) spg_numeric<m, n, p><<<nb, 256, 0, s>>>(X.nr, above, SPG_ARGS);                               \
+    }
+    switch (key) {
+        case 111: SPS(1) break;
+        case 131: SPS(3) break;
+        case 336: SPB(3, 3, 6) break;
+        case 636: SPB(6, 3, 6) break;
+        case 666: SPB(6, 6, 6) break;
+        default: throw Error(SCR_E_UNIMPLEMENTED, "spgemm block shape " + std::to_string(key));
+    }
 #undef SPS
 #undef SPB
-    } else {
-#define SPN(m, n, p) spg_numeric<m, n, p><<<nb, 256, 0, s>>>(X.nr, X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v)
-        switch (key) {
-            case 111: SPN(1, 1, 1); break;
-            case 131: SPN(1, 3, 1); break;
-            case 336: SPN(3, 3, 6); break;
-            case 636: SPN(6, 3, 6); break;
-            case 666: SPN(6, 6, 6); break;
-            default: throw Error(SCR_E_UNIMPLEMENTED, "spgemm block shape " + std::to_string(key));
-        }
-#undef SPN
-    }
+#undef SPG_ARGS
     check_launch("spg_numeric");
 }
 
@@ -674,14 +790,14 @@ DBsr spgemm(const DBsr& X, const DBsr& Y, const uint8_t* rowmask, Arena& ar, hip
     C.rp = ar.make<int32_t>(X.nr + 1);
     int32_t* cnt = ar.make<int32_t>(X.nr + 1);
     int32_t* win = ar.make<int32_t>(2 * X.nr + 1);
-    struct Head { int maxwin, wmax; };     // widest window, longest row
+    struct Head { int maxwin, wmax, overflow; };     // widest window, longest row
     Head* head = ar.make<Head>(1);
     Head h{};
     zero_dev(head, sizeof(Head), s);
     // rows that meet SPG_WIDE candidates or more (by the mean lengths of both factors) take four wavefronts
     const bool wide = X.nr > 0 && Y.nr > 0 &&
                       (double)X.nnzb * (double)Y.nnzb >= (double)SPG_WIDE * (double)X.nr * (double)Y.nr;
-    const int seg = (int)(std::min<int64_t>(Y.nc > 0 ? Y.nc : 1, SPG_PSEG) + 3) / 4 * 4;
+    const int seg = (int)(std::min<int64_t>(Y.nc > 0 ? Y.nc : 1, SPG_WIN) + 3) / 4 * 4;
     const unsigned grid = (unsigned)cdiv(X.nr, wide ? 1 : 4);
     const size_t lds = (size_t)seg * (wide ? 1 : 4);
 #define SPP(ph)                                                                                                    \
@@ -691,20 +807,50 @@ DBsr spgemm(const DBsr& X, const DBsr& Y, const uint8_t* rowmask, Arena& ar, hip
     else if (X.nr > 0)                                                                                             \
         spg_pattern_k<ph, 1><<<grid, 256, lds, s>>>(X.nr, seg, X.rp, X.ci, Y.rp, Y.ci, rowmask, win, cnt,          \
                                                     C.rp, C.ci)
+#define SPH(ph, lds, hs, retry)                                                                                    \
+    if (wide)                                                                                                      \
+        spg_hash_k<ph, 4><<<(unsigned)X.nr, 4 * WAVE, lds, s>>>(X.nr, hs, retry, X.rp, X.ci, Y.rp, Y.ci, win, cnt, \
+                                                               C.rp, C.ci, &head->overflow);                       \
+    else                                                                                                           \
+        spg_hash_k<ph, 1><<<(unsigned)X.nr, WAVE, lds, s>>>(X.nr, hs, retry, X.rp, X.ci, Y.rp, Y.ci, win, cnt,     \
+                                                            C.rp, C.ci, &head->overflow)
+    auto totals = [&]() {      // C.rp, C.nnzb and h from the counts
+        if (X.nr > 0)
+            spg_max_k<<<(unsigned)std::min<int64_t>(cdiv(X.nr, 256), 256), 256, 0, s>>>(X.nr, cnt, win, &head->wmax,
+                                                                                        &head->maxwin);
+        check_launch("spg_count");
+        HIPCHK(hipMemcpyAsync(&h, head, sizeof(Head), hipMemcpyDeviceToHost, s));
+        C.nnzb = scan_i32(cnt, C.rp, X.nr, ar, s);      // synchronises
+    };
     SPP(0);
-    if (X.nr > 0)
-        spg_max_k<<<(unsigned)std::min<int64_t>(cdiv(X.nr, 256), 256), 256, 0, s>>>(X.nr, cnt, win, &head->wmax,
-                                                                                    &head->maxwin);
-    check_launch("spg_count");
-    HIPCHK(hipMemcpyAsync(&h, head, sizeof(Head), hipMemcpyDeviceToHost, s));
-    C.nnzb = scan_i32(cnt, C.rp, X.nr, ar, s);      // synchronises
+    totals();
+    const bool far = h.maxwin > SPG_WIN;
+    if (far) {
+        // the counts of the rows that the pattern kernel left
+        for (int hs = HS_COUNT, retry = 0;; hs *= 4, retry = 1) {
+            SPH(0, (size_t)hs * sizeof(int), hs, retry);
+            check_launch("spg_hash");
+            HIPCHK(hipMemcpyAsync(&h, head, sizeof(Head), hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+            if (!h.overflow) break;
+            if (hs >= HS_MAX) throw Error(SCR_E_INVALID, "Galerkin product row wider than " + std::to_string(HMAX) + " blocks");
+            zero_dev(&head->overflow, sizeof(int), s);
+        }
+        totals();
+    }
     if (h.wmax >= HMAX) throw Error(SCR_E_INVALID, "Galerkin product row wider than " + std::to_string(HMAX) + " blocks");
     C.wmax = h.wmax;
     C.wmax_cols = h.maxwin;
     C.ci = ar.make<int32_t>(C.nnzb > 0 ? C.nnzb : 1);
     C.v = ar.make<double>((C.nnzb > 0 ? C.nnzb : 1) * C.br * C.bc);
     SPP(1);
+    if (far) {
+        int hs = WAVE;
+        while (hs < 2 * h.wmax) hs <<= 1;
+        SPH(1, (size_t)(hs + h.wmax) * sizeof(int), hs, 0);
+    }
 #undef SPP
+#undef SPH
     check_launch("spg_fill");
     ar.free(cnt); ar.free(win); ar.free(head);
     spgemm_numeric(X, Y, C, s);
@@ -1394,8 +1540,10 @@ __global__ void tr_fill_k(int64_t nr, const int32_t* __restrict__ rp, const int3
 }
 // the entries of each transposed row in ascending order (source rows are unique within a row): a wavefront per
 // row, the place of an entry from the prefix counts of a map of the row's keys (TR_SEG keys of its window at
-// a time), as in the products above; rows of a thousand entries cost no more per entry than short ones
+// a time), as in the products above; rows of a thousand entries cost no more per entry than short ones.  A short
+// row of a wide window counts the smaller keys of each entry instead: its work does not depend on the numbering.
 constexpr int TR_SEG = 8192;
+constexpr int TR_PAIRS = 512;     // comparisons of a wavefront in about the time that a segment of the map takes
 __global__ void __launch_bounds__(WAVE) tr_sort_k(int64_t ntr, const int32_t* __restrict__ trp, const int32_t* __restrict__ tci,
                                                   const int32_t* __restrict__ src, int32_t* __restrict__ oci,
                                                   int32_t* __restrict__ osrc) {
@@ -1416,6 +1564,17 @@ __global__ void __launch_bounds__(WAVE) tr_sort_k(int64_t ntr, const int32_t* __
         const int a = __shfl_xor(k0, o, WAVE), b = __shfl_xor(k1, o, WAVE);
         k0 = a < k0 ? a : k0;
         k1 = b > k1 ? b : k1;
+    }
+    const int len = hi - lo;
+    if (k1 - k0 >= TR_SEG && (int64_t)len * ((len + WAVE - 1) / WAVE) <= TR_PAIRS * ((int64_t)(k1 - k0) / TR_SEG + 1)) {
+        for (int32_t p = lo + lane; p < hi; p += WAVE) {
+            const int32_t k = tci[p];
+            int rank = 0;
+            for (int32_t u = lo; u < hi; ++u) rank += tci[u] < k;
+            oci[lo + rank] = k;
+            osrc[lo + rank] = src[p];
+        }
+        return;
     }
     int before = 0;
     for (int64_t s0 = k0; s0 <= k1; s0 += TR_SEG) {

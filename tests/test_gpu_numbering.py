@@ -1,0 +1,162 @@
+"""Set-up on numberings that are not local.  A row of a set-up product whose columns span more than one map of
+flags (8,192 columns) or of places (32,768) takes hash tables, and a transposed row in that case counts smaller
+keys, so the time follows the matrix and not the order of its rows."""
+import time
+
+import numpy as np
+import pytest
+import scipy.sparse as sps
+
+import synth
+from tests.test_gpu_parity import _grid_with_hubs, _product_in_x_order
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def scr():
+    import paper_2206_06996_amd.scr as m
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(scr):
+    c = scr.Context(0)
+    yield c
+    c.destroy()
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def test_setup_time_does_not_follow_the_numbering(scr, ctx):
+    """A tube of 320,000 rows in layers, and the same renumbered at random: windows of 40 maps.  Once per map
+    every candidate would be read 40 times (2.6 times the layered set-up); read once, the shuffled gathers
+    leave 1.1 to 1.3 times."""
+    s = synth.generate(synth.tube_params(300e3, 1.0, 10.0))
+    n = s.n_b
+    rp, ci, val, xyz = dev(s.rp), dev(s.ci), dev(s.val.reshape(-1, 16)), dev(s.xyz)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    new = torch.randperm(n, generator=g, device="cuda")
+    rows = torch.repeat_interleave(torch.arange(n, device="cuda"), (rp[1:] - rp[:-1]).long())
+    key, order = torch.sort(new[rows] * n + new[ci.long()])
+    rp2 = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp2[1:] = torch.cumsum(torch.bincount(key // n, minlength=n), 0)
+    xyz2 = torch.empty_like(xyz)
+    xyz2[new] = xyz
+    systems = [(rp, ci, val.reshape(-1), xyz), (rp2, (key % n).int(), val[order].reshape(-1).contiguous(), xyz2)]
+    best = [1e9, 1e9]
+    print(f"[gpu] set-ups n_b={n}", flush=True)
+    for _ in range(4):
+        for k, args in enumerate(systems):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            h = scr.amg_setup(ctx, scr.SCR_SYSTEM, *args)
+            torch.cuda.synchronize()
+            best[k] = min(best[k], time.perf_counter() - t)
+            h.destroy()
+    print(f"[gpu] layered {1e3 * best[0]:.1f} ms, shuffled {1e3 * best[1]:.1f} ms", flush=True)
+    assert best[1] <= 1.7 * best[0]
+
+
+def test_products_over_wide_windows_bitwise(scr, ctx):
+    """A shuffled grid of 640 x 640 nodes with hub rows: more than 32,768 aggregates, so every product of level 0
+    takes hash tables in both phases, and the hub rows of A P (more than 1,024 columns) overflow the first one.
+    Equal bit for bit to the products in row order, on the structural patterns; R = P^T."""
+    A = _grid_with_hubs(n=640, hubs=3, stride=800, spread=True).tocoo()
+    n = A.shape[0]
+    new = np.random.default_rng(5).permutation(n)
+    A = sps.csr_matrix((A.data, (new[A.row], new[A.col])), shape=(n, n))
+    A.sort_indices()
+    rp, ci, v = A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data.astype(np.float64)
+    print(f"[gpu] shuffled grid n={n} nnz={A.nnz}", flush=True)
+    h = scr.amg_setup(ctx, scr.MESH_SYSTEM, dev(rp), dev(ci), dev(v), None, scr.amg_opts())
+    na = h.hier_level_info(2, 0)["nagg"]
+    assert na > 32768
+
+    def g(f, l=0):
+        return h.hier_level_copy(2, l, f)
+    P, R = (g("P.rp"), g("P.ci"), g("P.v")), (g("R.rp"), g("R.ci"), g("R.v"))
+    Pt = sps.csr_matrix((P[2].reshape(-1), P[1], P[0]), shape=(n, na)).T.tocsr()
+    Pt.sort_indices()
+    assert np.array_equal(R[0], Pt.indptr) and np.array_equal(R[1], Pt.indices) and np.array_equal(R[2].reshape(-1), Pt.data)
+    one = lambda M, shape: sps.csr_matrix((np.ones(M[1].size), M[1], M[0]), shape=shape)
+    pat = (one((rp, ci), (n, n)) @ one(P, (n, na))).tocsr()
+    pat.sort_indices()
+    assert np.diff(pat.indptr).max() > 1024
+    ap = pat.indptr.astype(np.int32), pat.indices.astype(np.int32)
+    AP = _product_in_x_order((g("A.rp"), g("A.ci"), g("A.v")), P, ap)
+    crp, cci = g("A.rp", 1), g("A.ci", 1)
+    cpat = (one(R, (na, n)) @ pat).tocsr()
+    cpat.sort_indices()
+    assert np.array_equal(crp, cpat.indptr) and np.array_equal(cci, cpat.indices)
+    Ac = _product_in_x_order(R, (*ap, AP), (crp, cci))
+    dead = np.nonzero(g("dead").reshape(-1))[0]
+    for a in dead:
+        Ac[crp[a] + int(np.nonzero(cci[crp[a]:crp[a + 1]] == a)[0][0]), 0, 0] = 1.0
+    assert np.array_equal(g("A.v", 1), Ac)
+    h.destroy()
+
+
+def test_schur_approximation_of_far_couplings(scr, ctx):
+    """Rows of 49 blocks, most of them far apart: a row of D G meets about 2,400 candidates (four wavefronts a row)
+    and has more than 1,024 distinct columns (a second, larger table).  S^ = C - D diag(A)^-1 G against scipy on
+    the structural pattern: sums of at most 150 products, 1e-13 of the largest entry; and new values into
+    the kept pattern."""
+    n = 9000
+    rng = np.random.default_rng(11)
+    i = np.arange(n)
+    near = np.concatenate([np.stack([i, (i + d) % n], 1) for d in (1, 2, 3)])
+    far = np.stack([np.repeat(i, 21), rng.integers(0, n, 21 * n)], 1)
+    e = np.concatenate([near, far])
+    e = e[e[:, 0] != e[:, 1]]
+    keys = np.unique(np.concatenate([e[:, 0] * n + e[:, 1], e[:, 1] * n + e[:, 0], i * n + i]))
+    r, c = keys // n, keys % n
+    dist = np.minimum((r - c) % n, (c - r) % n)
+    rp = np.searchsorted(r, np.arange(n + 1)).astype(np.int32)
+    ci = c.astype(np.int32)
+    assert keys.size >= 46 * n
+
+    def system(seed):
+        rng = np.random.default_rng(seed)
+        K = np.zeros((keys.size, 4, 4))
+        w = np.where(dist <= 3, -1.0, -0.01)
+        K[:, :3, :3] = w[:, None, None] * np.eye(3)
+        K[:, 3, 3] = 0.1 * w
+        K[r == c] = np.diag([8.0, 8.5, 9.0, 1.0])
+        off = r != c
+        K[off, :3, 3] = rng.uniform(-0.05, 0.05, (off.sum(), 3))
+        K[off, 3, :3] = rng.uniform(-0.05, 0.05, (off.sum(), 3))
+        return K
+
+    def check(h, K):
+        G = sps.bsr_matrix((K[:, :3, 3:], ci, rp), shape=(3 * n, n)).tocsr()
+        D = sps.bsr_matrix((K[:, 3:, :3], ci, rp), shape=(n, 3 * n)).tocsr()
+        C = sps.csr_matrix((K[:, 3, 3], ci, rp), shape=(n, n))
+        d = np.zeros((n, 3))
+        d[r[r == c]] = np.diagonal(K[r == c][:, :3, :3], axis1=1, axis2=2)
+        S = (C - D @ sps.diags(1.0 / d.reshape(-1)) @ G).tocsr()
+        one = sps.csr_matrix((np.ones(keys.size), ci, rp), shape=(n, n))
+        pat = (one + one @ one).tocsr()
+        pat.sort_indices()
+        grp, gci, gv = h.matrix_copy("Shat")
+        assert np.array_equal(grp, pat.indptr) and np.array_equal(gci, pat.indices)
+        assert np.diff(grp).max() > 1024
+        err = abs(sps.csr_matrix((gv.reshape(-1), gci, grp), shape=(n, n)) - S).max()
+        assert err <= 1e-13 * abs(S).max()
+
+    xyz = rng.uniform(0, 1, (n, 3))
+    K = system(1)
+    print(f"[gpu] far couplings n={n} nnzb={keys.size}", flush=True)
+    h = scr.amg_setup(ctx, scr.SCR_SYSTEM, dev(rp), dev(ci), dev(K.reshape(-1)), dev(xyz.reshape(-1)))
+    check(h, K)
+    K = system(2)
+    scr.amg_update(h, dev(rp), dev(ci), dev(K.reshape(-1)))
+    check(h, K)
+    h.destroy()
