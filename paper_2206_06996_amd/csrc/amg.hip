@@ -447,16 +447,18 @@ __global__ void __launch_bounds__(NW * WAVE) spg_hash_k(int64_t nr, int hs, int 
     }
 }
 
-// numeric phase of the rows whose columns span more than `above`: lane owns output blocks; accumulates
-// X_iq * Y_kc over q in ascending order
+// numeric phase of the rows too long for the forms below (more than fit_map columns, fit_hash where they span more
+// than SPG_SEG): lane owns output blocks; accumulates X_iq * Y_kc over q in ascending order
+constexpr int SPG_SEG = 32768;     // columns of one map of places
 template <int M, int N, int P>
-__global__ void __launch_bounds__(256) spg_numeric(int64_t nr, int above, const int32_t* __restrict__ xrp,
+__global__ void __launch_bounds__(256) spg_numeric(int64_t nr, int fit_map, int fit_hash, const int32_t* __restrict__ xrp,
                                                    const int32_t* __restrict__ xci, const double* __restrict__ xv, const int32_t* __restrict__ yrp,
                                                    const int32_t* __restrict__ yci, const double* __restrict__ yv,
                                                    const int32_t* __restrict__ crp, const int32_t* __restrict__ cci,
                                                    double* __restrict__ cv) {
     int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
-    if (i >= nr || crp[i + 1] <= crp[i] || cci[crp[i + 1] - 1] - cci[crp[i]] < above) return;
+    if (i >= nr || crp[i + 1] <= crp[i]) return;
+    if (crp[i + 1] - crp[i] <= (cci[crp[i + 1] - 1] - cci[crp[i]] >= SPG_SEG ? fit_hash : fit_map)) return;
     int lane = threadIdx.x & (WAVE - 1);
     for (int32_t p = crp[i] + lane; p < crp[i + 1]; p += WAVE) {
         int32_t c = cci[p];
@@ -487,7 +489,6 @@ __global__ void __launch_bounds__(256) spg_numeric(int64_t nr, int above, const 
 // Nothing waits for a sum, so the loads of SPG_PASS passes are in flight.
 // The row's columns as {bits, columns before the word} of each 32 columns of the window: a column's place is
 // one 8-byte LDS read and a population count.  Rows that span more than SPG_SEG columns: a hash table.
-constexpr int SPG_SEG = 32768;
 struct SpgWord { uint32_t bits; int32_t before; };
 // fills map[0 .. ceil(sn / 32)) for the columns [s0, s0 + sn) of cci[lo, hi), `before` of which come before s0
 // (the NT threads of a workgroup); returns the columns up to the segment's end on the first wavefront
@@ -578,22 +579,21 @@ __device__ __forceinline__ void spg_add_in_order(double* sums, int p, double v, 
     }
 }
 
-// scalar rows of C (M = P = 1, inner dimension N), one wavefront per row; the rows that span more than SPG_SEG
-// columns (HASH) or the others.  Dynamic LDS: wmax sums, then the map or table.
+// scalar rows of C (M = P = 1, inner dimension N), one wavefront per row; of the rows of up to `fit` columns those
+// that span more than SPG_SEG (HASH) or the others.  Dynamic LDS: `fit` sums, then the map or table.
 template <int N, bool HASH>
-__global__ void __launch_bounds__(WAVE) spg_scalar_k(int64_t nr, int wmax, const int32_t* __restrict__ xrp,
+__global__ void __launch_bounds__(WAVE) spg_scalar_k(int64_t nr, int fit, const int32_t* __restrict__ xrp,
                                                      const int32_t* __restrict__ xci, const double* __restrict__ xv,
                                                      const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
                                                      const double* __restrict__ yv, const int32_t* __restrict__ crp,
                                                      const int32_t* __restrict__ cci, double* __restrict__ cv) {
     extern __shared__ double sums[];
-    SpgWord* map = reinterpret_cast<SpgWord*>(sums + wmax);
+    SpgWord* map = reinterpret_cast<SpgWord*>(sums + fit);
     const int64_t i = blockIdx.x;
     if (i >= nr) return;
     const int lane = threadIdx.x;
     const int32_t lo = crp[i], hi = crp[i + 1];
-    if (hi <= lo) return;
-    if ((cci[hi - 1] - cci[lo] >= SPG_SEG) != HASH) return;
+    if (hi <= lo || hi - lo > fit || (cci[hi - 1] - cci[lo] >= SPG_SEG) != HASH) return;
     for (int p = lane; p < hi - lo; p += WAVE) sums[p] = 0.0;
     const int32_t x0 = xrp[i], x1 = xrp[i + 1];
     const SpgPlaces<HASH, WAVE> place(map, cci, lo, hi, lane);
@@ -672,25 +672,24 @@ __global__ void __launch_bounds__(WAVE) spg_scalar_k(int64_t nr, int wmax, const
 // block rows (M x P blocks of C, inner dimension N), MP / 9 wavefronts per row: each owns 9 entries of every
 // block, so that each sum has one owner and the sums in LDS (18 or 36 doubles per block
 // column, which bound the rows in flight) serve 2 or 4 wavefronts; a pass takes 7 candidates, one lane
-// per entry.  Rows and dynamic LDS as above (wmax * M * P sums).
+// per entry.  Rows and dynamic LDS as above (fit * M * P sums).
 constexpr int SPG_E = 9;
 struct SpgCand { int32_t t, lp; };     // Y index; X entry (bits 24-29) and place in the row (bits 0-23)
 template <int M, int N, int P, bool HASH>
 __global__ void __launch_bounds__(M* P / SPG_E* WAVE)
-    spg_block_k(int64_t nr, int wmax, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci,
+    spg_block_k(int64_t nr, int fit, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci,
                 const double* __restrict__ xv, const int32_t* __restrict__ yrp, const int32_t* __restrict__ yci,
                 const double* __restrict__ yv, const int32_t* __restrict__ crp, const int32_t* __restrict__ cci,
                 double* __restrict__ cv) {
     constexpr int MP = M * P, E = SPG_E, NW = MP / E, CPP = WAVE / E, NT = NW * WAVE;
     extern __shared__ double sums[];
     __shared__ SpgCand batch[NT];
-    SpgWord* map = reinterpret_cast<SpgWord*>(sums + (size_t)wmax * MP);
+    SpgWord* map = reinterpret_cast<SpgWord*>(sums + (size_t)fit * MP);
     const int64_t i = blockIdx.x;
     if (i >= nr) return;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int32_t lo = crp[i], hi = crp[i + 1];
-    if (hi <= lo) return;
-    if ((cci[hi - 1] - cci[lo] >= SPG_SEG) != HASH) return;
+    if (hi <= lo || hi - lo > fit || (cci[hi - 1] - cci[lo] >= SPG_SEG) != HASH) return;
     for (int p = tid; p < (hi - lo) * MP; p += NT) sums[p] = 0.0;
     const int32_t x0 = xrp[i], x1 = xrp[i + 1];
     const int slot = lane / E;                  // lane 63 holds no candidate (slot 7)
@@ -740,35 +739,37 @@ __global__ void __launch_bounds__(M* P / SPG_E* WAVE)
     for (int p = tid; p < (hi - lo) * MP; p += NT) cv[(int64_t)lo * MP + p] = sums[p];
 }
 
-// numeric phase of C = X Y into C's pattern: the sums in LDS where the longest row's fit, else the pull form;
-// rows that span more than SPG_SEG columns apart (SPG_LDS: two workgroups a CU)
-constexpr size_t SPG_LDS = 68 * 1024;
+// numeric phase of C = X Y into C's pattern: the rows whose sums and map or table fit into LDS (SPG_LDS: two
+// workgroups a CU), and the longer ones by the pull form
+constexpr int SPG_LDS = 68 * 1024;
 static void spgemm_numeric(const DBsr& X, const DBsr& Y, DBsr& C, hipStream_t s) {
     if (X.nr <= 0) return;
-    const int key = X.br * 100 + X.bc * 10 + Y.bc;
-    const size_t sums = (size_t)C.wmax * C.br * C.bc * sizeof(double);
-    const bool wide = C.wmax_cols > SPG_SEG;
-    const size_t lds = sums + (size_t)(std::min(C.wmax_cols, SPG_SEG) + 31) / 32 * sizeof(SpgWord);
-    size_t slots = WAVE;
-    while (slots < 2 * (size_t)C.wmax) slots <<= 1;
-    const size_t ldsh = sums + slots * sizeof(SpgWord);
-    const size_t most = SPG_LDS - (C.br * C.bc > 1 ? C.br * C.bc / SPG_E * WAVE * sizeof(SpgCand) : 0);
-    const bool map = lds <= most, hash = map && wide && ldsh <= most, pull = !map || (wide && !hash);
+    const int key = X.br * 100 + X.bc * 10 + Y.bc, mp = C.br * C.bc;
+    const int most = SPG_LDS - (mp > 1 ? mp / SPG_E * WAVE * (int)sizeof(SpgCand) : 0), sum = mp * (int)sizeof(double);
+    const int words = (std::min(C.wmax_cols, SPG_SEG) + 31) / 32 * (int)sizeof(SpgWord);
+    const int fit_map = std::min(C.wmax, (most - words) / sum);
+    // (the table of twice the columns is a power of two: the size that leaves room for the longest row)
+    int fit_hash = 0, table = 0;
+    for (int t = WAVE; C.wmax_cols > SPG_SEG && fit_hash < C.wmax && t * (int)sizeof(SpgWord) < most; t <<= 1) {
+        const int f = std::min({C.wmax, t / 2, (most - t * (int)sizeof(SpgWord)) / sum});
+        if (f > fit_hash) { fit_hash = f; table = t * (int)sizeof(SpgWord); }
+    }
+    const bool wide = fit_hash > 0, pull = fit_map < C.wmax || (wide && fit_hash < C.wmax);
+    const size_t lds = (size_t)(fit_map * sum + words), ldsh = (size_t)(fit_hash * sum + table);
     const unsigned nb = (unsigned)cdiv(X.nr, 4);
-    const int above = map ? SPG_SEG : 0;
 #define SPG_ARGS X.rp, X.ci, X.v, Y.rp, Y.ci, Y.v, C.rp, C.ci, C.v
 #define SPS(n)                                                                                                  \
     {                                                                                                           \
-        if (map) spg_scalar_k<n, false><<<(unsigned)X.nr, WAVE, lds, s>>>(X.nr, C.wmax, SPG_ARGS);              \
-        if (hash) spg_scalar_k<n, true><<<(unsigned)X.nr, WAVE, ldsh, s>>>(X.nr, C.wmax, SPG_ARGS);             \
-        if (pull) spg_numeric<1, n, 1><<<nb, 256, 0, s>>>(X.nr, above, SPG_ARGS);                               \
+        spg_scalar_k<n, false><<<(unsigned)X.nr, WAVE, lds, s>>>(X.nr, fit_map, SPG_ARGS);                      \
+        if (wide) spg_scalar_k<n, true><<<(unsigned)X.nr, WAVE, ldsh, s>>>(X.nr, fit_hash, SPG_ARGS);           \
+        if (pull) spg_numeric<1, n, 1><<<nb, 256, 0, s>>>(X.nr, fit_map, fit_hash, SPG_ARGS);                   \
     }
 #define SPB(m, n, p)                                                                                            \
     {                                                                                                           \
         constexpr int T = m * p / SPG_E * WAVE;                                                                 \
-        if (map) spg_block_k<m, n, p, false><<<(unsigned)X.nr, T, lds, s>>>(X.nr, C.wmax, SPG_ARGS);            \
-        if (hash) spg_block_k<m, n, p, true><<<(unsigned)X.nr, T, ldsh, s>>>(X.nr, C.wmax, SPG_ARGS);           \
-        if (pull) spg_numeric<m, n, p><<<nb, 256, 0, s>>>(X.nr, above, SPG_ARGS);                               \
+        spg_block_k<m, n, p, false><<<(unsigned)X.nr, T, lds, s>>>(X.nr, fit_map, SPG_ARGS);                    \
+        if (wide) spg_block_k<m, n, p, true><<<(unsigned)X.nr, T, ldsh, s>>>(X.nr, fit_hash, SPG_ARGS);         \
+        if (pull) spg_numeric<m, n, p><<<nb, 256, 0, s>>>(X.nr, fit_map, fit_hash, SPG_ARGS);                   \
     }
     switch (key) {
         case 111: SPS(1) break;

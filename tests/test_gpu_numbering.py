@@ -65,11 +65,12 @@ def test_setup_time_does_not_follow_the_numbering(scr, ctx):
     assert best[1] <= 1.7 * best[0]
 
 
-def test_products_over_wide_windows_bitwise(scr, ctx):
+@pytest.mark.parametrize("stride,widest", [(800, 1024), (400, 2048)])
+def test_products_over_wide_windows_bitwise(scr, ctx, stride, widest):
     """A shuffled grid of 640 x 640 nodes with hub rows: more than 32,768 aggregates, so every product of level 0
-    takes hash tables in both phases, and the hub rows of A P (more than 1,024 columns) overflow the first one.
-    Equal bit for bit to the products in row order, on the structural patterns; R = P^T."""
-    A = _grid_with_hubs(n=640, hubs=3, stride=800, spread=True).tocoo()
+    takes hash tables in both phases, and the hub rows of A P overflow the first one (more than 1,024 columns) or are
+    too long for the second phase's (2,048).  Equal bit for bit to the products in row order, on the structural patterns; R = P^T."""
+    A = _grid_with_hubs(n=640, hubs=3, stride=stride, spread=True).tocoo()
     n = A.shape[0]
     new = np.random.default_rng(5).permutation(n)
     A = sps.csr_matrix((A.data, (new[A.row], new[A.col])), shape=(n, n))
@@ -89,7 +90,7 @@ def test_products_over_wide_windows_bitwise(scr, ctx):
     one = lambda M, shape: sps.csr_matrix((np.ones(M[1].size), M[1], M[0]), shape=shape)
     pat = (one((rp, ci), (n, n)) @ one(P, (n, na))).tocsr()
     pat.sort_indices()
-    assert np.diff(pat.indptr).max() > 1024
+    assert np.diff(pat.indptr).max() > widest
     ap = pat.indptr.astype(np.int32), pat.indices.astype(np.int32)
     AP = _product_in_x_order((g("A.rp"), g("A.ci"), g("A.v")), P, ap)
     crp, cci = g("A.rp", 1), g("A.ci", 1)
@@ -159,4 +160,58 @@ def test_schur_approximation_of_far_couplings(scr, ctx):
     K = system(2)
     scr.amg_update(h, dev(rp), dev(ci), dev(K.reshape(-1)))
     check(h, K)
+    h.destroy()
+
+
+def test_block_products_over_wide_windows_bitwise(scr, ctx):
+    """A shuffled system of 4x4 blocks on a 640 x 640 grid: A P and R (A P) of level 0 (3x6 and 6x6 blocks) over more
+    than 32,768 aggregates.  400 rows of A_1 against the products in row order: pattern and values equal."""
+    m = 640
+    n = m * m
+    i = np.arange(n).reshape(m, m)
+    e = np.concatenate([np.stack([i[:, :-1].ravel(), i[:, 1:].ravel()], 1), np.stack([i[:-1].ravel(), i[1:].ravel()], 1)])
+    rng = np.random.default_rng(17)
+    new = rng.permutation(n)
+    r, c = new[np.concatenate([e[:, 0], e[:, 1], i.ravel()])], new[np.concatenate([e[:, 1], e[:, 0], i.ravel()])]
+    order = np.lexsort((c, r))
+    r, c = r[order], c[order]
+    rp = np.searchsorted(r, np.arange(n + 1)).astype(np.int32)
+    ci = c.astype(np.int32)
+    K = rng.uniform(-0.01, 0.01, (r.size, 4, 4))
+    K -= np.eye(4)
+    K[r == c] = rng.uniform(-0.01, 0.01, (n, 4, 4)) + np.diag([4.5, 4.6, 4.7, 4.5])
+    xyz = np.empty((n, 3))
+    xyz[new] = np.stack([i.ravel() // m, i.ravel() % m, rng.uniform(0, 1, n)], 1)
+    print(f"[gpu] shuffled block grid n={n}", flush=True)
+    h = scr.amg_setup(ctx, scr.SCR_SYSTEM, dev(rp), dev(ci), dev(K.reshape(-1)), dev(xyz),
+                      scr.amg_opts(theta=0.02))
+    na = h.hier_level_info(0, 0)["nagg"]
+    assert na > 32768
+
+    def g(f, l=0):
+        return h.hier_level_copy(0, l, f)
+
+    def rows_of(M, rows):           # the rows of a block CSR triple, renumbered from 0
+        mrp, mci, mv = M
+        q = np.concatenate([np.arange(mrp[x], mrp[x + 1]) for x in rows])
+        return np.concatenate([[0], np.cumsum(mrp[rows + 1] - mrp[rows])]).astype(np.int32), mci[q], mv[q]
+    A, P, R = (tuple(g(f"{M}.{f}") for f in ("rp", "ci", "v")) for M in "APR")
+    rows = np.sort(rng.choice(na, 400, replace=False))
+    Rs = rows_of(R, rows)
+    mid = np.unique(Rs[1])
+    As = rows_of(A, mid)
+    Rs = Rs[0], np.searchsorted(mid, Rs[1]).astype(np.int32), Rs[2]
+    one = lambda M, shape: sps.csr_matrix((np.ones(M[1].size), M[1], M[0]), shape=shape)
+    pat = (one(As, (mid.size, n)) @ one(P, (n, na))).tocsr()
+    pat.sort_indices()
+    ap = pat.indptr.astype(np.int32), pat.indices.astype(np.int32)
+    AP = _product_in_x_order(As, P, ap)
+    cpat = (one(Rs, (rows.size, mid.size)) @ pat).tocsr()
+    cpat.sort_indices()
+    crp, cci, cv = rows_of((g("A.rp", 1), g("A.ci", 1), g("A.v", 1)), rows)
+    assert np.array_equal(crp, cpat.indptr) and np.array_equal(cci, cpat.indices)
+    assert cci.max() - cci.min() > 32768
+    dead = g("dead").reshape(na, 6)[rows]
+    assert not dead.any()
+    assert np.array_equal(cv, _product_in_x_order(Rs, (*ap, AP), (crp, cci)))
     h.destroy()
