@@ -1122,6 +1122,9 @@ __global__ void __launch_bounds__(BR * WAVE) bsrt_rows_k(const int32_t* __restri
 }
 
 constexpr int64_t BSRT_ROWS = 2048;
+// 1x1 blocks: four wavefronts per row
+template <typename T>
+static bool bsrt_shared(const DBsrT<T>& R) { return R.nr < BSRT_ROWS && R.nnzb >= WAVE * R.nr; }
 template <typename T>
 void bsrt_mv(const DBsrT<T>& R, const T* x, T* y, hipStream_t s) {
     if (R.nr == 0) return;
@@ -1130,7 +1133,7 @@ void bsrt_mv(const DBsrT<T>& R, const T* x, T* y, hipStream_t s) {
     const unsigned g = (unsigned)cdiv(R.nr, 4), gr = (unsigned)R.nr;
     switch (key) {
         case 11:
-            if (few && R.nnzb >= WAVE * R.nr) bsrt_mv_k<T, 1, 1, 4><<<gr, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+            if (bsrt_shared(R)) bsrt_mv_k<T, 1, 1, 4><<<gr, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
             else bsrt_mv_k<T, 1, 1, 1><<<g, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
             break;
         case 63:
@@ -1512,33 +1515,48 @@ void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool do
 template void sell_mv3<double>(const DSell<double>&, const double*, const double*, double*, int, bool, hipStream_t);
 template void sell_mv3<float>(const DSell<float>&, const float*, const float*, float*, int, bool, hipStream_t);
 
-// y = R x for 1x1 R (rows of R are long; one row per wavefront, the lane tree of bsrt_mv_k)
-template <typename T>
+// y = R x for 1x1 R: bsrt_mv_k on three columns (its wavefronts per row, lane tree and sums of the parts, for its
+// bits: four wavefronts a row change the mesh motion at 7k and 300k nodes by less than the runs differ, 0.78 and
+// 2.98 ms)
+template <typename T, int WPR>
 __global__ void __launch_bounds__(256) bsrt_mv3_k(int64_t nr, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x, T* __restrict__ y) {
-    int64_t row = xcd_tile(blockIdx.x, gridDim.x) * 4 + (threadIdx.x / WAVE);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t row = xcd_tile(blockIdx.x, gridDim.x) * (4 / WPR) + wv / WPR;
     if (row >= nr) return;
-    int lane = threadIdx.x & (WAVE - 1);
+    const int lane = threadIdx.x & (WAVE - 1);
     T acc[3] = {0, 0, 0};
-    int64_t q0 = rp[row], len = rp[row + 1] - q0;
-    for (int64_t j = lane; j < len; j += WAVE) {
+    const int64_t q0 = rp[row], len = rp[row + 1] - q0;
+    for (int64_t j = wv % WPR * WAVE + lane; j < len; j += WPR * WAVE) {
         int64_t c = ci[q0 + j];
         const T vv = v[q0 + j];
 #pragma unroll
         for (int k = 0; k < 3; ++k) acc[k] += vv * x[3 * c + k];
     }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        T sum = wave_sum(acc[k]);
-        if (lane == 0) y[3 * row + k] = sum;
+    for (int k = 0; k < 3; ++k) acc[k] = wave_sum(acc[k]);
+    if constexpr (WPR == 1) {
+        if (lane < 3) y[3 * row + lane] = lane == 0 ? acc[0] : lane == 1 ? acc[1] : acc[2];
+    } else {
+        static_assert(WPR == 4, "one row per workgroup: its threads meet at the barrier or leave together");
+        __shared__ T part[WPR][3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (lane == 0) part[wv][k] = acc[k];
+        __syncthreads();
+        if (wv != 0 || lane >= 3) return;
+        T sum = part[0][lane];
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) sum += part[w][lane];
+        y[3 * row + lane] = sum;
     }
 }
 template <typename T>
 void bsrt_mv3(const DBsrT<T>& R, const T* x, T* y, hipStream_t s) {
     if (R.br != 1 || R.bc != 1) throw Error(SCR_E_UNIMPLEMENTED, "bsrt_mv3: 1x1 blocks only");
-    int64_t nblk = cdiv(R.nr, 4);
-    if (nblk == 0) return;
-    bsrt_mv3_k<T><<<nblk, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+    if (R.nr == 0) return;
+    if (bsrt_shared(R)) bsrt_mv3_k<T, 4><<<(unsigned)R.nr, 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
+    else bsrt_mv3_k<T, 1><<<(unsigned)cdiv(R.nr, 4), 256, 0, s>>>(R.nr, R.rp, R.ci, R.v, x, y);
     check_launch("bsrt_mv3");
 }
 template void bsrt_mv3<double>(const DBsrT<double>&, const double*, double*, hipStream_t);
@@ -1697,7 +1715,8 @@ __global__ void __launch_bounds__(256) dense_mv_k(int64_t n, const double* __res
             bb[u] = (double)b[q];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc += c + u * WAVE < n ? m[u] * bb[u] : 0.0;
+        for (int u = 0; u < U; ++u)
+            if (c + u * WAVE < n) acc += m[u] * bb[u];
     }
     acc = wave_sum(acc);
     if (lane == 0) x[row] = (T)acc;
