@@ -465,8 +465,21 @@ KStat GmresT<T>::solve(OpT<T>& A, OpT<T>& M, const T* b, T* x, double tol, int m
     GLay L{m};
     const double* host_ = slot_.h;
     // A start from zero takes the first residual's norm from the right-hand side's, and x is written (not
-    // added to) by the first update: `fresh` until then, and every way out before it clears x.
+    // added to) by the first update: `fresh` until then, and every way out before it clears x, an error of
+    // the operators among them.
     bool fresh = !use_x0;
+    struct Clear {
+        const bool& fresh;
+        T* x;
+        size_t bytes;
+        hipStream_t s;
+        ~Clear() {
+            try {
+                if (fresh) zero_dev(x, bytes, s);
+            } catch (...) {      // the device is lost, and the first error is on its way to the caller
+            }
+        }
+    } clear{fresh, x, n * sizeof(T), s};
     double bn;
     if (fresh) {
         dot_part_k<T><<<G, RTPB, 0, s>>>(n, b, b, part);
@@ -478,14 +491,11 @@ KStat GmresT<T>::solve(OpT<T>& A, OpT<T>& M, const T* b, T* x, double tol, int m
         bn = device_norm(b, n, red_, slot_, s);
     }
     if (bn == 0.0) {
-        zero_dev(x, n * sizeof(T), s);
+        fresh = true;
         st.converged = true;
         return st;
     }
-    if (!std::isfinite(bn)) {
-        if (fresh) zero_dev(x, n * sizeof(T), s);
-        throw Error(SCR_E_BREAKDOWN, "non-finite right-hand side");
-    }
+    if (!std::isfinite(bn)) throw Error(SCR_E_BREAKDOWN, "non-finite right-hand side");
     double est = INFINITY;
     int64_t nblk = cdiv(n, 256);
     for (;;) {
@@ -529,10 +539,7 @@ KStat GmresT<T>::solve(OpT<T>& A, OpT<T>& M, const T* b, T* x, double tol, int m
             slot_.wait(s);
             ++st.iters;
             ++j;
-            if (host_[S_FLAG] != 0.0) {
-                if (fresh) zero_dev(x, n * sizeof(T), s);
-                throw Error(SCR_E_BREAKDOWN, "non-finite value in the Arnoldi process");
-            }
+            if (host_[S_FLAG] != 0.0) throw Error(SCR_E_BREAKDOWN, "non-finite value in the Arnoldi process");
             est = host_[S_EST];
             if (host_[S_HN] == 0.0) break;   // happy breakdown: the Krylov space is invariant
             if (est <= tol * bn || st.iters >= maxit) break;
@@ -547,7 +554,6 @@ KStat GmresT<T>::solve(OpT<T>& A, OpT<T>& M, const T* b, T* x, double tol, int m
             break;
         }
     }
-    if (fresh) zero_dev(x, n * sizeof(T), s);
     return st;
 }
 

@@ -63,3 +63,24 @@ def test_gmres_at_every_kernel_width(scr, nodes, precond, restart):
     assert rc == 0 and not x.any()
     h.destroy()
     ctx.destroy()
+
+
+def test_an_error_inside_a_solve_from_zero_leaves_zero(scr):
+    """G scaled by 2^700 and D by 2^-700: S^ is as before, and the right-hand side of the inner velocity solve of
+    Algorithm 2 overflows.  The pressure solve around it has not written its result yet and leaves zero."""
+    s = synth.generate(synth.default_params(mode=0, m_core=2, n_bl=1, n_wall=1, nz=8, R=1.0, L=2.0))
+    ctx = scr.Context(0)
+    K = s.val.reshape(-1, 4, 4).copy()
+    K[:, :3, 3] *= 2.0 ** 700
+    K[:, 3, :3] *= 2.0 ** -700
+    print(f"[gpu] error inside a solve n_b={s.n_b}", flush=True)
+    h = scr.amg_setup(ctx, scr.SCR_SYSTEM, dev(s.rp), dev(s.ci), dev(K.reshape(-1)), dev(s.xyz.reshape(-1)))
+    x = np.zeros(4 * s.n_b)
+    x[3 * s.n_b:] = np.random.default_rng(2).uniform(-1, 1, s.n_b)
+    y = torch.full((4 * s.n_b,), 7.0, dtype=torch.float64, device="cuda")
+    with pytest.raises(scr.ScrError) as e:
+        scr.scr_apply(h, "SCR", dev(x), y)
+    assert e.value.status == -4
+    assert not y[3 * s.n_b:].any()
+    h.destroy()
+    ctx.destroy()
