@@ -84,3 +84,73 @@ def test_an_error_inside_a_solve_from_zero_leaves_zero(scr):
     assert not y[3 * s.n_b:].any()
     h.destroy()
     ctx.destroy()
+
+
+# Iterations of the same solves with every sum in a launch of its own and every column loaded by itself, the form
+# that these kernels were written from; (its_A, its_S, its_I, calls of each)
+EXACT = [
+    # 3 x 13,344 and 13,344 unknowns: one element a thread; inner bases of 17, 36 and 43 columns
+    (700, {}, (64, 72, 1222), (4, 2, 72)),
+    (700, dict(cheb_degree=1), (168, 72, 3111), (4, 2, 72)),
+    # 3 x 25,242: four elements a thread for the velocity
+    (25e3, {}, (62, 79, 1263), (4, 2, 79)),
+    (25e3, dict(cheb_degree=1), (160, 79, 3314), (4, 2, 79)),
+    # 3 x 204,711: beyond the sums by the next kernel for the velocity; up to 62 columns for the pressure
+    (200e3, {}, (95, 125, 3150), (4, 2, 125)),
+]
+
+
+@pytest.mark.parametrize("nodes,amg,its,calls", EXACT)
+def test_inner_solves_to_rounding(scr, nodes, amg, its, calls):
+    """Inner solves to 1e-11 and 1e-12 make Algorithm 1 an exact preconditioner: two outer iterations, and the
+    iterations of each inner solve as above (+-1 a solve: the order of the sums differs).  A wrong coefficient for
+    one width of the basis shows in the first or in the second."""
+    s = synth.generate(synth.tube_params(nodes, 1.0, 5.0))
+    print(f"[gpu] inner solves n_b={s.n_b} {amg}", flush=True)
+    ctx = scr.Context(0)
+    h = scr.amg_setup(ctx, scr.SCR_SYSTEM, dev(s.rp), dev(s.ci), dev(s.val.reshape(-1)), dev(s.xyz.reshape(-1)),
+                      scr.amg_opts(**amg))
+    b = synth.rhs(3, 4 * s.n_b, s.mask)
+    x = torch.empty(4 * s.n_b, dtype=torch.float64, device="cuda")
+    rc, st = scr.scr_solve(h, dev(b), x, scr.solve_opts(tol=1e-9, tol_A=1e-12, tol_S=1e-11, tol_I=1e-12, restart_inner=63,
+                                                        max_it_A=300, max_it_S=300, max_it_I=300))
+    got = [(st["its_" + k], st["calls_" + k]) for k in "ASI"]
+    print(f"[gpu] outer {st['outer_it']} (iterations, solves) {got}", flush=True)
+    assert rc == 0 and st["outer_it"] == 2
+    assert residual(s, b, x.cpu().numpy()) <= 1e-11
+    for (i, n), ref, nref in zip(got, its, calls):
+        assert i / n > 8 and abs(i / n - ref / nref) <= 1
+    h.destroy()
+    ctx.destroy()
+
+
+# one element a thread, four, the longest vectors whose partials the next kernel adds, and beyond
+@pytest.mark.parametrize("nodes,n,its", [(60e3, 54777, 12), (100e3, 109512, 13), (300e3, 308550, 14), (600e3, 570103, 15)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_cg_at_every_grid(scr, nodes, n, its, precision):
+    """CG (precision 0) and flexible CG (1) on the three columns: the iterations of the form with a launch for each
+    sum (+-1), the residual of the recurrence and the true one at the tolerance; a column that is done (zero) stays."""
+    s = synth.generate(synth.tube_params(nodes, 1.0, 5.0))
+    assert s.n_phys == n
+    print(f"[gpu] cg n={n} precision={precision}", flush=True)
+    ctx = scr.Context(0)
+    h = scr.amg_setup(ctx, scr.MESH_SYSTEM, dev(s.Lrp), dev(s.Lci), dev(s.Lval), None, scr.amg_opts(precision=precision))
+    b = synth.rhs(31, 3 * n, np.repeat(s.Lmask, 3)).reshape(-1, 3)
+    b[:, 1] *= 1e-3
+    rows = np.repeat(np.arange(n), np.diff(s.Lrp))
+    for cols in ((0, 1, 2), (0, 2)):
+        bb = np.zeros_like(b)
+        bb[:, cols] = b[:, cols]
+        x = torch.full((3 * n,), float("nan"), dtype=torch.float64, device="cuda")
+        rc, st = scr.mesh_motion_solve(h, dev(bb.reshape(-1)), x, scr.solve_opts(tol=1e-10))
+        xs = x.cpu().numpy().reshape(-1, 3)
+        assert rc == 0
+        for c in range(3):
+            if c not in cols:
+                assert st["mesh_its"][c] == 0 and not xs[:, c].any()
+                continue
+            r = bb[:, c] - np.bincount(rows, weights=s.Lval * xs[s.Lci, c], minlength=n)
+            assert abs(st["mesh_its"][c] - its) <= 1
+            assert np.linalg.norm(r) <= 1.01e-10 * np.linalg.norm(bb[:, c])
+    h.destroy()
+    ctx.destroy()
