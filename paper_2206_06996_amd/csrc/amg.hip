@@ -2066,13 +2066,6 @@ __global__ void rowmask_k(int64_t nr, const int32_t* __restrict__ agg, uint8_t* 
 }
 
 // ====================================================================== hierarchy construction
-static int64_t read_i32(const int32_t* p, hipStream_t s) {
-    int32_t v = 0;
-    HIPCHK(hipMemcpyAsync(&v, p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    return v;
-}
-
 // D^-1 (into L.Dinv) and lambda_hat = max abs row sum of D^-1 A (into L.lam)
 void level_diag(LevelSetup& L, int l, int* err, unsigned long long* lamd, hipStream_t s) {
     const int64_t nr = L.A.nr;

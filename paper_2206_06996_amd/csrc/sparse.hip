@@ -459,7 +459,8 @@ template DBsrT<float> bsrt_from_bsr<float>(const DBsr&, Arena&, hipStream_t);
 //     V-cycle of AMG(S^) 1,160 -> 1,570 us).
 //     Consecutive sweeps run in opposite directions (xcd_tile), so that each starts with what the last one
 //     left in the caches: that V-cycle 1,285 -> 1,120 us, of AMG(A) 1,366 -> 1,342, at 41k nodes 300 -> 282.
-//   * Prolongators and restrictions are read once a cycle: FP64 segments of three or more values nontemporal.
+//   * Prolongators and restrictions are read once a cycle: segments of three or more FP64 values and the 3x6
+//     prolongators of both types nontemporal; the square (6x6) prolongators of the coarse levels go by size.
 constexpr int KEEP_PARTS = 16;
 constexpr double KEEP_BYTES = 160.0 * (1 << 20);
 __device__ __forceinline__ bool keep_slice(int64_t sl, int keep) { return (int)(sl % KEEP_PARTS) < keep; }
@@ -724,7 +725,7 @@ static int waves_per_slice(const DSell<T>& A) {
 }
 
 // the 3*BC values of slot t of a lane (layout of rl_vidx): FP64 in 16-byte pairs, FP32 in 16-byte
-// quads, nontemporal
+// quads
 template <typename T, int BC, bool KEEP>
 __device__ __forceinline__ void rl_load(const T* __restrict__ v, int64_t t, int lane, T (&vv)[3 * BC]) {
     constexpr int E = 3 * BC, Q = sizeof(T) == 8 ? 2 : 4;
@@ -773,8 +774,8 @@ static int rl_waves_per_slice(const DSell<T>& A) {
 // ---- block-row lanes (3xBC, BC = 3 or 6): r[0..2] = sum over the lane's slots of block * x[col]
 // Two slots per step (both slots' columns, then their values and x vectors are loaded before
 // use); FP32 3x6 takes one slot per step (18 values and an x 6-vector).  Measured on the refined
-// tube: two 3x6 FP64 slots per step make the level-0 prolongation 3.5 % faster.  FP64 values are
-// streamed with nontemporal loads (read once per call; measured: a gain in FP64, a loss in FP32).
+// tube: two 3x6 FP64 slots per step make the level-0 prolongation 3.5 % faster.  KEEP: through the caches or
+// nontemporal (keep_slice; 3x6 always nontemporal).
 // CAP: also copy the 3x3 block of column irow (the diagonal block of the lane's row) into dg; the
 // first match is the stored block (padding slots that repeat the row's last column hold zeros and
 // come after it)
@@ -936,8 +937,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_
 
 template <typename T, int BR, int BC>
 static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
-    constexpr bool SPLIT = true;
-    const int wps = SPLIT ? waves_per_slice(A) : 1, keep = keep_of(A);
+    const int wps = waves_per_slice(A), keep = keep_of(A);
     if (A.nslices == 0) return;
 #define MV(W)                                                                                                  \
     {                                                                                                          \
@@ -951,11 +951,11 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
             default: sell_mv_k<T, BR, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                      \
     }
-    if (!SPLIT || wps == 1) MV(1)
-    else if (wps == 2) MV((SPLIT ? 2 : 1))
-    else if (wps == 4) MV((SPLIT ? 4 : 1))
-    else if (wps == 8) MV((SPLIT ? 8 : 1))
-    else MV((SPLIT ? 16 : 1))
+    if (wps == 1) MV(1)
+    else if (wps == 2) MV(2)
+    else if (wps == 4) MV(4)
+    else if (wps == 8) MV(8)
+    else MV(16)
 #undef MV
     check_launch("sell_mv");
 }
@@ -990,11 +990,9 @@ void sell_mv(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool dow
     int key = A.br * 10 + A.bc;
     switch (key) {
         case 11: sell_mv_dispatch_mode<T, 1, 1>(A, x, b, y, mode, down, s); break;
-        case 33: sell_mv_dispatch_mode<T, 3, 3>(A, x, b, y, mode, down, s); break;
         case 66: sell_mv_dispatch_mode<T, 6, 6>(A, x, b, y, mode, down, s); break;
         case 31: sell_mv_dispatch_mode<T, 3, 1>(A, x, b, y, mode, down, s); break;
         case 13: sell_mv_dispatch_mode<T, 1, 3>(A, x, b, y, mode, down, s); break;
-        case 36: sell_mv_dispatch_mode<T, 3, 6>(A, x, b, y, mode, down, s); break;
         case 44: sell_mv_dispatch_mode<T, 4, 4>(A, x, b, y, mode, down, s); break;
         default: throw Error(SCR_E_UNIMPLEMENTED, "sell_mv: block shape " + std::to_string(A.br) + "x" + std::to_string(A.bc));
     }
@@ -1373,10 +1371,7 @@ void smooth_step(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* 
                  bool read_d, bool write_d, bool zero_in, bool down, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     switch (A.br) {
         case 1: smooth_dispatch<T, 1>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1); break;
-        case 3:
-            if (A.rowlane) smooth_rl3<T>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1);
-            else smooth_dispatch<T, 3>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1);
-            break;
+        case 3: smooth_rl3<T>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1); break;
         case 6: smooth_dispatch<T, 6>(A, Dinv, b, xin, d, xout, (T)c1, (T)c2, read_d, write_d, zero_in, down, s, e0, e1); break;
         default: throw Error(SCR_E_UNIMPLEMENTED, "smooth_step: block size");
     }
