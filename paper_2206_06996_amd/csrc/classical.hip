@@ -550,10 +550,17 @@ __global__ void l1_diag_k(int64_t nr, const int32_t* __restrict__ rp, const int3
 //  2. the first wavefront, over the sweep positions q: lane q forms its new value, it is broadcast,
 //     and every later position subtracts its coupling to it (the fresh part of each row's sum, in
 //     sweep order).
-// Bound by latency: a launch, the chain rp -> entries -> x of the first phase and 64 dependent steps of the
-// second.  The second is unrolled, so that no step waits for its coupling from LDS, and its row's data are
-// loaded before the first: 12.2 -> 9.2 us a sweep at 20,800 rows of 45 entries (16 lanes per row: 14.2, one
-// workgroup per CU).  128 registers let two domains share a CU.
+// Few domains are bound by latency: a launch, the chain rp -> entries -> x of the first phase and 64 dependent
+// steps of the second, which is unrolled and reads its couplings ahead, so that no step waits for LDS: 12.2 ->
+// 9.2 us a sweep at 20,800 rows of 45 entries (16 lanes per row: 14.2, one workgroup per CU).  Many domains are
+// bound by what a CU issues: four steps are unrolled, and three FP64 columns, whose second phase is the longest,
+// read only the couplings that are there (AHEAD).  Three FP64 columns, forward / backward sweep, read ahead -> only
+// those: 129k nodes of 15 entries (2,023 domains) 43.6 / 47.1 -> 37.4 / 43.5 us, 309k 92.3 / 100.2 -> 76.3 / 87.0,
+// a 640 x 640 grid of 5 entries 138.8 / 155.9 -> 111.3 / 129.9; at 55k (856 domains) 20.3 / 22.9 against 21.9 /
+// 24.6, and of the one-column and FP32 cycles none is faster without; hence GS_FEW.  The second phase's row data
+// are loaded when it begins: before the first, they cost a domain in four its place on the CU (111 registers for
+// 96; the mesh solve at 309k nodes 3.99 against 4.35 ms, of 11.6k nodes 0.68 against 0.71).
+constexpr int64_t GS_FEW = 1024;    // domains, four a CU
 constexpr int GS_TRI = GS_DOM * (GS_DOM - 1) / 2;
 constexpr int GS_L = 8;             // lanes per row in the first phase
 constexpr int GS_W = GS_DOM * GS_L / WAVE;   // wavefronts per domain in the first phase
@@ -572,8 +579,8 @@ __device__ __forceinline__ float readlane_t(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-template <typename T, int NC, bool BWD>
-__global__ void __launch_bounds__(GS_W * WAVE, NC == 1 ? 4 : 1) hgs_k(int64_t nr, const int32_t* __restrict__ rp,
+template <typename T, int NC, bool BWD, bool FEW>
+__global__ void __launch_bounds__(GS_W * WAVE) hgs_k(int64_t nr, const int32_t* __restrict__ rp,
                                                    const int32_t* __restrict__ ci, const T* __restrict__ v,
                                                    const T* __restrict__ dinv, const T* __restrict__ ell,
                                                    const T* __restrict__ b, const T* __restrict__ xold,
@@ -590,20 +597,6 @@ __global__ void __launch_bounds__(GS_W * WAVE, NC == 1 ? 4 : 1) hgs_k(int64_t nr
     const int64_t il = BWD ? hi - 1 - lane : lo + lane;
     const bool own = lane < n;
     const int32_t rs = own ? rp[il] : 0, re = own ? rp[il + 1] : 0;
-    // what the second phase needs of the row at sweep position `lane` is on its way during the first
-    T dv = T(0), ev = T(0), bi[NC], xo[NC];
-    const bool l1 = ell != nullptr && xold != nullptr;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) bi[c] = xo[c] = T(0);
-    if (wv == 0 && own) {
-        dv = dinv[il];
-        if (l1) ev = ell[il];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            bi[c] = b[NC * il + c];
-            if (l1) xo[c] = xold[NC * il + c];
-        }
-    }
     for (int e = threadIdx.x; e < GS_DOM + GS_TRI; e += GS_W * WAVE) Fpad[e] = T(0);
     __syncthreads();
     // phase 1: sweep position tt on GS_L lanes
@@ -656,23 +649,39 @@ __global__ void __launch_bounds__(GS_W * WAVE, NC == 1 ? 4 : 1) hgs_k(int64_t nr
     __syncthreads();
     if (wv != 0) return;
     // phase 2 (first wavefront): the row at sweep position `lane`
+    const bool l1 = ell != nullptr && xold != nullptr;
+    const T dv = own ? dinv[il] : T(0);
+    const T ev = own && l1 ? ell[il] : T(0);
     T r[NC], xn[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        r[c] = own ? bi[c] - so_sh[c][lane] : T(0);
-        if (own && l1) r[c] = r[c] + ev * xo[c];
+        r[c] = own ? b[NC * il + c] - so_sh[c][lane] : T(0);
+        if (own && l1) r[c] = r[c] + ev * xold[NC * il + c];
         xn[c] = T(0);
     }
-    // unrolled, so that the couplings are read ahead of the chain (positions from n on hold zeros)
-#pragma unroll 16
-    for (int q = 0; q < GS_DOM; ++q) {
-        T f = F[gs_tri(0, q) + lane];
-        f = lane > q ? f : T(0);
+    constexpr bool AHEAD = FEW || NC == 1 || sizeof(T) == 4;
+    constexpr int STEPS = FEW ? 16 : 4;
+    if constexpr (AHEAD) {
+        // (positions from n on hold zeros)
+#pragma unroll STEPS
+        for (int q = 0; q < GS_DOM; ++q) {
+            T f = F[gs_tri(0, q) + lane];
+            f = lane > q ? f : T(0);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const T t = r[c] * dv;
-            if (lane == q) xn[c] = t;
-            r[c] = r[c] - f * readlane_t(t, q);
+            for (int c = 0; c < NC; ++c) {
+                const T t = r[c] * dv;
+                if (lane == q) xn[c] = t;
+                r[c] = r[c] - f * readlane_t(t, q);
+            }
+        }
+    } else {
+        for (int q = 0; q < n; ++q) {
+            const T f = lane > q && lane < n ? F[gs_tri(lane, q)] : T(0);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (lane == q) xn[c] = r[c] * dv;
+                r[c] = r[c] - f * readlane_t(xn[c], q);
+            }
         }
     }
     if (own) {
@@ -687,8 +696,13 @@ void hgs(const DBsr& A, const T* v, const T* Dinv, const T* ell, const T* b, con
          hipStream_t s) {
     const unsigned g = (unsigned)cdiv(A.nr, GS_DOM);     // one workgroup per domain
     if (!g) return;
-    if (backward) hgs_k<T, NC, true><<<g, GS_W * WAVE, 0, s>>>(A.nr, A.rp, A.ci, v, Dinv, ell, b, xold, x);
-    else hgs_k<T, NC, false><<<g, GS_W * WAVE, 0, s>>>(A.nr, A.rp, A.ci, v, Dinv, ell, b, xold, x);
+#define HGS(BWD, FEW) hgs_k<T, NC, BWD, FEW><<<g, GS_W * WAVE, 0, s>>>(A.nr, A.rp, A.ci, v, Dinv, ell, b, xold, x)
+    if (g <= GS_FEW) {
+        if (backward) HGS(true, true); else HGS(false, true);
+    } else {
+        if (backward) HGS(true, false); else HGS(false, false);
+    }
+#undef HGS
     check_launch("hybrid_gs");
 }
 

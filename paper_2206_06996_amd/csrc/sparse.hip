@@ -1442,7 +1442,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t n
                                                   const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x,
                                                   const T* __restrict__ b, T* __restrict__ y) {
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int wv = threadIdx.x / WAVE;
     const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
@@ -1564,7 +1564,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t ns
                                                  const T* __restrict__ v, const T* __restrict__ Dinv,
                                                  const T* __restrict__ b, const T* __restrict__ xin, T* __restrict__ d,
                                                  T* __restrict__ xout, T c1, T c2) {
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int wv = threadIdx.x / WAVE;
     const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const bool live = sl < nslices;
     const int lane = threadIdx.x & (WAVE - 1);

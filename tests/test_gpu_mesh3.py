@@ -51,3 +51,28 @@ def test_columns_bitwise_the_one_column_cycle(scr, nodes, coarse_max, precision)
         assert wrong == 0, (c, wrong, s.n_phys)
     h.destroy()
     ctx.destroy()
+
+
+# the classical kind: hybrid Gauss-Seidel sweeps of up to 1,024 domains of 64 rows, and of more
+@pytest.mark.parametrize("nodes", [700, 25e3, 140e3])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_classical_columns_bitwise_the_one_column_cycle(scr, nodes, precision):
+    s = synth.generate(synth.tube_params(nodes, 1.0, 5.0))
+    print(f"[gpu] classical mesh columns n={s.n_phys} precision={precision}", flush=True)
+    ctx = scr.Context(0)
+    h = scr.amg_setup(ctx, scr.MESH_SYSTEM, dev(s.Lrp), dev(s.Lci), dev(s.Lval), None,
+                      scr.amg_opts(amg_type=1, precision=precision))
+    b = synth.rhs(31, 3 * s.n_phys, np.repeat(s.Lmask, 3))
+    x = torch.zeros(3 * s.n_phys, dtype=torch.float64, device="cuda")
+    scr.mesh_motion_solve(h, dev(b), x, scr.solve_opts(tol=1e-30, max_it=1))
+    xs = x.cpu().numpy()
+    for c in range(3):
+        z = torch.empty(s.n_phys, dtype=torch.float64, device="cuda")
+        scr.scr_apply(h, "VL", dev(b[c::3]), z)
+        z, xc = z.cpu().numpy(), xs[c::3]
+        k = np.argmax(np.abs(z))
+        a = xc[k] / z[k]
+        wrong = min(np.count_nonzero(xc != (a + u * np.spacing(a)) * z) for u in range(-3, 4))
+        assert wrong == 0, (c, wrong, s.n_phys)
+    h.destroy()
+    ctx.destroy()
