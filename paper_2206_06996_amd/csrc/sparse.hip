@@ -4,8 +4,6 @@
 // are not dense contractions).
 #include <hip/hip_ext.h>
 
-#include <type_traits>
-
 #include "kernels.h"
 
 namespace scr {
@@ -454,7 +452,9 @@ template DBsrT<float> bsrt_from_bsr<float>(const DBsr&, Arena&, hipStream_t);
 //     spread evenly (k of every KEEP_PARTS), so that both kinds are in flight at all times.  One V-cycle of
 //     AMG(A), all nontemporal -> this: 22k nodes FP64 188 -> 152 us, 41k 319 -> 277, 100k 588 -> 538, 300k
 //     1,427 -> 1,337 (through the caches: 1,530), 700k 3,022 -> 2,950 (3,312); FP32 41k 235 -> 192, 100k
-//     370 -> 326, 300k 812 -> 755, 700k 1,684 -> 1,551.  96 to 192 MB are within 2 %.
+//     370 -> 326, 300k 812 -> 755, 700k 1,684 -> 1,551.  96 to 192 MB are within 2 %.  Of a matrix more than eight
+//     times as large nothing is kept: one slice in 16 gains its V-cycles less than 0.3 % (1.2M and 1.5M nodes)
+//     and costs the product by itself 3-5 % (295 against 286 us and 368 against 351).
 //   * 1x1 matrices always use the caches: two 16-byte loads share each line (nontemporal: 300k nodes FP64
 //     V-cycle of AMG(S^) 1,160 -> 1,570 us).
 //     Consecutive sweeps run in opposite directions (xcd_tile), so that each starts with what the last one
@@ -468,7 +468,8 @@ template <typename T>
 static int keep_of(const DSell<T>& A) {
     const double slot = A.rowlane ? WAVE * (3.0 * A.bc * sizeof(T) + 4.0) : WAVE * (double)A.bc * sizeof(T) + A.rps * 4.0;
     const double bytes = slot * (double)A.slots;
-    return bytes <= KEEP_BYTES ? KEEP_PARTS : (int)(KEEP_PARTS * KEEP_BYTES / bytes);
+    if (bytes <= KEEP_BYTES) return KEEP_PARTS;
+    return 8 * KEEP_BYTES < bytes ? 0 : (int)(KEEP_PARTS * KEEP_BYTES / bytes);
 }
 // (Keep: whether the size decides, and the choice where it does not)
 template <typename T, int BR, int BC> struct Keep {
@@ -581,43 +582,31 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
     T acc = 0;
     if (o0 >= o1) return acc;
     // software-pipelined as the block-row-lane loop: column indices one step ahead, x gathers and
-    // the next indices issued before the values, one memory round trip per step; a last step that is
-    // not full takes one slot alone (U = 2) or repeats the last slot with zero values
+    // the next indices issued before the values, one memory round trip per step; the slots of a last step
+    // that is not full are taken alone
     int32_t c[U];     // int32 until used, so that no sign extension waits for the load
 #pragma unroll
     for (int u = 0; u < U; ++u) c[u] = ci[(o0 + u < o1 ? o0 + u : o1 - 1) * RPS + cl];
-    auto step = [&](int64_t t, auto full) {
+    int64_t t = o0;
+    for (; t + U <= o1; t += U) {
         T xx[U][BC], vv[U][BC];
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < BC; ++k) xx[u][k] = xat((int64_t)c[u], k);
         int32_t cn[U];
-        if (full) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * RPS + cl];
-        }
+        for (int u = 0; u < U; ++u) cn[u] = ci[(t + U + u < o1 ? t + U + u : o1 - 1) * RPS + cl];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = full || t + u < o1;
-            sell_vals<T, BC, KEEP>(v, in ? t + u : o1 - 1, lane, vv[u]);
-            if (!in) {
-#pragma unroll
-                for (int k = 0; k < BC; ++k) vv[u][k] = 0;
-            }
-        }
+        for (int u = 0; u < U; ++u) sell_vals<T, BC, KEEP>(v, t + u, lane, vv[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < BC; ++k) acc += vv[u][k] * xx[u][k];
-        if (full) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) c[u] = cn[u];
-        }
-    };
-    int64_t t = o0;
-    for (; t + U <= o1; t += U) step(t, std::true_type{});
+        for (int u = 0; u < U; ++u) c[u] = cn[u];
+    }
     if constexpr (U == 2) {
         if (t < o1) {     // its index is already here
             T xx[BC], vv[BC];
@@ -627,8 +616,14 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
 #pragma unroll
             for (int k = 0; k < BC; ++k) acc += vv[k] * xx[k];
         }
-    } else if (t < o1) {
-        step(t, std::false_type{});
+    } else {
+        for (; t < o1; ++t) {
+            const int64_t col = ci[t * RPS + cl];
+            T vv[BC];
+            sell_vals<T, BC, KEEP>(v, t, lane, vv);
+#pragma unroll
+            for (int k = 0; k < BC; ++k) acc += vv[k] * xat(col, k);
+        }
     }
     return acc;
 }
@@ -713,11 +708,15 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
 // 392 us a V-cycle, in FP64 at 41k 346 -> 334) and up to 16 waves.  Measured on the refined tube (A/B on one box): a cap of 64K
 // instead of 16K waves puts 8 waves on each slice of AMG(A)'s level 1 (55 slots) and 4 on AMG(S^)'s
 // level 0 and makes the FP64 solve 5 % faster; 16 waves per slice on level 1 is slower again.
+// The couplings G (3x1, three lanes of a row gather the same x) and D (1x3) have 15 short slots a slice: beyond
+// `few` G keeps one wavefront per slice (by the rule / so: 117k nodes 30.6 / 28.0 us, 425k 59.4 / 49.3, 1.2M 172 / 159),
+// D up to 2,048 slices (52k nodes 26.0 / 23.4, 117k 33.2 / 29.9; 221k 39.0 / 41.8, 425k 57.3 / 62.8).
 template <typename T>
 static int waves_per_slice(const DSell<T>& A) {
     if (A.nslices <= 0) return 1;
     int64_t avg = A.slots / A.nslices;
     const bool few = A.nslices < (A.br == 6 ? 2048 : 512);
+    if (!few && (A.br > A.bc || (A.br < A.bc && A.nslices < 2048))) return 1;
     const int wmax = few ? 16 : 8, per = !few ? 3 : A.br == 6 ? 2 : 4;
     int w = 1;
     while (w < wmax && A.nslices * w < 65536 && avg >= per * (w * 2)) w *= 2;
