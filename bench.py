@@ -257,7 +257,9 @@ def _kt_bytes(levels):
                     add(f"bsrt_rows_k<{tn},{k},{b}>", nc * 384, rbytes, f"{name}{l} R")
                 else:
                     add(f"bsrt_mv_k<{tn},1,1,4>", nc * 256, rbytes, f"{name}{l} R")
-                    add(f"bsrt_mv3_k<{tn}>", ceil(nc / 4) * 256, L["nnzR"] * (tb + 4.0) + nr * 3 * tb + nc * (4.0 + 3 * tb), f"{name}{l} R")
+                    for w in (1, 4):
+                        add(f"bsrt_mv3_k<{tn},{w}>", ceil(nc * w / 4) * 256,
+                            L["nnzR"] * (tb + 4.0) + nr * 3 * tb + nc * (4.0 + 3 * tb), f"{name}{l} R")
     nb, nnzb = levels["n_b"], levels["nnzb"]
     for mode in (0, 1):
         add(f"sell_mv_split4_k<{mode}>", ceil(ceil(nb / 16) / 4) * 256,
@@ -284,7 +286,7 @@ def kernel_table(trace_dir, levels_json):
     files = glob.glob(os.path.join(trace_dir, "**", "*kernel_trace.csv"), recursive=True)
     if not files:
         raise SystemExit(f"no *kernel_trace.csv under {trace_dir}")
-    agg = {}
+    agg, strange = {}, {}
     total_ns = 0.0
     for f in files:
         for r in csv.DictReader(open(f)):
@@ -297,6 +299,8 @@ def kernel_table(trace_dir, levels_json):
             a["ns"] += ns
             key = _kt_key(name)
             hit = shapes.get(key, {}).get(grid) if key else None
+            if key in shapes and not hit:       # slice_grid and sell_parts have parted, or another matrix
+                strange[key] = strange.get(key, 0) + 1
             if hit:
                 a["bytes"] += hit[0]
                 a["bytes_ns"] += ns
@@ -323,6 +327,8 @@ def kernel_table(trace_dir, levels_json):
     print(f"\nKernels with a byte count (every dispatch matched to a level): {tt / 1e6:.1f} ms of {total_ns / 1e6:.1f} ms "
           f"kernel time ({100 * tt / total_ns:.1f} %), {tb / 1e9:.2f} GB algorithmic, "
           f"{tb / tt:.0f} GB/s = {tb / tt / HBM_PEAK_GBS:.3f} of 8 TB/s.")
+    for key, n in sorted(strange.items()):
+        print(f"warning: {n} dispatches of {key} have a grid that no level gives", file=sys.stderr)
 
 
 def load_reference(workload):
