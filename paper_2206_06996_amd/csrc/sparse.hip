@@ -574,7 +574,7 @@ __device__ __forceinline__ T sell_row_dot_g(int64_t o0, int64_t o1, int lane, co
 
 // acc = sum over the lane's row segments of v . x[col*BC : col*BC+BC]; cl = the lane's block row
 // within the slice (column indices are stored once per block row, RPS per slot)
-template <typename T, int BC, int RPS, bool KEEP, typename XF>
+template <typename T, int BC, int RPS, bool KEEP, bool SHORT, typename XF>
 __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int cl, const int32_t* __restrict__ ci,
                                           const T* __restrict__ v, XF xat) {
     if constexpr (BC == 1 && RPS == WAVE) return sell_row_dot_g<T>(o0, o1, lane, ci, v, xat);
@@ -583,7 +583,8 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
     if (o0 >= o1) return acc;
     // software-pipelined as the block-row-lane loop: column indices one step ahead, x gathers and
     // the next indices issued before the values, one memory round trip per step; the slots of a last step
-    // that is not full are taken alone
+    // that is not full are taken alone, or (SHORT: few slots a wavefront) the step repeats the last slot with
+    // zero values: alone, seven slots of a shared slice of G are seven round trips; so, K at 1.2M nodes 556 -> 567 us
     int32_t c[U];     // int32 until used, so that no sign extension waits for the load
 #pragma unroll
     for (int u = 0; u < U; ++u) c[u] = ci[(o0 + u < o1 ? o0 + u : o1 - 1) * RPS + cl];
@@ -615,6 +616,27 @@ __device__ __forceinline__ T sell_row_dot(int64_t o0, int64_t o1, int lane, int 
             sell_vals<T, BC, KEEP>(v, t, lane, vv);
 #pragma unroll
             for (int k = 0; k < BC; ++k) acc += vv[k] * xx[k];
+        }
+    } else if constexpr (SHORT) {
+        if (t < o1) {     // its indices are already here
+            T xx[U][BC], vv[U][BC];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < BC; ++k) xx[u][k] = xat((int64_t)c[u], k);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                sell_vals<T, BC, KEEP>(v, t + u < o1 ? t + u : o1 - 1, lane, vv[u]);
+                if (t + u >= o1) {
+#pragma unroll
+                    for (int k = 0; k < BC; ++k) vv[u][k] = 0;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < BC; ++k) acc += vv[u][k] * xx[u][k];
         }
     } else {
         for (; t < o1; ++t) {
@@ -681,9 +703,9 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
         int64_t a, e;
         slice_part<WPS, (BR == 1 && BC == 1) ? SELL_G : 1>(off[sl], off[sl + 1], wv % WPS, a, e);
         using K = Keep<T, BR, BC>;
-        if constexpr (!K::BY_SIZE) acc = sell_row_dot<T, BC, RPS, K::ALWAYS>(a, e, lane, cl, ci, v, xat);
-        else acc = keep_slice(sl, keep) ? sell_row_dot<T, BC, RPS, true>(a, e, lane, cl, ci, v, xat)
-                                        : sell_row_dot<T, BC, RPS, false>(a, e, lane, cl, ci, v, xat);
+        if constexpr (!K::BY_SIZE) acc = sell_row_dot<T, BC, RPS, K::ALWAYS, (WPS > 1)>(a, e, lane, cl, ci, v, xat);
+        else acc = keep_slice(sl, keep) ? sell_row_dot<T, BC, RPS, true, (WPS > 1)>(a, e, lane, cl, ci, v, xat)
+                                        : sell_row_dot<T, BC, RPS, false, (WPS > 1)>(a, e, lane, cl, ci, v, xat);
     }
     if (WPS > 1) {
         __shared__ T red[SliceGroup<WPS>::SPB * WPS][WAVE];
@@ -1012,7 +1034,7 @@ __global__ void __launch_bounds__(256) sell_mv_split4_k(int64_t nr, int64_t nsli
     int lane = threadIdx.x & (WAVE - 1);
     const double* xp = x + 3 * nr;
     auto xat = [&](int64_t c, int k) { return k < 3 ? x[3 * c + k] : xp[c]; };
-    double acc = sell_row_dot<double, 4, RPS, false>(off[sl], off[sl + 1], lane, lane / 4, ci, v, xat);
+    double acc = sell_row_dot<double, 4, RPS, false, false>(off[sl], off[sl + 1], lane, lane / 4, ci, v, xat);
     int64_t i = rowid[sl * RPS + lane / 4];
     if (i < 0) return;
     int r = lane & 3;
@@ -1184,9 +1206,9 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
         auto xat = [&](int64_t c, int k) { return xin[c * B + k]; };
         int64_t a, e;
         slice_part<WPS, B == 1 ? SELL_G : 1>(off[sl], off[sl + 1], wv % WPS, a, e);
-        if constexpr (B == 1) acc = sell_row_dot<T, B, RPS, true>(a, e, lane, cl, ci, v, xat);
-        else acc = keep_slice(sl, keep) ? sell_row_dot<T, B, RPS, true>(a, e, lane, cl, ci, v, xat)
-                                        : sell_row_dot<T, B, RPS, false>(a, e, lane, cl, ci, v, xat);
+        if constexpr (B == 1) acc = sell_row_dot<T, B, RPS, true, (WPS > 1)>(a, e, lane, cl, ci, v, xat);
+        else acc = keep_slice(sl, keep) ? sell_row_dot<T, B, RPS, true, (WPS > 1)>(a, e, lane, cl, ci, v, xat)
+                                        : sell_row_dot<T, B, RPS, false, (WPS > 1)>(a, e, lane, cl, ci, v, xat);
     }
     if (WPS > 1) {
         __shared__ T red[SliceGroup<WPS>::SPB * WPS][WAVE];
