@@ -262,8 +262,9 @@ def _kt_bytes(levels):
                             L["nnzR"] * (tb + 4.0) + nr * 3 * tb + nc * (4.0 + 3 * tb), f"{name}{l} R")
     nb, nnzb = levels["n_b"], levels["nnzb"]
     for mode in (0, 1):
-        add(f"sell_mv_split4_k<{mode}>", ceil(ceil(nb / 16) / 4) * 256,
-            nnzb * (16 * 8.0 + 4.0) + nb * (4.0 + 32.0 * (2 + mode)), "K")
+        for short in (0, 1):
+            add(f"sell_mv_split4_k<{mode},{short}>", ceil(ceil(nb / 16) / 4) * 256,
+                nnzb * (16 * 8.0 + 4.0) + nb * (4.0 + 32.0 * (2 + mode)), "K")
     return shapes
 
 
