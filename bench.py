@@ -246,9 +246,9 @@ def _kt_bytes(levels):
                     for w in (1, 2, 4, 8):
                         add(f"sell_mv_rl3_k<{tn},{k},2,{w}>", slice_grid(nr, 1, w), pbytes, f"{name}{l} P")
                 for w in (1, 2, 4, 8, 16):
-                    add(f"sell_mv_k<{tn},{b},{k},2,{w}>", slice_grid(nr, b, w), pbytes, f"{name}{l} P")
+                    add(f"sell_mv_k<{tn},{b},{k},2,{w}>", slice_grid(nr, b, w, nnzp if b == k else 0), pbytes, f"{name}{l} P")
                     if b == 1:
-                        add(f"sell_mv3_k<{tn},2,{w}>", slice_grid(nr, 1, w),
+                        add(f"sell_mv3_k<{tn},2,{w}>", slice_grid(nr, 1, w, nnzp),
                             nnzp * (tb + 4.0) + nc * 3 * tb + nr * (4.0 + 6 * tb), f"{name}{l} P")
                 # restriction y = R x (R: nc x nr blocks k x b)
                 rbytes = L["nnzR"] * (k * b * tb + 4.0) + nr * b * tb + nc * (4.0 + k * tb)
