@@ -223,9 +223,10 @@ def _kt_bytes(levels):
                             add(f"smooth_k<{tn},{b},{rd},{wd},0,{w}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l}")
                             add(f"smooth_k<{tn},{b},0,{wd},1,{w}>", slice_grid(nr, b, w, nnz), zero, f"{name}{l}")
                             if b == 1:
-                                add(f"smooth3_k<{tn},{rd},{wd},0,{w}>", slice_grid(nr, 1, w, nnz),
-                                    nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * (3 + rd + wd)), f"{name}{l}")
-                                add(f"smooth3_k<{tn},0,{wd},1,{w}>", slice_grid(nr, 1, w, nnz), nr * (4.0 + 3 * tb * (2 + wd)),
+                                for lo in (0, 1):
+                                    add(f"smooth3_k<{tn},{rd},{wd},0,{w},{lo}>", slice_grid(nr, 1, w, nnz),
+                                        nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * (3 + rd + wd)), f"{name}{l}")
+                                add(f"smooth3_k<{tn},0,{wd},1,{w},0>", slice_grid(nr, 1, w, nnz), nr * (4.0 + 3 * tb * (2 + wd)),
                                     f"{name}{l}")
                 # products with A_l (residual y = b - A x: x, b read, y written)
                 for mode in (0, 1, 3):
@@ -237,8 +238,9 @@ def _kt_bytes(levels):
                     for w in (1, 2, 4, 8, 16):
                         add(f"sell_mv_k<{tn},{b},{b},{mode},{w}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l} A")
                         if b == 1:
-                            add(f"sell_mv3_k<{tn},{mode},{w}>", slice_grid(nr, 1, w, nnz), nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * nv),
-                                f"{name}{l} A")
+                            for lo in (0, 1):
+                                add(f"sell_mv3_k<{tn},{mode},{w},{lo}>", slice_grid(nr, 1, w, nnz),
+                                    nnz * (tb + 4.0) + nr * (4.0 + 3 * tb * nv), f"{name}{l} A")
                 # prolongation y += P x (P: nr x nc blocks b x k; x coarse, y read and written)
                 nc, nnzp = L["nagg"], L["nnzP"]
                 pbytes = nnzp * (b * k * tb + 4.0) + nc * k * tb + nr * (4.0 + 2 * b * tb)
@@ -248,8 +250,9 @@ def _kt_bytes(levels):
                 for w in (1, 2, 4, 8, 16):
                     add(f"sell_mv_k<{tn},{b},{k},2,{w}>", slice_grid(nr, b, w, nnzp if b == k else 0), pbytes, f"{name}{l} P")
                     if b == 1:
-                        add(f"sell_mv3_k<{tn},2,{w}>", slice_grid(nr, 1, w, nnzp),
-                            nnzp * (tb + 4.0) + nc * 3 * tb + nr * (4.0 + 6 * tb), f"{name}{l} P")
+                        for lo in (0, 1):
+                            add(f"sell_mv3_k<{tn},2,{w},{lo}>", slice_grid(nr, 1, w, nnzp),
+                                nnzp * (tb + 4.0) + nc * 3 * tb + nr * (4.0 + 6 * tb), f"{name}{l} P")
                 # restriction y = R x (R: nc x nr blocks k x b)
                 rbytes = L["nnzR"] * (k * b * tb + 4.0) + nr * b * tb + nc * (4.0 + k * tb)
                 add(f"bsrt_mv_k<{tn},{k},{b},1>", ceil(nc / 4) * 256, rbytes, f"{name}{l} R")

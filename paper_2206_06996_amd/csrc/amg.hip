@@ -2193,6 +2193,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(const DBsr& A0, const double* B0, int
     {
         LevelSetup l0;
         l0.A = bsr_alloc(A0.nr, A0.nc, A0.br, A0.bc, A0.nnzb, ar);
+        l0.A.wmax = A0.wmax;
         copy_dev(l0.A.rp, A0.rp, (A0.nr + 1) * sizeof(int32_t), s);
         copy_dev(l0.A.ci, A0.ci, A0.nnzb * sizeof(int32_t), s);
         copy_dev(l0.A.v, A0.v, A0.nnzb * A0.br * A0.bc * sizeof(double), s);

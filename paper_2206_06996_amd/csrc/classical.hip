@@ -1046,6 +1046,7 @@ void setup_levels(ClassicalBase& H, const DBsr& A0, const scr_amg_opts& o, Arena
         const int b = A0.br;
         const int64_t n = A0.nr * b;
         l0.A = bsr_alloc(n, A0.nc * b, 1, 1, A0.nnzb * b * b, ar);
+        l0.A.wmax = A0.wmax * b;
         l0.b = 1; l0.k = 1;
         l0.func = ar.make<uint8_t>(n > 0 ? n : 1);
         if (A0.nr) to_scalar_k<<<(unsigned)cdiv(A0.nr, 256), 256, 0, s>>>(A0.nr, b, A0.rp, A0.ci, A0.v, l0.A.rp, l0.A.ci,

@@ -283,7 +283,8 @@ struct DBsr {
     int32_t* rp = nullptr;
     int32_t* ci = nullptr;
     double* v = nullptr;
-    int wmax = 0, wmax_cols = 0;     // results of spgemm: the longest row, and the widest (last - first column + 1)
+    int wmax = 0;                    // the longest row: of products, and of input matrices if it has SELL_LONG entries
+    int wmax_cols = 0;               // of products: the widest row (last - first column + 1)
 };
 
 // Sliced ELL, two lane mappings.
@@ -315,6 +316,7 @@ struct DBsr {
 // slices of 21 rows for scalar-row lanes, 6 slices of 64 rows for block-row lanes (measured).
 constexpr int SELL_SIGMA = 16;
 constexpr int SELL_SIGMA_ROWLANE = 6;
+constexpr int SELL_LONG = 1024;    // rows of so many entries change the three-column sweeps (slice_wave)
 template <typename T>
 struct DSell {
     int64_t nr = 0, nc = 0;
@@ -325,6 +327,7 @@ struct DSell {
     int64_t nslices = 0;
     int64_t slots = 0;          // sum over slices of the slice length
     int64_t nnzb = 0;           // stored blocks before padding (algorithmic count)
+    bool long_rows = false;     // a row has SELL_LONG entries or more
     int32_t* off = nullptr;     // nslices + 1 (slot offsets)
     int32_t* rowid = nullptr;   // nslices * rps
     int32_t* ci = nullptr;

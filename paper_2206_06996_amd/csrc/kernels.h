@@ -66,9 +66,10 @@ template <typename T>
 void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T* d, T* xout, double c1, double c2,
                   bool read_d, bool write_d, bool zero_in, bool down, hipStream_t s);
 template <typename T> void dense_mv3(int64_t n, const double* M, const T* b, T* x, hipStream_t s);
-// validate a square BSR (device); returns error bits (synchronises)
+// validate a square BSR (device); returns error bits (synchronises).  longest: receives the longest row's entries, or
+// 0 if no row has SELL_LONG
 int validate_bsr(int64_t nr, int bs, int64_t nnzb, const int32_t* rp, const int32_t* ci, const double* v,
-                 Arena& ar, hipStream_t s);
+                 Arena& ar, hipStream_t s, int* longest = nullptr);
 
 // ---------------------------------------------------------------- operator forms (assemble.hip)
 // The linear(ised) semi-discrete residual of the unified continuum (Sec. 3.1, 3.2 at rest, 3.5) is

@@ -509,7 +509,8 @@ scr_status amg_setup(scr_ctx* ctx, int kind, const scr_bsr* K, const double* coo
         HIPCHK(hipMemcpyAsync(&ends[1], K->row_ptr + nb, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         if (ends[0] != 0 || ends[1] != K->nnzb) throw Error(SCR_E_INVALID, "row_ptr[0] != 0 or row_ptr[n] != nnzb");
-        int bits = validate_bsr(nb, K->bs, K->nnzb, K->row_ptr, K->col_idx, K->val, ar, s);
+        int longest = 0;
+        int bits = validate_bsr(nb, K->bs, K->nnzb, K->row_ptr, K->col_idx, K->val, ar, s, &longest);
         if (bits) {
             std::string m = "malformed matrix:";
             if (bits & 1) m += " row_ptr";
@@ -522,6 +523,7 @@ scr_status amg_setup(scr_ctx* ctx, int kind, const scr_bsr* K, const double* coo
         }
         DBsr& Km = h->K;
         Km.nr = Km.nc = nb; Km.br = Km.bc = K->bs; Km.nnzb = K->nnzb;
+        Km.wmax = longest;
         Km.rp = ar.make<int32_t>(nb + 1);
         Km.ci = ar.make<int32_t>(K->nnzb);
         Km.v = ar.make<double>(K->nnzb * K->bs * K->bs);

@@ -365,6 +365,7 @@ template <typename T>
 DSell<T> sell_from_bsr(const DBsr& A, Arena& ar, hipStream_t s) {
     DSell<T> S;
     S.nr = A.nr; S.nc = A.nc; S.br = A.br; S.bc = A.bc; S.nnzb = A.nnzb;
+    S.long_rows = A.wmax >= SELL_LONG;
     S.rowlane = A.br == 3 && (A.bc == 3 || A.bc == 6);
     S.rps = S.rowlane ? WAVE : WAVE / A.br;
     S.sp = sell_parts(A);
@@ -1465,12 +1466,22 @@ __device__ __forceinline__ void sell_row_dot3(int64_t o0, int64_t o1, int lane, 
             for (int k = 0; k < 3; ++k) acc[k] += vv[j] * xx[j][k];
     }
 }
-template <typename T, int MODE, int WPS>
+// The wavefront of the workgroup: a scalar, or (LONG: matrices with a row of SELL_LONG entries) a value per lane.
+// Ten CG iterations on three columns, scalar / per lane: tubes of 100k nodes 2.08 / 2.15 ms, of 1M 16.8 / 17.8, with
+// the V-cycle in FP32 11.7 / 12.7; a 200 x 200 grid with four rows of 10,000 entries 24.4 / 20.0, of 5,000
+// 12.8 / 10.6, of 1,250 5.4 / 5.2, of 630 3.2 / 3.2 (over a long slice the scalar form's launches alternate between
+// 108 and 140 us).
+template <bool LONG>
+__device__ __forceinline__ int slice_wave() {
+    if constexpr (LONG) return threadIdx.x / WAVE;
+    else return __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+}
+template <typename T, int MODE, int WPS, bool LONG>
 __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t nslices, bool down, int sp, const int32_t* __restrict__ off,
                                                   const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                   const T* __restrict__ v, const T* __restrict__ x,
                                                   const T* __restrict__ b, T* __restrict__ y) {
-    const int wv = threadIdx.x / WAVE;
+    const int wv = slice_wave<LONG>();
     const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
@@ -1521,17 +1532,26 @@ void sell_mv3(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool do
         constexpr int W_ = W;                                                                                   \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W_>::SPB)), th(SliceGroup<W_>::THREADS);                    \
         switch (mode) {                                                                                         \
-            case 0: sell_mv3_k<T, 0, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv3_k<T, 1, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv3_k<T, 2, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv3_k<T, 3, W_><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv3_k<T, 0, W_, LONG><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv3_k<T, 1, W_, LONG><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv3_k<T, 2, W_, LONG><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv3_k<T, 3, W_, LONG><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                       \
     }
-    if (wps == 1) MV3(1)
-    else if (wps == 2) MV3(2)
-    else if (wps == 4) MV3(4)
-    else if (wps == 8) MV3(8)
+#define MV3W()            \
+    if (wps == 1) MV3(1)  \
+    else if (wps == 2) MV3(2) \
+    else if (wps == 4) MV3(4) \
+    else if (wps == 8) MV3(8) \
     else MV3(16)
+    if (A.long_rows) {
+        constexpr bool LONG = true;
+        MV3W()
+    } else {
+        constexpr bool LONG = false;
+        MV3W()
+    }
+#undef MV3W
 #undef MV3
     check_launch("sell_mv3");
 }
@@ -1586,13 +1606,13 @@ template void bsrt_mv3<double>(const DBsrT<double>&, const double*, double*, hip
 template void bsrt_mv3<float>(const DBsrT<float>&, const float*, float*, hipStream_t);
 
 // one smoothing step on three columns (1x1 blocks): as smooth_k with B = 1, per column
-template <typename T, bool RD, bool WD, bool ZERO, int WPS>
+template <typename T, bool RD, bool WD, bool ZERO, int WPS, bool LONG>
 __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth3_k(int64_t nslices, bool down, int sp, const int32_t* __restrict__ off,
                                                  const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ Dinv,
                                                  const T* __restrict__ b, const T* __restrict__ xin, T* __restrict__ d,
                                                  T* __restrict__ xout, T c1, T c2) {
-    const int wv = threadIdx.x / WAVE;
+    const int wv = slice_wave<LONG>();
     const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const bool live = sl < nslices;
     const int lane = threadIdx.x & (WAVE - 1);
@@ -1650,11 +1670,13 @@ void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T*
     if (A.nslices == 0) return;
     const T C1 = (T)c1, C2 = (T)c2;
     int wps = zero_in ? 1 : waves_per_slice(A);
+#define S3L(RD, WD, Z, W, LONG)                                                                                  \
+    smooth3_k<T, RD, WD, Z, W, LONG><<<(unsigned)cdiv(A.nslices, SliceGroup<W>::SPB), SliceGroup<W>::THREADS, 0, s>>>( \
+        A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, xout, C1, C2)
 #define S3W(RD, WD, Z, W)                                                                                        \
     do {                                                                                                         \
-        dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), th(SliceGroup<W>::THREADS);                        \
-        smooth3_k<T, RD, WD, Z, W><<<g, th, 0, s>>>(A.nslices, down, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d, xout,  \
-                                                   C1, C2);                                                      \
+        if (!Z && A.long_rows) S3L(RD, WD, Z, W, !Z);                                                            \
+        else S3L(RD, WD, Z, W, false);                                                                           \
     } while (0)
 #define S3(RD, WD, Z)                                                                                            \
     do {                                                                                                         \
@@ -1673,6 +1695,7 @@ void smooth_step3(const DSell<T>& A, const T* Dinv, const T* b, const T* xin, T*
     }
 #undef S3
 #undef S3W
+#undef S3L
     check_launch("smooth_step3");
 }
 template void smooth_step3<double>(const DSell<double>&, const double*, const double*, const double*, double*,
@@ -1757,6 +1780,7 @@ template void dense_mv<float>(int64_t, const double*, const float*, float*, hipS
 // ---------------------------------------------------------------- input validation
 // bits: 1 row_ptr, 2 column out of range, 4 unsorted/duplicate, 8 missing diagonal,
 //       16 non-finite value, 32 zero on the velocity diagonal (bs 4) or the diagonal (bs 1)
+// flags[1]: the longest row, if it has SELL_LONG entries (no atomics for others)
 // One wavefront per row (lane l checks entries lo + l, lo + l + 64, ...); the bits found are OR-ed
 // over the wavefront and raised by one atomic.
 __global__ void __launch_bounds__(256) validate_k(int64_t nr, int bs, int64_t nnzb, const int32_t* __restrict__ rp,
@@ -1790,21 +1814,23 @@ __global__ void __launch_bounds__(256) validate_k(int64_t nr, int bs, int64_t nn
         }
     }
     if (!__any(diag)) f |= 8;
+    if (lane == 0 && hi - lo >= SELL_LONG) atomicMax(flags + 1, (int)(hi - lo));
     for (int o = WAVE / 2; o > 0; o >>= 1) f |= __shfl_xor(f, o, WAVE);
     if (lane == 0 && f) atomicOr(flags, f);
 }
 
 int validate_bsr(int64_t nr, int bs, int64_t nnzb, const int32_t* rp, const int32_t* ci, const double* v, Arena& ar,
-                 hipStream_t s) {
-    int* flags = ar.make<int>(1);
-    zero_dev(flags, sizeof(int), s);
+                 hipStream_t s, int* longest) {
+    int* flags = ar.make<int>(2);
+    zero_dev(flags, 2 * sizeof(int), s);
     if (nr > 0) validate_k<<<cdiv(nr, 256 / WAVE), 256, 0, s>>>(nr, bs, nnzb, rp, ci, v, flags);
     check_launch("validate");
-    int h = 0;
-    HIPCHK(hipMemcpyAsync(&h, flags, sizeof(int), hipMemcpyDeviceToHost, s));
+    int h[2] = {0, 0};
+    HIPCHK(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     ar.free(flags);
-    return h;
+    if (longest) *longest = h[1];
+    return h[0];
 }
 
 }  // namespace scr

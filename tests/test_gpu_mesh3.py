@@ -76,3 +76,39 @@ def test_classical_columns_bitwise_the_one_column_cycle(scr, nodes, precision):
         assert wrong == 0, (c, wrong, s.n_phys)
     h.destroy()
     ctx.destroy()
+
+
+# a grid whose last row couples to `longest` - 1 nodes: both sides of the length that changes the sweeps
+@pytest.mark.parametrize("longest", [1023, 1024, 4097])
+@pytest.mark.parametrize("amg_type", [0, 1])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_columns_bitwise_with_a_long_row(scr, longest, amg_type, precision):
+    sps = pytest.importorskip("scipy.sparse")
+    n, eps = 64, 1e-3
+    T = sps.diags([-np.ones(n - 1), 2 * np.ones(n), -np.ones(n - 1)], [-1, 0, 1])
+    L = sps.kron(sps.identity(n), T) + sps.kron(T, sps.identity(n))
+    w = np.where(np.arange(n * n) < longest - 1, eps, 0.0)
+    B = sps.csr_matrix(-w[:, None])
+    B.eliminate_zeros()
+    A = sps.bmat([[L + sps.diags(w), B], [B.T, sps.csr_matrix([[w.sum() + 1.0]])]], format="csr")
+    A.sort_indices()
+    N = A.shape[0]
+    assert np.diff(A.indptr).max() == longest
+    print(f"[gpu] mesh columns, longest row {longest} kind={amg_type} precision={precision}", flush=True)
+    ctx = scr.Context(0)
+    h = scr.amg_setup(ctx, scr.MESH_SYSTEM, dev(A.indptr.astype(np.int32)), dev(A.indices.astype(np.int32)), dev(A.data),
+                      None, scr.amg_opts(amg_type=amg_type, precision=precision))
+    b = synth.rhs(31, 3 * N)
+    x = torch.zeros(3 * N, dtype=torch.float64, device="cuda")
+    scr.mesh_motion_solve(h, dev(b), x, scr.solve_opts(tol=1e-30, max_it=1))
+    xs = x.cpu().numpy()
+    for c in range(3):
+        z = torch.empty(N, dtype=torch.float64, device="cuda")
+        scr.scr_apply(h, "VL", dev(b[c::3]), z)
+        z, xc = z.cpu().numpy(), xs[c::3]
+        k = np.argmax(np.abs(z))
+        a = xc[k] / z[k]
+        wrong = min(np.count_nonzero(xc != (a + u * np.spacing(a)) * z) for u in range(-3, 4))
+        assert wrong == 0, (c, wrong, N)
+    h.destroy()
+    ctx.destroy()
