@@ -220,8 +220,9 @@ def _kt_bytes(levels):
                                 add(f"smooth_rl3_k<{tn},{rd},{wd},0,{w}>", slice_grid(nr, 1, w), byts, f"{name}{l}")
                             add(f"smooth_rl3_k<{tn},0,{wd},1,1>", slice_grid(nr, 1, 1), zero, f"{name}{l}")
                         for w in (1, 2, 4, 8, 16):
-                            add(f"smooth_k<{tn},{b},{rd},{wd},0,{w}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l}")
-                            add(f"smooth_k<{tn},{b},0,{wd},1,{w}>", slice_grid(nr, b, w, nnz), zero, f"{name}{l}")
+                            for lo in (0, 1):
+                                add(f"smooth_k<{tn},{b},{rd},{wd},0,{w},{lo}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l}")
+                            add(f"smooth_k<{tn},{b},0,{wd},1,{w},0>", slice_grid(nr, b, w, nnz), zero, f"{name}{l}")
                             if b == 1:
                                 for lo in (0, 1):
                                     add(f"smooth3_k<{tn},{rd},{wd},0,{w},{lo}>", slice_grid(nr, 1, w, nnz),
@@ -236,7 +237,8 @@ def _kt_bytes(levels):
                         for w in (1, 2, 4, 8):
                             add(f"sell_mv_rl3_k<{tn},3,{mode},{w}>", slice_grid(nr, 1, w), byts, f"{name}{l} A")
                     for w in (1, 2, 4, 8, 16):
-                        add(f"sell_mv_k<{tn},{b},{b},{mode},{w}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l} A")
+                        for lo in (0, 1):
+                            add(f"sell_mv_k<{tn},{b},{b},{mode},{w},{lo}>", slice_grid(nr, b, w, nnz), byts, f"{name}{l} A")
                         if b == 1:
                             for lo in (0, 1):
                                 add(f"sell_mv3_k<{tn},{mode},{w},{lo}>", slice_grid(nr, 1, w, nnz),
@@ -248,7 +250,9 @@ def _kt_bytes(levels):
                     for w in (1, 2, 4, 8):
                         add(f"sell_mv_rl3_k<{tn},{k},2,{w}>", slice_grid(nr, 1, w), pbytes, f"{name}{l} P")
                 for w in (1, 2, 4, 8, 16):
-                    add(f"sell_mv_k<{tn},{b},{k},2,{w}>", slice_grid(nr, b, w, nnzp if b == k else 0), pbytes, f"{name}{l} P")
+                    for lo in (0, 1):
+                        add(f"sell_mv_k<{tn},{b},{k},2,{w},{lo}>", slice_grid(nr, b, w, nnzp if b == k else 0), pbytes,
+                            f"{name}{l} P")
                     if b == 1:
                         for lo in (0, 1):
                             add(f"sell_mv3_k<{tn},2,{w},{lo}>", slice_grid(nr, 1, w, nnzp),

@@ -316,7 +316,7 @@ struct DBsr {
 // slices of 21 rows for scalar-row lanes, 6 slices of 64 rows for block-row lanes (measured).
 constexpr int SELL_SIGMA = 16;
 constexpr int SELL_SIGMA_ROWLANE = 6;
-constexpr int SELL_LONG = 1024;    // rows of so many entries change the three-column sweeps (slice_wave)
+constexpr int SELL_LONG = 512;    // a row of so many entries changes the 1x1 sweeps and products (slice_wave)
 template <typename T>
 struct DSell {
     int64_t nr = 0, nc = 0;

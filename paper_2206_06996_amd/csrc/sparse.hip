@@ -681,13 +681,25 @@ __device__ __forceinline__ T parts_sum(T acc, int lane, int sp) {
     }
 }
 
-template <typename T, int BR, int BC, int MODE, int WPS>
+// The wavefront of the workgroup: a scalar, or (LONG: 1x1 matrices with a row of SELL_LONG entries) a value per lane.
+// Over a long slice the scalar form's launches alternate between 108 and 140 us, though the loops are alike; over
+// short ones it is the faster.  Scalar / per lane: ten CG iterations on three columns, tubes of 100k nodes
+// 2.08 / 2.15 ms, of 1M 16.8 / 17.8, with FP32 V-cycles 11.7 / 12.7; 200 x 200 grids with four rows of 10,000
+// entries 24.4 / 20.0, of 5,000 12.8 / 10.6, of 835 4.05 / 3.77, of 560 3.00 / 2.81.  V-cycles on one column, FP32:
+// 5,000 entries 626 / 560 us, 835 279 / 264; a solve at 300k nodes is 0.4 % slower per lane, a Schur product at 1.5M
+// 1.1 %.
+template <bool LONG>
+__device__ __forceinline__ int slice_wave() {
+    if constexpr (LONG) return threadIdx.x / WAVE;
+    else return __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+}
+template <typename T, int BR, int BC, int MODE, int WPS, bool LONG>
 __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t nslices, bool down, int keep, int sp, const int32_t* __restrict__ off,
                                                  const int32_t* __restrict__ rowid, const int32_t* __restrict__ ci,
                                                  const T* __restrict__ v, const T* __restrict__ x,
                                                  const T* __restrict__ b, T* __restrict__ y) {
     constexpr int RPS = WAVE / BR;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int wv = slice_wave<LONG>();
     const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool live = sl < nslices;
@@ -957,8 +969,8 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_rl3_k(int64_
     }
 }
 
-template <typename T, int BR, int BC>
-static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
+template <typename T, int BR, int BC, bool LONG>
+static void sell_mv_launch(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
     const int wps = waves_per_slice(A), keep = keep_of(A);
     if (A.nslices == 0) return;
 #define MV(W)                                                                                                  \
@@ -967,10 +979,10 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
         int64_t nblk = cdiv(A.nslices, SliceGroup<W_>::SPB);                                                   \
         dim3 g((unsigned)nblk), t(SliceGroup<W_>::THREADS);                                                     \
         switch (mode) {                                                                                        \
-            case 0: sell_mv_k<T, BR, BC, 0, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 1: sell_mv_k<T, BR, BC, 1, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            case 2: sell_mv_k<T, BR, BC, 2, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
-            default: sell_mv_k<T, BR, BC, 3, W_><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 0: sell_mv_k<T, BR, BC, 0, W_, LONG><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 1: sell_mv_k<T, BR, BC, 1, W_, LONG><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            case 2: sell_mv_k<T, BR, BC, 2, W_, LONG><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
+            default: sell_mv_k<T, BR, BC, 3, W_, LONG><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, x, b, y); break; \
         }                                                                                                      \
     }
     if (wps == 1) MV(1)
@@ -980,6 +992,11 @@ static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* 
     else MV(16)
 #undef MV
     check_launch("sell_mv");
+}
+template <typename T, int BR, int BC>
+static void sell_mv_dispatch_mode(const DSell<T>& A, const T* x, const T* b, T* y, int mode, bool down, hipStream_t s) {
+    if (BR == 1 && BC == 1 && A.long_rows) sell_mv_launch<T, BR, BC, BR == 1 && BC == 1>(A, x, b, y, mode, down, s);
+    else sell_mv_launch<T, BR, BC, false>(A, x, b, y, mode, down, s);
 }
 
 template <typename T>
@@ -1181,7 +1198,7 @@ template void bsrt_mv<float>(const DBsrT<float>&, const float*, float*, hipStrea
 // ---------------------------------------------------------------- fused smoother step
 // dn = c1*d + c2*Dinv*(b - A xin) ; xout = xin + dn.  One lane per scalar row; the block
 // residual of a block row is gathered from its B lanes with shuffles to apply Dinv.
-template <typename T, int B, bool RD, bool WD, bool ZERO, int WPS>
+template <typename T, int B, bool RD, bool WD, bool ZERO, int WPS, bool LONG>
 __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nslices, bool down, int keep, int sp, const int32_t* __restrict__ off,
                                                 const int32_t* __restrict__ rowid,
                                                 const int32_t* __restrict__ ci, const T* __restrict__ v,
@@ -1189,7 +1206,7 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) smooth_k(int64_t nsl
                                                 const T* __restrict__ xin, T* __restrict__ d, T* __restrict__ xout,
                                                 T c1, T c2) {
     constexpr int RPS = WAVE / B;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int wv = slice_wave<LONG>();
     const int64_t sl = xcd_tile(blockIdx.x, gridDim.x, down) * SliceGroup<WPS>::SPB + wv / WPS;
     const bool live = sl < nslices;
     const int lane = threadIdx.x & (WAVE - 1);
@@ -1364,16 +1381,21 @@ static void smooth_dispatch(const DSell<T>& A, const T* Dinv, const T* b, const 
                             bool rd, bool wd, bool zero, bool down, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const int wps = zero ? 1 : waves_per_slice(A), keep = keep_of(A);
     if (A.nslices == 0) return;
-#define SKW(RD, WD, Z, W)                                                                                          \
+#define SKL(RD, WD, Z, W, LONG)                                                                                    \
     do {                                                                                                           \
         dim3 g((unsigned)cdiv(A.nslices, SliceGroup<W>::SPB)), t(SliceGroup<W>::THREADS);                          \
         if (e0)                                                                                                    \
-            hipExtLaunchKernelGGL((smooth_k<T, B, RD, WD, Z, W>), g, t, 0, s, e0, e1, 0, A.nslices, down, keep, A.sp,          \
+            hipExtLaunchKernelGGL((smooth_k<T, B, RD, WD, Z, W, LONG>), g, t, 0, s, e0, e1, 0, A.nslices, down, keep, A.sp,          \
                                   (const int32_t*)A.off, (const int32_t*)A.rowid, (const int32_t*)A.ci,            \
                                   (const T*)A.v, Dinv, b, xin, d, xout, c1, c2);                                   \
         else                                                                                                       \
-            smooth_k<T, B, RD, WD, Z, W><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, Dinv, b, xin, d,    \
-                                                        xout, c1, c2);                                             \
+            smooth_k<T, B, RD, WD, Z, W, LONG><<<g, t, 0, s>>>(A.nslices, down, keep, A.sp, A.off, A.rowid, A.ci, A.v, \
+                                                              Dinv, b, xin, d, xout, c1, c2);                      \
+    } while (0)
+#define SKW(RD, WD, Z, W)                                                                                          \
+    do {                                                                                                           \
+        if (B == 1 && !Z && A.long_rows) SKL(RD, WD, Z, W, (B == 1 && !Z));                                        \
+        else SKL(RD, WD, Z, W, false);                                                                             \
     } while (0)
 #define SK(RD, WD, Z)                                                                                              \
     do {                                                                                                           \
@@ -1392,6 +1414,7 @@ static void smooth_dispatch(const DSell<T>& A, const T* Dinv, const T* b, const 
     }
 #undef SK
 #undef SKW
+#undef SKL
     check_launch("smooth_step");
 }
 
@@ -1465,16 +1488,6 @@ __device__ __forceinline__ void sell_row_dot3(int64_t o0, int64_t o1, int lane, 
 #pragma unroll
             for (int k = 0; k < 3; ++k) acc[k] += vv[j] * xx[j][k];
     }
-}
-// The wavefront of the workgroup: a scalar, or (LONG: matrices with a row of SELL_LONG entries) a value per lane.
-// Ten CG iterations on three columns, scalar / per lane: tubes of 100k nodes 2.08 / 2.15 ms, of 1M 16.8 / 17.8, with
-// the V-cycle in FP32 11.7 / 12.7; a 200 x 200 grid with four rows of 10,000 entries 24.4 / 20.0, of 5,000
-// 12.8 / 10.6, of 1,250 5.4 / 5.2, of 630 3.2 / 3.2 (over a long slice the scalar form's launches alternate between
-// 108 and 140 us).
-template <bool LONG>
-__device__ __forceinline__ int slice_wave() {
-    if constexpr (LONG) return threadIdx.x / WAVE;
-    else return __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
 }
 template <typename T, int MODE, int WPS, bool LONG>
 __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv3_k(int64_t nslices, bool down, int sp, const int32_t* __restrict__ off,

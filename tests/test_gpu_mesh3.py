@@ -79,7 +79,7 @@ def test_classical_columns_bitwise_the_one_column_cycle(scr, nodes, precision):
 
 
 # a grid whose last row couples to `longest` - 1 nodes: both sides of the length that changes the sweeps
-@pytest.mark.parametrize("longest", [1023, 1024, 4097])
+@pytest.mark.parametrize("longest", [511, 512, 4097])
 @pytest.mark.parametrize("amg_type", [0, 1])
 @pytest.mark.parametrize("precision", [0, 1])
 def test_columns_bitwise_with_a_long_row(scr, longest, amg_type, precision):
