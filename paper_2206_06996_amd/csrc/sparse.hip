@@ -743,15 +743,19 @@ __global__ void __launch_bounds__(SliceGroup<WPS>::THREADS) sell_mv_k(int64_t ns
 // 392 us a V-cycle, in FP64 at 41k 346 -> 334) and up to 16 waves.  Measured on the refined tube (A/B on one box): a cap of 64K
 // instead of 16K waves puts 8 waves on each slice of AMG(A)'s level 1 (55 slots) and 4 on AMG(S^)'s
 // level 0 and makes the FP64 solve 5 % faster; 16 waves per slice on level 1 is slower again.
-// The couplings G (3x1, three lanes of a row gather the same x) and D (1x3) have 15 short slots a slice: beyond
-// `few` G keeps one wavefront per slice (by the rule / so: 117k nodes 30.6 / 28.0 us, 425k 59.4 / 49.3, 1.2M 172 / 159),
-// D up to 2,048 slices (52k nodes 26.0 / 23.4, 117k 33.2 / 29.9; 221k 39.0 / 41.8, 425k 57.3 / 62.8).
+// The couplings G (3x1, three lanes of a row gather the same x) and D (1x3) have 15 short slots a slice: from 1,400
+// slices on G keeps one wavefront per slice (by the rule / so: 636 slices 4.4 / 4.8 us, 1,202 5.7 / 6.1, 1,578
+// 6.7 / 6.2, 2,869 9.4 / 7.9; 425k nodes 59.4 / 49.3, 1.2M 172 / 159), D from 800 to 2,048 slices (518 slices
+// 8.0 / 9.4, 664 8.9 / 9.6, 942 11.8 / 10.1, 1,400 17.0 / 15.4, 1,847 18.8 / 16.0, 3,453 39.0 / 41.8), but for those
+// just beyond one wavefront per SIMD (1,156 slices 13.8 / 15.0).
 template <typename T>
 static int waves_per_slice(const DSell<T>& A) {
     if (A.nslices <= 0) return 1;
     int64_t avg = A.slots / A.nslices;
     const bool few = A.nslices < (A.br == 6 ? 2048 : 512);
-    if (!few && (A.br > A.bc || (A.br < A.bc && A.nslices < 2048))) return 1;
+    const int64_t n = A.nslices;
+    if (A.br > A.bc && n >= 1400) return 1;
+    if (A.br < A.bc && n >= 800 && n < 2048 && !(n > 1024 && n < 1280)) return 1;
     const int wmax = few ? 16 : 8, per = !few ? 3 : A.br == 6 ? 2 : 4;
     int w = 1;
     while (w < wmax && A.nslices * w < 65536 && avg >= per * (w * 2)) w *= 2;
